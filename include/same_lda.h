@@ -232,7 +232,8 @@ int same_lda_get_timing(same_lda_t* h, double* draw_ms_total, int64_t* launches)
  *   - the Philox4x32-10 block function against the three published known-answer vectors
  *     (Salmon et al., SC'11);
  *   - the integer reciprocal used in the pmf walk against the correctly rounded 1/x for EVERY
- *     integer x in [1, 2^24);
+ *     integer x in [1, 2^24), and the short forms of the draw's quotients against the division (for every
+ *     operand where the operand is one number, for seeded pairs where it is two);
  *   - the exclusive sum and the stable radix sort that build the work list, on a seeded million
  *     items, against the host's sum and the (key, position) order.
  * *failures (host) receives the number of mismatches; 0 means all hold.                         */

@@ -58,22 +58,35 @@ __device__ __forceinline__ float from_lane_below(float v)
 __device__ __forceinline__ float top_position(float U, uint32_t R, float u)
 {
     const float a = -flog(u);
-    const float z = a / (float)R;
-    float e = expneg(z);
-    e = e > 1.0f ? 1.0f : e;
+    const float z = quot_int(a, (float)R);                         // 2^-24 < a < 17
+    const float e = __builtin_fminf(expneg(z), 1.0f);
     float y = (R == 1u) ? U * u : U * e;
     if (!(y > 0.0f)) y = U;
     return y;
 }
 
+// The first of N ascending values (N a power of two) that reaches y, when the last one is known to: its index; prev
+// becomes the value before it (it comes in as the value before the first).  A search whose answer stays in registers: at
+// N = 8 it takes 3 comparisons and 10 selections where a walk along the values takes 7 and 14.
+template <int N>
+__device__ __forceinline__ int first_reaching(float (&P)[N], float y, float& prev)
+{
+    int idx = 0;
+#pragma unroll
+    for (int h = N / 2; h > 0; h >>= 1) {
+        const bool below = !(P[h - 1] >= y);
+        prev = below ? P[h - 1] : prev;
+        idx = below ? idx + h : idx;
+#pragma unroll
+        for (int j = 0; j < h - 1; ++j) P[j] = below ? P[j + h] : P[j];
+    }
+    return idx;
+}
+
 #ifndef SAME_REFILL_MIN
 #define SAME_REFILL_MIN 24
 #endif
-#ifndef SAME_WALK_ROUNDS
-#define SAME_WALK_ROUNDS 1
-#endif
 constexpr int kRefillMin = SAME_REFILL_MIN;     // idle lanes that make the wave fetch new tasks
-constexpr int kWalkRounds = SAME_WALK_ROUNDS;   // rounds of kWalkSteps pmf terms per trip, while some lane needs them
 
 // VEC: K is a multiple of 4 (16-byte loads), else element-wise loads (TB = 0).  TB: 16-byte loads per matrix that
 // a lane has in flight at a time: a block of T = 4 ceil(K / 128) topics is read in T / (4 TB) batches of TB loads
@@ -143,15 +156,15 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
     // ---- the draw of that task: a per-lane state machine
     uint32_t R = 0;         // copies not yet placed, all of them below U
     float U = 0.0f;
-    int lt = 0;             // block that holds U
     int top = K;            // the copies left belong to topics below top
     uint32_t step = 0;      // steps taken: the next one uses words 2*(step & 1), +1 of block step >> 1
     uint32_t xs2 = 0, xs3 = 0;   // the second half of the last Philox block, for the odd step
     int st = 0;             // 0: between steps, 1: walking a single-piece binomial,
                             // 3: holds a binomial of several pieces, waiting for the wave to share it
-    uint32_t bR = 0, L = 0, xw = 0, bstep = 0;
+    uint32_t bR = 0, L = 0, bstep = 0;
     float r = 0.f, lq = 0.f, pm = 0.f, cdf = 0.f, u = 0.f;
-    bool flip = false, stalled = false;
+    float xf = 0.f, left = 0.f;                                    // the walk: successes so far, trials left
+    bool flip = false;
     int kk = 0;
 
     // Adds row i of the LDS counts to the matrix row of document doc and clears it (whole wave).
@@ -185,7 +198,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
             key.tau_lo = (uint32_t)tau; key.tau_hi = (uint32_t)((uint64_t)tau >> 32) & 0xFFu;
             pre = primary_pre(key);
             open = true;
-            lt = nblk - 1; top = K; step = 0; st = 0;
+            top = K; step = 0; st = 0;
         }
         const int n_idle = (int)__popcll(idle_mask);
         next += n_idle < avail ? n_idle : avail;
@@ -219,10 +232,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
                 if (take && d == dn) myrow = free_row;
             }
         }
-        if (UNIFORM) {
-            // all weights are 1: block l holds min(T, K - l*T) topics
-            if (take) for (int l = 0; l < nblk; ++l) sums[lane * kSumStride + l] = (float)(min(K, (l + 1) * T) - l * T);
-        } else {
+        if (!UNIFORM) {
             const int k0 = hl * T;
             // the next pair of new lanes: one for each half-wave (the last one twice if their number is odd)
             auto pick = [&](uint64_t& rem) {
@@ -450,9 +460,15 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
         __syncthreads();
         if (take) {
             float run = 0.0f;
-            for (int l = 0; l < nblk; ++l) {
-                run = run + sums[lane * kSumStride + l];
-                sums[lane * kSumStride + l] = run;
+            if (UNIFORM) {
+                run = (float)K;                                    // weights of one need no sums
+            } else {
+                for (int l = 0; l < nblk; ++l) {
+                    run = run + sums[lane * kSumStride + l];
+                    sums[lane * kSumStride + l] = run;
+                }
+                // the steps' search probes up to the next power of two
+                if (KC == 0) for (int l = nblk; (l & (l - 1)) != 0; ++l) sums[lane * kSumStride + l] = run;
             }
             U = run;
         }
@@ -543,74 +559,90 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
                     xa = xs2; xb = xs3;
                 }
                 const float y = top_position(U, R, uniform_from_word(xa));
-                // the first block whose cumulative weight reaches y (S_lt >= U >= y)
-                int lo = 0, hi = lt;
-#pragma unroll
-                for (int it = 0; it < 5; ++it) {
-                    const int mid = (lo + hi) >> 1;
-                    const bool ge = sums[lane * kSumStride + mid] >= y;
-                    hi = ge ? mid : hi;
-                    lo = ge ? lo : (mid < hi ? mid + 1 : hi);
-                }
-                const int l = hi;
-                const float base = l > 0 ? sums[lane * kSumStride + l - 1] : 0.0f;
-                // inside the block: rebuild P_k from the block's weights, count the topics still below y
-                const int k0 = l * T;
-                const float* __restrict__ th = UNIFORM ? nullptr : a.theta + (size_t)d * K;   // the task's rows
-                const float* __restrict__ ph = UNIFORM ? nullptr : a.phi + (size_t)w * K;
-                int below = 0;
-                float prev = base, rs = 0.0f;
-                auto visit = [&](float wk) {
-                    rs = rs + wk;
-                    const float P = base + rs;
-                    const bool lt_y = !(P >= y);
-                    below += lt_y ? 1 : 0;
-                    prev = lt_y ? P : prev;
-                };
-                if (UNIFORM) {
-                    for (int j = 0; j < T; ++j) visit(k0 + j < K ? 1.0f : 0.0f);
-                } else if (VEC && TB > 0) {
-                    auto reload = [&](auto whole) {
-                        constexpr bool WHOLE = decltype(whole)::value;
-                        for (int b = 0; b < nb; ++b) {
-                            const int kb = k0 + 4 * TB * b;
-                            float4 pv[TB > 0 ? TB : 1], tv[TB > 0 ? TB : 1];
-#pragma unroll
-                            for (int c = 0; c < TB; ++c) {
-                                const bool in = WHOLE || kb + 4 * c < K;
-                                pv[c] = in ? *reinterpret_cast<const float4*>(ph + kb + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                                tv[c] = in ? *reinterpret_cast<const float4*>(th + kb + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                            }
-#pragma unroll
-                            for (int c = 0; c < TB; ++c) {
-                                visit(tv[c].x * pv[c].x);
-                                visit(tv[c].y * pv[c].y);
-                                visit(tv[c].z * pv[c].z);
-                                visit(tv[c].w * pv[c].w);
-                            }
-                        }
-                    };
-                    if (nblk * T == K) reload(std::true_type{}); else reload(std::false_type{});
-                } else if (VEC) {
-                    for (int c = 0; c < T / 4; ++c) {
-                        const int k = k0 + 4 * c;
-                        if (k < K) {
-                            const float4 x = *reinterpret_cast<const float4*>(ph + k);
-                            const float4 t = *reinterpret_cast<const float4*>(th + k);
-                            visit(t.x * x.x);
-                            visit(t.y * x.y);
-                            visit(t.z * x.z);
-                            visit(t.w * x.w);
-                        }
-                    }
+                int k;                                             // the step's topic: the first with P_k >= y
+                float prev = 0.0f;                                 // P_{k-1}
+                if (UNIFORM) {                                     // weights of one: P_k = k + 1, exactly
+                    const float c = __builtin_ceilf(y);
+                    prev = c - 1.0f;
+                    k = (int)prev;
                 } else {
-                    for (int j = 0; j < T; ++j) {
-                        const int k = k0 + j;
-                        if (k < K) visit(th[k] * ph[k]);
+                    // the first block whose cumulative weight reaches y (S_31 >= U >= y; entries past the last block
+                    // repeat it), and prev = the cumulative weight below that block
+                    const float* S = sums + lane * kSumStride;
+                    int l = 0;
+#pragma unroll
+                    for (int h = kMaxBlocks / 2; h > 0; h >>= 1) {
+                        if (KC == 0 && h >= nblk) continue;
+                        const float v = S[l + h - 1];
+                        const bool below = !(v >= y);
+                        prev = below ? v : prev;
+                        l = below ? l + h : l;
+                    }
+                    if (KC == 0) l = min(l, nblk - 1);             // (only negative weights could lead past it)
+                    // inside the block: rebuild P_k from the block's weights.  Its last P_k is the block's cumulative
+                    // weight, the same sum in the same order, so the search ends inside the block.
+                    const int k0 = l * T;
+                    const float* __restrict__ th = a.theta + (size_t)d * K;   // the task's rows
+                    const float* __restrict__ ph = a.phi + (size_t)w * K;
+                    const float base = prev;
+                    float rs = 0.0f;
+                    if (VEC && TB > 0) {
+                        auto reload = [&](auto whole) {
+                            constexpr bool WHOLE = decltype(whole)::value;
+                            constexpr int N = TB > 0 ? 4 * TB : 4;
+                            int at = 0;
+                            bool found = false;
+                            float before = base;                   // P of the topic before the batch
+                            for (int b = 0; b < nb; ++b) {
+                                const int kb = k0 + N * b;
+                                float4 pv[N / 4], tv[N / 4];
+#pragma unroll
+                                for (int c = 0; c < N / 4; ++c) {
+                                    const bool in = WHOLE || kb + 4 * c < K;
+                                    pv[c] = in ? *reinterpret_cast<const float4*>(ph + kb + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+                                    tv[c] = in ? *reinterpret_cast<const float4*>(th + kb + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+                                }
+                                float P[N];
+#pragma unroll
+                                for (int c = 0; c < N / 4; ++c) {
+                                    rs = rs + tv[c].x * pv[c].x; P[4 * c + 0] = base + rs;
+                                    rs = rs + tv[c].y * pv[c].y; P[4 * c + 1] = base + rs;
+                                    rs = rs + tv[c].z * pv[c].z; P[4 * c + 2] = base + rs;
+                                    rs = rs + tv[c].w * pv[c].w; P[4 * c + 3] = base + rs;
+                                }
+                                if (ONE) {
+                                    at = first_reaching<N>(P, y, prev);
+                                } else {
+                                    const float last = P[N - 1];
+                                    float pb = before;
+                                    const int ib = N * b + first_reaching<N>(P, y, pb);
+                                    const bool here = !found && (b == nb - 1 || last >= y);
+                                    at = here ? ib : at;
+                                    prev = here ? pb : prev;
+                                    found = found || here;
+                                    before = last;
+                                }
+                            }
+                            k = k0 + at;
+                        };
+                        if (nblk * T == K) reload(std::true_type{}); else reload(std::false_type{});
+                    } else {
+                        int at = 0;
+                        auto visit = [&](float wk) {
+                            rs = rs + wk;
+                            const float P = base + rs;
+                            const bool below = !(P >= y);
+                            at += below ? 1 : 0;
+                            prev = below ? P : prev;
+                        };
+                        for (int j = 0; j < T; ++j) {
+                            const int kj = k0 + j;
+                            if (kj < K) visit(th[kj] * ph[kj]);
+                        }
+                        k = k0 + at;
                     }
                 }
-                const int kend = min(k0 + T, top) - 1;            // the block's last topic not yet passed
-                const int k = max(min(k0 + below, kend), 0);
+                k = max(min(k, top - 1), 0);
                 SAME_COUNT(a, 3, 1);                               // block reloads
                 // the step's topic, its top copy, and the binomial of the copies that share the topic
                 const uint32_t Rm = R - 1u;
@@ -618,7 +650,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
                 const float q = width / y;
                 kk = k;
                 bstep = step;
-                U = prev; lt = l; top = k; step += 1u;
+                U = prev; top = k; step += 1u;
                 if (Rm == 0u || !(q > 0.0f)) {
                     ek = k; en = 1u;
                     R = Rm;
@@ -629,15 +661,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
                     flip = q > 0.5f;
                     const float qq = flip ? 1.0f - q : q;
                     const float s1 = 1.0f - qq;
-                    r = qq / s1;
+                    r = quot_1(qq, s1);
                     lq = log1m(qq);
                     bR = Rm;
                     R = Rm;                                        // the binomial's share comes off when it is known
                     u = uniform_from_word(xb);
                     if (((float)Rm * qq) <= kPieceMean) {          // one piece of Rm trials
-                        L = Rm;
                         const float pm0 = expneg((float)Rm * lq);
-                        xw = 0; pm = pm0; cdf = pm0; stalled = false;
+                        xf = 0.0f; left = (float)Rm; pm = pm0; cdf = pm0;
                         st = 1;
                     } else {                                       // pieces of L trials: shared by the wave
                         L = (uint32_t)(kPieceMean / qq);
@@ -660,32 +691,33 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
             }
         }
         if (__any(st == 1)) {
-            const bool walking = st == 1;
-            bool more = walking && !stalled && u > cdf && xw < L;
-            for (int round = 0; round < kWalkRounds && __any(more); ++round) {
-                if (lane == 0) SAME_COUNT(a, 12, 1);               // rounds of pmf terms
-#pragma unroll
-                for (int i = 0; i < kWalkSteps; ++i) {
-                    const uint32_t xn = xw + 1u;
-                    float pmn = pm * r;
-                    pmn = pmn * (float)(L - xn + 1u);
-                    pmn = pmn * inv_int((float)xn);
-                    const float next_cdf = cdf + pmn;
-                    const bool still = next_cdf == cdf;
-                    if (more) SAME_COUNT(a, 4, 1);                 // pmf terms
-                    xw = more ? xn : xw;
-                    pm = more ? pmn : pm;
-                    cdf = (more && !still) ? next_cdf : cdf;
-                    stalled = stalled || (more && still);
-                    more = more && !still && u > cdf && xw < L;
+            // Up to kWalkSteps terms of the pmf per trip, lane by lane: a lane that has its count drops out of the loop
+            // (the execution mask costs scalar instructions, selections would cost vector ones) and the wave leaves it
+            // with its last lane.  The numbers of successes and of trials left are whole floats below 2^24: exact.
+            if (lane == 0) SAME_COUNT(a, 12, 1);                       // trips with a walk
+            if (st == 1) {
+                bool more = u > cdf;
+                int i = 0;
+                while (more) {
+                    SAME_COUNT(a, 4, 1);                           // pmf terms
+                    xf = xf + 1.0f;
+                    pm = pm * r;
+                    pm = pm * left;
+                    pm = pm * inv_int(xf);
+                    left = left - 1.0f;
+                    const float next_cdf = cdf + pm;
+                    more = next_cdf != cdf && left > 0.0f && u > next_cdf;
+                    cdf = next_cdf;
+                    if (++i == kWalkSteps) break;
                 }
-            }
-            if (walking && !more) {                                // the binomial is known
-                const uint32_t nk = flip ? bR - xw : xw;
-                ek = kk; en = 1u + nk;
-                R -= nk;
-                st = 0;
-                SAME_COUNT(a, 5, 1);
+                if (!more) {                                       // the binomial is known
+                    const uint32_t x = (uint32_t)xf;
+                    const uint32_t nk = flip ? bR - x : x;
+                    ek = kk; en = 1u + nk;
+                    R -= nk;
+                    st = 0;
+                    SAME_COUNT(a, 5, 1);
+                }
             }
         }
         if (!DEBUG && !pool_dry) {

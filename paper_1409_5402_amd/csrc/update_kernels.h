@@ -10,13 +10,26 @@
 
 namespace same {
 
-// Self-test: reciprocal of every integer in [1, 2^24) and the published Philox known answers.
+// Self-test: reciprocal of every integer in [1, 2^24); the quotients of quot_1 for every operand it is used with; quot_int for
+// a seeded numerator over every integer and four over those whose reciprocals round worst; the published Philox known answers.
 __global__ void selftest_kernel(unsigned long long* __restrict__ failures)
 {
     const uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= 1u && x < (1u << 24)) {
         const float fx = (float)x;
         if (inv_int(fx) != 1.0f / fx) atomicAdd(failures, 1ull);
+        for (uint32_t i = 0; i < (x < 4096u || x >= (1u << 24) - 4096u ? 64u : 4u); ++i) {
+            const float a = -flog(uniform_from_word((x * 64u + i) * 0x9E3779B9u));
+            if (quot_int(a, fx) != a / fx) atomicAdd(failures, 1ull);
+        }
+        float f = __uint_as_float(0x3F800000u | (x & 0x007FFFFFu));    // every mantissa (twice)
+        if (f > 1.41421354f) f = f * 0.5f;
+        const float a = f - 1.0f, b = f + 1.0f;
+        if (quot_1(a, b) != a / b) atomicAdd(failures, 1ull);
+    }
+    for (uint32_t i = x + 1u; i <= 0x3F000000u; i += gridDim.x * blockDim.x) {   // every binary32 in (0, 1/2]
+        const float v = __uint_as_float(i), d1 = 1.0f - v, d2 = 2.0f - v;
+        if (quot_1(v, d1) != v / d1 || quot_1(v, d2) != v / d2) atomicAdd(failures, 1ull);
     }
     if (x < 3u) {
         const uint32_t in[3][6] = {{0u, 0u, 0u, 0u, 0u, 0u},
