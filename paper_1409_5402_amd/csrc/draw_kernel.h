@@ -83,10 +83,16 @@ __device__ __forceinline__ int first_reaching(float (&P)[N], float y, float& pre
     return idx;
 }
 
-#ifndef SAME_REFILL_MIN
-#define SAME_REFILL_MIN 24
-#endif
-constexpr int kRefillMin = SAME_REFILL_MIN;     // idle lanes that make the wave fetch new tasks
+// Idle lanes that make the wave fetch new tasks: kRefillMin; fewer are enough when the last refill is kRefillLateTrips
+// trips back, since tasks are then long and a refill is a small part of their cost (from a flat posterior, 83 steps per
+// task, 12 of the 64 lanes were idle on average; converged, a refill comes every three trips).
+constexpr int kRefillMin = 24;
+constexpr int kRefillLate = 8;
+constexpr int kRefillLateTrips = 8;
+// Binomials of several pieces wait for kPoolMin of them, or for kPoolTrips trips: from a flat posterior five of the 64
+// lanes waited at any time for eight to gather.  (1, 2, 4, 8 trips: 9.62, 9.59, 9.80, 10.4 ms there against 12.4 without
+// the limit; converged 11.02, 10.83, 10.73, 10.73 ms.)
+constexpr int kPoolTrips = 4;
 
 // VEC: K is a multiple of 4 (16-byte loads), else element-wise loads (TB = 0).  TB: 16-byte loads per matrix that
 // a lane has in flight at a time: a block of T = 4 ceil(K / 128) topics is read in T / (4 TB) batches of TB loads
@@ -100,24 +106,52 @@ constexpr int kRefillMin = SAME_REFILL_MIN;     // idle lanes that make the wave
 // same left-to-right order through a chain of lane-to-lane shifts; the block sums are the same bits.  The steps'
 // reloads of single blocks stay as they are (a lane's block belongs to its own task).
 //
-// The launch positions are handed out in segments of kSegment consecutive positions through a counter in
-// device memory (a.counter, zero at launch): a workgroup (one wave) takes a segment, its lanes take the
-// segment's tasks as they become free, and when the segment is used up the wave takes the next one.  Tasks
-// differ widely in the number of steps they need (one for most, a hundred for a few): a lane that waited
-// for the slowest of 64 fixed tasks would idle most of the time, and a wave with a fixed share of the matrix
-// would end with one lane busy.  Whenever kRefillMin lanes are idle the wave stops stepping, gives each idle
-// lane the next position, scans the new tasks (two per instruction) and goes on.
-#ifndef SAME_SEGMENT
-#define SAME_SEGMENT 512
-#endif
-constexpr int kSegment = SAME_SEGMENT;
+// The launch positions (tasks in storage order) are shared out in rounds.  A launch has as many workgroups (of one wave)
+// as the device holds at once.  In round 0 every workgroup owns a.first consecutive positions, about half of an equal
+// share, without asking; in round r a share has a.first / 2^r positions (at least kShareMin), and a workgroup draws a
+// ticket for one when its own positions are used up.  Its lanes take positions as they become free: tasks differ widely
+// in the number of steps they need (one for most, a hundred for a few), so a lane that waited for the slowest of 64
+// fixed tasks would idle most of the time, and a wave with a fixed share of the matrix would end with one lane busy.
+// Whenever kRefillMin lanes are idle the wave stops stepping, gives each idle lane the next position, scans the new tasks
+// (two per instruction) and goes on.
+//
+// Tickets: one counter for every kGroups-th workgroup, zero at launch.  The device does one returning atomic on an
+// address in about 16 ns whatever asks for it; with one counter for segments of 512 positions those atomics were the
+// whole time of small launches (98,000 tasks: 86 us, 26 without) and a fifth of a launch of 9 million tasks
+// (0.567 -> 0.466 ms).  Halving shares need some ten tickets per workgroup, all told, and end with small ones.
+constexpr int kShareMin = 64;           // (32 and 128 measured within 1 %)
+constexpr int kShareAll = 128;          // up to this many positions per workgroup round 0 covers everything
+constexpr int kGroups = 32;             // (8 and 64 measured within 1 %)
+constexpr int kCounterStride = 32;      // words between two counters: a cache line each
+constexpr int kCounterWords = kGroups * kCounterStride;
+
+struct Shares { int32_t waves, first; };   // workgroups of a launch, positions of a share of round 0
+inline Shares shares_for(int64_t n, int64_t resident)
+{
+    Shares s;
+    const int64_t per = (n + resident - 1) / resident;
+    if (per <= kShareAll) {                                        // fewer workgroups, none with less than a wave's worth
+        s.first = per < kWave ? kWave : (int32_t)per;
+        s.waves = (int32_t)((n + s.first - 1) / s.first);
+    } else {
+        s.first = (int32_t)(per / (2 * kShareMin) * kShareMin);
+        s.waves = (int32_t)resident;
+    }
+    return s;
+}
+__device__ __forceinline__ int32_t share_of_round(int32_t first, int round)
+{
+    const int32_t s = round < 31 ? (first >> round) & ~31 : 0;
+    return s < kShareMin ? kShareMin : s;
+}
 
 template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ? 4 : 3))) void draw_kernel(DrawArgs a)
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 2 ? 4 : 3)))) void draw_kernel(DrawArgs a)
 {
     extern __shared__ uint32_t lds[];
-    float* sums = reinterpret_cast<float*>(lds);                   // [64 lanes][kSumStride]: block sums, then running sums
-    uint32_t* acc = lds + kMaxBlocks;                              // piece totals by owner lane: lane l's is acc[l * kSumStride],
+    constexpr int kStride = UNIFORM ? 1 : kSumStride;              // (weights of one need no sums)
+    float* sums = reinterpret_cast<float*>(lds);                   // [64 lanes][kStride]: block sums, then running sums
+    uint32_t* acc = lds + (UNIFORM ? 0 : kMaxBlocks);              // piece totals by owner lane: lane l's is acc[l * kStride],
                                                                    // the word of its row of sums that pads the stride
     const int lane = threadIdx.x;
     const int K = KC > 0 ? KC : a.K;                              // KC: the number of topics where it is known at compile time
@@ -129,17 +163,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
     // in storage order: the 64 lanes hold tasks of one or two documents at a time).  Counts are added here and
     // reach the matrix in one pass over the row when the wave has left the document; tasks of a document that
     // has no row here add to the matrix at once.
-    uint32_t* stage = lds + (size_t)kWave * kSumStride + lane;     // [3][64] pairs on their way to the pair list
-    uint32_t* rows = lds + (size_t)kWave * (kSumStride + 3);       // [n_rows][K]
+    uint32_t* rows = lds + (size_t)kWave * kStride;                // [n_rows][K]
     const int n_rows = DEBUG ? 0 : doc_rows(K);
     int tag0 = -1, tag1 = -1;                                      // the documents of rows 0 and 1 (wave-uniform), -1: free
     int myrow = -1;                                                // the row of this lane's document, -1: none
     for (int i = lane; i < n_rows * K; i += kWave) rows[i] = 0u;
-    int32_t next = 0, end = 0;                                     // the wave's segment: positions not yet handed out
-    bool drained = false;                                          // the counter has passed the last position
+    // the wave's positions not yet handed out
+    int32_t next = (int32_t)((int64_t)blockIdx.x * a.first < a.n ? (int64_t)blockIdx.x * a.first : a.n);
+    int32_t end = (int32_t)((int64_t)next + a.first < a.n ? (int64_t)next + a.first : a.n);
+    bool drained = false;                                          // nothing is left to take
     uint32_t chunk_next = 0, chunk_end = 0;                        // the wave's share of the chunk pool not yet handed out
     bool pool_dry = a.chunks == nullptr;                           // the pool has no chunk left for this wave
-    acc[lane * kSumStride] = 0u;
+    acc[lane * kStride] = 0u;
 
     // ---- the lane's current task
 #ifdef SAME_STATS
@@ -149,6 +184,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
     int32_t d = 0, w = 0;
     Scatter sc;
     sc.drow = 0; sc.wrow = kNone; sc.slot = kNone; sc.npairs = 0;
+    Staged staged;          // its last pairs, on their way to the pair list
     StreamKey key;
     key.seed_lo = a.seed_lo; key.seed_hi = a.seed_hi; key.tau_lo = 0; key.tau_hi = 0; key.pass = a.pass;
     PrimaryPre pre = primary_pre(key);
@@ -167,6 +203,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
     bool flip = false;
     int kk = 0;
 
+    int trips = 0;          // trips since the last refill
+    int waited = 0;         // trips since a binomial of several pieces has been waiting
+
     // Adds row i of the LDS counts to the matrix row of document doc and clears it (whole wave).
     auto flush_row = [&](int i, int doc) {
         __syncthreads();
@@ -181,7 +220,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
     // per half-wave: lane hl of a half owns block hl), each new lane turns its sums into running sums.
     auto refill = [&](uint64_t idle_mask) {
         const bool idle = (idle_mask >> lane) & 1ull;
-        if (idle && open) { sc.close(a, true, stage); open = false; }
+        if (idle && open) { sc.close(a, true, staged); open = false; }
         const int rank = (int)__popcll(idle_mask & ((1ull << lane) - 1ull));
         const int avail = end - next;
         const bool take = idle && rank < avail;
@@ -211,9 +250,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
             for (int round = 0; round < n_rows; ++round) {
                 const uint64_t used0 = __ballot(myrow == 0), used1 = __ballot(myrow == 1);
                 const int free_row = used0 == 0 ? 0 : ((n_rows > 1 && used1 == 0) ? 1 : -1);
-                int dn = (take && myrow < 0) ? d : 0x7FFFFFFF;         // the lowest new document without a row
-                for (int o = 32; o > 0; o >>= 1) dn = min(dn, __shfl_xor(dn, o));
-                if (dn == 0x7FFFFFFF) break;
+                const uint64_t rowless = __ballot(take && myrow < 0);
+                if (rowless == 0) break;
+                const int dn = __builtin_amdgcn_readlane(d, __ffsll((unsigned long long)rowless) - 1);   // the lowest of their documents
                 if (free_row < 0) {
                     // one row (n_rows == 1) in use: it goes to the new document if that one now has more lanes than
                     // the row's document has left; the lanes that stay behind add to the matrix directly from here on
@@ -519,12 +558,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
                     if (next_cdf == cdfj) break;
                     cdfj = next_cdf;
                 }
-                if (xj > 0) atomicAdd(acc + owner * kSumStride, xj);
+                if (xj > 0) atomicAdd(acc + owner * kStride, xj);
             }
         }
         __syncthreads();
         uint32_t part = 0;
-        if (st == 3) { part = acc[lane * kSumStride]; acc[lane * kSumStride] = 0u; }
+        if (st == 3) { part = acc[lane * kStride]; acc[lane * kStride] = 0u; }
         __syncthreads();
         return part;
     };
@@ -679,7 +718,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
         }
         {
             const uint64_t pend = __ballot(st == 3);
-            if (pend != 0 && (__popcll((unsigned long long)pend) >= kPoolMin || !__any(st == 1 || (st == 0 && R > 0)))) {
+            const bool share = pend != 0 && (__popcll((unsigned long long)pend) >= kPoolMin || waited >= kPoolTrips ||
+                                             !__any(st == 1 || (st == 0 && R > 0)));
+            waited = (pend != 0 && !share) ? waited + 1 : 0;
+            if (share) {
                 const uint32_t part = pool(pend);
                 if (st == 3) {
                     const uint32_t nk = flip ? bR - part : part;
@@ -737,7 +779,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
                     if (lane == 0) SAME_COUNT(a, 14, 1);               // batches of chunks taken
                 }
                 const uint32_t mine = chunk_next + (uint32_t)__popcll((unsigned long long)(need_mask & ((1ull << lane) - 1ull)));
-                if (need && mine < chunk_end) { sc.extend(a, mine, stage); SAME_COUNT(a, 15, 1); }
+                if (need && mine < chunk_end) { sc.extend(a, mine, staged); SAME_COUNT(a, 15, 1); }
                 chunk_next = chunk_end - chunk_next < cnt ? chunk_end : chunk_next + cnt;
             }
         }
@@ -749,36 +791,53 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TB <= 2 ?
         }
 #endif
         if (en > 0u) {
-            if (myrow >= 0) { atomicAdd(rows + myrow * K + ek, en); sc.emit_word(a, ek, en, stage); }
-            else sc.emit(a, ek, en, stage);
+            if (myrow >= 0) atomicAdd(rows + myrow * K + ek, en);
+            else atomicAdd(a.ndk + (size_t)sc.drow * K + ek, en);
+            sc.emit_word(a, ek, en, staged);
         }
     };
 
     for (;;) {
         const uint64_t idle_mask = __ballot(st == 0 && R == 0);
-        if (!drained && (__popcll((unsigned long long)idle_mask) >= kRefillMin || idle_mask == ~0ull)) {
-            if (next >= end) {                                     // the next segment (all lanes obtain the same value)
-                uint32_t first = 0;
-                if (lane == 0) first = atomicAdd(a.counter, (uint32_t)kSegment);
-                first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
-                drained = (int64_t)first >= a.n;
-                next = drained ? 0 : (int32_t)first;
-                end = drained ? 0 : (int32_t)((int64_t)first + kSegment < a.n ? (int64_t)first + kSegment : a.n);
+        const int n_idle = (int)__popcll((unsigned long long)idle_mask);
+        if (!drained && (n_idle >= kRefillMin || (n_idle >= kRefillLate && trips >= kRefillLateTrips) || n_idle == kWave)) {
+            if (next >= end) {                                     // the next share (all lanes obtain the same values)
+                const int64_t waves = (int64_t)gridDim.x;          // a multiple of kGroups where round 0 does not cover all
+                int64_t from = waves * a.first;                    // where round 1 begins
+                int32_t size = 0;
+                if (from < a.n) {
+                    const uint32_t group = blockIdx.x % kGroups, per_round = gridDim.x / kGroups;
+                    uint32_t t = 0;                                // this group's ticket: shares t * kGroups + group of a round
+                    if (lane == 0) t = atomicAdd(a.counter + kCounterStride * group, 1u);
+                    t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+                    int round = 1;
+                    size = share_of_round(a.first, 1);
+                    while (t >= per_round && from < a.n) {
+                        from += waves * size; t -= per_round; round += 1;
+                        size = share_of_round(a.first, round);
+                    }
+                    from += ((int64_t)t * kGroups + group) * size;
+                }
+                drained = from >= a.n;
+                next = drained ? 0 : (int32_t)from;
+                end = drained ? 0 : (int32_t)(from + size < a.n ? from + size : a.n);
             }
             if (next < end) {
                 if (lane == 0) SAME_COUNT(a, 13, 1);               // refills
                 refill(idle_mask);
+                trips = 0;
                 continue;
             }
         }
         if (idle_mask == ~0ull) break;                             // nothing in flight and nothing left to take
         trip();
+        trips += 1;
     }
-    if (open) sc.close(a, true, stage);
+    if (open) sc.close(a, true, staged);
     if (n_rows > 0 && tag0 >= 0) flush_row(0, tag0);
     if (n_rows > 1 && tag1 >= 0) flush_row(1, tag1);
 }
 
-inline size_t draw_lds_bytes(int K) { return 4u * ((size_t)kWave * (size_t)(kSumStride + 3) + (size_t)doc_rows(K) * (size_t)K); }
+inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kWave * (size_t)(uniform ? 1 : kSumStride) + (size_t)doc_rows(K) * (size_t)K); }
 
 }  // namespace same

@@ -27,10 +27,6 @@ namespace {
 thread_local std::string g_init_error;
 
 constexpr int32_t kTileDocs = 16;   // documents per tile of the processing order
-#ifndef SAME_GRID_PER_CU
-#define SAME_GRID_PER_CU 16
-#endif
-constexpr int64_t kDrawGrid = 256 * SAME_GRID_PER_CU;   // workgroups of the multinomial draw kernel: as many as are resident at once (sixteen waves per compute unit)
 constexpr int kGammaRows = 64;      // rows of n_wk per workgroup of the sampled phi step
 
 // Device copy of one sparse matrix plus its draw work list.
@@ -129,14 +125,17 @@ struct same_lda {
     float* phi = nullptr;          // [V][K]
     uint32_t* nwk = nullptr;       // [V][K]
     unsigned long long* nk = nullptr;  // [K]
-    uint32_t* draw_counter = nullptr;  // [3] counters of the draw kernel: segments and chunks taken by a launch on the handle's
-                                       // stream, segments taken by a launch on the copy stream
+    uint32_t* draw_counter = nullptr;  // counters of the draw kernel: tickets (kCounterWords) and chunks taken (one word) by a
+                                       // launch on the handle's stream, tickets of a launch on the copy stream
     uint32_t* chunks = nullptr;        // pool of chunks that continue full pair-list slots (launches on the handle's stream)
     uint32_t n_chunks = 0;             // chunks allocated
     int64_t chunk_limit = -1;          // chunks a launch may use (-1: all of them); lowered by tests of the fallback
     double* gamma_partial = nullptr;   // [ceil(V / kGammaRows)][K] block sums of the sampled phi step
     float* gamma_total = nullptr;      // [K]
     double* vb_psi = nullptr;          // [K] psi of the column sums of lambda (variational E-step)
+    struct Resident { const void* kernel; int64_t groups; };
+    Resident resident[32] = {};    // draw kernels used so far and how many of their workgroups run at once
+    int n_resident = 0;
     bool timing = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> events;   // recorded, not yet read
     std::vector<std::pair<hipEvent_t, hipEvent_t>> pool;     // free event pairs
@@ -488,16 +487,34 @@ int check_m(same_lda* h, int32_t m, const Matrix& M)
 int prepare_counter(same_lda* h, same::DrawArgs& a, hipStream_t st)
 {
     const bool beside = st == h->copy_stream && st != h->stream;
-    a.counter = beside ? h->draw_counter + 2 : h->draw_counter;
-    a.chunk_counter = h->draw_counter + 1;
+    a.counter = h->draw_counter + (beside ? same::kCounterWords + 1 : 0);
+    a.chunk_counter = h->draw_counter + same::kCounterWords;
     if (beside || !a.pairs) { a.chunks = nullptr; a.n_chunks = 0; }
-    hipLaunchKernelGGL(same::zero_u32_kernel, dim3(1), dim3(64), 0, st, a.counter, (size_t)(beside ? 1 : 2));
+    hipLaunchKernelGGL(same::zero_u32_kernel, dim3(grid_for(same::kCounterWords + 1)), dim3(256), 0, st, a.counter,
+                       (size_t)(beside ? same::kCounterWords : same::kCounterWords + 1));
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }
 
+// Workgroups of kernel f that the device holds at once, a multiple of kGroups.  Asked once per handle and kernel.
+int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t* out)
+{
+    for (int i = 0; i < h->n_resident; ++i)
+        if (h->resident[i].kernel == f) { *out = h->resident[i].groups; return SAME_LDA_OK; }
+    int dev = 0, cus = 0, per_cu = 0;
+    HIP_TRY(h, hipGetDevice(&dev));
+    HIP_TRY(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    HIP_TRY(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, lds));
+    if (per_cu < 1) per_cu = 1;
+    int64_t n = (int64_t)cus * per_cu / same::kGroups * same::kGroups;
+    if (n < same::kGroups) n = same::kGroups;
+    if (h->n_resident < (int)(sizeof h->resident / sizeof h->resident[0])) h->resident[h->n_resident++] = {f, n};
+    *out = n;
+    return SAME_LDA_OK;
+}
+
 template <bool DEBUG>
-int launch_draw(same_lda* h, const same::DrawArgs& a, bool uniform, bool poisson, hipStream_t st)
+int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipStream_t st)
 {
     if (a.n <= 0) return SAME_LDA_OK;
     const int T = same::kWave;
@@ -511,29 +528,34 @@ int launch_draw(same_lda* h, const same::DrawArgs& a, bool uniform, bool poisson
         else if (a.K % same::kBlk == 0) hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG>), grid, block, lds, st, a);
         else                       hipLaunchKernelGGL((same::poisson_draw_kernel<false, DEBUG>), grid, block, lds, st, a);
     } else {
-        // Workgroups take segments of launch positions from a counter until none is left: as many workgroups as
-        // the chip holds at once, so that it is full from the first moment to the last.
-        const int64_t segments = (a.n + same::kSegment - 1) / same::kSegment;
-        dim3 grid((unsigned)(segments < kDrawGrid ? segments : kDrawGrid));
         // blocks of 4 * ceil(K / 128) topics, read in batches of one, two or four 16-byte loads per matrix
         // (K = 512 and K = 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
         // kernel is bound by vector-ALU issue, the extra additions of that form cost more than the fewer cache lines save)
-        const size_t lds = same::draw_lds_bytes(a.K);
         const bool vec = a.K % 4 == 0;
         const int quads = same::block_len(a.K) / 4;                // 16-byte loads per block and matrix
         const int tb = quads % 4 == 0 ? 4 : (quads % 2 == 0 ? 2 : 1);
         const bool one = quads == tb;
-        if (uniform)             hipLaunchKernelGGL((same::draw_kernel<true, false, DEBUG, 0, true>), grid, block, lds, st, a);
-        else if (!vec)           hipLaunchKernelGGL((same::draw_kernel<false, false, DEBUG, 0, true>), grid, block, lds, st, a);
-        else if (tb == 1 && one) hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 1, true>), grid, block, lds, st, a);
-        else if (a.K == 256)     hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 2, true, 256>), grid, block, lds, st, a);
-        else if (a.K == 1024)    hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 4, false, 1024, true>), grid, block, lds, st, a);
-        else if (a.K == 512)     hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 4, true, 512, true>), grid, block, lds, st, a);
-        else if (tb == 2 && one) hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 2, true>), grid, block, lds, st, a);
-        else if (tb == 4 && one) hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 4, true>), grid, block, lds, st, a);
-        else if (tb == 1)        hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 1, false>), grid, block, lds, st, a);
-        else if (tb == 2)        hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 2, false>), grid, block, lds, st, a);
-        else                     hipLaunchKernelGGL((same::draw_kernel<false, true, DEBUG, 4, false>), grid, block, lds, st, a);
+        const void* f;
+        if (uniform)             f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
+        else if (!vec)           f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
+        else if (tb == 1 && one) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 1, true>);
+        else if (a.K == 256)     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true, 256>);
+        else if (a.K == 1024)    f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false, 1024, true>);
+        else if (a.K == 512)     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true>);
+        else if (tb == 2 && one) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true>);
+        else if (tb == 4 && one) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true>);
+        else if (tb == 1)        f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 1, false>);
+        else if (tb == 2)        f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, false>);
+        else                     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false>);
+        // As many one-wave workgroups as the chip holds at once, each with a share of the positions.
+        const size_t lds = same::draw_lds_bytes(a.K, uniform);
+        int64_t resident = 0;
+        int rc = resident_groups(h, f, T, lds, &resident);
+        if (rc) return rc;
+        const same::Shares sh = same::shares_for(a.n, resident);
+        a.first = sh.first;
+        void* args[] = {&a};
+        HIP_TRY(h, hipLaunchKernel(f, dim3((unsigned)sh.waves), block, args, lds, st));
     }
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
@@ -546,7 +568,7 @@ unsigned long long* g_stats = nullptr;   // profiling builds only
 same::DrawArgs draw_args(const same_lda* h, const Matrix& M, Copies c, uint32_t pass_word, bool with_words)
 {
     same::DrawArgs a;
-    a.n = M.n_tasks; a.counter = nullptr; a.t_doc = M.t_doc; a.t_word = M.t_word; a.t_g = M.t_g; a.order = M.order; a.cost = M.cost; a.ids = nullptr;
+    a.n = M.n_tasks; a.counter = nullptr; a.first = 0; a.t_doc = M.t_doc; a.t_word = M.t_word; a.t_g = M.t_g; a.order = M.order; a.cost = M.cost; a.ids = nullptr;
     a.theta = M.theta; a.phi = h->phi; a.ndk = M.ndk; a.nwk = with_words ? h->nwk : nullptr;
     // a pair holds a count below 2^(32 - kPairShift): m * largest group must fit
     // (a Poisson count may exceed its rate: four times the rate plus 128 is beyond any count the walk can return)
@@ -732,7 +754,7 @@ int same_lda_init(same_lda_t** out, const same_lda_csc* X, int32_t K, float alph
     if (!rc) rc = dev_alloc(h, &h->gamma_partial, (size_t)((h->V + kGammaRows - 1) / kGammaRows) * K);
     if (!rc) rc = dev_alloc(h, &h->gamma_total, (size_t)K);
     if (!rc) rc = dev_alloc(h, &h->vb_psi, (size_t)K);
-    if (!rc) rc = dev_alloc(h, &h->draw_counter, (size_t)3);
+    if (!rc) rc = dev_alloc(h, &h->draw_counter, (size_t)(2 * same::kCounterWords + 1));
     if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m0), pass_word(0, 0), true, true, false, h->stream);
     if (!rc) rc = update_theta(h, h->X, (float)m0, h->stream);
     if (!rc) rc = update_phi(h, (float)m0, 1.0f, h->stream);
@@ -927,12 +949,12 @@ int same_lda_task_count(const same_lda_t* h, int64_t* count)
 }
 
 namespace {
-// Device memory of same_lda_debug_draw_noalloc: the segment counter of the draw kernel, the staged task ids and
+// Device memory of same_lda_debug_draw_noalloc: the ticket counters of the draw kernel, the staged task ids and
 // the count rows.  One copy per GPU (a file-scope device array), kept until the process ends.
 constexpr int32_t kNoAllocMaxTasks = 4096;
 constexpr size_t kNoAllocMaxCounts = (size_t)1 << 20;
 struct NoAllocScratch {
-    uint32_t counter[64];
+    uint32_t counter[same::kCounterWords];
     int64_t  ids[kNoAllocMaxTasks];
     uint32_t counts[kNoAllocMaxCounts];
 };
@@ -1020,7 +1042,7 @@ int same_lda_debug_draw_noalloc(same_lda_t* h, int32_t m_t, const int64_t* task_
     same::DrawArgs a = draw_args(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false);
     a.n = n; a.ids = S->ids; a.ndk = S->counts; a.nwk = nullptr; a.cost = nullptr;
     a.counter = S->counter;
-    if ((rc = zero_u32(h, S->counter, 1, h->stream))) return rc;
+    if ((rc = zero_u32(h, S->counter, same::kCounterWords, h->stream))) return rc;
     if ((rc = launch_draw<true>(h, a, false, false, h->stream))) return rc;
     HIP_TRY(h, hipMemcpyAsync(counts_out, S->counts, counts * 4, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));

@@ -23,7 +23,8 @@ constexpr int kPoolMin = SAME_POOL_MIN; // waiting multi-piece variables that tr
 
 struct DrawArgs {
     int64_t         n;          // tasks in this launch
-    uint32_t*       counter;    // multinomial form: first launch position not yet taken by a workgroup (zero at launch)
+    uint32_t*       counter;    // multinomial form: [kCounterWords] tickets for shares of the positions (zero at launch)
+    int32_t         first;      // multinomial form: launch positions of a workgroup's first share
     const int32_t*  t_doc;      // [n_tasks] document of the task
     const int32_t*  t_word;     // [n_tasks] word of the task
     const uint32_t* t_g;        // [n_tasks] tokens in the task's group
@@ -72,11 +73,20 @@ constexpr int kHotCopies = 32;          // copies of a hot word's row
 // places more than 15 pairs (most tasks do while the posterior is still flat) continues in chunks of the same
 // shape taken from a pool: the header of a full slot or chunk names the chunk that follows it, the header of
 // the last one holds its number of pairs.  When the pool is used up the remaining counts go straight to the
-// word's row.  Pairs are collected in LDS (stage: this lane's three words, kWave words apart) and written four
-// at a time, the fourth from its register, with one 16-byte store: the memory system handles a 16-byte write
-// as fast as a 4-byte one.
+// word's row.  The last pairs are kept in three registers that shift, and written four at a time with one
+// 16-byte store: the memory system handles a 16-byte write as fast as a 4-byte one.
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint32_t kInPool = 0x80000000u;   // Scatter::slot: the index is one of the pool's chunks, not of the pair list's slots
+
+// The last three pairs of a task, the newest in p2: the npairs & 3 of them that are not yet written are among them.
+struct Staged {
+    uint32_t p0 = 0u, p1 = 0u, p2 = 0u;
+    __device__ __forceinline__ void push(uint32_t pair)
+    {
+        const uint32_t a = p1, b = p2;
+        p0 = a; p1 = b; p2 = pair;
+    }
+};
 
 // The struct holds row and slot numbers, not addresses: a lane keeps it for the whole life of its task, and
 // registers decide how many waves a compute unit holds.
@@ -91,27 +101,24 @@ struct Scatter {
         uint32_t* base = (slot & kInPool) ? a.chunks : a.pairs;
         return base + (size_t)(slot & ~kInPool) * kPairWords;
     }
-    // words 4q .. 4q+3 of the slot: the three staged words and a fourth
-    __device__ __forceinline__ void store_quad(const DrawArgs& a, uint32_t q, const uint32_t* stage, uint32_t fourth) const
+    // words 4q .. 4q+3 of the slot
+    __device__ __forceinline__ void store_quad(const DrawArgs& a, uint32_t q, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) const
     {
-        uint4 v;
-        v.x = stage[0]; v.y = stage[kWave]; v.z = stage[2 * kWave]; v.w = fourth;
-        *reinterpret_cast<uint4*>(slot_words(a) + 4u * q) = v;
+        *reinterpret_cast<uint4*>(slot_words(a) + 4u * q) = make_uint4(w0, w1, w2, w3);
     }
-    __device__ __forceinline__ void emit(const DrawArgs& a, int k, uint32_t n, uint32_t* stage)
+    __device__ __forceinline__ void emit(const DrawArgs& a, int k, uint32_t n, Staged& t)
     {
         atomicAdd(a.ndk + (size_t)drow * a.K + k, n);
-        emit_word(a, k, n, stage);
+        emit_word(a, k, n, t);
     }
     // the word's half alone (the caller has added the count to the document's row itself)
-    __device__ __forceinline__ void emit_word(const DrawArgs& a, int k, uint32_t n, uint32_t* stage)
+    __device__ __forceinline__ void emit_word(const DrawArgs& a, int k, uint32_t n, Staged& t)
     {
         if (slot != kNone) {
             if (npairs < (uint32_t)(kPairWords - 1)) {
-                const uint32_t j = npairs & 3u;
                 const uint32_t pair = (uint32_t)k | (n << kPairShift);
-                if (j == 3u) store_quad(a, npairs >> 2, stage, pair);   // pairs 0-3, 4-7 or 8-11
-                else stage[j * kWave] = pair;
+                if ((npairs & 3u) == 3u) store_quad(a, npairs >> 2, t.p0, t.p1, t.p2, pair);   // pairs 0-3, 4-7 or 8-11
+                t.push(pair);
                 npairs += 1;
             } else {
                 atomicAdd(a.nwk + (size_t)wrow * a.K + k, n);      // full and no chunk to go on with: straight to the row
@@ -121,24 +128,23 @@ struct Scatter {
         }
     }
     __device__ __forceinline__ bool full() const { return slot != kNone && npairs >= (uint32_t)(kPairWords - 1); }
-    // a full slot (pairs 12-14 are still staged) goes on in chunk idx of the pool
-    __device__ __forceinline__ void extend(const DrawArgs& a, uint32_t idx, uint32_t* stage)
+    // a full slot (pairs 12-14 are not yet written) goes on in chunk idx of the pool
+    __device__ __forceinline__ void extend(const DrawArgs& a, uint32_t idx, const Staged& t)
     {
-        store_quad(a, 3u, stage, kPairLink | idx);
+        store_quad(a, 3u, t.p0, t.p1, t.p2, kPairLink | idx);
         slot = kInPool | idx;
         npairs = 0;
     }
-    // the staged pairs and the header of the last slot or chunk: how many pairs it holds
-    __device__ __forceinline__ void close(const DrawArgs& a, bool live, uint32_t* stage) const
+    // the unwritten pairs and the header of the last slot or chunk: how many pairs it holds
+    __device__ __forceinline__ void close(const DrawArgs& a, bool live, const Staged& t) const
     {
         if (slot != kNone && live) {
-            const uint32_t q = npairs >> 2;
-            if (q == 3u) {                                         // the header shares the last quad
-                store_quad(a, 3u, stage, npairs);
-            } else {
-                if ((npairs & 3u) != 0u) store_quad(a, q, stage, 0u);   // words past the last pair are never read
-                slot_words(a)[kPairWords - 1] = npairs;
-            }
+            // the j unwritten pairs come first in their quad; words past the last pair are never read
+            const uint32_t q = npairs >> 2, j = npairs & 3u;
+            const uint32_t x0 = t.p0, x1 = t.p1, x2 = t.p2;
+            const uint32_t w0 = j == 1u ? x2 : (j == 2u ? x1 : x0), w1 = j == 2u ? x2 : x1;
+            if (j != 0u || q == 3u) store_quad(a, q, w0, w1, x2, npairs);   // q = 3: the header shares the last quad
+            if (q != 3u) slot_words(a)[kPairWords - 1] = npairs;
         }
     }
 };

@@ -1,0 +1,38 @@
+"""Launch shapes of the multinomial draw: every position of a launch is drawn once whatever the number of tasks is -
+less than a wave's worth, one share per workgroup exactly used or one task over, halving shares with tickets, ragged
+ends.  Counts against the oracle, element by element (whole numbers, so no tolerance)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1409_5402_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def matrix(n_tasks, V, seed):
+    """n_tasks nonzeros with counts 1 or 2, V per document (the last document ragged), words in ascending order."""
+    rng = np.random.default_rng(seed)
+    full, rest = divmod(n_tasks, V)
+    lens = [V] * full + ([rest] if rest else [])
+    colptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rowidx = np.concatenate([np.arange(n, dtype=np.int32) for n in lens])
+    val = rng.integers(1, 3, size=n_tasks).astype(np.float32)
+    return oracle.CSC(len(lens), V, colptr, rowidx, val)
+
+
+# workgroups at once at K = 4: at most 256 * 20 (five waves per SIMD), at least 256 * 16; shares of up to 128 positions
+# are handed out without tickets
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 4096 * 64 + 1, 4608 * 128, 4608 * 128 + 1, 5120 * 128 + 1, 5120 * 200 + 77])
+def test_every_position_is_drawn_once(n):
+    X = matrix(n, V=min(n, 251), seed=n % 1000)
+    K, m = 4, 3
+    o = oracle.OracleLDA(X, K, 0.3, 0.05, seed=5, m0=1, G=8)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.3, 0.05, 5, 1, 8)
+    assert np.array_equal(g.get(binding.NDK), o.ndk) and np.array_equal(g.get(binding.NWK), o.nwk)
+    for _ in range(2):
+        o.sweep(m)
+        g.sweep(m)
+        assert np.array_equal(g.get(binding.NDK), o.ndk)
+        assert np.array_equal(g.get(binding.NWK), o.nwk)
+    g.close()
