@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     const int lane = threadIdx.x;
     const int K = KC > 0 ? KC : a.K;                              // KC: the number of topics where it is known at compile time
     const int T = (TB > 0 && ONE) ? 4 * TB : block_len(K);         // topics per block
-    const int nb = (TB > 0 && !ONE) ? T / (4 * TB) : 1;            // batches of loads per block
+    const int nb = (TB > 0 && !ONE) ? T / (4 * (TB > 0 ? TB : 1)) : 1;   // batches of loads per block
     const int nblk = (K + T - 1) / T;                              // blocks in use (<= 32)
     const int half = lane >> 5, hl = lane & 31;
     // Rows of the new document counts kept in LDS while the wave works on their documents (the launch positions are

@@ -17,6 +17,7 @@
 #include <stdint.h>
 
 #include "rng_binom.h"
+#include "update_kernels.h"
 
 namespace same {
 
@@ -87,52 +88,74 @@ __device__ __forceinline__ float gamma_variable(float a, uint32_t seed_lo, uint3
     return g < 1e-30f ? 1e-30f : g;
 }
 
-// theta[d][k] = Gamma(n_dk + m*alpha) / m
-__global__ void gamma_theta_kernel(const uint32_t* __restrict__ ndk, float* __restrict__ theta, size_t n, int K,
-                                   float mf, float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass)
+// theta[d][k] = Gamma(n_dk + m*alpha) / m; rows_per_block documents per workgroup
+__global__ __launch_bounds__(256) void gamma_theta_kernel(const uint32_t* __restrict__ ndk, float* __restrict__ theta, int D, int K,
+                                                         float mf, float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass,
+                                                         int rows_per_block)
 {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint32_t d = (uint32_t)(i / (size_t)K), k = (uint32_t)(i % (size_t)K);
-        const float a = (float)ndk[i] + prior;
-        theta[i] = gamma_variable(a, seed_lo, seed_hi, d, k, pass) / mf;
-    }
+    const RowSplit<1> s(K);
+    if (s.group >= s.groups) return;
+    const int r0 = blockIdx.x * rows_per_block, r1 = min(D, r0 + rows_per_block);
+    for (int k = s.unit; k < K; k += s.groups == 1 ? 256 : K)
+        for (int d = r0 + s.group; d < r1; d += s.groups) {
+            const size_t i = (size_t)d * K + k;
+            const float a = (float)ndk[i] + prior;
+            theta[i] = gamma_variable(a, seed_lo, seed_hi, (uint32_t)d, (uint32_t)k, pass) / mf;
+        }
 }
 
-// phi[w][k] = Gamma(n_wk + m*beta), and the sum of each topic over this block's rows (double, row order)
-__global__ void gamma_phi_kernel(const uint32_t* __restrict__ nwk, float* __restrict__ phi, int V, int K,
-                                 float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass,
-                                 int rows_per_block, double* __restrict__ partial)
+// phi[w][k] = Gamma(n_wk + m*beta), and the sum of each topic over this block's rows (double, in a fixed order).  A hot
+// word's row first takes in its copies, as in phi_update_kernel.  1024 threads per workgroup: the variables are long
+// chains of arithmetic, and the block sums' scratch fixes the number of workgroups, not that of waves.
+constexpr int kGammaThreads = 1024;
+__global__ __launch_bounds__(kGammaThreads) void gamma_phi_kernel(uint32_t* __restrict__ nwk, const int16_t* __restrict__ hot_of,
+                                                                 int hot_max, int hot_copies, float* __restrict__ phi, int V, int K,
+                                                                 float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass,
+                                                                 int rows_per_block, double* __restrict__ partial)
 {
+    __shared__ double sh[kGammaThreads];
+    const RowSplit<1, kGammaThreads> s(K);
     const int r0 = blockIdx.x * rows_per_block;
     const int r1 = min(V, r0 + rows_per_block);
-    for (int k = threadIdx.x; k < K; k += blockDim.x) {
+    for (int k = s.unit; k < K; k += s.groups == 1 ? kGammaThreads : K) {
         double acc = 0.0;
-        for (int r = r0; r < r1; ++r) {
-            const size_t i = (size_t)r * K + k;
-            const float g = gamma_variable((float)nwk[i] + prior, seed_lo, seed_hi, (uint32_t)r, (uint32_t)k, pass);
-            phi[i] = g;
-            acc += (double)g;
+        if (s.group < s.groups) {
+            for (int r = r0 + s.group; r < r1; r += s.groups) {
+                const size_t i = (size_t)r * K + k;
+                uint32_t n[1] = {nwk[i]};
+                const int hot = hot_of ? (int)hot_of[r] : -1;
+                if (hot >= 0 && take_in_copies<1>(nwk, V, K, hot, hot_max, hot_copies, k, n)) nwk[i] = n[0];
+                const float g = gamma_variable((float)n[0] + prior, seed_lo, seed_hi, (uint32_t)r, (uint32_t)k, pass);
+                phi[i] = g;
+                acc += (double)g;
+            }
+        }
+        if (s.groups > 1) {
+            sh[threadIdx.x] = acc;
+            __syncthreads();
+            if (s.group != 0) break;
+            for (int g = 1; g < s.groups; ++g) acc += sh[g * K + k];
         }
         partial[(size_t)blockIdx.x * K + k] = acc;
     }
 }
 
-// total[k] = sum of the block sums in block order (double), rounded to binary32
-__global__ void gamma_phi_totals_kernel(const double* __restrict__ partial, int blocks, int K, float* __restrict__ total)
+// total[k] = sum of the block sums (double, in a fixed order), rounded to binary32
+__global__ __launch_bounds__(256) void gamma_phi_totals_kernel(const double* __restrict__ partial, int blocks, int K, float* __restrict__ total)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= K) return;
-    double acc = 0.0;
-    for (int b = 0; b < blocks; ++b) acc += partial[(size_t)b * K + k];
-    total[k] = (float)acc;
+    column_sums(partial, blocks, K, [&](int k, double sum) { total[k] = (float)sum; });
 }
 
-__global__ void gamma_phi_normalise_kernel(float* __restrict__ phi, size_t n, int K, const float* __restrict__ total)
+__global__ __launch_bounds__(256) void gamma_phi_normalise_kernel(float* __restrict__ phi, int V, int K, const float* __restrict__ total,
+                                                                 int rows_per_block)
 {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        phi[i] = phi[i] / total[i % (size_t)K];
+    const RowSplit<1> s(K);
+    if (s.group >= s.groups) return;
+    const int r0 = blockIdx.x * rows_per_block, r1 = min(V, r0 + rows_per_block);
+    for (int k = s.unit; k < K; k += s.groups == 1 ? 256 : K) {
+        const float t = total[k];
+        for (int r = r0 + s.group; r < r1; r += s.groups) phi[(size_t)r * K + k] = phi[(size_t)r * K + k] / t;
+    }
 }
 
 }  // namespace same

@@ -27,6 +27,7 @@ namespace {
 thread_local std::string g_init_error;
 
 constexpr int32_t kTileDocs = 16;   // documents per tile of the processing order
+constexpr int kSecondCounters = same::kCounterWords + 32;   // where the copy stream's tickets start (a cache line of their own)
 constexpr int kGammaRows = 64;      // rows of n_wk per workgroup of the sampled phi step
 
 // Device copy of one sparse matrix plus its draw work list.
@@ -481,20 +482,19 @@ int check_m(same_lda* h, int32_t m, const Matrix& M)
     return check_accumulators(h, (double)m, 0.0, M);
 }
 
-// The multinomial kernel's counters for a launch on st, set to zero on st (a launch of its own, so that the
-// events around the draw kernel bracket that kernel alone).  Launches on the copy stream have no pair list and
-// therefore no use for the chunk pool: they run beside launches on the handle's stream, which own it.
-int prepare_counter(same_lda* h, same::DrawArgs& a, hipStream_t st)
+// The multinomial kernel's counters for a launch on st, which must be zero when it starts.  Launches on the copy stream
+// have no pair list and therefore no use for the chunk pool: they run beside launches on the handle's stream, which own it.
+bool beside(const same_lda* h, hipStream_t st) { return st == h->copy_stream && st != h->stream; }
+size_t counter_words(const same_lda* h, hipStream_t st) { return beside(h, st) ? same::kCounterWords : same::kCounterWords + 1; }
+
+void assign_counters(same_lda* h, same::DrawArgs& a, hipStream_t st)
 {
-    const bool beside = st == h->copy_stream && st != h->stream;
-    a.counter = h->draw_counter + (beside ? same::kCounterWords + 1 : 0);
+    a.counter = h->draw_counter + (beside(h, st) ? kSecondCounters : 0);
     a.chunk_counter = h->draw_counter + same::kCounterWords;
-    if (beside || !a.pairs) { a.chunks = nullptr; a.n_chunks = 0; }
-    hipLaunchKernelGGL(same::zero_u32_kernel, dim3(grid_for(same::kCounterWords + 1)), dim3(256), 0, st, a.counter,
-                       (size_t)(beside ? same::kCounterWords : same::kCounterWords + 1));
-    HIP_TRY(h, hipGetLastError());
-    return SAME_LDA_OK;
+    if (beside(h, st) || !a.pairs) { a.chunks = nullptr; a.n_chunks = 0; }
 }
+
+int zero_u32(same_lda* h, uint32_t* p, size_t n, hipStream_t st);
 
 // Workgroups of kernel f that the device holds at once, a multiple of kGroups.  Asked once per handle and kernel.
 int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t* out)
@@ -609,22 +609,50 @@ int update_theta(same_lda* h, Matrix& M, float m, hipStream_t st)
 {
     const size_t n = (size_t)M.D * h->K;
     if (n == 0) return SAME_LDA_OK;
-    hipLaunchKernelGGL(same::theta_update_kernel, dim3(grid_for(n)), dim3(256), 0, st, M.ndk, M.theta, n,
+    hipLaunchKernelGGL(same::theta_update_kernel, dim3(grid_for((n + 3) / 4)), dim3(256), 0, st, M.ndk, M.theta, n,
                        m, h->alpha);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }
 
-int update_phi(same_lda* h, float m, float rho, hipStream_t st)
+// n_k of the counts in h->nwk (cleared by run_pass), and theta of M unless it is null.
+int update_totals(same_lda* h, Matrix* M, int32_t n_hot, float m, hipStream_t st)
 {
-    const size_t n = (size_t)h->V * h->K;
-    hipLaunchKernelGGL(same::zero_u64_kernel, dim3(1), dim3(256), 0, st, h->nk, (size_t)h->K);
-    const int rows_per_block = 64;
-    const int blocks = (h->V + rows_per_block - 1) / rows_per_block;
-    hipLaunchKernelGGL(same::topic_totals_kernel, dim3(blocks), dim3(256), 0, st, h->nwk, h->V, h->K, h->nk,
-                       rows_per_block);
-    hipLaunchKernelGGL(same::phi_update_kernel, dim3(grid_for(n)), dim3(256), 0, st, h->nwk, h->nk, h->phi, n,
-                       h->K, m, h->beta, (float)h->V * h->beta, rho);
+    same::TotalsArgs a;
+    a.nwk = h->nwk; a.nk = h->nk; a.V = h->V; a.K = h->K;
+    a.n_hot = n_hot; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
+    // at least two turns of four rows per thread, and at most 512 workgroups (64-bit atomics per topic)
+    const int rows = h->V + n_hot * same::kHotCopies, at_once = 8 * same::rows_at_once(h->K);
+    a.rows_per_block = (rows + 511) / 512;
+    if (a.rows_per_block < at_once) a.rows_per_block = at_once;
+    a.total_blocks = (rows + a.rows_per_block - 1) / a.rows_per_block;
+    a.ndk = M ? M->ndk : nullptr; a.theta = M ? M->theta : nullptr;
+    a.n_theta = M ? (size_t)M->D * h->K : 0; a.mf = m; a.alpha = h->alpha;
+    const unsigned blocks = (unsigned)(a.total_blocks + (a.n_theta ? grid_for((a.n_theta + 3) / 4) : 0));
+    if (h->K % 4 == 0) hipLaunchKernelGGL(same::totals_theta_kernel<4>, dim3(blocks), dim3(256), 0, st, a);
+    else               hipLaunchKernelGGL(same::totals_theta_kernel<1>, dim3(blocks), dim3(256), 0, st, a);
+    HIP_TRY(h, hipGetLastError());
+    return SAME_LDA_OK;
+}
+
+// The collapsed update: n_k and theta in one launch, phi in another.
+int update_collapsed(same_lda* h, Matrix& M, float m, float rho, hipStream_t st)
+{
+    const int32_t n_hot = M.n_hot;
+    int rc = update_totals(h, &M, n_hot, m, st);
+    if (rc) return rc;
+    same::PhiArgs a;
+    a.nwk = h->nwk; a.nk = h->nk; a.phi = h->phi; a.hot_of = n_hot > 0 ? M.hot_of : nullptr;
+    a.V = h->V; a.K = h->K; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
+    a.mf = m; a.beta = h->beta; a.vbeta = (float)h->V * h->beta; a.rho = rho;
+    // up to eight rows per thread, fewer where that leaves less than four workgroups per compute unit
+    const int at_once = same::rows_at_once(h->K);
+    int turns = h->V / (at_once * 1024);
+    turns = turns < 1 ? 1 : (turns > 8 ? 8 : turns);
+    a.rows_per_block = turns * at_once;
+    const unsigned blocks = (unsigned)((h->V + a.rows_per_block - 1) / a.rows_per_block);
+    if (h->K % 4 == 0) hipLaunchKernelGGL(same::phi_update_kernel<4>, dim3(blocks), dim3(256), 0, st, a);
+    else               hipLaunchKernelGGL(same::phi_update_kernel<1>, dim3(blocks), dim3(256), 0, st, a);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }
@@ -632,28 +660,29 @@ int update_phi(same_lda* h, float m, float rho, hipStream_t st)
 // theta of M drawn from its Dirichlet conditional (unnormalised, mean n_dk/m + alpha).
 int sample_theta(same_lda* h, Matrix& M, float m, uint32_t pword, hipStream_t st)
 {
-    const size_t n = (size_t)M.D * h->K;
-    if (n == 0) return SAME_LDA_OK;
-    hipLaunchKernelGGL(same::gamma_theta_kernel, dim3(grid_for(n)), dim3(256), 0, st, M.ndk, M.theta, n, h->K, m,
-                       m * h->alpha, (uint32_t)h->seed, (uint32_t)(h->seed >> 32), pword);
+    if (M.D == 0) return SAME_LDA_OK;
+    const int rows = 4 * (h->K >= 256 ? 1 : 256 / h->K);
+    hipLaunchKernelGGL(same::gamma_theta_kernel, dim3((unsigned)((M.D + rows - 1) / rows)), dim3(256), 0, st, M.ndk, M.theta, M.D, h->K, m,
+                       m * h->alpha, (uint32_t)h->seed, (uint32_t)(h->seed >> 32), pword, rows);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }
 
 // phi drawn from its Dirichlet conditionals: Gamma variables, their sums over words in a fixed order, division.
-int sample_phi(same_lda* h, float m, uint32_t pword, hipStream_t st)
+int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_t st)
 {
-    const size_t n = (size_t)h->V * h->K;
     const int blocks = (h->V + kGammaRows - 1) / kGammaRows;
     // the topic totals are part of the readable state, kept current as after a collapsed update
-    hipLaunchKernelGGL(same::zero_u64_kernel, dim3(1), dim3(256), 0, st, h->nk, (size_t)h->K);
-    hipLaunchKernelGGL(same::topic_totals_kernel, dim3(blocks), dim3(256), 0, st, h->nwk, h->V, h->K, h->nk, kGammaRows);
-    hipLaunchKernelGGL(same::gamma_phi_kernel, dim3(blocks), dim3(256), 0, st, h->nwk, h->phi, h->V, h->K,
-                       m * h->beta, (uint32_t)h->seed, (uint32_t)(h->seed >> 32), pword, kGammaRows, h->gamma_partial);
-    hipLaunchKernelGGL(same::gamma_phi_totals_kernel, dim3((h->K + 255) / 256), dim3(256), 0, st, h->gamma_partial,
+    const int rc = update_totals(h, nullptr, M.n_hot, m, st);
+    if (rc) return rc;
+    hipLaunchKernelGGL(same::gamma_phi_kernel, dim3(blocks), dim3(same::kGammaThreads), 0, st, h->nwk, M.n_hot > 0 ? M.hot_of : nullptr,
+                       same::kHotMax, same::kHotCopies, h->phi, h->V, h->K, m * h->beta, (uint32_t)h->seed, (uint32_t)(h->seed >> 32),
+                       pword, kGammaRows, h->gamma_partial);
+    hipLaunchKernelGGL(same::gamma_phi_totals_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, st, h->gamma_partial,
                        blocks, h->K, h->gamma_total);
-    hipLaunchKernelGGL(same::gamma_phi_normalise_kernel, dim3(grid_for(n)), dim3(256), 0, st, h->phi, n, h->K,
-                       h->gamma_total);
+    const int rows = 8 * (h->K >= 256 ? 1 : 256 / h->K);
+    hipLaunchKernelGGL(same::gamma_phi_normalise_kernel, dim3((unsigned)((h->V + rows - 1) / rows)), dim3(256), 0, st, h->phi, h->V, h->K,
+                       h->gamma_total, rows);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }
@@ -663,15 +692,21 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
              hipStream_t st)
 {
     int rc;
-    if ((rc = zero_u32(h, M.ndk, (size_t)M.D * h->K, st))) return rc;
-    if (with_words && (rc = zero_u32(h, h->nwk, nwk_elements(h), st))) return rc;   // the hot words' copies too
     if (!uniform && c.poisson && M.n_tiles > 0) {               // the Poisson kernel takes its tasks in cost order
         hipLaunchKernelGGL(same::reorder_kernel, dim3((unsigned)M.n_tiles), dim3(256), 0, st, M.tile_start, M.cost,
                            M.order);
         HIP_TRY(h, hipGetLastError());
     }
     same::DrawArgs a = draw_args(h, M, c, pword, with_words);
-    if (!c.poisson && (rc = prepare_counter(h, a, st))) return rc;
+    assign_counters(h, a, st);
+    {   // one launch of its own, so that the events around the draw kernel bracket that kernel alone.  The hot words'
+        // copies need no clearing: the parameter update that follows every pass with words leaves them clear.
+        const size_t cells = (size_t)M.D * h->K, word_cells = with_words ? (size_t)h->V * h->K : 0;
+        const same::ClearArgs z = {{M.ndk, h->nwk, a.counter, reinterpret_cast<uint32_t*>(h->nk)},
+                                   {cells, word_cells, counter_words(h, st), with_words ? (size_t)2 * h->K : 0}};
+        hipLaunchKernelGGL(same::clear_kernel, dim3(grid_for((cells > word_cells ? cells : word_cells) / 4 + 1)), dim3(256), 0, st, z);
+        HIP_TRY(h, hipGetLastError());
+    }
     // the events bracket the draw kernel alone
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     if (timed) {
@@ -688,16 +723,11 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
         h->events.push_back(ev);
     }
     if (a.pairs && a.n > 0) {
-        const int rows = same::reduce_rows(h->K);
-        const int64_t blocks = (M.n_slots + same::kReduceChunk - 1) / same::kReduceChunk;
-        hipLaunchKernelGGL(same::word_reduce_kernel, dim3((unsigned)blocks), dim3(same::kReduceThreads),
+        const int chunk = same::reduce_chunk(M.n_slots), rows = same::reduce_rows(h->K, chunk);
+        const int64_t blocks = (M.n_slots + chunk - 1) / chunk;
+        hipLaunchKernelGGL(same::word_reduce_kernel, dim3((unsigned)blocks), dim3((unsigned)(chunk / 2)),
                            (size_t)rows * h->K * sizeof(uint32_t), st, a.pairs, a.chunks, a.n_chunks, M.slot_word, M.n_slots,
-                           h->K, rows, h->nwk);
-        HIP_TRY(h, hipGetLastError());
-    }
-    if (a.hot_of) {
-        hipLaunchKernelGGL(same::hot_fold_kernel, dim3((unsigned)((M.n_hot * h->K + 255) / 256)), dim3(256), 0, st, h->nwk,
-                           M.hot_word, M.n_hot, h->V, h->K);
+                           h->K, rows, chunk, h->nwk);
         HIP_TRY(h, hipGetLastError());
     }
     return SAME_LDA_OK;
@@ -754,10 +784,10 @@ int same_lda_init(same_lda_t** out, const same_lda_csc* X, int32_t K, float alph
     if (!rc) rc = dev_alloc(h, &h->gamma_partial, (size_t)((h->V + kGammaRows - 1) / kGammaRows) * K);
     if (!rc) rc = dev_alloc(h, &h->gamma_total, (size_t)K);
     if (!rc) rc = dev_alloc(h, &h->vb_psi, (size_t)K);
-    if (!rc) rc = dev_alloc(h, &h->draw_counter, (size_t)(2 * same::kCounterWords + 1));
+    if (!rc) rc = dev_alloc(h, &h->draw_counter, (size_t)kSecondCounters + same::kCounterWords);
+    if (!rc) rc = zero_u32(h, h->nwk + (size_t)h->V * K, nwk_elements(h) - (size_t)h->V * K, h->stream);   // the hot words' copies
     if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m0), pass_word(0, 0), true, true, false, h->stream);
-    if (!rc) rc = update_theta(h, h->X, (float)m0, h->stream);
-    if (!rc) rc = update_phi(h, (float)m0, 1.0f, h->stream);
+    if (!rc) rc = update_collapsed(h, h->X, (float)m0, 1.0f, h->stream);
     if (!rc) { hipError_t e = hipStreamSynchronize(h->stream); if (e != hipSuccess) rc = fail(h, SAME_LDA_EHIP, "init: %s", hipGetErrorString(e)); }
     if (rc) { g_init_error = h->error; same_lda_free(h); return rc; }
     h->pass = 1;
@@ -772,8 +802,7 @@ int same_lda_sweep(same_lda_t* h, int32_t m_t, float rho_t)
     if (!(rho_t > 0.f) || rho_t > 1.f) return fail(h, SAME_LDA_EINVAL, "rho must be in (0, 1] (got %g)", (double)rho_t);
     int rc = check_m(h, m_t, h->X);
     if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream);
-    if (!rc) rc = update_theta(h, h->X, (float)m_t, h->stream);
-    if (!rc) rc = update_phi(h, (float)m_t, rho_t, h->stream);
+    if (!rc) rc = update_collapsed(h, h->X, (float)m_t, rho_t, h->stream);
     if (!rc) h->pass += 1;
     return rc;
 }
@@ -784,7 +813,7 @@ int same_lda_sweep_sampled(same_lda_t* h, int32_t m_t)
     int rc = check_m(h, m_t, h->X);
     if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream);
     if (!rc) rc = sample_theta(h, h->X, (float)m_t, pass_word(h->pass, 2), h->stream);
-    if (!rc) rc = sample_phi(h, (float)m_t, pass_word(h->pass, 3), h->stream);
+    if (!rc) rc = sample_phi(h, h->X, (float)m_t, pass_word(h->pass, 3), h->stream);
     if (!rc) h->pass += 1;
     return rc;
 }
@@ -795,8 +824,7 @@ int same_lda_sweep_poisson(same_lda_t* h, float m_t, float rho_t)
     if (!(rho_t > 0.f) || rho_t > 1.f) return fail(h, SAME_LDA_EINVAL, "rho must be in (0, 1] (got %g)", (double)rho_t);
     int rc = check_mf(h, m_t, h->X);
     if (!rc) rc = run_pass(h, h->X, Copies::real(m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream);
-    if (!rc) rc = update_theta(h, h->X, m_t, h->stream);
-    if (!rc) rc = update_phi(h, m_t, rho_t, h->stream);
+    if (!rc) rc = update_collapsed(h, h->X, m_t, rho_t, h->stream);
     if (!rc) h->pass += 1;
     return rc;
 }
@@ -1001,7 +1029,8 @@ int debug_draw(same_lda_t* h, Copies c, const int64_t* task_ids, int32_t n, uint
     if (!rc) {
         same::DrawArgs a = draw_args(h, h->X, c, pass_word(h->pass, 0), false);
         a.n = n; a.ids = ids_d; a.ndk = out_d; a.nwk = nullptr; a.cost = nullptr;
-        if (!c.poisson) rc = prepare_counter(h, a, h->stream);
+        assign_counters(h, a, h->stream);
+        rc = zero_u32(h, a.counter, counter_words(h, h->stream), h->stream);
         if (!rc) rc = launch_draw<true>(h, a, false, c.poisson, h->stream);
     }
     if (!rc) {
@@ -1108,7 +1137,7 @@ int same_lda_vb_exp_elog_beta(same_lda_t* h, const float* lambda, float* b_out, 
     static_assert(same::kVbRows == kGammaRows, "the column sums reuse the block-sum buffer of the sampled phi step");
     const int blocks = (h->V + same::kVbRows - 1) / same::kVbRows;
     hipLaunchKernelGGL(same::vb_colsum_kernel, dim3(blocks), dim3(256), 0, h->stream, lambda, h->V, h->K, h->gamma_partial);
-    hipLaunchKernelGGL(same::vb_colpsi_kernel, dim3((h->K + 255) / 256), dim3(256), 0, h->stream, h->gamma_partial, blocks, h->K,
+    hipLaunchKernelGGL(same::vb_colpsi_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, h->stream, h->gamma_partial, blocks, h->K,
                        h->vb_psi);
     hipLaunchKernelGGL(same::vb_exp_elog_beta_kernel, dim3((unsigned)((h->V + 3) / 4)), dim3(256), 0, h->stream, lambda, h->V, h->K,
                        h->vb_psi, b_out, shift_out);

@@ -61,7 +61,7 @@ struct DrawArgs {
 // over many topics, fill their pair-list slot and send the rest straight to the row) are a bottleneck of
 // their own: atomics on a handful of lines are served by a handful of memory channels, one after the other.
 // Such a word therefore gets kHotCopies private copies of its row behind the matrix; a workgroup adds to the
-// copy picked by its index, and hot_fold_kernel adds the copies to the word's row afterwards.
+// copy picked by its index, and the parameter update adds the copies to the word's row and clears them.
 constexpr int kHotMax = 256;            // words that may be hot (those holding at least 1/256 of all tokens)
 constexpr int kHotCopies = 32;          // copies of a hot word's row
 
@@ -168,41 +168,25 @@ __device__ __forceinline__ Scatter make_scatter(const DrawArgs& a, int64_t row, 
     return s;
 }
 
-// Adds the copies of the hot words' rows (rows V .. V + kHotCopies*kHotMax of the matrix) to the words' own
-// rows and clears them.  Runs alone on its stream after the draw and the pair-list reduction.
-__global__ void hot_fold_kernel(uint32_t* __restrict__ nwk, const int32_t* __restrict__ hot_word, int n_hot, int V, int K)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_hot * K) return;
-    const int hw = i / K, k = i - hw * K;
-    uint32_t total = 0;
-    for (int c = 0; c < kHotCopies; ++c) {
-        uint32_t* p = nwk + ((size_t)V + (size_t)c * kHotMax + (size_t)hw) * K + k;
-        total += *p;
-        *p = 0u;
-    }
-    if (total) nwk[(size_t)hot_word[hw] * K + k] += total;
-}
-
 // Adds the recorded pairs to the word rows.  Slots are in word order and exist only for words with
 // at least kSlotMinTasks tasks: a workgroup takes kReduceChunk consecutive slots, sums the pairs of
 // the first `rows` words it meets in an LDS table and sends the rest straight to [V][K]; the table is
 // then added to the rows it stands for.  A thread reads a slot with four 16-byte loads and starts with the
 // quad picked by its index: tasks of one word have their large counts at the same topics in the same places
 // of their slots, and aligned walks would meet at one address.
-constexpr int kReduceChunk = 2048;
+constexpr int kReduceChunk = 2048;       // slots per workgroup of a long list; shorter lists take fewer (reduce_chunk)
 constexpr int kSlotMinTasks = 2;         // (32 measured 1.5 % slower on the resident matrix and 5 % on a minibatch: the direct
                                         // updates of rare words are atomics on lines that have long left the cache)
-constexpr int kReduceThreads = 1024;    // two slots per thread: the kernel waits on its loads, many waves hide that
+constexpr int kReduceThreads = 1024;    // at most: two slots per thread, the kernel waits on its loads, many waves hide that
 
 __global__ __launch_bounds__(kReduceThreads) void word_reduce_kernel(const uint32_t* __restrict__ pairs,
                                                           const uint32_t* __restrict__ chunks, uint32_t n_chunks,
                                                           const int32_t* __restrict__ slot_word, int64_t n, int K,
-                                                          int rows, uint32_t* __restrict__ nwk)
+                                                          int rows, int chunk, uint32_t* __restrict__ nwk)
 {
     extern __shared__ uint32_t tab[];                              // [rows][K]
-    const int64_t s0 = (int64_t)blockIdx.x * kReduceChunk;
-    const int64_t s1 = s0 + kReduceChunk < n ? s0 + kReduceChunk : n;
+    const int64_t s0 = (int64_t)blockIdx.x * chunk;
+    const int64_t s1 = s0 + chunk < n ? s0 + chunk : n;
     const int32_t w0 = slot_word[s0];
     for (int i = threadIdx.x; i < rows * K; i += blockDim.x) tab[i] = 0u;
     __syncthreads();
@@ -249,6 +233,9 @@ __global__ __launch_bounds__(kReduceThreads) void word_reduce_kernel(const uint3
     }
 }
 
-inline int reduce_rows(int K) { const int r = 16384 / K; return r < 1 ? 1 : (r > 64 ? 64 : r); }
+// Slots per workgroup, two per thread: kReduceChunk, or as few as leave two workgroups per compute unit.  The table
+// shrinks with it.
+inline int reduce_chunk(int64_t n) { int c = 256; while (c < kReduceChunk && (int64_t)c * 512 < n) c *= 2; return c; }
+inline int reduce_rows(int K, int chunk) { const int r = 8 * chunk / K; return r < 1 ? 1 : (r > 64 ? 64 : r); }
 
 }  // namespace same

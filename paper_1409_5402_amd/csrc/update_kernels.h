@@ -44,6 +44,21 @@ __global__ void selftest_kernel(unsigned long long* __restrict__ failures)
     }
 }
 
+// Clears up to four arrays in one launch (each aligned to 16 bytes): a launch costs some 4.5 us whatever it does, and a
+// sweep needs four things cleared.
+struct ClearArgs { uint32_t* p[4]; size_t n[4]; };
+__global__ __launch_bounds__(256) void clear_kernel(ClearArgs a)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x, i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const size_t quads = a.n[j] / 4;
+        uint4* p = reinterpret_cast<uint4*>(a.p[j]);
+        for (size_t i = i0; i < quads; i += stride) p[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (i0 < (a.n[j] & 3u)) a.p[j][4 * quads + i0] = 0u;
+    }
+}
+
 __global__ void zero_u32_kernel(uint32_t* __restrict__ p, size_t n)
 {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -79,54 +94,192 @@ __global__ __launch_bounds__(256) void reorder_kernel(const int32_t* __restrict_
     }
 }
 
-// n_k = sum over words of n_wk[w][k], exact in 64-bit integers (any order gives the same value).
-// Each block sums a slab of rows; thread t owns column (t mod K') of every row group.
-__global__ void topic_totals_kernel(const uint32_t* __restrict__ nwk, int V, int K,
-                                    unsigned long long* __restrict__ nk, int rows_per_block)
+// How the kernels over [rows][K] matrices share a row's topics out: a thread owns one unit of W consecutive topics (W = 4,
+// 16-byte accesses, where K is a multiple of 4, else 1), a workgroup of 256 threads G = 256 / (K / W) rows at a time (one,
+// in several turns, where a row has more than 256 units; the sampled phi step does the same with 1024 threads).  What depends on the topic alone is then computed once per
+// thread, and no element needs a remainder by K.
+template <int W, int THREADS = 256>
+struct RowSplit {
+    int units, groups, unit, group;
+    __device__ __forceinline__ explicit RowSplit(int K)
+    {
+        units = K / W;
+        groups = units >= THREADS ? 1 : THREADS / units;
+        unit = groups == 1 ? (int)threadIdx.x : (int)threadIdx.x % units;
+        group = groups == 1 ? 0 : (int)threadIdx.x / units;
+    }
+};
+inline int rows_at_once(int K) { const int units = K % 4 == 0 ? K / 4 : K; return units >= 256 ? 1 : 256 / units; }
+
+template <int W>
+__device__ __forceinline__ void load_unit(const uint32_t* __restrict__ p, uint32_t (&v)[W])
 {
-    const int r0 = blockIdx.x * rows_per_block;
-    const int r1 = min(V, r0 + rows_per_block);
-    for (int k = threadIdx.x; k < K; k += blockDim.x) {
-        unsigned long long acc = 0ull;
-        for (int r = r0; r < r1; ++r) acc += nwk[(size_t)r * K + k];
-        if (acc) atomicAdd(nk + k, acc);
+    if constexpr (W == 4) {
+        const uint4 q = *reinterpret_cast<const uint4*>(p);
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else {
+        v[0] = *p;
     }
 }
 
-// theta = n_dk / m + alpha   (divide, then add)
-__global__ void theta_update_kernel(const uint32_t* __restrict__ ndk, float* __restrict__ theta,
-                                    size_t n, float mf, float alpha)
+// theta = n_dk / m + alpha   (divide, then add), n elements from thread `first` of `stride` on
+__device__ __forceinline__ void theta_update(const uint32_t* __restrict__ ndk, float* __restrict__ theta, size_t n, float mf, float alpha,
+                                             size_t first, size_t stride)
 {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const float avg = (float)ndk[i] / mf;
-        theta[i] = avg + alpha;
+    const size_t quads = n / 4;
+    for (size_t i = first; i < quads; i += stride) {
+        const uint4 c = reinterpret_cast<const uint4*>(ndk)[i];
+        float4 t;
+        t.x = (float)c.x / mf + alpha;
+        t.y = (float)c.y / mf + alpha;
+        t.z = (float)c.z / mf + alpha;
+        t.w = (float)c.w / mf + alpha;
+        reinterpret_cast<float4*>(theta)[i] = t;
+    }
+    if (first < (n & 3u)) theta[4 * quads + first] = (float)ndk[4 * quads + first] / mf + alpha;
+}
+
+__global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __restrict__ ndk, float* __restrict__ theta,
+                                                          size_t n, float mf, float alpha)
+{
+    theta_update(ndk, theta, n, mf, alpha, (size_t)blockIdx.x * 256u + threadIdx.x, (size_t)gridDim.x * 256u);
+}
+
+// n_k = sum over words of n_wk[w][k], exact in 64-bit integers (any order gives the same value), and, beside it in the
+// same launch, theta.  The first total_blocks workgroups take rows_per_block rows each of the word-count matrix and of
+// the hot words' copies that follow it (row V + copy * hot_max + number; only the n_hot numbers in use), four rows of
+// loads in flight per thread; one 64-bit atomic per topic and workgroup (a few hundred of them: 1563 on every topic's
+// address were most of the 55 us this took at V = 100,000, K = 256).  The other workgroups update theta.
+struct TotalsArgs {
+    const uint32_t* nwk; unsigned long long* nk; int V, K, n_hot, hot_max, hot_copies, rows_per_block, total_blocks;
+    const uint32_t* ndk; float* theta; size_t n_theta; float mf, alpha;
+};
+
+template <int W>
+__global__ __launch_bounds__(256) void totals_theta_kernel(TotalsArgs a)
+{
+    if ((int)blockIdx.x >= a.total_blocks) {
+        theta_update(a.ndk, a.theta, a.n_theta, a.mf, a.alpha, (size_t)(blockIdx.x - a.total_blocks) * 256u + threadIdx.x,
+                     (size_t)(gridDim.x - a.total_blocks) * 256u);
+        return;
+    }
+    __shared__ unsigned long long sh[256 * W];
+    const RowSplit<W> s(a.K);
+    const int rows = a.V + a.n_hot * a.hot_copies;
+    const int r0 = blockIdx.x * a.rows_per_block, r1 = min(rows, r0 + a.rows_per_block);
+    auto row = [&](int r) {
+        int64_t at = r;
+        if (r >= a.V) { const int j = r - a.V; at = a.V + (int64_t)(j / a.n_hot) * a.hot_max + j % a.n_hot; }
+        return a.nwk + (size_t)at * a.K;
+    };
+    for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
+        unsigned long long acc[W] = {};
+        if (s.group < s.groups) {
+            for (int r = r0 + s.group; r < r1; r += 4 * s.groups) {
+                uint32_t v[4][W];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int rj = r + j * s.groups;
+                    load_unit<W>(row(rj < r1 ? rj : r) + W * u, v[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (r + j * s.groups < r1) for (int c = 0; c < W; ++c) acc[c] += v[j][c];
+            }
+        }
+        if (s.groups > 1) {                                        // the row groups' sums of a topic
+            for (int c = 0; c < W; ++c) sh[threadIdx.x * W + c] = acc[c];
+            __syncthreads();
+            if (s.group == 0)
+                for (int g = 1; g < s.groups; ++g)
+                    for (int c = 0; c < W; ++c) acc[c] += sh[(g * s.units + s.unit) * W + c];
+            if (s.group != 0) break;
+        }
+        for (int c = 0; c < W; ++c) if (acc[c]) atomicAdd(a.nk + W * u + c, acc[c]);
     }
 }
 
-// phi_hat = (n_wk/m + beta) / (n_k/m + V*beta);  phi = rho == 1 ? phi_hat : (1-rho)*phi + rho*phi_hat
-__global__ void phi_update_kernel(const uint32_t* __restrict__ nwk, const unsigned long long* __restrict__ nk,
-                                  float* __restrict__ phi, size_t n, int K, float mf, float beta,
-                                  float vbeta, float rho)
+// The copies of a hot word's row (scatter.h): their counts of the W topics from `at` on are added to n and
+// the copies are left clear.  True if there were any.
+template <int W>
+__device__ __forceinline__ bool take_in_copies(uint32_t* __restrict__ nwk, int V, int K, int hot, int hot_max, int hot_copies, int at,
+                                               uint32_t (&n)[W])
 {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    const float one_minus_rho = 1.0f - rho;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const int k = (int)(i % (size_t)K);
-        const float avg_k = (float)nk[k] / mf;
-        const float den = avg_k + vbeta;
-        const float avg = (float)nwk[i] / mf;
-        const float num = avg + beta;
-        const float hat = num / den;
-        if (rho == 1.0f) {
-            phi[i] = hat;
-        } else {
-            const float keep = one_minus_rho * phi[i];
-            const float add = rho * hat;
-            phi[i] = keep + add;
+    uint32_t any = 0u;
+    for (int copy = 0; copy < hot_copies; ++copy) {
+        uint32_t* p = nwk + ((size_t)V + (size_t)copy * hot_max + hot) * K + at;
+        uint32_t v[W];
+        load_unit<W>(p, v);
+        for (int c = 0; c < W; ++c) { if (v[c]) p[c] = 0u; n[c] += v[c]; any |= v[c]; }
+    }
+    return any != 0u;
+}
+
+// phi_hat = (n_wk/m + beta) / (n_k/m + V*beta);  phi = rho == 1 ? phi_hat : (1-rho)*phi + rho*phi_hat.
+// A hot word's row first takes in its copies, which are left clear.
+struct PhiArgs {
+    uint32_t* nwk; const unsigned long long* nk; float* phi; const int16_t* hot_of;   // hot_of null: no hot words
+    int V, K, hot_max, hot_copies, rows_per_block;
+    float mf, beta, vbeta, rho;
+};
+
+template <int W>
+__global__ __launch_bounds__(256) void phi_update_kernel(PhiArgs a)
+{
+    const RowSplit<W> s(a.K);
+    if (s.group >= s.groups) return;
+    const int r0 = blockIdx.x * a.rows_per_block, r1 = min(a.V, r0 + a.rows_per_block);
+    const float one_minus_rho = 1.0f - a.rho;
+    for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
+        float den[W];
+#pragma unroll
+        for (int c = 0; c < W; ++c) den[c] = (float)a.nk[W * u + c] / a.mf + a.vbeta;
+        for (int r = r0 + s.group; r < r1; r += s.groups) {
+            const size_t at = (size_t)r * a.K + W * u;
+            uint32_t n[W];
+            load_unit<W>(a.nwk + at, n);
+            const int hot = a.hot_of ? (int)a.hot_of[r] : -1;
+            if (hot >= 0 && take_in_copies<W>(a.nwk, a.V, a.K, hot, a.hot_max, a.hot_copies, W * u, n))
+                for (int c = 0; c < W; ++c) a.nwk[at + c] = n[c];
+            float hat[W];
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                const float num = (float)n[c] / a.mf + a.beta;
+                hat[c] = num / den[c];
+            }
+            if (a.rho != 1.0f) {
+#pragma unroll
+                for (int c = 0; c < W; ++c) {
+                    const float keep = one_minus_rho * a.phi[at + c];
+                    const float add = a.rho * hat[c];
+                    hat[c] = keep + add;
+                }
+            }
+            if constexpr (W == 4) *reinterpret_cast<float4*>(a.phi + at) = make_float4(hat[0], hat[1], hat[2], hat[3]);
+            else a.phi[at] = hat[0];
         }
     }
 }
+
+// finish(k, sum over b of partial[b][k]) for every topic: 8 topics per workgroup of 256 threads, 32 threads each over every
+// 32nd block sum, whose results are added in a fixed order (sums repeat from run to run).  One thread per topic, as it
+// was, is a chain of `blocks` dependent loads: 190 to 370 us for 782 to 1563 blocks, 9 us so.
+template <class Finish>
+__device__ __forceinline__ void column_sums(const double* __restrict__ partial, int blocks, int K, Finish finish)
+{
+    __shared__ double sh[32][8];
+    const int c = threadIdx.x & 7, slice = threadIdx.x >> 3;
+    const int k = blockIdx.x * 8 + c;
+    double acc = 0.0;
+    if (k < K) for (int b = slice; b < blocks; b += 32) acc += partial[(size_t)b * K + k];
+    sh[slice][c] = acc;
+    __syncthreads();
+    if (slice == 0 && k < K) {
+        for (int s = 1; s < 32; ++s) acc += sh[s][c];
+        finish(k, acc);
+    }
+}
+inline unsigned column_sum_blocks(int K) { return (unsigned)((K + 7) / 8); }
 
 // log of each document's theta total (double, summed left to right)
 __global__ void doc_log_total_kernel(const float* __restrict__ theta, int D, int K, double* __restrict__ out)

@@ -40,14 +40,10 @@ __global__ __launch_bounds__(256) void vb_colsum_kernel(const float* __restrict_
     }
 }
 
-// psi_total[k] = psi(sum_w lambda[w][k]): the block sums are added in block order (results repeat from run to run)
-__global__ void vb_colpsi_kernel(const double* __restrict__ partial, int blocks, int K, double* __restrict__ psi_total)
+// psi_total[k] = psi(sum_w lambda[w][k])
+__global__ __launch_bounds__(256) void vb_colpsi_kernel(const double* __restrict__ partial, int blocks, int K, double* __restrict__ psi_total)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= K) return;
-    double s = 0.0;
-    for (int b = 0; b < blocks; ++b) s += partial[(size_t)b * K + k];
-    psi_total[k] = digamma_d(s);
+    column_sums(partial, blocks, K, [&](int k, double sum) { psi_total[k] = digamma_d(sum); });
 }
 
 // One wave per word: e_k = psi(lambda[w][k]) - psi_total[k] (= E[log beta_kw]); shift[w] = max_k e_k;
