@@ -172,8 +172,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     int32_t next = (int32_t)((int64_t)blockIdx.x * a.first < a.n ? (int64_t)blockIdx.x * a.first : a.n);
     int32_t end = (int32_t)((int64_t)next + a.first < a.n ? (int64_t)next + a.first : a.n);
     bool drained = false;                                          // nothing is left to take
-    uint32_t chunk_next = 0, chunk_end = 0;                        // the wave's share of the chunk pool not yet handed out
-    bool pool_dry = a.chunks == nullptr;                           // the pool has no chunk left for this wave
+    ChunkSupply supply(a);
     acc[lane * kStride] = 0u;
 
     // ---- the lane's current task
@@ -183,7 +182,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     bool open = false;      // a task was taken and its slot of the pair list is not yet closed
     int32_t d = 0, w = 0;
     Scatter sc;
-    sc.drow = 0; sc.wrow = kNone; sc.slot = kNone; sc.npairs = 0;
+    sc.drow = 0; sc.dst = nullptr; sc.npairs = 0;
     Staged staged;          // its last pairs, on their way to the pair list
     StreamKey key;
     key.seed_lo = a.seed_lo; key.seed_hi = a.seed_hi; key.tau_lo = 0; key.tau_hi = 0; key.pass = a.pass;
@@ -220,7 +219,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     // per half-wave: lane hl of a half owns block hl), each new lane turns its sums into running sums.
     auto refill = [&](uint64_t idle_mask) {
         const bool idle = (idle_mask >> lane) & 1ull;
-        if (idle && open) { sc.close(a, true, staged); open = false; }
+        if (idle && open) { sc.close(true, staged); open = false; }
         const int rank = (int)__popcll(idle_mask & ((1ull << lane) - 1ull));
         const int avail = end - next;
         const bool take = idle && rank < avail;
@@ -233,7 +232,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
 #ifdef SAME_STATS
             R_task_g = a.t_g[tau];
 #endif
-            sc = make_scatter<DEBUG>(a, pos, tau, d, w);
+            sc = make_scatter<DEBUG>(a, pos, tau, d);
             key.tau_lo = (uint32_t)tau; key.tau_hi = (uint32_t)((uint64_t)tau >> 32) & 0xFFu;
             pre = primary_pre(key);
             open = true;
@@ -762,27 +761,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                 }
             }
         }
-        if (!DEBUG && !pool_dry) {
-            // lanes whose slot (or chunk) is full go on in a new chunk: the wave hands out consecutive chunks of its
-            // share of the pool and takes the next kChunkBatch from the pool's counter when they do not suffice
-            const bool need = en > 0u && sc.full();
-            const uint64_t need_mask = __ballot(need);
-            if (need_mask != 0) {
-                const uint32_t cnt = (uint32_t)__popcll((unsigned long long)need_mask);
-                if (chunk_end - chunk_next < cnt) {
-                    uint32_t first = 0;
-                    if (lane == 0) first = atomicAdd(a.chunk_counter, (uint32_t)kChunkBatch);
-                    first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
-                    pool_dry = first >= a.n_chunks;
-                    chunk_next = pool_dry ? 0u : first;
-                    chunk_end = pool_dry ? 0u : (a.n_chunks - first < (uint32_t)kChunkBatch ? a.n_chunks : first + (uint32_t)kChunkBatch);
-                    if (lane == 0) SAME_COUNT(a, 14, 1);               // batches of chunks taken
-                }
-                const uint32_t mine = chunk_next + (uint32_t)__popcll((unsigned long long)(need_mask & ((1ull << lane) - 1ull)));
-                if (need && mine < chunk_end) { sc.extend(a, mine, staged); SAME_COUNT(a, 15, 1); }
-                chunk_next = chunk_end - chunk_next < cnt ? chunk_end : chunk_next + cnt;
-            }
-        }
+        if (!DEBUG) supply.give(a, lane, sc, en > 0u && sc.full(), staged);
 #ifdef SAME_STATS
         if (en > 0u && sc.full()) {                                // a count that goes straight to the word's row
             const uint32_t g = R_task_g;
@@ -793,7 +772,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
         if (en > 0u) {
             if (myrow >= 0) atomicAdd(rows + myrow * K + ek, en);
             else atomicAdd(a.ndk + (size_t)sc.drow * K + ek, en);
-            sc.emit_word(a, ek, en, staged);
+            sc.emit_word(a, ek, en, w, staged);
         }
     };
 
@@ -833,7 +812,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
         trip();
         trips += 1;
     }
-    if (open) sc.close(a, true, staged);
+    if (open) sc.close(true, staged);
     if (n_rows > 0 && tag0 >= 0) flush_row(0, tag0);
     if (n_rows > 1 && tag1 >= 0) flush_row(1, tag1);
 }

@@ -109,6 +109,7 @@ __global__ __launch_bounds__(256) void gamma_theta_kernel(const uint32_t* __rest
 // chains of arithmetic, and the block sums' scratch fixes the number of workgroups, not that of waves.
 constexpr int kGammaThreads = 1024;
 __global__ __launch_bounds__(kGammaThreads) void gamma_phi_kernel(uint32_t* __restrict__ nwk, const int16_t* __restrict__ hot_of,
+                                                                 const uint32_t* __restrict__ hot_used,
                                                                  int hot_max, int hot_copies, float* __restrict__ phi, int V, int K,
                                                                  float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass,
                                                                  int rows_per_block, double* __restrict__ partial)
@@ -117,13 +118,14 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_phi_kernel(uint32_t* __re
     const RowSplit<1, kGammaThreads> s(K);
     const int r0 = blockIdx.x * rows_per_block;
     const int r1 = min(V, r0 + rows_per_block);
+    const bool copies = hot_of != nullptr && *hot_used != 0u;
     for (int k = s.unit; k < K; k += s.groups == 1 ? kGammaThreads : K) {
         double acc = 0.0;
         if (s.group < s.groups) {
             for (int r = r0 + s.group; r < r1; r += s.groups) {
                 const size_t i = (size_t)r * K + k;
                 uint32_t n[1] = {nwk[i]};
-                const int hot = hot_of ? (int)hot_of[r] : -1;
+                const int hot = copies ? (int)hot_of[r] : -1;
                 if (hot >= 0 && take_in_copies<1>(nwk, V, K, hot, hot_max, hot_copies, k, n)) nwk[i] = n[0];
                 const float g = gamma_variable((float)n[0] + prior, seed_lo, seed_hi, (uint32_t)r, (uint32_t)k, pass);
                 phi[i] = g;

@@ -111,7 +111,9 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
     const float Nf = live ? a.mf * (float)a.t_g[tau] : 0.0f;
     const float* __restrict__ th = a.theta + (size_t)d * K;
     const float* __restrict__ ph = a.phi + (size_t)w * K;
-    Scatter sc = make_scatter<DEBUG>(a, row, tau, d, w);
+    Scatter sc = make_scatter<DEBUG>(a, row, tau, d);
+    if (!live) sc.dst = nullptr;                                   // (the last task's slot is its own lane's)
+    ChunkSupply supply(a);
     Staged staged;
     acc[lane] = 0u;
 
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
     // Variables cut into pieces.  The pieces are independent (own uniform each): those of all the
     // lanes in state 3 are numbered consecutively and dealt out over the 64 lanes; every owner
     // receives the total of its pieces through an LDS counter.
-    auto pool = [&](uint64_t pend) {
+    auto pool = [&](uint64_t pend) -> uint32_t {
         const uint32_t mine = (st == 3) ? np : 0u;
         uint32_t total = 0;
         for (uint64_t p = pend; p != 0; p &= p - 1) total += __shfl(mine, __ffsll((unsigned long long)p) - 1);
@@ -194,13 +196,14 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
             }
         }
         __syncthreads();
+        uint32_t nk = 0;
         if (st == 3) {
-            const uint32_t nk = acc[lane];
+            nk = acc[lane];
             acc[lane] = 0u;
-            if (nk > 0) { sc.emit(a, kk, nk, staged); SAME_COUNT(a, 5, 1); }
             st = 0;
         }
         __syncthreads();
+        return nk;
     };
 
     // One trip of the machine for the whole wave: lanes in state 0 take their next queued topic,
@@ -209,6 +212,8 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
     auto trip = [&]() {
         if (lane == 0) SAME_COUNT(a, 2, 1);
         busy += (st != 0 || cnt > 0) ? 1u : 0u;
+        uint32_t en = 0;        // the count this trip settles for this lane: en copies to topic kk_done
+        int kk_done = 0;
         if (st == 0 && cnt > 0) {
             const float wq = __uint_as_float(que[(qh * qw + 0) * kWave + lane]);
             const float Mq = __uint_as_float(que[(qh * qw + 1) * kWave + lane]);
@@ -235,7 +240,7 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
         }
         {
             const uint64_t pend = __ballot(st == 3);
-            if (pend != 0 && (__popcll((unsigned long long)pend) >= kPoolMin || !__any(st == 1))) pool(pend);
+            if (pend != 0 && (__popcll((unsigned long long)pend) >= kPoolMin || !__any(st == 1))) { en = pool(pend); kk_done = kk; }
         }
         if (__any(st == 1)) {
             const bool walking = st == 1;
@@ -254,9 +259,15 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
                 stalled = stalled || (go && still);
             }
             if (walking && (stalled || !(u > cdf))) {              // the piece is finished
-                if (xw > 0) { sc.emit(a, kk, xw, staged); SAME_COUNT(a, 5, 1); }
+                en = xw; kk_done = kk;
                 st = 0;
             }
+        }
+        if (!DEBUG) supply.give(a, lane, sc, en > 0u && sc.full(), staged);
+        if (en > 0u) {
+            SAME_COUNT(a, 5, 1);
+            atomicAdd(a.ndk + (size_t)sc.drow * a.K + kk_done, en);
+            sc.emit_word(a, kk_done, en, w, staged);
         }
     };
 
@@ -298,7 +309,7 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
         }
     }
     while (__any(st != 0 || cnt > 0)) trip();
-    sc.close(a, live, staged);
+    sc.close(live, staged);
     // The ordering key for the next pass: a running mean (weight 1/4 on this pass) predicts a task's next
     // cost a little better than this pass's cost alone.
     if (!DEBUG && live && a.cost) a.cost[tau] = (3u * a.cost[tau] + busy + 2u) >> 2;

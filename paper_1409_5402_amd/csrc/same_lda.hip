@@ -53,7 +53,7 @@ struct Matrix {
     float*    theta = nullptr;     // [D][K]
     uint32_t* ndk = nullptr;       // [D][K]
     // pair list of the word-count update (training matrices only; absent if it did not fit)
-    uint32_t* pairs = nullptr;     // [n_tasks][kPairWords]
+    uint32_t* pairs = nullptr;     // [n_slots][kSlotWords]
     int64_t   n_slots = 0;         // tasks of frequent words, each with a slot
     int32_t*  t_slot = nullptr;    // [n_tasks] slot of each task (rank in (word, task id) order), -1 if none
     int32_t*  slot_word = nullptr; // [n_slots] word of each slot
@@ -126,8 +126,8 @@ struct same_lda {
     float* phi = nullptr;          // [V][K]
     uint32_t* nwk = nullptr;       // [V][K]
     unsigned long long* nk = nullptr;  // [K]
-    uint32_t* draw_counter = nullptr;  // counters of the draw kernel: tickets (kCounterWords) and chunks taken (one word) by a
-                                       // launch on the handle's stream, tickets of a launch on the copy stream
+    uint32_t* draw_counter = nullptr;  // counters of the draw kernel: tickets (kCounterWords), chunks taken and the hot words' mark
+                                       // (a word each) of a launch on the handle's stream, tickets of a launch on the copy stream
     uint32_t* chunks = nullptr;        // pool of chunks that continue full pair-list slots (launches on the handle's stream)
     uint32_t n_chunks = 0;             // chunks allocated
     int64_t chunk_limit = -1;          // chunks a launch may use (-1: all of them); lowered by tests of the fallback
@@ -236,7 +236,7 @@ hipError_t exclusive_sum(Temps& tmp, const uint32_t* in, uint32_t* out, size_t n
 // than a quarter of the free device memory.  A failed allocation leaves the handle without a pool.
 void ensure_chunks(same_lda* h, int64_t n_slots)
 {
-    const int64_t per_slot_most = ((int64_t)h->K - 1) / (same::kPairWords - 1);      // ceil((K - 15) / 15), 0 up to K = 15
+    const int64_t per_slot_most = h->K <= 3 ? 0 : ((int64_t)h->K - 3 + 14) / 15;     // a task places at most K pairs, three in its slot
     const int64_t per_slot = per_slot_most < 8 ? per_slot_most : 8;
     int64_t want = n_slots * per_slot;
     if (want > 0) want += 64 * (int64_t)same::kChunkBatch;                            // unused ends of the waves' shares
@@ -416,7 +416,7 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
             HIP_TRY(h, hipStreamSynchronize(st));
             M.n_slots = (int64_t)stats.n_slots;
             ok = M.n_slots > 0 &&
-                 h->cache.get(reinterpret_cast<void**>(&M.pairs), (size_t)M.n_slots * same::kPairWords * sizeof(uint32_t)) == hipSuccess;
+                 h->cache.get(reinterpret_cast<void**>(&M.pairs), (size_t)M.n_slots * same::kSlotWords * sizeof(uint32_t)) == hipSuccess;
             if (ok) ensure_chunks(h, M.n_slots);
         }
         if (!ok) {
@@ -427,7 +427,7 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
     }
     HIP_TRY(h, hipStreamSynchronize(st));   // the temporaries are handed back on return
     // blocks worth keeping for the next matrix of this size: the matrix itself and the temporaries
-    const size_t matrix_bytes = (size_t)nnz * 12 + n * 28 + (size_t)M.n_slots * 68 + (size_t)D * K * 8;
+    const size_t matrix_bytes = (size_t)nnz * 12 + n * 28 + (size_t)M.n_slots * 20 + (size_t)D * K * 8;
     if (h->cache.limit < 2 * matrix_bytes + ((size_t)1 << 30)) h->cache.limit = 2 * matrix_bytes + ((size_t)1 << 30);
     return SAME_LDA_OK;
 }
@@ -485,7 +485,8 @@ int check_m(same_lda* h, int32_t m, const Matrix& M)
 // The multinomial kernel's counters for a launch on st, which must be zero when it starts.  Launches on the copy stream
 // have no pair list and therefore no use for the chunk pool: they run beside launches on the handle's stream, which own it.
 bool beside(const same_lda* h, hipStream_t st) { return st == h->copy_stream && st != h->stream; }
-size_t counter_words(const same_lda* h, hipStream_t st) { return beside(h, st) ? same::kCounterWords : same::kCounterWords + 1; }
+size_t counter_words(const same_lda* h, hipStream_t st) { return beside(h, st) ? same::kCounterWords : same::kCounterWords + 2; }
+uint32_t* hot_used(const same_lda* h) { return h->draw_counter + same::kCounterWords + 1; }
 
 void assign_counters(same_lda* h, same::DrawArgs& a, hipStream_t st)
 {
@@ -523,6 +524,7 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         const int64_t blocks = (a.n + T - 1) / T;
         if (blocks >= (int64_t)1 << 31) return fail(h, SAME_LDA_EINVAL, "too many draw tasks for one launch");
         dim3 grid((unsigned)blocks);
+        a.chunk_share = (uint32_t)(a.n_chunks / 2 / blocks);
         const size_t lds = same::poisson_lds_bytes();
         if (a.K == 256)            hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 256>), grid, block, lds, st, a);
         else if (a.K % same::kBlk == 0) hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG>), grid, block, lds, st, a);
@@ -554,6 +556,7 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         if (rc) return rc;
         const same::Shares sh = same::shares_for(a.n, resident);
         a.first = sh.first;
+        a.chunk_share = a.n_chunks / 2 / (uint32_t)sh.waves;
         void* args[] = {&a};
         HIP_TRY(h, hipLaunchKernel(f, dim3((unsigned)sh.waves), block, args, lds, st));
     }
@@ -578,13 +581,15 @@ same::DrawArgs draw_args(const same_lda* h, const Matrix& M, Copies c, uint32_t 
     a.t_slot = M.t_slot;
     // the chunk pool continues full slots in the multinomial kernel
     const uint32_t usable = h->chunk_limit >= 0 && h->chunk_limit < (int64_t)h->n_chunks ? (uint32_t)h->chunk_limit : h->n_chunks;
-    const bool pool = a.pairs && !c.poisson && h->chunks && usable > 0;
+    const bool pool = a.pairs && h->chunks && usable > 0;
     a.chunks = pool ? h->chunks : nullptr;
     a.chunk_counter = nullptr;
     a.n_chunks = pool ? usable : 0u;
+    a.chunk_share = 0;
     a.K = h->K; a.m = c.m; a.mf = c.mf; a.seed_lo = (uint32_t)h->seed; a.seed_hi = (uint32_t)(h->seed >> 32);
     a.pass = pass_word;
     a.V = h->V;
+    a.hot_used = h->draw_counter + same::kCounterWords + 1;
     a.hot_of = (with_words && M.n_hot > 0) ? M.hot_of : nullptr;
 #ifdef SAME_STATS
     a.stats = g_stats;
@@ -619,7 +624,7 @@ int update_theta(same_lda* h, Matrix& M, float m, hipStream_t st)
 int update_totals(same_lda* h, Matrix* M, int32_t n_hot, float m, hipStream_t st)
 {
     same::TotalsArgs a;
-    a.nwk = h->nwk; a.nk = h->nk; a.V = h->V; a.K = h->K;
+    a.nwk = h->nwk; a.nk = h->nk; a.V = h->V; a.K = h->K; a.hot_used = hot_used(h);
     a.n_hot = n_hot; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
     // at least two turns of four rows per thread, and at most 512 workgroups (64-bit atomics per topic)
     const int rows = h->V + n_hot * same::kHotCopies, at_once = 8 * same::rows_at_once(h->K);
@@ -642,7 +647,7 @@ int update_collapsed(same_lda* h, Matrix& M, float m, float rho, hipStream_t st)
     int rc = update_totals(h, &M, n_hot, m, st);
     if (rc) return rc;
     same::PhiArgs a;
-    a.nwk = h->nwk; a.nk = h->nk; a.phi = h->phi; a.hot_of = n_hot > 0 ? M.hot_of : nullptr;
+    a.nwk = h->nwk; a.nk = h->nk; a.phi = h->phi; a.hot_of = n_hot > 0 ? M.hot_of : nullptr; a.hot_used = hot_used(h);
     a.V = h->V; a.K = h->K; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
     a.mf = m; a.beta = h->beta; a.vbeta = (float)h->V * h->beta; a.rho = rho;
     // up to eight rows per thread, fewer where that leaves less than four workgroups per compute unit
@@ -675,7 +680,7 @@ int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_
     // the topic totals are part of the readable state, kept current as after a collapsed update
     const int rc = update_totals(h, nullptr, M.n_hot, m, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(same::gamma_phi_kernel, dim3(blocks), dim3(same::kGammaThreads), 0, st, h->nwk, M.n_hot > 0 ? M.hot_of : nullptr,
+    hipLaunchKernelGGL(same::gamma_phi_kernel, dim3(blocks), dim3(same::kGammaThreads), 0, st, h->nwk, M.n_hot > 0 ? M.hot_of : nullptr, hot_used(h),
                        same::kHotMax, same::kHotCopies, h->phi, h->V, h->K, m * h->beta, (uint32_t)h->seed, (uint32_t)(h->seed >> 32),
                        pword, kGammaRows, h->gamma_partial);
     hipLaunchKernelGGL(same::gamma_phi_totals_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, st, h->gamma_partial,

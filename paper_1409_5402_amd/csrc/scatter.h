@@ -13,9 +13,10 @@ namespace same {
 #define SAME_POOL_MIN 8
 #endif
 constexpr int kWave = 64;               // lanes per workgroup (one wave)
-constexpr int kPairWords = 16;          // words of a pair-list slot: up to 15 (topic, count) pairs and a header
-constexpr uint32_t kPairLink = 0x80000000u;   // header bit: the slot is full and the chunk named by the other bits goes on
-constexpr int kChunkBatch = 256;        // chunks a wave takes from the pool at a time
+constexpr int kSlotWords = 4;           // words of a pair-list slot: up to 3 (topic, count) pairs and a header
+constexpr int kPairWords = 16;          // words of a chunk that continues it: up to 15 pairs and a header
+constexpr uint32_t kFirstPair = kPairWords - kSlotWords;   // a slot is filled and written like the last quarter of a chunk
+constexpr uint32_t kPairLink = 0x80000000u;   // header bit: slot or chunk is full and the chunk named by the other bits goes on
 constexpr int kPairShift = 11;          // a pair is topic | count << 11 (topics < 2048, counts < 2^21)
 constexpr int kWalkSteps = SAME_WALK_STEPS;   // pmf steps per trip of a draw machine
 constexpr float kPieceMean = 32.0f;     // a binomial / Poisson variable whose mean exceeds this is cut into pieces
@@ -35,16 +36,18 @@ struct DrawArgs {
     const float*    phi;        // [V][K]
     uint32_t*       ndk;        // [D][K]   (debug launches: [n][K] output rows)
     uint32_t*       nwk;        // [V][K] or null
-    uint32_t*       pairs;      // [n_slots][kPairWords] pair list in word order, or null (update nwk directly)
+    uint32_t*       pairs;      // [n_slots][kSlotWords] pair list in word order, or null (update nwk directly)
     const int32_t*  t_slot;     // [n_tasks] slot of each task in the pair list, -1 for a task without one
     uint32_t*       chunks;     // [n_chunks][kPairWords] pool of chunks that continue full slots, or null
     uint32_t*       chunk_counter;  // first chunk of the pool not yet taken by a wave (zero at launch)
     uint32_t        n_chunks;   // chunks in the pool (below 2^31)
+    uint32_t        chunk_share;    // chunks that are each workgroup's own; the rest is taken from the counter in batches
     int32_t         K;
     uint32_t        m;          // copies per token (multinomial form)
     float           mf;         // copies per token (Poisson form: any positive real)
     uint32_t        seed_lo, seed_hi, pass;
     int32_t         V;          // rows of nwk that are words; the copies of the hot words' rows follow them
+    uint32_t*       hot_used;   // set when a copy of a hot word's row has taken a count (zero at launch)
     const int16_t*  hot_of;     // [V] index of a hot word among the hot words, -1 for the others (null: no hot words)
 #ifdef SAME_STATS
     unsigned long long* stats;  // profiling builds only: event counters
@@ -69,14 +72,14 @@ constexpr int kHotCopies = 32;          // copies of a hot word's row
 // several waves may hold tasks of one document).  The word's row is updated either the same way or, when
 // the launch has a pair list, later by word_reduce_kernel: the task records (topic, count) in its slot of
 // the list (slots are in word order), so that the scattered updates of [V][K] become one streaming pass
-// with all updates of a row close together.  A slot is 16 words: 15 pairs and, last, a header.  A task that
-// places more than 15 pairs (most tasks do while the posterior is still flat) continues in chunks of the same
-// shape taken from a pool: the header of a full slot or chunk names the chunk that follows it, the header of
-// the last one holds its number of pairs.  When the pool is used up the remaining counts go straight to the
-// word's row.  The last pairs are kept in three registers that shift, and written four at a time with one
-// 16-byte store: the memory system handles a 16-byte write as fast as a 4-byte one.
-constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr uint32_t kInPool = 0x80000000u;   // Scatter::slot: the index is one of the pool's chunks, not of the pair list's slots
+// with all updates of a row close together.  A slot is four words: three pairs and, last, a header.  A task that
+// places more than three pairs continues in chunks of 15 pairs and a header taken from a pool: the header of a full
+// slot or chunk names the chunk that follows it, the header of the last one tells its number of pairs.  When the
+// pool is used up the remaining counts go straight to the word's row.  The last pairs are kept in three registers that
+// shift, and written four words at a time with one 16-byte store: the memory system handles a 16-byte write as fast as
+// a 4-byte one.  So a task of up to three pairs costs one scattered 16-byte store, and the pass over the list reads
+// 16 bytes for it.  (Slots of 16 words took a second scattered store for the header and 64 bytes to read for every
+// task, most of which place one to four pairs.)  Chunks are consecutive for the lanes of a wave: dense stores.
 
 // The last three pairs of a task, the newest in p2: the npairs & 3 of them that are not yet written are among them.
 struct Staged {
@@ -88,91 +91,111 @@ struct Staged {
     }
 };
 
-// The struct holds row and slot numbers, not addresses: a lane keeps it for the whole life of its task, and
-// registers decide how many waves a compute unit holds.
+// The place of the next four pairs is kept as an address: computing it from a slot number again for every store took
+// some ten vector instructions in nearly every trip of the draw machine (some lane stores in most).
 struct Scatter {
     uint32_t drow;      // row of a.ndk that takes the counts (the document; debug launches: the task's output row)
-    uint32_t wrow;      // row of a.nwk that takes direct updates (the word, or this workgroup's copy of a hot word's row), kNone: none
-    uint32_t slot;      // the slot (or, with kInPool, the chunk) the task is filling, kNone: none
-    uint32_t npairs;    // pairs in it
+    uint4* dst;         // where the next four words go, in a slot of the pair list or a chunk; null: the task has no slot
+    uint32_t npairs;    // pairs in that chunk (in a slot: kFirstPair more than there are)
 
-    __device__ __forceinline__ uint32_t* slot_words(const DrawArgs& a) const
+    // straight to row w of the word counts, or to this workgroup's copy of it if the word is hot
+    __device__ __forceinline__ void emit_row(const DrawArgs& a, int k, uint32_t n, int32_t w) const
     {
-        uint32_t* base = (slot & kInPool) ? a.chunks : a.pairs;
-        return base + (size_t)(slot & ~kInPool) * kPairWords;
+        const int hot = a.hot_of ? (int)a.hot_of[w] : -1;
+        size_t row = (size_t)w;
+        if (hot >= 0) {
+            row = (size_t)a.V + (size_t)(blockIdx.x % kHotCopies) * kHotMax + (size_t)hot;
+            *a.hot_used = 1u;
+        }
+        atomicAdd(a.nwk + row * a.K + k, n);
     }
-    // words 4q .. 4q+3 of the slot
-    __device__ __forceinline__ void store_quad(const DrawArgs& a, uint32_t q, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) const
+    // the word's half of a count (the caller adds it to the document's row itself)
+    __device__ __forceinline__ void emit_word(const DrawArgs& a, int k, uint32_t n, int32_t w, Staged& t)
     {
-        *reinterpret_cast<uint4*>(slot_words(a) + 4u * q) = make_uint4(w0, w1, w2, w3);
-    }
-    __device__ __forceinline__ void emit(const DrawArgs& a, int k, uint32_t n, Staged& t)
-    {
-        atomicAdd(a.ndk + (size_t)drow * a.K + k, n);
-        emit_word(a, k, n, t);
-    }
-    // the word's half alone (the caller has added the count to the document's row itself)
-    __device__ __forceinline__ void emit_word(const DrawArgs& a, int k, uint32_t n, Staged& t)
-    {
-        if (slot != kNone) {
-            if (npairs < (uint32_t)(kPairWords - 1)) {
-                const uint32_t pair = (uint32_t)k | (n << kPairShift);
-                if ((npairs & 3u) == 3u) store_quad(a, npairs >> 2, t.p0, t.p1, t.p2, pair);   // pairs 0-3, 4-7 or 8-11
-                t.push(pair);
-                npairs += 1;
-            } else {
-                atomicAdd(a.nwk + (size_t)wrow * a.K + k, n);      // full and no chunk to go on with: straight to the row
-            }
-        } else if (wrow != kNone) {
-            atomicAdd(a.nwk + (size_t)wrow * a.K + k, n);
+        if (dst != nullptr && npairs < (uint32_t)(kPairWords - 1)) {
+            const uint32_t pair = (uint32_t)k | (n << kPairShift);
+            if ((npairs & 3u) == 3u) { *dst = make_uint4(t.p0, t.p1, t.p2, pair); dst += 1; }   // a chunk's pairs 0-3, 4-7 or 8-11
+            t.push(pair);
+            npairs += 1;
+        } else if (a.nwk != nullptr) {
+            emit_row(a, k, n, w);                                  // no slot, or full and no chunk to go on with
         }
     }
-    __device__ __forceinline__ bool full() const { return slot != kNone && npairs >= (uint32_t)(kPairWords - 1); }
-    // a full slot (pairs 12-14 are not yet written) goes on in chunk idx of the pool
+    __device__ __forceinline__ bool full() const { return dst != nullptr && npairs >= (uint32_t)(kPairWords - 1); }
+    // a full slot or chunk (its last three pairs are not yet written) goes on in chunk idx of the pool
     __device__ __forceinline__ void extend(const DrawArgs& a, uint32_t idx, const Staged& t)
     {
-        store_quad(a, 3u, t.p0, t.p1, t.p2, kPairLink | idx);
-        slot = kInPool | idx;
+        *dst = make_uint4(t.p0, t.p1, t.p2, kPairLink | idx);
+        dst = reinterpret_cast<uint4*>(a.chunks + (size_t)idx * kPairWords);
         npairs = 0;
     }
     // the unwritten pairs and the header of the last slot or chunk: how many pairs it holds
-    __device__ __forceinline__ void close(const DrawArgs& a, bool live, const Staged& t) const
+    __device__ __forceinline__ void close(bool live, const Staged& t) const
     {
-        if (slot != kNone && live) {
+        if (dst != nullptr && live) {
             // the j unwritten pairs come first in their quad; words past the last pair are never read
             const uint32_t q = npairs >> 2, j = npairs & 3u;
             const uint32_t x0 = t.p0, x1 = t.p1, x2 = t.p2;
             const uint32_t w0 = j == 1u ? x2 : (j == 2u ? x1 : x0), w1 = j == 2u ? x2 : x1;
-            if (j != 0u || q == 3u) store_quad(a, q, w0, w1, x2, npairs);   // q = 3: the header shares the last quad
-            if (q != 3u) slot_words(a)[kPairWords - 1] = npairs;
+            if (j != 0u || q == 3u) *dst = make_uint4(w0, w1, x2, npairs);   // q = 3: the header shares the last quad
+            if (q != 3u) reinterpret_cast<uint32_t*>(dst)[kPairWords - 1 - 4u * q] = npairs;
         }
     }
 };
 
 template <bool DEBUG>
-__device__ __forceinline__ Scatter make_scatter(const DrawArgs& a, int64_t row, int64_t tau, int32_t d, int32_t w)
+__device__ __forceinline__ Scatter make_scatter(const DrawArgs& a, int64_t row, int64_t tau, int32_t d)
 {
     Scatter s;
     s.drow = DEBUG ? (uint32_t)row : (uint32_t)d;
-    s.wrow = kNone;
-    s.slot = kNone;
-    if (!DEBUG && a.nwk != nullptr) {
-        const int hot = a.hot_of ? (int)a.hot_of[w] : -1;
-        s.wrow = hot < 0 ? (uint32_t)w : (uint32_t)a.V + (uint32_t)(blockIdx.x % kHotCopies) * (uint32_t)kHotMax + (uint32_t)hot;
-        if (a.pairs != nullptr) {
-            const int32_t slot_id = a.t_slot[tau];
-            if (slot_id >= 0) s.slot = (uint32_t)slot_id;
-        }
+    s.dst = nullptr;
+    s.npairs = kFirstPair;
+    if (!DEBUG && a.pairs != nullptr) {
+        const int32_t slot_id = a.t_slot[tau];
+        if (slot_id >= 0) s.dst = reinterpret_cast<uint4*>(a.pairs + (size_t)slot_id * kSlotWords);
     }
-    s.npairs = 0;
     return s;
 }
+
+// A wave's chunks: its own share of the pool (half the pool is shared out that way: a launch rarely needs more, and the
+// counter's atomics are returning ones on one address, 16 ns each), then batches from the counter.
+constexpr uint32_t kChunkBatch = 256;
+struct ChunkSupply {
+    uint32_t next, end;     // not yet handed out
+    bool dry;               // the pool has none left for this wave
+    __device__ __forceinline__ explicit ChunkSupply(const DrawArgs& a)
+    {
+        next = end = 0u;
+        dry = a.chunks == nullptr;
+        if (!dry) { next = blockIdx.x * a.chunk_share; end = next + a.chunk_share; }
+    }
+    // Whole wave: lanes that need one (their slot or chunk is full) go on in a new chunk.
+    __device__ __forceinline__ void give(const DrawArgs& a, int lane, Scatter& sc, bool need, const Staged& staged)
+    {
+        if (dry) return;
+        const uint64_t need_mask = __ballot(need);
+        if (need_mask == 0) return;
+        const uint32_t cnt = (uint32_t)__popcll((unsigned long long)need_mask);
+        if (end - next < cnt) {
+            uint32_t first = 0;
+            if (lane == 0) first = atomicAdd(a.chunk_counter, kChunkBatch);
+            first = gridDim.x * a.chunk_share + (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+            dry = first >= a.n_chunks;
+            next = dry ? 0u : first;
+            end = dry ? 0u : (a.n_chunks - first < kChunkBatch ? a.n_chunks : first + kChunkBatch);
+            if (lane == 0) SAME_COUNT(a, 14, 1);                   // batches of chunks taken
+        }
+        const uint32_t mine = next + (uint32_t)__popcll((unsigned long long)(need_mask & ((1ull << lane) - 1ull)));
+        if (need && mine < end) { sc.extend(a, mine, staged); SAME_COUNT(a, 15, 1); }
+        next = end - next < cnt ? end : next + cnt;
+    }
+};
 
 // Adds the recorded pairs to the word rows.  Slots are in word order and exist only for words with
 // at least kSlotMinTasks tasks: a workgroup takes kReduceChunk consecutive slots, sums the pairs of
 // the first `rows` words it meets in an LDS table and sends the rest straight to [V][K]; the table is
-// then added to the rows it stands for.  A thread reads a slot with four 16-byte loads and starts with the
-// quad picked by its index: tasks of one word have their large counts at the same topics in the same places
+// then added to the rows it stands for.  A thread reads a slot with one 16-byte load, a chunk with four, and starts with
+// the quad of a chunk picked by its index: tasks of one word have their large counts at the same topics in the same places
 // of their slots, and aligned walks would meet at one address.
 constexpr int kReduceChunk = 2048;       // slots per workgroup of a long list; shorter lists take fewer (reduce_chunk)
 constexpr int kSlotMinTasks = 2;         // (32 measured 1.5 % slower on the resident matrix and 5 % on a minibatch: the direct
@@ -191,29 +214,33 @@ __global__ __launch_bounds__(kReduceThreads) void word_reduce_kernel(const uint3
     for (int i = threadIdx.x; i < rows * K; i += blockDim.x) tab[i] = 0u;
     __syncthreads();
     for (int64_t s = s0 + threadIdx.x; s < s1; s += blockDim.x) {
-        const uint32_t* __restrict__ src = pairs + (size_t)s * kPairWords;
+        const uint4 slot = reinterpret_cast<const uint4*>(pairs)[s];
         const int32_t w = slot_word[s];
         const bool in_tab = w - w0 < rows;
         uint32_t* dst = in_tab ? tab + (size_t)(w - w0) * K : nwk + (size_t)w * K;
-        const uint32_t t = threadIdx.x & 3u;                       // which quad of the slot this thread starts with
-        for (;;) {                                                 // the slot, then the chunks that continue it
-            const uint4* __restrict__ s4 = reinterpret_cast<const uint4*>(src);
-            uint4 q[4];                                            // the whole slot: four 16-byte loads in flight
+        auto add = [&](uint32_t p) { atomicAdd(dst + (p & ((1u << kPairShift) - 1u)), p >> kPairShift); };
+        uint32_t head = slot.w;
+        {
+            const uint32_t cnt = (head & kPairLink) ? 3u : head - kFirstPair;   // 0 to 3
+            if (cnt > 0u && cnt <= 3u) add(slot.x);
+            if (cnt > 1u && cnt <= 3u) add(slot.y);
+            if (cnt == 3u) add(slot.z);
+        }
+        const uint32_t t = threadIdx.x & 3u;                       // which quad of a chunk this thread starts with
+        while ((head & kPairLink) != 0u && (head & ~kPairLink) < n_chunks) {   // the chunks that continue the slot
+            const uint4* __restrict__ s4 = reinterpret_cast<const uint4*>(chunks + (size_t)(head & ~kPairLink) * kPairWords);
+            uint4 q[4];                                            // the whole chunk: four 16-byte loads in flight
 #pragma unroll
             for (uint32_t i = 0; i < 4u; ++i) q[i] = s4[(t + i) & 3u];
-            const uint32_t head = t == 0u ? q[3].w : (t == 1u ? q[2].w : (t == 2u ? q[1].w : q[0].w));
-            const bool linked = (head & kPairLink) != 0u;
-            const uint32_t cnt = (linked || head > (uint32_t)(kPairWords - 1)) ? (uint32_t)(kPairWords - 1) : head;
+            head = t == 0u ? q[3].w : (t == 1u ? q[2].w : (t == 2u ? q[1].w : q[0].w));
+            const uint32_t cnt = ((head & kPairLink) != 0u || head > (uint32_t)(kPairWords - 1)) ? (uint32_t)(kPairWords - 1) : head;
 #pragma unroll
             for (uint32_t i = 0; i < 4u; ++i) {
                 const uint32_t first = 4u * ((t + i) & 3u);        // index of the quad's first pair
                 const uint32_t p[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
 #pragma unroll
-                for (uint32_t j = 0; j < 4u; ++j)
-                    if (first + j < cnt) atomicAdd(dst + (p[j] & ((1u << kPairShift) - 1u)), p[j] >> kPairShift);
+                for (uint32_t j = 0; j < 4u; ++j) if (first + j < cnt) add(p[j]);
             }
-            if (!linked || (head & ~kPairLink) >= n_chunks) break;
-            src = chunks + (size_t)(head & ~kPairLink) * kPairWords;
         }
     }
     __syncthreads();

@@ -152,6 +152,7 @@ __global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __res
 // address were most of the 55 us this took at V = 100,000, K = 256).  The other workgroups update theta.
 struct TotalsArgs {
     const uint32_t* nwk; unsigned long long* nk; int V, K, n_hot, hot_max, hot_copies, rows_per_block, total_blocks;
+    const uint32_t* hot_used;              // 0: the copies have taken nothing
     const uint32_t* ndk; float* theta; size_t n_theta; float mf, alpha;
 };
 
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(256) void totals_theta_kernel(TotalsArgs a)
     }
     __shared__ unsigned long long sh[256 * W];
     const RowSplit<W> s(a.K);
-    const int rows = a.V + a.n_hot * a.hot_copies;
+    const int rows = a.V + (a.n_hot > 0 && *a.hot_used != 0u ? a.n_hot * a.hot_copies : 0);
     const int r0 = blockIdx.x * a.rows_per_block, r1 = min(rows, r0 + a.rows_per_block);
     auto row = [&](int r) {
         int64_t at = r;
@@ -206,11 +207,19 @@ __device__ __forceinline__ bool take_in_copies(uint32_t* __restrict__ nwk, int V
                                                uint32_t (&n)[W])
 {
     uint32_t any = 0u;
-    for (int copy = 0; copy < hot_copies; ++copy) {
-        uint32_t* p = nwk + ((size_t)V + (size_t)copy * hot_max + hot) * K + at;
-        uint32_t v[W];
-        load_unit<W>(p, v);
-        for (int c = 0; c < W; ++c) { if (v[c]) p[c] = 0u; n[c] += v[c]; any |= v[c]; }
+    uint32_t* first = nwk + ((size_t)V + (size_t)hot) * K + at;
+    const size_t step = (size_t)hot_max * K;
+    constexpr int kTurn = 8;                                       // copies whose loads are in flight together
+    for (int copy = 0; copy < hot_copies; copy += kTurn) {
+        uint32_t v[kTurn][W];
+#pragma unroll
+        for (int j = 0; j < kTurn; ++j) load_unit<W>(first + (size_t)(copy + j) * step, v[j]);
+#pragma unroll
+        for (int j = 0; j < kTurn; ++j)
+            for (int c = 0; c < W; ++c) {
+                if (v[j][c]) first[(size_t)(copy + j) * step + c] = 0u;
+                n[c] += v[j][c]; any |= v[j][c];
+            }
     }
     return any != 0u;
 }
@@ -219,6 +228,7 @@ __device__ __forceinline__ bool take_in_copies(uint32_t* __restrict__ nwk, int V
 // A hot word's row first takes in its copies, which are left clear.
 struct PhiArgs {
     uint32_t* nwk; const unsigned long long* nk; float* phi; const int16_t* hot_of;   // hot_of null: no hot words
+    const uint32_t* hot_used;              // 0: their copies have taken nothing
     int V, K, hot_max, hot_copies, rows_per_block;
     float mf, beta, vbeta, rho;
 };
@@ -229,6 +239,7 @@ __global__ __launch_bounds__(256) void phi_update_kernel(PhiArgs a)
     const RowSplit<W> s(a.K);
     if (s.group >= s.groups) return;
     const int r0 = blockIdx.x * a.rows_per_block, r1 = min(a.V, r0 + a.rows_per_block);
+    const bool copies = a.hot_of != nullptr && *a.hot_used != 0u;
     const float one_minus_rho = 1.0f - a.rho;
     for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
         float den[W];
@@ -238,7 +249,7 @@ __global__ __launch_bounds__(256) void phi_update_kernel(PhiArgs a)
             const size_t at = (size_t)r * a.K + W * u;
             uint32_t n[W];
             load_unit<W>(a.nwk + at, n);
-            const int hot = a.hot_of ? (int)a.hot_of[r] : -1;
+            const int hot = copies ? (int)a.hot_of[r] : -1;
             if (hot >= 0 && take_in_copies<W>(a.nwk, a.V, a.K, hot, a.hot_max, a.hot_copies, W * u, n))
                 for (int c = 0; c < W; ++c) a.nwk[at + c] = n[c];
             float hat[W];

@@ -36,3 +36,30 @@ def test_every_position_is_drawn_once(n):
         assert np.array_equal(g.get(binding.NDK), o.ndk)
         assert np.array_equal(g.get(binding.NWK), o.nwk)
     g.close()
+
+
+@pytest.mark.parametrize("form", ["multinomial", "poisson"])
+@pytest.mark.parametrize("limit", [-1, 0, 7, 300])
+def test_pairs_beyond_a_slot(form, limit):
+    """Tasks of zero to some forty pairs: three fit a slot, the rest goes on in chunks of 15 (chains of up to three) or,
+    where the pool is used up or lowered to nothing, to the word rows - hot words' copies among them (twelve words)."""
+    rng = np.random.default_rng(31)
+    counts = rng.integers(0, 9, size=(300, 12))
+    cols = [np.flatnonzero(r) for r in counts]
+    X = oracle.CSC(300, 12, np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32),
+                   np.concatenate(cols).astype(np.int32), counts[counts > 0].astype(np.float32))
+    K = 40
+    o = oracle.OracleLDA(X, K, 0.4, 0.05, seed=9, m0=1, G=3)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.4, 0.05, 9, 1, 3)
+    g.debug_chunk_limit(limit)
+    for m in (60, 1, 20):
+        if form == "poisson":
+            o.sweep_poisson(m * 0.7)
+            g.sweep_poisson(m * 0.7)
+        else:
+            o.sweep(m)
+            g.sweep(m)
+        assert np.array_equal(g.get(binding.NDK), o.ndk)
+        assert np.array_equal(g.get(binding.NWK), o.nwk)
+        np.testing.assert_allclose(g.get(binding.PHI), o.phi, rtol=1e-6)
+    g.close()
