@@ -38,10 +38,15 @@
 namespace same {
 
 constexpr int kMaxBlocks = 32;                  // blocks of topics per task (= lanes of a half-wave)
-constexpr int kSumStride = kMaxBlocks + 1;      // words between the block sums of two tasks in LDS: lanes that
-                                                // read the same block of 64 different tasks hit 32 different banks
+constexpr int kSumStride = kMaxBlocks + 1;      // words between the block sums of two tasks in LDS (more than 64 topics): lanes
+                                                // that read the same block of 64 different tasks hit 32 different banks
 
 __host__ __device__ inline int block_len(int K) { return 4 * ((K + 127) / 128); }
+
+// Lanes that scan a task, and words between the sums of two tasks in LDS: a power of two that covers the blocks of up to
+// 128 topics (blocks of four: one 16-byte load per lane and matrix), 32 beyond, and a padding word.
+__host__ __device__ inline int scan_lanes(int K) { return K <= 16 ? 4 : (K <= 32 ? 8 : (K <= 64 ? 16 : kMaxBlocks)); }
+__host__ __device__ inline int sum_stride(int K) { return scan_lanes(K) + 1; }
 
 // Rows of document counts a wave keeps in LDS: two up to K = 128, one up to K = 1024 (4 KB at most), none beyond.
 // A second row at K = 256 would serve the waves that straddle two documents, but its kilobyte costs two of the
@@ -63,6 +68,33 @@ __device__ __forceinline__ float top_position(float U, uint32_t R, float u)
     float y = (R == 1u) ? U * u : U * e;
     if (!(y > 0.0f)) y = U;
     return y;
+}
+
+// Four consecutive floats of a row of K at topic e.  ALIGNED (K is a multiple of 4): one aligned load, zeros from K on.
+// Else: one load that needs only the alignment of a float, moved back where it would leave the row; shift_quad then puts
+// the four products in their places.
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <bool ALIGNED, bool WHOLE>
+__device__ __forceinline__ float4 load_quad(const float* __restrict__ row, int e, int K)
+{
+    if constexpr (ALIGNED) {
+        return (WHOLE || e < K) ? *reinterpret_cast<const float4*>(row + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+        const float4_any v = *reinterpret_cast<const float4_any*>(row + (e < K - 4 ? e : K - 4));
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+}
+// x holds the values of topics min(e, K-4) ..: moves them so that x[0] is topic e's; topics from K on are zero
+template <bool ALIGNED>
+__device__ __forceinline__ void shift_quad(float (&x)[4], int e, int K)
+{
+    if constexpr (!ALIGNED) {
+        const int s = e - (K - 4);                                 // places to move by, none if negative
+        const bool one = s > 0 && (s & 1) != 0, two = s > 0 && (s & 2) != 0, all = s >= 4;
+        x[0] = one ? x[1] : x[0]; x[1] = one ? x[2] : x[1]; x[2] = one ? x[3] : x[2]; x[3] = one ? 0.f : x[3];
+        x[0] = two ? x[2] : x[0]; x[1] = two ? x[3] : x[1]; x[2] = two ? 0.f : x[2]; x[3] = two ? 0.f : x[3];
+        x[0] = all ? 0.f : x[0]; x[1] = all ? 0.f : x[1]; x[2] = all ? 0.f : x[2]; x[3] = all ? 0.f : x[3];
+    }
 }
 
 // The first of N ascending values (N a power of two) that reaches y, when the last one is known to: its index; prev
@@ -93,6 +125,9 @@ constexpr int kRefillLateTrips = 8;
 // lanes waited at any time for eight to gather.  (1, 2, 4, 8 trips: 9.62, 9.59, 9.80, 10.4 ms there against 12.4 without
 // the limit; converged 11.02, 10.83, 10.73, 10.73 ms.)
 constexpr int kPoolTrips = 4;
+#ifndef SAME_W1
+#define SAME_W1 4
+#endif
 
 // VEC: K is a multiple of 4 (16-byte loads), else element-wise loads (TB = 0).  TB: 16-byte loads per matrix that
 // a lane has in flight at a time: a block of T = 4 ceil(K / 128) topics is read in T / (4 TB) batches of TB loads
@@ -146,12 +181,13 @@ __device__ __forceinline__ int32_t share_of_round(int32_t first, int round)
 }
 
 template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 2 ? 4 : 3)))) void draw_kernel(DrawArgs a)
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB == 1 && ONE ? SAME_W1 : (TB <= 2 || (TB == 4 && ONE) ? 4 : 3))))) void draw_kernel(DrawArgs a)
 {
     extern __shared__ uint32_t lds[];
-    constexpr int kStride = UNIFORM ? 1 : kSumStride;              // (weights of one need no sums)
+    constexpr bool SMALL = !UNIFORM && KC == 0 && (TB == 0 || (TB == 1 && ONE));   // up to 128 topics: blocks of four
+    const int kStride = UNIFORM ? 1 : (SMALL ? sum_stride(a.K) : kSumStride);      // (weights of one need no sums)
     float* sums = reinterpret_cast<float*>(lds);                   // [64 lanes][kStride]: block sums, then running sums
-    uint32_t* acc = lds + (UNIFORM ? 0 : kMaxBlocks);              // piece totals by owner lane: lane l's is acc[l * kStride],
+    uint32_t* acc = lds + (kStride - 1);                           // piece totals by owner lane: lane l's is acc[l * kStride],
                                                                    // the word of its row of sums that pads the stride
     const int lane = threadIdx.x;
     const int K = KC > 0 ? KC : a.K;                              // KC: the number of topics where it is known at compile time
@@ -280,7 +316,59 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                 if (rem) { lb = __ffsll((unsigned long long)rem) - 1; rem &= rem - 1; }
                 return half ? lb : la;
             };
-            if (VEC && TB > 0) {
+            if constexpr (SMALL && TB > 0) {
+                // Up to 128 topics: scan_lanes lanes of the wave per task, 64 / scan_lanes tasks per load.  The words and
+                // documents of the new tasks are brought into the order of their ranks first (a lane of rank r keeps
+                // task r's), so that a group of lanes finds its next task by a lane-to-lane read.
+                const int per = scan_lanes(K), at_once = kWave / per;
+                const int sub = lane & (per - 1), grp = lane / per, n_new = (int)__popcll((unsigned long long)fresh);
+                const int to = (take ? rank : 63) * 4;             // idle lanes that took nothing all write to lane 63 ...
+                int who = __builtin_amdgcn_ds_permute(to, take ? lane : -1);
+                if (n_new < kWave && lane >= n_new) who = 0;       // ... which then has no task of its own
+                const int32_t w_r = __shfl(w, who), d_r = __shfl(d, who);
+                const int e = 4 * sub;
+                auto fetch = [&](int i, float4& p, float4& t, int& src) {
+                    int r = i * at_once + grp;
+                    r = r < n_new ? r : n_new - 1;                 // past the last one: its task once more
+                    const int32_t pw = __shfl(w_r, r), pd = __shfl(d_r, r);
+                    src = __shfl(who, r);
+                    p = load_quad<VEC, false>(a.phi + (size_t)pw * K, e, K);
+                    t = load_quad<VEC, false>(a.theta + (size_t)pd * K, e, K);
+                };
+                auto total = [&](const float4& p, const float4& t, int src) {
+                    float x[4] = {t.x * p.x, t.y * p.y, t.z * p.z, t.w * p.w};
+                    shift_quad<VEC>(x, e, K);
+                    float rs = 0.0f + x[0];
+                    rs = rs + x[1];
+                    rs = rs + x[2];
+                    rs = rs + x[3];
+                    if (sub < nblk) sums[src * kStride + sub] = rs;
+                };
+                if (n_new > 0) {
+                    float4 p0, t0, p1, t1;
+                    int s0, s1;
+                    const int turns = (n_new + at_once - 1) / at_once;
+                    fetch(0, p0, t0, s0);
+                    int i = 0;
+                    for (; i + 2 < turns; i += 2) {                // the loads of the next turn behind every sum
+                        fetch(i + 1, p1, t1, s1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        total(p0, t0, s0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        fetch(i + 2, p0, t0, s0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        total(p1, t1, s1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (i + 1 < turns) {
+                        fetch(i + 1, p1, t1, s1);
+                        total(p0, t0, s0);
+                        total(p1, t1, s1);
+                    } else {
+                        total(p0, t0, s0);
+                    }
+                }
+            } else if constexpr (TB > 0) {
                 // Where every block is whole (K = 32 T: 256 at T = 8) the loads need no bounds.  Blocks of one batch
                 // (ONE) and of two batches of four loads go through the pipeline in run(); blocks of other shapes load
                 // the next batch into a second set of registers before the current one is summed (the load there sits
@@ -297,17 +385,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                         const int32_t pd = __shfl(d, it.src), pw = __shfl(w, it.src);
                         const int kb = COAL ? 128 * TB * it.b + 4 * hl : k0 + 4 * TB * it.b;
                         constexpr int kStep = COAL ? 128 : 4;      // topics between two loads of a lane
-                        const float* __restrict__ tp = a.theta + (size_t)pd * K + kb;
-                        const float* __restrict__ pp = a.phi + (size_t)pw * K + kb;
 #pragma unroll
                         for (int c = 0; c < TB; ++c) {
-                            if (WHOLE || kb + 4 * c < K) {
-                                pv[c] = *reinterpret_cast<const float4*>(pp + kStep * c);
-                                tv[c] = *reinterpret_cast<const float4*>(tp + kStep * c);
-                            } else {
-                                pv[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-                                tv[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-                            }
+                            pv[c] = load_quad<VEC, WHOLE>(a.phi + (size_t)pw * K, kb + kStep * c, K);
+                            tv[c] = load_quad<VEC, WHOLE>(a.theta + (size_t)pd * K, kb + kStep * c, K);
                         }
                     };
                     float rs = 0.0f;
@@ -317,12 +398,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                             // add its products left to right, the running sum handed from lane to lane.  Every lane
                             // runs all kNL stages; stage j is meaningful in the block's lane j, and the block's last lane
                             // ends with the same sum, rounded in the same order, as one lane that adds the block alone.
-                            constexpr int kNL = KC / 128;
-                            static_assert(!COAL || (KC >= 256 && KC % 128 == 0 && 16 % (KC / 128) == 0), "blocks must not straddle loads");
+                            constexpr int kNL = ONE ? TB : 2 * TB; // lanes per block of 16 (one batch) or 32 topics (two)
+                            static_assert(!COAL || TB == 4, "blocks must not straddle loads");
 #pragma unroll
                             for (int c = 0; c < TB; ++c) {
-                                const float x0 = tv[c].x * pv[c].x, x1 = tv[c].y * pv[c].y;
-                                const float x2 = tv[c].z * pv[c].z, x3 = tv[c].w * pv[c].w;
+                                float x[4] = {tv[c].x * pv[c].x, tv[c].y * pv[c].y, tv[c].z * pv[c].z, tv[c].w * pv[c].w};
+                                shift_quad<VEC>(x, 128 * (TB * it.b + c) + 4 * hl, K);
+                                const float x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
                                 float s = 0.0f;
 #pragma unroll
                                 for (int j = 0; j < kNL; ++j) {
@@ -333,18 +415,20 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                                     s = s + x3;
                                 }
                                 if ((hl & (kNL - 1)) == kNL - 1)
-                                    sums[it.src * kSumStride + (TB * it.b + c) * (32 / kNL) + hl / kNL] = s;
+                                    sums[it.src * kStride + (TB * it.b + c) * (32 / kNL) + hl / kNL] = s;
                             }
                             return;
                         }
 #pragma unroll
                         for (int c = 0; c < TB; ++c) {
-                            rs = rs + tv[c].x * pv[c].x;
-                            rs = rs + tv[c].y * pv[c].y;
-                            rs = rs + tv[c].z * pv[c].z;
-                            rs = rs + tv[c].w * pv[c].w;
+                            float x[4] = {tv[c].x * pv[c].x, tv[c].y * pv[c].y, tv[c].z * pv[c].z, tv[c].w * pv[c].w};
+                            shift_quad<VEC>(x, k0 + 4 * (TB * it.b + c), K);
+                            rs = rs + x[0];
+                            rs = rs + x[1];
+                            rs = rs + x[2];
+                            rs = rs + x[3];
                         }
-                        if (it.last) { sums[it.src * kSumStride + hl] = rs; rs = 0.0f; }
+                        if (it.last) { sums[it.src * kStride + hl] = rs; rs = 0.0f; }
                     };
                     // Blocks of one batch, or of two (K = 1024).  The new tasks of a refill are worked off in runs whose
                     // document stays the same (a document's tasks are consecutive): the run's theta values are loaded once,
@@ -383,8 +467,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                             const int kb = kb0 + kBatch * bt;
 #pragma unroll
                             for (int c = 0; c < TB; ++c)
-                                p[c] = (WHOLE || kb + 4 * c < K) ? *reinterpret_cast<const float4*>(row_cur + kb + kStep * c)
-                                                                  : make_float4(0.f, 0.f, 0.f, 0.f);
+                                p[c] = load_quad<VEC, WHOLE>(row_cur, kb + kStep * c, K);
                         };
                         auto sum_batch = [&](const float4* p, int src, int bt) {
                             Item it{src, bt, bt == NB - 1, true};
@@ -412,9 +495,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                                 for (int bt = 0; bt < NB; ++bt)
 #pragma unroll
                                     for (int c = 0; c < TB; ++c) {
-                                        const int kb = kb0 + kBatch * bt;
-                                        tv[bt][c] = (WHOLE || kb + 4 * c < K) ? *reinterpret_cast<const float4*>(tp + kb + kStep * c)
-                                                                               : make_float4(0.f, 0.f, 0.f, 0.f);
+                                        tv[bt][c] = load_quad<VEC, WHOLE>(tp, kb0 + kBatch * bt + kStep * c, K);
                                     }
                                 held = doc;
                             }
@@ -465,33 +546,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                         consume(pb, tb, nxt);
                     }
                 };
-                if (nblk * T == K) run(std::true_type{}); else run(std::false_type{});
-            } else {
+                if (KC > 0 || (VEC && !COAL && nblk * T == K)) run(std::true_type{}); else run(std::false_type{});
+            } else {   // fewer than four topics
                 while (fresh) {
                     const int src = pick(fresh);
                     const int32_t pd = __shfl(d, src), pw = __shfl(w, src);
                     const float* __restrict__ tp = a.theta + (size_t)pd * K;
                     const float* __restrict__ pp = a.phi + (size_t)pw * K;
                     float rs = 0.0f;
-                    if (VEC) {
-                        for (int c = 0; c < T / 4; ++c) {
-                            const int k = k0 + 4 * c;
-                            if (k < K) {
-                                const float4 x = *reinterpret_cast<const float4*>(pp + k);
-                                const float4 t = *reinterpret_cast<const float4*>(tp + k);
-                                rs = rs + t.x * x.x;
-                                rs = rs + t.y * x.y;
-                                rs = rs + t.z * x.z;
-                                rs = rs + t.w * x.w;
-                            }
-                        }
-                    } else {
-                        for (int j = 0; j < T; ++j) {
-                            const int k = k0 + j;
-                            if (k < K) rs = rs + tp[k] * pp[k];
-                        }
-                    }
-                    sums[src * kSumStride + hl] = rs;
+                    for (int j = 0; j < T; ++j) if (k0 + j < K) rs = rs + tp[k0 + j] * pp[k0 + j];
+                    if (hl < nblk) sums[src * kStride + hl] = rs;
                 }
             }
         }
@@ -502,11 +566,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                 run = (float)K;                                    // weights of one need no sums
             } else {
                 for (int l = 0; l < nblk; ++l) {
-                    run = run + sums[lane * kSumStride + l];
-                    sums[lane * kSumStride + l] = run;
+                    run = run + sums[lane * kStride + l];
+                    sums[lane * kStride + l] = run;
                 }
                 // the steps' search probes up to the next power of two
-                if (KC == 0) for (int l = nblk; (l & (l - 1)) != 0; ++l) sums[lane * kSumStride + l] = run;
+                if (KC == 0) for (int l = nblk; (l & (l - 1)) != 0; ++l) sums[lane * kStride + l] = run;
             }
             U = run;
         }
@@ -606,7 +670,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                 } else {
                     // the first block whose cumulative weight reaches y (S_31 >= U >= y; entries past the last block
                     // repeat it), and prev = the cumulative weight below that block
-                    const float* S = sums + lane * kSumStride;
+                    const float* S = sums + lane * kStride;
                     int l = 0;
 #pragma unroll
                     for (int h = kMaxBlocks / 2; h > 0; h >>= 1) {
@@ -624,7 +688,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     const float* __restrict__ ph = a.phi + (size_t)w * K;
                     const float base = prev;
                     float rs = 0.0f;
-                    if (VEC && TB > 0) {
+                    if (TB > 0) {
                         auto reload = [&](auto whole) {
                             constexpr bool WHOLE = decltype(whole)::value;
                             constexpr int N = TB > 0 ? 4 * TB : 4;
@@ -636,17 +700,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                                 float4 pv[N / 4], tv[N / 4];
 #pragma unroll
                                 for (int c = 0; c < N / 4; ++c) {
-                                    const bool in = WHOLE || kb + 4 * c < K;
-                                    pv[c] = in ? *reinterpret_cast<const float4*>(ph + kb + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                                    tv[c] = in ? *reinterpret_cast<const float4*>(th + kb + 4 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+                                    pv[c] = load_quad<VEC, WHOLE>(ph, kb + 4 * c, K);
+                                    tv[c] = load_quad<VEC, WHOLE>(th, kb + 4 * c, K);
                                 }
                                 float P[N];
 #pragma unroll
                                 for (int c = 0; c < N / 4; ++c) {
-                                    rs = rs + tv[c].x * pv[c].x; P[4 * c + 0] = base + rs;
-                                    rs = rs + tv[c].y * pv[c].y; P[4 * c + 1] = base + rs;
-                                    rs = rs + tv[c].z * pv[c].z; P[4 * c + 2] = base + rs;
-                                    rs = rs + tv[c].w * pv[c].w; P[4 * c + 3] = base + rs;
+                                    float x[4] = {tv[c].x * pv[c].x, tv[c].y * pv[c].y, tv[c].z * pv[c].z, tv[c].w * pv[c].w};
+                                    shift_quad<VEC>(x, kb + 4 * c, K);
+                                    rs = rs + x[0]; P[4 * c + 0] = base + rs;
+                                    rs = rs + x[1]; P[4 * c + 1] = base + rs;
+                                    rs = rs + x[2]; P[4 * c + 2] = base + rs;
+                                    rs = rs + x[3]; P[4 * c + 3] = base + rs;
                                 }
                                 if (ONE) {
                                     at = first_reaching<N>(P, y, prev);
@@ -663,7 +728,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                             }
                             k = k0 + at;
                         };
-                        if (nblk * T == K) reload(std::true_type{}); else reload(std::false_type{});
+                        if (KC > 0 || (VEC && nblk * T == K)) reload(std::true_type{}); else reload(std::false_type{});
                     } else {
                         int at = 0;
                         auto visit = [&](float wk) {
@@ -817,6 +882,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     if (n_rows > 1 && tag1 >= 0) flush_row(1, tag1);
 }
 
-inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kWave * (size_t)(uniform ? 1 : kSumStride) + (size_t)doc_rows(K) * (size_t)K); }
+inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kWave * (size_t)(uniform ? 1 : sum_stride(K)) + (size_t)doc_rows(K) * (size_t)K); }
 
 }  // namespace same

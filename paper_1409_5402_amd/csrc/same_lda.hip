@@ -514,6 +514,19 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t
     return SAME_LDA_OK;
 }
 
+// The draw kernel for blocks of 4 * quads topics, read in batches of tb quads (VEC: rows are aligned to 16 bytes).
+template <bool VEC, bool DEBUG>
+const void* draw_kernel_for(int quads, int tb)
+{
+    if (quads == 1)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, true>);
+    if (quads == 2)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 2, true>);
+    if (quads == 4)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, true, 0, true>);
+    if (quads == 8)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, false, 0, true>);
+    if (tb == 1)                 return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, false>);
+    if (tb == 2)                 return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 2, false>);
+    return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, false>);
+}
+
 template <bool DEBUG>
 int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipStream_t st)
 {
@@ -533,22 +546,16 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         // blocks of 4 * ceil(K / 128) topics, read in batches of one, two or four 16-byte loads per matrix
         // (K = 512 and K = 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
         // kernel is bound by vector-ALU issue, the extra additions of that form cost more than the fewer cache lines save)
-        const bool vec = a.K % 4 == 0;
         const int quads = same::block_len(a.K) / 4;                // 16-byte loads per block and matrix
         const int tb = quads % 4 == 0 ? 4 : (quads % 2 == 0 ? 2 : 1);
-        const bool one = quads == tb;
-        const void* f;
+        const void* f = nullptr;
         if (uniform)             f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
-        else if (!vec)           f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
-        else if (tb == 1 && one) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 1, true>);
+        else if (a.K < 4)        f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
         else if (a.K == 256)     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true, 256>);
         else if (a.K == 1024)    f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false, 1024, true>);
         else if (a.K == 512)     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true>);
-        else if (tb == 2 && one) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true>);
-        else if (tb == 4 && one) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true>);
-        else if (tb == 1)        f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 1, false>);
-        else if (tb == 2)        f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, false>);
-        else                     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false>);
+        else if (a.K % 4 == 0)   f = draw_kernel_for<true, DEBUG>(quads, tb);
+        else                     f = draw_kernel_for<false, DEBUG>(quads, tb);
         // As many one-wave workgroups as the chip holds at once, each with a share of the positions.
         const size_t lds = same::draw_lds_bytes(a.K, uniform);
         int64_t resident = 0;
