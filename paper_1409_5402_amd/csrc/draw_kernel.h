@@ -97,20 +97,21 @@ __device__ __forceinline__ void shift_quad(float (&x)[4], int e, int K)
     }
 }
 
-// The first of N ascending values (N a power of two) that reaches y, when the last one is known to: its index; prev
+// The first of N ascending values that reaches y, when the last one is known to: its index; prev
 // becomes the value before it (it comes in as the value before the first).  A search whose answer stays in registers: at
 // N = 8 it takes 3 comparisons and 10 selections where a walk along the values takes 7 and 14.
 template <int N>
 __device__ __forceinline__ int first_reaching(float (&P)[N], float y, float& prev)
 {
+    constexpr int M = N <= 4 ? 4 : (N <= 8 ? 8 : (N <= 16 ? 16 : 32));
     int idx = 0;
 #pragma unroll
-    for (int h = N / 2; h > 0; h >>= 1) {
-        const bool below = !(P[h - 1] >= y);
-        prev = below ? P[h - 1] : prev;
+    for (int h = M / 2; h > 0; h >>= 1) {
+        const bool below = h <= N && !(P[h <= N ? h - 1 : 0] >= y);    // (N is no power of two: the last value stands for the rest)
+        prev = below ? P[h <= N ? h - 1 : 0] : prev;
         idx = below ? idx + h : idx;
 #pragma unroll
-        for (int j = 0; j < h - 1; ++j) P[j] = below ? P[j + h] : P[j];
+        for (int j = 0; j < h - 1; ++j) if (j < N) P[j] = below ? P[j + h < N ? j + h : N - 1] : P[j];
     }
     return idx;
 }
@@ -125,9 +126,6 @@ constexpr int kRefillLateTrips = 8;
 // lanes waited at any time for eight to gather.  (1, 2, 4, 8 trips: 9.62, 9.59, 9.80, 10.4 ms there against 12.4 without
 // the limit; converged 11.02, 10.83, 10.73, 10.73 ms.)
 constexpr int kPoolTrips = 4;
-#ifndef SAME_W1
-#define SAME_W1 4
-#endif
 
 // VEC: K is a multiple of 4 (16-byte loads), else element-wise loads (TB = 0).  TB: 16-byte loads per matrix that
 // a lane has in flight at a time: a block of T = 4 ceil(K / 128) topics is read in T / (4 TB) batches of TB loads
@@ -181,7 +179,7 @@ __device__ __forceinline__ int32_t share_of_round(int32_t first, int round)
 }
 
 template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB == 1 && ONE ? SAME_W1 : (TB <= 2 || (TB == 4 && ONE) ? 4 : 3))))) void draw_kernel(DrawArgs a)
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 3 || KC == 512 ? 4 : 3)))) void draw_kernel(DrawArgs a)
 {
     extern __shared__ uint32_t lds[];
     constexpr bool SMALL = !UNIFORM && KC == 0 && (TB == 0 || (TB == 1 && ONE));   // up to 128 topics: blocks of four

@@ -514,17 +514,28 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t
     return SAME_LDA_OK;
 }
 
-// The draw kernel for blocks of 4 * quads topics, read in batches of tb quads (VEC: rows are aligned to 16 bytes).
+// The draw kernel for blocks of 4 * quads topics (VEC: rows are aligned to 16 bytes).  Up to 896 topics a block is one batch
+// of loads, up to 1024 two in the contiguous form, beyond that batches of the largest of 4, 2, 1 that divides it.  The
+// debug hook draws a handful of tasks: one kernel for all blocks of more than one quad.
 template <bool VEC, bool DEBUG>
-const void* draw_kernel_for(int quads, int tb)
+const void* draw_kernel_for(int quads)
 {
-    if (quads == 1)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, true>);
-    if (quads == 2)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 2, true>);
-    if (quads == 4)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, true, 0, true>);
-    if (quads == 8)              return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, false, 0, true>);
-    if (tb == 1)                 return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, false>);
-    if (tb == 2)                 return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 2, false>);
-    return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, false>);
+    if (quads == 1) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, true>);
+    if constexpr (!DEBUG) {
+        switch (quads) {
+            case 2:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 2, true>);
+            case 3:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 3, true>);
+            case 4:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 4, true>);
+            case 5:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 5, true>);
+            case 6:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 6, true>);
+            case 7:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 7, true>);
+            case 8:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 4, false, 0, true>);
+            default: break;
+        }
+        if (quads % 4 == 0) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 4, false>);
+        if (quads % 2 == 0) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 2, false>);
+    }
+    return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, false>);
 }
 
 template <bool DEBUG>
@@ -547,15 +558,14 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         // (K = 512 and K = 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
         // kernel is bound by vector-ALU issue, the extra additions of that form cost more than the fewer cache lines save)
         const int quads = same::block_len(a.K) / 4;                // 16-byte loads per block and matrix
-        const int tb = quads % 4 == 0 ? 4 : (quads % 2 == 0 ? 2 : 1);
         const void* f = nullptr;
-        if (uniform)             f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
-        else if (a.K < 4)        f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
-        else if (a.K == 256)     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true, 256>);
-        else if (a.K == 1024)    f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false, 1024, true>);
-        else if (a.K == 512)     f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true>);
-        else if (a.K % 4 == 0)   f = draw_kernel_for<true, DEBUG>(quads, tb);
-        else                     f = draw_kernel_for<false, DEBUG>(quads, tb);
+        if (uniform)      f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
+        else if (a.K < 4) f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
+        else if (!DEBUG && a.K == 256)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, false, 2, true, 256>);
+        else if (!DEBUG && a.K == 512)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, false, 4, true, 512, true>);
+        else if (!DEBUG && a.K == 1024) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, false, 4, false, 1024, true>);
+        else if (a.K % 4 == 0) f = draw_kernel_for<true, DEBUG>(quads);
+        else                   f = draw_kernel_for<false, DEBUG>(quads);
         // As many one-wave workgroups as the chip holds at once, each with a share of the positions.
         const size_t lds = same::draw_lds_bytes(a.K, uniform);
         int64_t resident = 0;
@@ -737,8 +747,8 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
     if (a.pairs && a.n > 0) {
         const int chunk = same::reduce_chunk(M.n_slots), rows = same::reduce_rows(h->K, chunk);
         const int64_t blocks = (M.n_slots + chunk - 1) / chunk;
-        hipLaunchKernelGGL(same::word_reduce_kernel, dim3((unsigned)blocks), dim3((unsigned)(chunk / 2)),
-                           (size_t)rows * h->K * sizeof(uint32_t), st, a.pairs, a.chunks, a.n_chunks, M.slot_word, M.n_slots,
+        hipLaunchKernelGGL(same::word_reduce_kernel, dim3((unsigned)blocks), dim3((unsigned)(chunk / 2 < same::kReduceThreads ? chunk / 2 : same::kReduceThreads)),
+                           (size_t)rows * (h->K + 1) * sizeof(uint32_t), st, a.pairs, a.chunks, a.n_chunks, M.slot_word, M.n_slots,
                            h->K, rows, chunk, h->nwk);
         HIP_TRY(h, hipGetLastError());
     }

@@ -194,30 +194,39 @@ struct ChunkSupply {
 // Adds the recorded pairs to the word rows.  Slots are in word order and exist only for words with
 // at least kSlotMinTasks tasks: a workgroup takes kReduceChunk consecutive slots, sums the pairs of
 // the first `rows` words it meets in an LDS table and sends the rest straight to [V][K]; the table is
-// then added to the rows it stands for.  A thread reads a slot with one 16-byte load, a chunk with four, and starts with
-// the quad of a chunk picked by its index: tasks of one word have their large counts at the same topics in the same places
-// of their slots, and aligned walks would meet at one address.
-constexpr int kReduceChunk = 2048;       // slots per workgroup of a long list; shorter lists take fewer (reduce_chunk)
+// then added to the rows it stands for.  A range of few words keeps several copies of their rows, one for every so many
+// threads and a word apart in the banks: tasks of one word have their large counts at the same topics.  A thread reads
+// a slot with one 16-byte load, a chunk with four, and starts with the quad of a chunk picked by its index.  Bound: memory,
+// 20 bytes per slot in a stream and a line per chunk.
+constexpr int kReduceChunk = 512;       // slots per workgroup of a long list; shorter lists take fewer (reduce_chunk).  2048, 1024 and 512
+                                        // measured 0.48, 0.45 and 0.43 ms for 20 million slots of which half go on in a chunk
+                                        // (more words than rows in a range send their counts straight to memory)
 constexpr int kSlotMinTasks = 2;         // (32 measured 1.5 % slower on the resident matrix and 5 % on a minibatch: the direct
                                         // updates of rare words are atomics on lines that have long left the cache)
-constexpr int kReduceThreads = 1024;    // at most: two slots per thread, the kernel waits on its loads, many waves hide that
+constexpr int kReduceThreads = kReduceChunk / 2;    // at most: two slots per thread, the kernel waits on its loads, many waves hide that
 
 __global__ __launch_bounds__(kReduceThreads) void word_reduce_kernel(const uint32_t* __restrict__ pairs,
                                                           const uint32_t* __restrict__ chunks, uint32_t n_chunks,
                                                           const int32_t* __restrict__ slot_word, int64_t n, int K,
                                                           int rows, int chunk, uint32_t* __restrict__ nwk)
 {
-    extern __shared__ uint32_t tab[];                              // [rows][K]
+    extern __shared__ uint32_t tab[];                              // [rows][K + 1]
     const int64_t s0 = (int64_t)blockIdx.x * chunk;
     const int64_t s1 = s0 + chunk < n ? s0 + chunk : n;
     const int32_t w0 = slot_word[s0];
-    for (int i = threadIdx.x; i < rows * K; i += blockDim.x) tab[i] = 0u;
+    const int32_t w1 = slot_word[s1 - 1];                          // the last word of the range
+    const int stride = K + 1;
+    const int words = w1 - w0 < rows ? w1 - w0 + 1 : rows;         // words with rows in the table
+    int copies = 1;
+    while (2 * copies * words <= rows && copies < 32) copies *= 2;
+    const int mine = threadIdx.x & (copies - 1);
+    for (int i = threadIdx.x; i < words * copies * stride; i += blockDim.x) tab[i] = 0u;
     __syncthreads();
     for (int64_t s = s0 + threadIdx.x; s < s1; s += blockDim.x) {
         const uint4 slot = reinterpret_cast<const uint4*>(pairs)[s];
         const int32_t w = slot_word[s];
         const bool in_tab = w - w0 < rows;
-        uint32_t* dst = in_tab ? tab + (size_t)(w - w0) * K : nwk + (size_t)w * K;
+        uint32_t* dst = in_tab ? tab + ((w - w0) * copies + mine) * stride : nwk + (size_t)w * K;
         auto add = [&](uint32_t p) { atomicAdd(dst + (p & ((1u << kPairShift) - 1u)), p >> kPairShift); };
         uint32_t head = slot.w;
         {
@@ -247,14 +256,15 @@ __global__ __launch_bounds__(kReduceThreads) void word_reduce_kernel(const uint3
     // A word whose slots all lie in this workgroup's range is updated by no other workgroup of this launch (and
     // nothing else runs beside the launch): its row takes plain additions.  Only the first and the last word of
     // the range may share their rows with the neighbours.
-    const int32_t w1 = slot_word[s1 - 1];                          // the last word of the range
     const bool first_shared = s0 > 0 && slot_word[s0 - 1] == w0;
     const bool last_shared = s1 < n && slot_word[s1] == w1;
     uint32_t* base = nwk + (size_t)w0 * K;                         // row w0 + r, topic k is at base[r*K + k]
-    for (int i = threadIdx.x; i < rows * K; i += blockDim.x) {
-        const uint32_t v = tab[i];
+    for (int i = threadIdx.x; i < words * K; i += blockDim.x) {
+        const int r = i / K, k = i - r * K;
+        uint32_t v = 0u;
+        for (int c = 0; c < copies; ++c) v += tab[(r * copies + c) * stride + k];
         if (v == 0u) continue;                                     // only rows of real words hold counts
-        const int32_t w = w0 + i / K;
+        const int32_t w = w0 + r;
         if ((w == w0 && first_shared) || (w == w1 && last_shared)) atomicAdd(base + i, v);
         else base[i] += v;
     }
