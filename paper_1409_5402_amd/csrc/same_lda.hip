@@ -755,6 +755,20 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
     return SAME_LDA_OK;
 }
 
+// mu of every nonzero of M from M's theta and the handle's phi
+void launch_sddmm(same_lda* h, const Matrix& M, float* mu)
+{
+    const int waves_per_block = 4;
+    const int64_t waves = (M.nnz + same::kSddmmChunk - 1) / same::kSddmmChunk;
+    const dim3 grid((unsigned)((waves + waves_per_block - 1) / waves_per_block)), block(64 * waves_per_block);
+    if (h->K % 4 == 0 && h->K <= 256)
+        hipLaunchKernelGGL(same::sddmm_small_kernel, grid, block, 0, h->stream, M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, mu);
+    else if (h->K % 4 == 0)
+        hipLaunchKernelGGL(same::sddmm_kernel<true>, grid, block, 0, h->stream, M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, mu);
+    else
+        hipLaunchKernelGGL(same::sddmm_kernel<false>, grid, block, 0, h->stream, M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, mu);
+}
+
 size_t state_bytes(const same_lda* h, int32_t which)
 {
     switch (which) {
@@ -904,10 +918,11 @@ int same_lda_loglik(same_lda_t* h, const same_lda_csc* Xtest, int32_t foldin_swe
     Matrix M;
     int rc = build_matrix(h, Xtest, h->V, h->K, h->G, M, h->stream, false);
     if (!rc) rc = check_m(h, m_eval, M);
-    double* doc_log = nullptr; double* part = nullptr;
+    double* doc_log = nullptr; double* part = nullptr; float* mu = nullptr;
     const int nblocks = (int)((M.nnz + 255) / 256);
     if (!rc) rc = dev_alloc(h, &doc_log, (size_t)M.D);
     if (!rc) rc = dev_alloc(h, &part, (size_t)nblocks);
+    if (!rc) rc = dev_alloc(h, &mu, (size_t)M.nnz);
     if (!rc) rc = run_pass(h, M, Copies::whole((uint32_t)m_eval), pass_word(0, 1), true, false, false, h->stream);
     if (!rc) rc = update_theta(h, M, (float)m_eval, h->stream);
     for (int32_t s = 1; !rc && s <= foldin_sweeps; ++s) {
@@ -916,10 +931,9 @@ int same_lda_loglik(same_lda_t* h, const same_lda_csc* Xtest, int32_t foldin_swe
     }
     double total = 0.0;
     if (!rc && M.nnz > 0) {
-        hipLaunchKernelGGL(same::doc_log_total_kernel, dim3((M.D + 255) / 256), dim3(256), 0, h->stream, M.theta,
-                           M.D, h->K, doc_log);
-        hipLaunchKernelGGL(same::loglik_kernel, dim3(nblocks), dim3(256), 0, h->stream, M.nnz, M.nz_doc, M.rowidx,
-                           M.val, M.theta, h->phi, h->K, doc_log, part);
+        hipLaunchKernelGGL(same::doc_log_total_kernel, dim3((M.D + 3) / 4), dim3(256), 0, h->stream, M.theta, M.D, h->K, doc_log);
+        launch_sddmm(h, M, mu);
+        hipLaunchKernelGGL(same::loglik_kernel, dim3(nblocks), dim3(256), 0, h->stream, M.nnz, M.nz_doc, M.val, mu, doc_log, part);
         std::vector<double> part_h((size_t)nblocks);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = hipMemcpyAsync(part_h.data(), part, (size_t)nblocks * 8, hipMemcpyDeviceToHost, h->stream);
@@ -932,7 +946,7 @@ int same_lda_loglik(same_lda_t* h, const same_lda_csc* Xtest, int32_t foldin_swe
     }
     if (!rc) *ll_per_word = M.tokens > 0.0 ? total / M.tokens : 0.0;
     if (rc) (void)hipStreamSynchronize(h->stream);         // nothing enqueued may still use the blocks handed back
-    dev_free(h, doc_log); dev_free(h, part);
+    dev_free(h, doc_log); dev_free(h, part); dev_free(h, mu);
     free_matrix(h, M);
     return rc;
 }
@@ -1123,24 +1137,13 @@ int same_lda_sddmm(same_lda_t* h, float* mu_out, int32_t out_on_device)
     if (!mu_out) return fail(h, SAME_LDA_EINVAL, "mu_out is null");
     float* dst = mu_out;
     if (!out_on_device) { int rc = dev_alloc(h, &dst, (size_t)M.nnz); if (rc) return rc; }
-    const int waves_per_block = 4;
-    const int64_t waves = (M.nnz + same::kSddmmChunk - 1) / same::kSddmmChunk;
-    const int64_t blocks = (waves + waves_per_block - 1) / waves_per_block;
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     if (h->timing) {
         if (!h->pool.empty()) { ev = h->pool.back(); h->pool.pop_back(); }
         else { HIP_TRY(h, hipEventCreate(&ev.first)); HIP_TRY(h, hipEventCreate(&ev.second)); }
         HIP_TRY(h, hipEventRecord(ev.first, h->stream));
     }
-    if (h->K % 4 == 0 && h->K <= 256)
-        hipLaunchKernelGGL(same::sddmm_small_kernel, dim3((unsigned)blocks), dim3(64 * waves_per_block), 0, h->stream,
-                           M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, dst);
-    else if (h->K % 4 == 0)
-        hipLaunchKernelGGL(same::sddmm_kernel<true>, dim3((unsigned)blocks), dim3(64 * waves_per_block), 0, h->stream,
-                           M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, dst);
-    else
-        hipLaunchKernelGGL(same::sddmm_kernel<false>, dim3((unsigned)blocks), dim3(64 * waves_per_block), 0, h->stream,
-                           M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, dst);
+    launch_sddmm(h, M, dst);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && h->timing) { e = hipEventRecord(ev.second, h->stream); if (e == hipSuccess) h->events.push_back(ev); }
     if (e == hipSuccess && !out_on_device) {
@@ -1161,8 +1164,13 @@ int same_lda_vb_exp_elog_beta(same_lda_t* h, const float* lambda, float* b_out, 
     hipLaunchKernelGGL(same::vb_colsum_kernel, dim3(blocks), dim3(256), 0, h->stream, lambda, h->V, h->K, h->gamma_partial);
     hipLaunchKernelGGL(same::vb_colpsi_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, h->stream, h->gamma_partial, blocks, h->K,
                        h->vb_psi);
-    hipLaunchKernelGGL(same::vb_exp_elog_beta_kernel, dim3((unsigned)((h->V + 3) / 4)), dim3(256), 0, h->stream, lambda, h->V, h->K,
-                       h->vb_psi, b_out, shift_out);
+#define SAME_ELOG_LAUNCH(N) hipLaunchKernelGGL(same::vb_exp_elog_beta_kernel<N>, dim3((unsigned)((h->V + 3) / 4)), dim3(256), 0, \
+                                               h->stream, lambda, h->V, h->K, h->vb_psi, b_out, shift_out)
+    if (h->K <= 64)        SAME_ELOG_LAUNCH(1);
+    else if (h->K <= 256)  SAME_ELOG_LAUNCH(4);
+    else if (h->K <= 1024) SAME_ELOG_LAUNCH(16);
+    else                   SAME_ELOG_LAUNCH(32);
+#undef SAME_ELOG_LAUNCH
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }

@@ -13,16 +13,24 @@
 
 namespace same {
 
-// psi(x) for x > 0: the recurrence psi(x) = psi(x + 1) - 1/x up to x >= 6, then the asymptotic series
-// ln x - 1/(2x) - sum_n B_2n / (2n x^2n) through x^-14 (below 1e-12 there).
+// psi(x) for x > 0: below 6 the recurrence psi(x) = psi(x + 6) - sum_i 1/(x+i), i = 0..5, the sum as one quotient N/D of
+// polynomials with positive terms (D = x(x+1)..(x+5), N its derivative), then the asymptotic series
+// ln x - 1/(2x) - sum_n B_2n / (2n x^2n) through x^-14 (below 1e-12 there).  Two divisions instead of up to eight.
 __device__ __forceinline__ double digamma_d(double x)
 {
     double r = 0.0;
-    while (x < 6.0) { r -= 1.0 / x; x += 1.0; }
-    const double f = 1.0 / (x * x);
+    if (x < 6.0) {
+        double D = x, N = 1.0;
+#pragma unroll
+        for (int i = 1; i < 6; ++i) { const double y = x + (double)i; N = __builtin_fma(N, y, D); D = D * y; }
+        r = -(N / D);
+        x += 6.0;
+    }
+    const double inv = 1.0 / x;
+    const double f = inv * inv;
     const double t = f * (1.0 / 12.0 - f * (1.0 / 120.0 - f * (1.0 / 252.0 - f * (1.0 / 240.0 - f * (1.0 / 132.0
                      - f * (691.0 / 32760.0 - f * (1.0 / 12.0)))))));
-    return r + log(x) - 0.5 / x - t;
+    return r + log(x) - 0.5 * inv - t;
 }
 
 constexpr int kVbRows = 64;             // rows of lambda per workgroup of the column sums
@@ -49,6 +57,8 @@ __global__ __launch_bounds__(256) void vb_colpsi_kernel(const double* __restrict
 // One wave per word: e_k = psi(lambda[w][k]) - psi_total[k] (= E[log beta_kw]); shift[w] = max_k e_k;
 // b[w][k] = exp(e_k - shift[w]).  The largest entry of a row is 1: a word's row never underflows as a whole,
 // whatever the size of its lambda (psi(0.01) is -100.6, and exp of that is not a binary32 number).
+// N: topics per lane (64 N >= K); e_k stays in registers from the maximum to the exponential.
+template <int N>
 __global__ __launch_bounds__(256) void vb_exp_elog_beta_kernel(const float* __restrict__ lam, int V, int K,
                                                                const double* __restrict__ psi_total,
                                                                float* __restrict__ b, float* __restrict__ shift)
@@ -57,33 +67,63 @@ __global__ __launch_bounds__(256) void vb_exp_elog_beta_kernel(const float* __re
     const int w = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     if (w >= V) return;                                            // the whole wave
     const float* __restrict__ row = lam + (size_t)w * K;
+    double e[N];
     double top = -1.0e300;
-    for (int k = lane; k < K; k += 64) {
-        const double e = digamma_d((double)row[k]) - psi_total[k];
-        top = e > top ? e : top;
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        const int k = 64 * c + lane;
+        if (k < K) {
+            e[c] = digamma_d((double)row[k]) - psi_total[k];
+            top = e[c] > top ? e[c] : top;
+        }
     }
     for (int o = 32; o > 0; o >>= 1) {
         const double other = __shfl_xor(top, o);
         top = other > top ? other : top;
     }
-    for (int k = lane; k < K; k += 64)
-        b[(size_t)w * K + k] = (float)exp(digamma_d((double)row[k]) - psi_total[k] - top);
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        const int k = 64 * c + lane;
+        if (k < K) b[(size_t)w * K + k] = (float)exp(e[c] - top);
+    }
     if (lane == 0) shift[w] = (float)top;
+}
+
+// The sums of four values over the wave: lane l returns that of value l & 3.  Two steps inside groups of four lanes turn
+// four values per lane into one, the other four steps then work on a single value: 17 vector instructions where four
+// sums of their own take 44.
+__device__ __forceinline__ float wave_sum_4(const float (&v)[4], int lane)
+{
+    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0;
+    auto exchange = [](float keep, float give, auto ctrl) {
+        return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    const float r01 = exchange(b0 ? v[1] : v[0], b0 ? v[0] : v[1], std::integral_constant<int, 0xB1>{});   // lane ^ 1
+    const float r23 = exchange(b0 ? v[3] : v[2], b0 ? v[2] : v[3], std::integral_constant<int, 0xB1>{});
+    float r = exchange(b1 ? r23 : r01, b1 ? r01 : r23, std::integral_constant<int, 0x4E>{});               // lane ^ 2
+    r = dpp_add<0x124>(r);                                         // rotations inside a row of 16 by 4 and 8
+    r = dpp_add<0x128>(r);
+    auto p16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(r), __float_as_uint(r), false, false);     // rows 0 and 1, 2 and 3
+    r = __uint_as_float(p16[0]) + __uint_as_float(p16[1]);
+    auto p32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);     // the halves
+    return __uint_as_float(p32[0]) + __uint_as_float(p32[1]);
 }
 
 // One wave per document, lanes across topics (lane l owns topics 256 c + 4 l .. + 3 of chunk c: a row of b is read
 // with 16-byte loads, 1 KB per instruction), K a multiple of 4 and at most 256 CH.  The document's gamma, a and the
-// sums over its nonzeros stay in registers over all iterations; two nonzeros are in flight at a time (up to 256
+// sums over its nonzeros stay in registers over all iterations; two nonzeros are in flight at a time (up to 512
 // topics: four, and the next four behind them).
 template <int CH>
-__global__ __launch_bounds__(256) void vb_estep_kernel(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 6 : (CH == 2 ? 3 : 1)))) void vb_estep_kernel(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
                                                        const float* __restrict__ val, int32_t D, int K,
                                                        const float* __restrict__ b, const float* __restrict__ shift,
                                                        float alpha, int iters, float* __restrict__ gamma,
                                                        float* __restrict__ log_mu_out)
 {
     const int lane = threadIdx.x & 63;
-    const int32_t d = (int32_t)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    // one document per wave: its number is the same in every lane, so that word ids come through the scalar cache and a
+    // row's address is a scalar
+    const int32_t d = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     if (d >= D) return;                                            // the whole wave
     const int64_t lo = colptr[d], hi = colptr[d + 1];
     float* __restrict__ grow = gamma + (size_t)d * K;
@@ -112,67 +152,76 @@ __global__ __launch_bounds__(256) void vb_estep_kernel(const int32_t* __restrict
             a[c].w = in ? (float)exp(digamma_d(g[c][3]) - ps) : 0.f;
             acc[c][0] = 0.0; acc[c][1] = 0.0; acc[c][2] = 0.0; acc[c][3] = 0.0;
         }
-        if constexpr (CH == 1) {
-            // Up to 256 topics: kR nonzeros per round, and the rows of the next round are loaded while this round is
-            // worked off (their word ids were loaded a round earlier still).  Every round issues the same loads,
-            // past the document's end with the index of its last nonzero and a count of zero, so that the number of
-            // loads in flight behind the ones a round waits for is fixed and the wait lets them fly.
-            constexpr int kR = 2;                                  // nonzeros per round (even; four cost 171 registers and half the waves)
-            const int k = 4 * lane;
-            const bool in = k < K;
+        if constexpr (CH <= 2) {
+            // Up to 512 topics: four nonzeros per round, and the rows of the next round are loaded while this round is
+            // worked off.  Every round issues the same loads, past the document's end with the index of its last nonzero and
+            // a count of zero, so that the number of loads in flight behind the ones a round waits for is fixed and the wait
+            // lets them fly.  The four normalisers end in lanes l & 3 (wave_sum_4), so that one division serves all four; the
+            // quotients then go to scalar registers.  (Two nonzeros per round with a division and a tree of their own, ids
+            // in vector registers: 9.58 ms for 60,000 news-shaped documents and five iterations at K = 256, now 6.13 ms; with five
+            // and four waves per SIMD instead of six 6.57 and 6.46 ms.)
             const int64_t last = hi - 1;
-            auto ids = [&](int64_t i0, int32_t (&wv)[kR], float (&cv)[kR]) {
+            const int sub = lane & 3;
+            auto rows = [&](int64_t i0, float4 (&bv)[4][CH]) {
 #pragma unroll
-                for (int j = 0; j < kR; ++j) {
-                    const int64_t i = i0 + j;
-                    const int64_t ic = i < hi ? i : last;
-                    wv[j] = rowidx[ic];
-                    cv[j] = i < hi ? val[ic] : 0.f;
+                for (int j = 0; j < 4; ++j) {
+                    const int64_t i = i0 + j < hi ? i0 + j : last;
+                    const float* __restrict__ p = b + (size_t)rowidx[i] * K;
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        const int k = 256 * c + 4 * lane;
+                        bv[j][c] = k < K ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
                 }
             };
-            auto rows = [&](const int32_t (&wv)[kR], float4 (&bv)[kR]) {
+            auto counts = [&](int64_t i0) { const int64_t i = i0 + sub; return i < hi ? val[i] : 0.f; };
+            auto work = [&](int64_t i, const float4 (&bv)[4][CH], float cnt) {
+                float sj[4];
 #pragma unroll
-                for (int j = 0; j < kR; ++j)
-                    bv[j] = in ? *reinterpret_cast<const float4*>(b + (size_t)wv[j] * K + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int j = 0; j < 4; ++j) {
+                    float t = 0.f;
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        t = __builtin_fmaf(a[c].x, bv[j][c].x, t);
+                        t = __builtin_fmaf(a[c].y, bv[j][c].y, t);
+                        t = __builtin_fmaf(a[c].z, bv[j][c].z, t);
+                        t = __builtin_fmaf(a[c].w, bv[j][c].w, t);
+                    }
+                    sj[j] = t;
+                }
+                const float m = wave_sum_4(sj, lane);
+                const double q = cnt > 0.f ? (double)cnt / (double)m : 0.0;
+                const int qlo = __double2loint(q), qhi = __double2hiint(q);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double r = __hiloint2double(__builtin_amdgcn_readlane(qhi, j), __builtin_amdgcn_readlane(qlo, j));
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        acc[c][0] = __builtin_fma(r, (double)bv[j][c].x, acc[c][0]);
+                        acc[c][1] = __builtin_fma(r, (double)bv[j][c].y, acc[c][1]);
+                        acc[c][2] = __builtin_fma(r, (double)bv[j][c].z, acc[c][2]);
+                        acc[c][3] = __builtin_fma(r, (double)bv[j][c].w, acc[c][3]);
+                    }
+                }
+                if (log_mu_out != nullptr && it == iters - 1 && lane < 4 && i + lane < hi)
+                    log_mu_out[i + lane] = logf(m) + (shift ? shift[rowidx[i + lane]] : 0.f);
             };
             if (lo < hi) {
-                int32_t w[kR], nw[kR];
-                float cnt[kR], ncnt[kR];
-                float4 bv[kR], nbv[kR];
-                ids(lo, w, cnt);
-                ids(lo + kR, nw, ncnt);
-                rows(w, bv);
-                for (int64_t i = lo; i < hi; i += kR) {
-                    int32_t nnw[kR];
-                    float nncnt[kR];
-                    rows(nw, nbv);
-                    ids(i + 2 * kR, nnw, nncnt);
+                float4 b0[4][CH], b1[4][CH];
+                float c0 = counts(lo), c1;
+                rows(lo, b0);
+                for (int64_t i = lo; i < hi; i += 8) {             // two rounds per turn: no copies between the two sets
+                    rows(i + 4, b1);
+                    c1 = counts(i + 4);
                     __builtin_amdgcn_sched_barrier(0);             // the next round's loads first, then this round's work
-                    float m[kR];
-                    double r[kR];
-#pragma unroll
-                    for (int j = 0; j < kR; ++j) {
-                        float sj = 0.f;
-                        sj = __builtin_fmaf(a[0].x, bv[j].x, sj); sj = __builtin_fmaf(a[0].y, bv[j].y, sj);
-                        sj = __builtin_fmaf(a[0].z, bv[j].z, sj); sj = __builtin_fmaf(a[0].w, bv[j].w, sj);
-                        m[j] = wave_sum(sj);
-                        r[j] = cnt[j] > 0.f ? (double)cnt[j] / (double)m[j] : 0.0;
-                    }
-#pragma unroll
-                    for (int j = 0; j < kR; j += 2) {               // pairs of nonzeros, as in the loop for more topics
-                        acc[0][0] = __builtin_fma(r[j], (double)bv[j].x, __builtin_fma(r[j + 1], (double)bv[j + 1].x, acc[0][0]));
-                        acc[0][1] = __builtin_fma(r[j], (double)bv[j].y, __builtin_fma(r[j + 1], (double)bv[j + 1].y, acc[0][1]));
-                        acc[0][2] = __builtin_fma(r[j], (double)bv[j].z, __builtin_fma(r[j + 1], (double)bv[j + 1].z, acc[0][2]));
-                        acc[0][3] = __builtin_fma(r[j], (double)bv[j].w, __builtin_fma(r[j + 1], (double)bv[j + 1].w, acc[0][3]));
-                    }
-                    if (log_mu_out != nullptr && it == iters - 1 && lane == 0) {
-#pragma unroll
-                        for (int j = 0; j < kR; ++j)
-                            if (i + j < hi) log_mu_out[i + j] = logf(m[j]) + (shift ? shift[w[j]] : 0.f);
-                    }
+                    work(i, b0, c0);
                     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int j = 0; j < kR; ++j) { bv[j] = nbv[j]; w[j] = nw[j]; cnt[j] = ncnt[j]; nw[j] = nnw[j]; ncnt[j] = nncnt[j]; }
+                    if (i + 4 >= hi) break;
+                    rows(i + 8, b0);
+                    c0 = counts(i + 8);
+                    __builtin_amdgcn_sched_barrier(0);
+                    work(i + 4, b1, c1);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         } else
