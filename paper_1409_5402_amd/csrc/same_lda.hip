@@ -46,6 +46,9 @@ struct Matrix {
     int32_t*  tile_start = nullptr;// [n_tiles+1] first task id of every document tile
     uint32_t* cost = nullptr;      // [n_tasks] drain work each task reported in the last pass
     int32_t   n_tiles = 0;
+    int32_t*  heavy = nullptr;     // [n_heavy] ids of the tasks of at least heavy_from tokens
+    int64_t   n_heavy = 0;
+    uint32_t  heavy_from = ~0u;
     int32_t*  colptr = nullptr;    // [D+1]
     int32_t*  nz_doc = nullptr;    // [nnz]
     int32_t*  rowidx = nullptr;    // [nnz]
@@ -186,7 +189,7 @@ void free_matrix(same_lda* h, Matrix& M)
     dev_free(h, M.colptr); dev_free(h, M.t_doc); dev_free(h, M.t_word); dev_free(h, M.t_g); dev_free(h, M.order);
     dev_free(h, M.tile_start); dev_free(h, M.cost); dev_free(h, M.nz_doc); dev_free(h, M.rowidx); dev_free(h, M.val);
     dev_free(h, M.theta); dev_free(h, M.ndk); dev_free(h, M.pairs); dev_free(h, M.t_slot); dev_free(h, M.slot_word);
-    dev_free(h, M.hot_of); dev_free(h, M.hot_word);
+    dev_free(h, M.hot_of); dev_free(h, M.hot_word); dev_free(h, M.heavy);
     M = Matrix();
 }
 
@@ -305,32 +308,14 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
     HIP_TRY(h, tmp.get(&ntask, (size_t)nnz + 1));
     HIP_TRY(h, tmp.get(&tbase, (size_t)nnz + 1));
     hipLaunchKernelGGL(same::wl_init_stats, dim3(1), dim3(1), 0, st, d_stats);
-    if (D > 0) hipLaunchKernelGGL(same::wl_check_cols, dim3((unsigned)((D + 255) / 256)), dim3(256), 0, st, M.colptr, D, d_stats);
-    hipLaunchKernelGGL(same::wl_scan_nonzeros, dim3(grid_for((size_t)nnz + 1)), dim3(256), 0, st, M.colptr, M.rowidx,
-                       M.val, D, nnz, V, (uint32_t)G, M.nz_doc, ntask, d_stats);
-    // token totals per document and per word: they bound what the 32-bit count matrices must hold
-    unsigned long long *doc_tok = nullptr, *word_tok = nullptr, *stripes = nullptr;
+    // one pass over the matrix; the documents' token totals bound what the 32-bit count matrices must hold
+    unsigned long long* doc_tok = nullptr;
     HIP_TRY(h, tmp.get(&doc_tok, (size_t)D));
-    HIP_TRY(h, tmp.get(&word_tok, (size_t)V));
-    HIP_TRY(h, tmp.get(&stripes, (size_t)V * same::kTokenStripes));
-    hipLaunchKernelGGL(same::zero_u64_kernel, dim3(grid_for((size_t)V * same::kTokenStripes)), dim3(256), 0, st, stripes,
-                       (size_t)V * same::kTokenStripes);
-    if (nnz > 0)
-        hipLaunchKernelGGL(same::wl_word_tokens, dim3(grid_for((size_t)nnz)), dim3(256), 0, st, M.rowidx, M.val, nnz, V, stripes);
-    hipLaunchKernelGGL(same::wl_word_totals, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, stripes, V, word_tok, d_stats);
-    if (D > 0) {
-        hipLaunchKernelGGL(same::wl_doc_tokens, dim3((unsigned)((D + 255) / 256)), dim3(256), 0, st, M.colptr, M.rowidx,
-                           M.val, D, V, doc_tok, d_stats);
-        const int32_t most = D > V ? D : V;
-        hipLaunchKernelGGL(same::wl_token_argmax, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, st, doc_tok, D,
-                           word_tok, V, d_stats);
-        if (with_pairs) {                                      // the words whose rows get private copies (scatter.h)
-            if ((rc = dev_alloc(h, &M.hot_of, (size_t)V))) return rc;
-            if ((rc = dev_alloc(h, &M.hot_word, (size_t)same::kHotMax))) return rc;
-            hipLaunchKernelGGL(same::wl_hot_words, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, word_tok, V,
-                               (int32_t)same::kHotMax, M.hot_of, M.hot_word, d_stats);
-        }
-    }
+    hipLaunchKernelGGL(same::wl_scan_docs, dim3(grid_for((size_t)D * same::kDocLanes, 256, 1024)), dim3(256), 0, st, M.colptr, M.rowidx,
+                       M.val, D, nnz, V, (uint32_t)G, M.nz_doc, ntask, doc_tok, d_stats);
+    if (D > 0)
+        hipLaunchKernelGGL(same::wl_argmax, dim3((unsigned)((D + 255) / 256)), dim3(256), 0, st, doc_tok, D, &d_stats->max_doc_tokens,
+                           &d_stats->max_doc);
     HIP_TRY(h, hipGetLastError());
     same::BuildStats stats;
     HIP_TRY(h, hipMemcpyAsync(&stats, d_stats, sizeof(stats), hipMemcpyDeviceToHost, st));
@@ -347,9 +332,7 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
         return fail(h, SAME_LDA_ECSC, "too many draw tasks (%llu); raise tokens_per_draw", stats.n_tasks);
     const size_t n = (size_t)stats.n_tasks;
     M.n_tasks = (int64_t)n; M.max_group = stats.max_group; M.tokens = (double)stats.tokens;
-    M.max_doc_tokens = stats.max_doc_tokens; M.max_word_tokens = stats.max_word_tokens;
-    M.max_doc = (int32_t)stats.max_doc; M.max_word = (int32_t)stats.max_word;
-    M.n_hot = M.hot_of ? (int32_t)(stats.n_hot < (uint32_t)same::kHotMax ? stats.n_hot : (uint32_t)same::kHotMax) : 0;
+    M.max_doc_tokens = stats.max_doc_tokens; M.max_doc = (int32_t)stats.max_doc;
     M.with_words = with_pairs;
 
     // Processing order: documents are taken in tiles of kTileDocs (the theta rows a wave touches stay
@@ -374,10 +357,37 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
                        kTileDocs, M.n_tiles, M.tile_start);
     HIP_TRY(h, hipGetLastError());
 
+    // The heavy tasks, which the draw starts with; their number is known when the classes of the pass above are summed.
+    M.heavy_from = same::heavy_from(stats.sizes, stats.n_tasks);
+    for (int c = 1; c < same::kSizeClasses; ++c) if (same::class_start(c) >= M.heavy_from) M.n_heavy += (int64_t)stats.sizes[c];
+    if (M.n_heavy > 0) {
+        if ((rc = dev_alloc(h, &M.heavy, (size_t)M.n_heavy))) return rc;
+        hipLaunchKernelGGL(same::wl_heavy, dim3((unsigned)((n + same::kHeavyTile - 1) / same::kHeavyTile)), dim3(256), 0, st, M.t_g, (int64_t)n, (uint32_t)M.n_heavy, M.heavy, d_stats);
+        HIP_TRY(h, hipGetLastError());
+    }
+
     // Pair list: slots in (word, task id) order for the tasks of frequent words: a stable radix sort of the tasks
     // by word (worklist_kernels.h), the words' ranges in the sorted list, a flag per task of a word with enough
     // tasks, the flags' exclusive sum.  Optional: without it the draw kernel updates the word rows directly.
+    unsigned long long* word_tok = nullptr;
     if (with_pairs && n > 0) {
+        if ((rc = dev_alloc(h, &M.hot_of, (size_t)V))) return rc;
+        if ((rc = dev_alloc(h, &M.hot_word, (size_t)same::kHotMax))) return rc;
+        HIP_TRY(h, tmp.get(&word_tok, (size_t)V));
+        hipLaunchKernelGGL(same::zero_u64_kernel, dim3(grid_for((size_t)V)), dim3(256), 0, st, word_tok, (size_t)V);
+        // the words' token totals, the hot words among them, and what goes with every stats copy below
+        auto words_done = [&]() {
+            hipLaunchKernelGGL(same::wl_words, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, word_tok, V, (int32_t)same::kHotMax,
+                               M.hot_of, M.hot_word, d_stats);
+            hipLaunchKernelGGL(same::wl_argmax, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, word_tok, V, &d_stats->max_word_tokens,
+                               &d_stats->max_word);
+            hipError_t e = hipGetLastError();
+            if (e == hipSuccess) e = hipMemcpyAsync(&stats, d_stats, sizeof(stats), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            M.max_word_tokens = stats.max_word_tokens; M.max_word = (int32_t)stats.max_word;
+            M.n_hot = (int32_t)(stats.n_hot < (uint32_t)same::kHotMax ? stats.n_hot : (uint32_t)same::kHotMax);
+            return e;
+        };
         int bits = 1;
         while (((int64_t)1 << bits) < (int64_t)V) ++bits;
         const uint32_t tiles = (uint32_t)((n + same::kSortTile - 1) / same::kSortTile);
@@ -411,13 +421,17 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
             HIP_TRY(h, exclusive_sum(tmp, flag, pos, n + 1, st));
             hipLaunchKernelGGL(same::wl_slot_scatter, dim3(grid_for(n)), dim3(256), 0, st, keys, tasks, flag, pos,
                                (int64_t)n, M.t_slot, M.slot_word, d_stats);
-            HIP_TRY(h, hipGetLastError());
-            HIP_TRY(h, hipMemcpyAsync(&stats, d_stats, sizeof(stats), hipMemcpyDeviceToHost, st));
-            HIP_TRY(h, hipStreamSynchronize(st));
+            hipLaunchKernelGGL(same::wl_word_tokens, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, keys, tasks, M.t_g, (int64_t)n,
+                               word_tok);
+            HIP_TRY(h, words_done());
             M.n_slots = (int64_t)stats.n_slots;
             ok = M.n_slots > 0 &&
                  h->cache.get(reinterpret_cast<void**>(&M.pairs), (size_t)M.n_slots * same::kSlotWords * sizeof(uint32_t)) == hipSuccess;
             if (ok) ensure_chunks(h, M.n_slots);
+        } else {
+            (void)hipGetLastError();
+            hipLaunchKernelGGL(same::wl_word_tokens_plain, dim3(grid_for((size_t)nnz)), dim3(256), 0, st, M.rowidx, M.val, nnz, word_tok);
+            HIP_TRY(h, words_done());
         }
         if (!ok) {
             (void)hipGetLastError();
@@ -573,6 +587,7 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         if (rc) return rc;
         const same::Shares sh = same::shares_for(a.n, resident);
         a.first = sh.first;
+        if ((int64_t)sh.waves * sh.first >= a.n) { a.n_heavy = 0; a.heavy_from = ~0u; }   // every task starts at once
         a.chunk_share = a.n_chunks / 2 / (uint32_t)sh.waves;
         void* args[] = {&a};
         HIP_TRY(h, hipLaunchKernel(f, dim3((unsigned)sh.waves), block, args, lds, st));
@@ -603,6 +618,7 @@ same::DrawArgs draw_args(const same_lda* h, const Matrix& M, Copies c, uint32_t 
     a.chunk_counter = nullptr;
     a.n_chunks = pool ? usable : 0u;
     a.chunk_share = 0;
+    a.heavy = M.heavy; a.n_heavy = (int32_t)M.n_heavy; a.heavy_from = M.heavy_from;
     a.K = h->K; a.m = c.m; a.mf = c.mf; a.seed_lo = (uint32_t)h->seed; a.seed_hi = (uint32_t)(h->seed >> 32);
     a.pass = pass_word;
     a.V = h->V;
@@ -1064,7 +1080,7 @@ int debug_draw(same_lda_t* h, Copies c, const int64_t* task_ids, int32_t n, uint
     if (!rc) rc = zero_u32(h, out_d, (size_t)n * h->K, h->stream);
     if (!rc) {
         same::DrawArgs a = draw_args(h, h->X, c, pass_word(h->pass, 0), false);
-        a.n = n; a.ids = ids_d; a.ndk = out_d; a.nwk = nullptr; a.cost = nullptr;
+        a.n = n; a.ids = ids_d; a.ndk = out_d; a.nwk = nullptr; a.cost = nullptr; a.n_heavy = 0; a.heavy_from = ~0u;
         assign_counters(h, a, h->stream);
         rc = zero_u32(h, a.counter, counter_words(h, h->stream), h->stream);
         if (!rc) rc = launch_draw<true>(h, a, false, c.poisson, h->stream);
@@ -1105,7 +1121,7 @@ int same_lda_debug_draw_noalloc(same_lda_t* h, int32_t m_t, const int64_t* task_
     HIP_TRY(h, hipMemcpyAsync(S->ids, task_ids, (size_t)n * 8, hipMemcpyHostToDevice, h->stream));
     if ((rc = zero_u32(h, S->counts, counts, h->stream))) return rc;             // the array keeps the last call's contents
     same::DrawArgs a = draw_args(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false);
-    a.n = n; a.ids = S->ids; a.ndk = S->counts; a.nwk = nullptr; a.cost = nullptr;
+    a.n = n; a.ids = S->ids; a.ndk = S->counts; a.nwk = nullptr; a.cost = nullptr; a.n_heavy = 0; a.heavy_from = ~0u;
     a.counter = S->counter;
     if ((rc = zero_u32(h, S->counter, same::kCounterWords, h->stream))) return rc;
     if ((rc = launch_draw<true>(h, a, false, false, h->stream))) return rc;

@@ -26,6 +26,9 @@ struct DrawArgs {
     int64_t         n;          // tasks in this launch
     uint32_t*       counter;    // multinomial form: [kCounterWords] tickets for shares of the positions (zero at launch)
     int32_t         first;      // multinomial form: launch positions of a workgroup's first share
+    const int32_t*  heavy;      // multinomial form: [n_heavy] ids of the tasks of at least heavy_from tokens
+    int32_t         n_heavy;
+    uint32_t        heavy_from;
     const int32_t*  t_doc;      // [n_tasks] document of the task
     const int32_t*  t_word;     // [n_tasks] word of the task
     const uint32_t* t_g;        // [n_tasks] tokens in the task's group

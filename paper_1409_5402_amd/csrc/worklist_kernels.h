@@ -14,6 +14,7 @@ namespace same {
 // Filled by the kernels below; first_bad is the smallest (index << 2 | code) over all defects found,
 // ~0 if the matrix is sound: code 1 = column pointer decreases (index = document), 2 = word id out
 // of range, 3 = count not an integer in [1, 2^24) (index = nonzero).
+constexpr int kSizeClasses = 49;           // groups of up to 2^24 tokens
 struct BuildStats {
     unsigned long long tokens;
     unsigned long long n_tasks;
@@ -24,43 +25,156 @@ struct BuildStats {
     uint32_t max_group;
     uint32_t n_slots;
     uint32_t n_hot;                        // words holding at least 1/kHotMax of all tokens
+    uint32_t n_heavy;                      // tasks of at least heavy_from tokens (wl_heavy)
+    uint32_t sizes[kSizeClasses];          // tasks by size class (size_class)
 };
+
+// Size class of a group of g tokens: 0 for one token, then two classes per power of two (2, 3, 4-5, 6-7, 8-11, ...).
+__host__ __device__ inline int size_class(uint32_t g)
+{
+    if (g < 2u) return 0;
+    int e = 1;
+    while ((g >> (e + 1)) != 0u) ++e;
+    return 2 * e - 1 + (int)((g >> (e - 1)) & 1u);
+}
+__host__ __device__ inline uint32_t class_start(int c) { return c == 0 ? 1u : (2u + (uint32_t)((c - 1) & 1)) << ((c - 1) >> 1); }
+
+// The heavy tasks of a matrix: those of the largest size classes, as many whole classes as hold at most 1/kHeavyShare of the
+// tasks.  The draw starts with them (draw_kernel.h).  Returns the smallest heavy group; ~0 if there are none.
+constexpr uint32_t kHeavyShare = 256;      // (1/16, 1/64, 1/256, 1/1024: from a flat posterior 7.24, 7.30, 7.55, 7.7 ms against 9.4 without a
+                                           // list; converged 10.43, 10.21, 10.08, 10.05 ms against 10.05: heavy tasks taken out of their
+                                           // documents' order cost row changes and scans of single tasks)
+__host__ __device__ inline uint32_t heavy_from(const uint32_t* sizes, unsigned long long n_tasks)
+{
+    unsigned long long sum = 0ull;
+    uint32_t from = ~0u;
+    for (int c = kSizeClasses - 1; c > 0; --c) {
+        sum += sizes[c];
+        if (sum * kHeavyShare > n_tasks) break;
+        if (sizes[c]) from = class_start(c);
+    }
+    return from;
+}
 
 __global__ void wl_init_stats(BuildStats* s)
 {
     s->tokens = 0ull; s->n_tasks = 0ull; s->first_bad = ~0ull; s->max_group = 0u; s->n_slots = 0u;
-    s->max_doc_tokens = 0ull; s->max_word_tokens = 0ull; s->max_doc = ~0u; s->max_word = ~0u; s->n_hot = 0u;
+    s->max_doc_tokens = 0ull; s->max_word_tokens = 0ull; s->max_doc = ~0u; s->max_word = ~0u; s->n_hot = 0u; s->n_heavy = 0u;
+    for (int c = 0; c < kSizeClasses; ++c) s->sizes[c] = 0u;
 }
 
-// Token totals per document and per word (the largest values the count matrices can reach are m times
-// these).  Only entries that passed validation are counted.  Words: one thread per nonzero adds to one of
-// kTokenStripes copies of the per-word array (the most frequent words would otherwise receive one atomic per
-// document on a single address); wl_word_totals then adds the copies.  Documents: one thread per document.
-constexpr int kTokenStripes = 32;
+// One pass over the matrix, 16 lanes per document: column pointers, word ids and counts are checked, every nonzero gets
+// its document and its number of tasks, every document its token total (only entries that passed are counted; the
+// largest values the count matrices can reach are m times the totals).  Ranges are clamped to the matrix, so that broken
+// column pointers are reported and not followed.  (A search of the column pointers per nonzero and separate passes for
+// the totals of documents and words took 0.32, 0.10 and 0.43 ms for a minibatch of 7.7 million nonzeros.)
+// ntask has nnz + 1 entries; the last one is set to 0 so that an exclusive sum over all of them ends with the total.
+constexpr int kDocLanes = 16;
+__global__ __launch_bounds__(256) void wl_scan_docs(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
+                                                    const float* __restrict__ val, int32_t D, int64_t nnz, int32_t V, uint32_t G,
+                                                    int32_t* __restrict__ nz_doc, uint32_t* __restrict__ ntask,
+                                                    unsigned long long* __restrict__ doc_tok, BuildStats* s)
+{
+    __shared__ uint32_t sh_sizes[kSizeClasses];                    // little LDS: the pass runs beside the draw kernel, which leaves 12 KB
+    for (int c = threadIdx.x; c < kSizeClasses; c += 256) sh_sizes[c] = 0u;
+    __syncthreads();
+    unsigned long long tok = 0ull, tasks = 0ull, doc_max = 0ull;
+    uint32_t gmax = 0u, ones = 0u;
+    const int sub = threadIdx.x & (kDocLanes - 1);
+    const int32_t docs_at_once = (int32_t)(gridDim.x * (256 / kDocLanes));
+    if (blockIdx.x == 0 && threadIdx.x == 0) ntask[nnz] = 0u;
+    for (int32_t d = (int32_t)(blockIdx.x * (256 / kDocLanes) + threadIdx.x / kDocLanes); d < D; d += docs_at_once) {
+        const int64_t c0 = colptr[d], c1 = colptr[d + 1];
+        if (c1 < c0 && sub == 0) atomicMin(&s->first_bad, ((unsigned long long)d << 2) | 1ull);
+        const int64_t lo = c0 < 0 ? 0 : c0, hi = c1 < nnz ? c1 : nnz;
+        unsigned long long mine = 0ull;
+        for (int64_t i = lo + sub; i < hi; i += kDocLanes) {
+            nz_doc[i] = d;
+            const int32_t w = rowidx[i];
+            const float c = val[i];
+            uint32_t nt = 0u;
+            const bool number = c >= 1.0f && c < 16777216.0f;
+            if (w < 0 || w >= V) {
+                atomicMin(&s->first_bad, ((unsigned long long)i << 2) | 2ull);
+            } else if (!number || c != floorf(c)) {
+                atomicMin(&s->first_bad, ((unsigned long long)i << 2) | 3ull);
+            } else {
+                const uint32_t ci = (uint32_t)c;
+                nt = (ci + G - 1u) / G;
+                tok += ci; tasks += nt; mine += ci;
+                gmax = max(gmax, ci < G ? ci : G);
+                const uint32_t full = ci / G, rest = ci - full * G;   // the groups: full ones of G tokens and one of the rest
+                if (full > 0u) { if (G == 1u) ones += full; else atomicAdd(&sh_sizes[size_class(G)], full); }
+                if (rest > 0u) { if (rest == 1u) ones += 1u; else atomicAdd(&sh_sizes[size_class(rest)], 1u); }
+            }
+            ntask[i] = nt;
+        }
+        for (int o = kDocLanes / 2; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+        if (sub == 0) doc_tok[d] = mine;
+        doc_max = mine > doc_max ? mine : doc_max;
+    }
+    if (ones) atomicAdd(&sh_sizes[0], ones);
+    for (int o = 32; o > 0; o >>= 1) {
+        tok += __shfl_xor(tok, o); tasks += __shfl_xor(tasks, o);
+        gmax = max(gmax, __shfl_xor(gmax, o));
+        const unsigned long long other = __shfl_xor(doc_max, o);
+        doc_max = other > doc_max ? other : doc_max;
+    }
+    if ((threadIdx.x & 63) == 0) {
+        if (tok) atomicAdd(&s->tokens, tok);
+        if (tasks) atomicAdd(&s->n_tasks, tasks);
+        if (gmax) atomicMax(&s->max_group, gmax);
+        if (doc_max) atomicMax(&s->max_doc_tokens, doc_max);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < kSizeClasses; c += 256) if (sh_sizes[c]) atomicAdd(&s->sizes[c], sh_sizes[c]);
+}
 
-__global__ __launch_bounds__(256) void wl_word_tokens(const int32_t* __restrict__ rowidx, const float* __restrict__ val,
-                                                      int64_t nnz, int32_t V, unsigned long long* __restrict__ stripes)
+// Token totals per word from the tasks in word order: a wave takes 64 consecutive ones, adds up the runs of one word
+// lane by lane and sends each run's total with one atomic (the most frequent words would otherwise receive one per
+// document on a single address).
+__global__ __launch_bounds__(256) void wl_word_tokens(const int32_t* __restrict__ keys, const int32_t* __restrict__ tasks,
+                                                      const uint32_t* __restrict__ t_g, int64_t n,
+                                                      unsigned long long* __restrict__ word_tok)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int32_t key = i < n ? keys[i] : -1;
+    uint32_t sum = i < n ? t_g[tasks[i]] : 0u;                     // 64 groups of less than 2^24 tokens
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(sum, o);
+        const int32_t kup = __shfl_up(key, o);
+        if (lane >= o && kup == key) sum += up;
+    }
+    const int32_t next = __shfl_down(key, 1);
+    if (key >= 0 && (lane == 63 || next != key)) atomicAdd(word_tok + key, (unsigned long long)sum);
+}
+
+// The same from the nonzeros directly, one atomic each: for a matrix whose pair list did not fit.
+__global__ __launch_bounds__(256) void wl_word_tokens_plain(const int32_t* __restrict__ rowidx, const float* __restrict__ val,
+                                                            int64_t nnz, unsigned long long* __restrict__ word_tok)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    unsigned long long* mine = stripes + (size_t)(blockIdx.x % kTokenStripes) * V;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += stride) {
-        const int32_t w = rowidx[i];
-        const float c = val[i];
-        if (w < 0 || w >= V || !(c >= 1.0f) || c >= 16777216.0f) continue;
-        atomicAdd(mine + w, (unsigned long long)c);
-    }
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += stride)
+        atomicAdd(word_tok + rowidx[i], (unsigned long long)val[i]);
 }
 
-// word_tok[w] = sum of the copies; the largest one goes to the statistics (one atomic per workgroup).
-__global__ __launch_bounds__(256) void wl_word_totals(const unsigned long long* __restrict__ stripes, int32_t V,
-                                                      unsigned long long* __restrict__ word_tok, BuildStats* s)
+// The largest word total, and the hot words: those that hold at least one part in hot_max of all tokens (so at most
+// hot_max of them).  They are numbered in the order the threads arrive; the numbering only names the copies of their
+// rows, no result depends on it.  hot_of[w] = number or -1; hot_word[number] = w.
+__global__ __launch_bounds__(256) void wl_words(const unsigned long long* __restrict__ word_tok, int32_t V, int32_t hot_max,
+                                                int16_t* __restrict__ hot_of, int32_t* __restrict__ hot_word, BuildStats* s)
 {
     __shared__ unsigned long long sh[256];
     const int32_t w = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    unsigned long long tot = 0ull;
+    const unsigned long long tot = w < V ? word_tok[w] : 0ull;
     if (w < V) {
-        for (int c = 0; c < kTokenStripes; ++c) tot += stripes[(size_t)c * V + w];
-        word_tok[w] = tot;
+        int16_t idx = -1;
+        if (tot > 0ull && tot * (unsigned long long)hot_max >= s->tokens) {
+            const uint32_t at = atomicAdd(&s->n_hot, 1u);
+            if (at < (uint32_t)hot_max) { idx = (int16_t)at; hot_word[at] = w; }
+        }
+        hot_of[w] = idx;
     }
     sh[threadIdx.x] = tot;
     __syncthreads();
@@ -71,110 +185,49 @@ __global__ __launch_bounds__(256) void wl_word_totals(const unsigned long long* 
     if (threadIdx.x == 0 && sh[0]) atomicMax(&s->max_word_tokens, sh[0]);
 }
 
-__global__ __launch_bounds__(256) void wl_doc_tokens(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
-                                                     const float* __restrict__ val, int32_t D, int32_t V,
-                                                     unsigned long long* __restrict__ doc_tok, BuildStats* s)
-{
-    __shared__ unsigned long long sh[256];
-    const int32_t d = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    unsigned long long tot = 0ull;
-    if (d < D) {
-        for (int64_t i = colptr[d]; i < (int64_t)colptr[d + 1]; ++i) {
-            const int32_t w = rowidx[i];
-            const float c = val[i];
-            if (w < 0 || w >= V || !(c >= 1.0f) || c >= 16777216.0f) continue;
-            tot += (unsigned long long)c;
-        }
-        doc_tok[d] = tot;
-    }
-    sh[threadIdx.x] = tot;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) sh[threadIdx.x] = sh[threadIdx.x] > sh[threadIdx.x + off] ? sh[threadIdx.x] : sh[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && sh[0]) atomicMax(&s->max_doc_tokens, sh[0]);
-}
-
-// Hot words: those that hold at least one part in hot_max of all tokens (so at most hot_max of them).  They are
-// numbered in the order the threads arrive; the numbering only names the copies of their rows, no result
-// depends on it.  hot_of[w] = number or -1; hot_word[number] = w.
-__global__ void wl_hot_words(const unsigned long long* __restrict__ word_tok, int32_t V, int32_t hot_max,
-                             int16_t* __restrict__ hot_of, int32_t* __restrict__ hot_word, BuildStats* s)
-{
-    const int32_t w = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (w >= V) return;
-    int16_t idx = -1;
-    if (word_tok[w] > 0ull && word_tok[w] * (unsigned long long)hot_max >= s->tokens) {
-        const uint32_t at = atomicAdd(&s->n_hot, 1u);
-        if (at < (uint32_t)hot_max) { idx = (int16_t)at; hot_word[at] = w; }
-    }
-    hot_of[w] = idx;
-}
-
-// The lowest document and word ids that attain the two maxima (for the error message).
-__global__ void wl_token_argmax(const unsigned long long* __restrict__ doc_tok, int32_t D,
-                                const unsigned long long* __restrict__ word_tok, int32_t V, BuildStats* s)
+// The lowest id that attains a maximum (for the error message).
+__global__ void wl_argmax(const unsigned long long* __restrict__ tok, int32_t n, const unsigned long long* __restrict__ largest,
+                          uint32_t* __restrict__ id)
 {
     const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i < D && doc_tok[i] == s->max_doc_tokens) atomicMin(&s->max_doc, (uint32_t)i);
-    if (i < V && word_tok[i] == s->max_word_tokens) atomicMin(&s->max_word, (uint32_t)i);
+    if (i < n && tok[i] == *largest) atomicMin(id, (uint32_t)i);
 }
 
-__global__ void wl_check_cols(const int32_t* __restrict__ colptr, int32_t D, BuildStats* s)
+// The ids of the heavy tasks (heavy_from).  A workgroup takes kHeavyTile consecutive tasks and reserves the places of its
+// heavy ones with one atomic (one per wave was one in 16 ns: 1.2 ms for 7.7 million tasks); inside a tile they keep
+// their order, so that neighbours in the list are mostly of one document.  The order only decides when a task is drawn.
+constexpr int kHeavyTile = 4096;
+__global__ __launch_bounds__(256) void wl_heavy(const uint32_t* __restrict__ t_g, int64_t n, uint32_t capacity, int32_t* __restrict__ heavy,
+                                                BuildStats* s)
 {
-    const int32_t d = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (d < D && colptr[d + 1] < colptr[d]) atomicMin(&s->first_bad, ((unsigned long long)d << 2) | 1ull);
-}
-
-// Per nonzero: its document (the last d with colptr[d] <= i), validity, number of tasks.
-// ntask has nnz + 1 entries; the last one is set to 0 so that an exclusive sum over all of them
-// ends with the total.
-__global__ __launch_bounds__(256) void wl_scan_nonzeros(const int32_t* __restrict__ colptr,
-                                                        const int32_t* __restrict__ rowidx,
-                                                        const float* __restrict__ val, int32_t D, int64_t nnz,
-                                                        int32_t V, uint32_t G, int32_t* __restrict__ nz_doc,
-                                                        uint32_t* __restrict__ ntask, BuildStats* s)
-{
-    __shared__ unsigned long long sh_tok[256], sh_task[256];
-    __shared__ uint32_t sh_max[256];
-    unsigned long long tok = 0ull, tasks = 0ull;
-    uint32_t gmax = 0u;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= nnz; i += stride) {
-        if (i == nnz) { ntask[i] = 0u; break; }
-        int32_t lo = 0, hi = D;                                    // colptr[lo] <= i < colptr[hi] when sound
-        while (hi - lo > 1) { const int32_t mid = lo + (hi - lo) / 2; if ((int64_t)colptr[mid] <= i) lo = mid; else hi = mid; }
-        nz_doc[i] = lo;
-        const int32_t w = rowidx[i];
-        const float c = val[i];
-        uint32_t nt = 0u;
-        if (w < 0 || w >= V) {
-            atomicMin(&s->first_bad, ((unsigned long long)i << 2) | 2ull);
-        } else if (!(c >= 1.0f) || c >= 16777216.0f || c != floorf(c)) {
-            atomicMin(&s->first_bad, ((unsigned long long)i << 2) | 3ull);
-        } else {
-            const uint32_t ci = (uint32_t)c;
-            nt = (ci + G - 1u) / G;
-            tok += ci; tasks += nt;
-            gmax = max(gmax, ci < G ? ci : G);
-        }
-        ntask[i] = nt;
-    }
-    sh_tok[threadIdx.x] = tok; sh_task[threadIdx.x] = tasks; sh_max[threadIdx.x] = gmax;
+    __shared__ uint32_t from, first, wave_total[4];
+    if (threadIdx.x == 0) from = heavy_from(s->sizes, s->n_tasks);
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            sh_tok[threadIdx.x] += sh_tok[threadIdx.x + off];
-            sh_task[threadIdx.x] += sh_task[threadIdx.x + off];
-            sh_max[threadIdx.x] = max(sh_max[threadIdx.x], sh_max[threadIdx.x + off]);
-        }
-        __syncthreads();
+    constexpr int kEach = kHeavyTile / 256;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t i0 = (int64_t)blockIdx.x * kHeavyTile + (int64_t)wv * (kHeavyTile / 4) + lane;
+    uint64_t masks[kEach];
+    uint32_t total = 0;
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+        const int64_t i = i0 + 64 * j;
+        masks[j] = __ballot(i < n && t_g[i < n ? i : 0] >= from);
+        total += (uint32_t)__popcll((unsigned long long)masks[j]);
     }
+    if (lane == 0) wave_total[wv] = total;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        if (sh_tok[0]) atomicAdd(&s->tokens, sh_tok[0]);
-        if (sh_task[0]) atomicAdd(&s->n_tasks, sh_task[0]);
-        if (sh_max[0]) atomicMax(&s->max_group, sh_max[0]);
+        uint32_t all = 0;
+        for (int v = 0; v < 4; ++v) { const uint32_t t = wave_total[v]; wave_total[v] = all; all += t; }
+        first = all ? atomicAdd(&s->n_heavy, all) : 0u;
+    }
+    __syncthreads();
+    uint32_t at = first + wave_total[wv];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+        const uint32_t mine = at + (uint32_t)__popcll((unsigned long long)(masks[j] & ((1ull << lane) - 1ull)));
+        if (((masks[j] >> lane) & 1ull) && mine < capacity) heavy[mine] = (int32_t)(i0 + 64 * j);
+        at += (uint32_t)__popcll((unsigned long long)masks[j]);
     }
 }
 

@@ -63,3 +63,27 @@ def test_pairs_beyond_a_slot(form, limit):
         assert np.array_equal(g.get(binding.NWK), o.nwk)
         np.testing.assert_allclose(g.get(binding.PHI), o.phi, rtol=1e-6)
     g.close()
+
+
+@pytest.mark.parametrize("K", [24, 300])
+@pytest.mark.parametrize("G", [1, 3, 8, 1000])
+def test_heavy_tasks_are_drawn_once(G, K):
+    """Counts of one to two for most words and up to 900 for a few: the largest groups are drawn first and passed over
+    later.  Groups smaller than a count, of exactly a count, and no heavy group at all (G = 1)."""
+    rng = np.random.default_rng(8)
+    D, V = 150, 90
+    counts = rng.integers(0, 3, size=(D, V))
+    counts[rng.integers(0, D, 300), rng.integers(0, V, 300)] = rng.integers(3, 900, 300)
+    counts[7, :] = 0
+    cols = [np.flatnonzero(r) for r in counts]
+    X = oracle.CSC(D, V, np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32),
+                   np.concatenate(cols).astype(np.int32), counts[counts > 0].astype(np.float32))
+    o = oracle.OracleLDA(X, K, 0.2, 0.05, seed=13, m0=2, G=G)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.2, 0.05, 13, 2, G)
+    assert np.array_equal(g.get(binding.NDK), o.ndk) and np.array_equal(g.get(binding.NWK), o.nwk)
+    for m in (1, 11):
+        o.sweep(m)
+        g.sweep(m)
+        assert np.array_equal(g.get(binding.NDK), o.ndk)
+        assert np.array_equal(g.get(binding.NWK), o.nwk)
+    g.close()
