@@ -122,11 +122,6 @@ __device__ __forceinline__ int first_reaching(float (&P)[N], float y, float& pre
 constexpr int kRefillMin = 24;
 constexpr int kRefillLate = 8;
 constexpr int kRefillLateTrips = 8;
-// Binomials of several pieces wait for kPoolMin of them, or for kPoolTrips trips: from a flat posterior five of the 64
-// lanes waited at any time for eight to gather.  (1, 2, 4, 8 trips: 9.62, 9.59, 9.80, 10.4 ms there against 12.4 without
-// the limit; converged 11.02, 10.83, 10.73, 10.73 ms.)
-constexpr int kPoolTrips = 4;
-
 // VEC: K is a multiple of 4 (16-byte loads), else element-wise loads (TB = 0).  TB: 16-byte loads per matrix that
 // a lane has in flight at a time: a block of T = 4 ceil(K / 128) topics is read in T / (4 TB) batches of TB loads
 // per matrix, TB the largest of 1, 2, 4 that divides T / 4 (one batch of one up to K = 128, one of two up to 256,

@@ -23,11 +23,9 @@
 
 namespace same {
 
-#ifndef SAME_QCAP
-#define SAME_QCAP 8
-#endif
 constexpr int kBlk = 16;                // topics per block of the Poisson kernel's second pass
-constexpr int kQCap = SAME_QCAP;        // queued topics per lane between drains (drain when > kQCap - 4)
+constexpr int kQCap = 16;               // queued topics per lane between drains (drain when > kQCap - 4; 8, 12 and 16
+                                        // measured 3.12, 3.02 and 3.00 ms for 6 million tasks at K = 256)
 
 // The sixteen theta and phi values of one block, loaded ahead of their use (K % 16 == 0 only).
 struct PhiBlock { float4 v[kBlk / 4]; float4 t[kBlk / 4]; };
@@ -94,7 +92,8 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
     const int lane = threadIdx.x;
     const int K = KC > 0 ? KC : a.K;
     const int nblk = (K + kBlk - 1) / kBlk;
-    constexpr int qw = 3;                                          // words per queue entry
+    constexpr int qw = 2;                                          // words per queue entry: weight, random word with the topic's low bits
+    constexpr bool kHigh = KC == 0 || KC > 512;                    // topics may need more than nine bits
     uint32_t* que = lds;                                           // [kQCap][qw][64], a ring per lane
     uint32_t* acc = lds + (size_t)(qw * kQCap) * kWave;            // [64] piece totals by owner lane
     static_assert(kQCap <= 16, "two bits per ring slot in one register");
@@ -144,9 +143,9 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
     int qh = 0, cnt = 0;    // ring queue: position of the oldest entry, entries queued
     int st = 0;             // 0: between draws, 1: walking a single piece,
                             // 3: holds a variable of several pieces, waiting for the wave to share it
-    uint32_t np = 0, xw = 0;
-    float r = 0.f, pm = 0.f, cdf = 0.f, u = 0.f;
-    bool stalled = false;
+    uint32_t np = 0;
+    float r = 0.f, pm = 0.f, cdf = 0.f, u = 0.f, xf = 0.f;
+    int waited = 0;         // trips since a variable of several pieces has been waiting
     int kk = 0;
     uint32_t busy = 0;      // trips in which this lane had work: its cost for the next ordering
 
@@ -216,19 +215,18 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
         int kk_done = 0;
         if (st == 0 && cnt > 0) {
             const float wq = __uint_as_float(que[(qh * qw + 0) * kWave + lane]);
-            const float Mq = __uint_as_float(que[(qh * qw + 1) * kWave + lane]);
-            const uint32_t xk = que[(qh * qw + 2) * kWave + lane];
-            kk = (int)((xk & 511u) | (((khi >> (2 * qh)) & 3u) << 9));
+            const uint32_t xk = que[(qh * qw + 1) * kWave + lane];
+            kk = (int)((xk & 511u) | (kHigh ? ((khi >> (2 * qh)) & 3u) << 9 : 0u));
             u = uniform_from_word(xk);
             qh = (qh + 1 == kQCap) ? 0 : qh + 1;
             --cnt;
             const float scaled = Nf * wq;
-            const float lam = scaled / Mq;
+            const float lam = scaled / mu;
             if (lam > 0.0f) {
                 if (lam <= kPieceMean) {                           // one piece
                     r = lam;
                     const float pm0 = expneg(lam);
-                    xw = 0; pm = pm0; cdf = pm0; stalled = false;
+                    xf = 0.0f; pm = pm0; cdf = pm0;
                     st = 1;
                 } else {                                           // equal pieces: shared by the wave
                     np = (uint32_t)(lam / kPieceMean) + 1u;
@@ -240,27 +238,29 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
         }
         {
             const uint64_t pend = __ballot(st == 3);
-            if (pend != 0 && (__popcll((unsigned long long)pend) >= kPoolMin || !__any(st == 1))) { en = pool(pend); kk_done = kk; }
+            const bool share = pend != 0 && (__popcll((unsigned long long)pend) >= kPoolMin || waited >= kPoolTrips || !__any(st == 1));
+            waited = (pend != 0 && !share) ? waited + 1 : 0;
+            if (share) { en = pool(pend); kk_done = kk; }
         }
         if (__any(st == 1)) {
-            const bool walking = st == 1;
-#pragma unroll
-            for (int i = 0; i < kWalkSteps; ++i) {
-                const bool go = walking && !stalled && u > cdf;
-                const uint32_t xn = xw + 1u;
-                float pmn = pm * r;
-                pmn = pmn * inv_int((float)xn);
-                const float next = cdf + pmn;
-                const bool still = next == cdf;
-                if (go) SAME_COUNT(a, 4, 1);                       // walk steps
-                xw = go ? xn : xw;
-                pm = go ? pmn : pm;
-                cdf = (go && !still) ? next : cdf;
-                stalled = stalled || (go && still);
-            }
-            if (walking && (stalled || !(u > cdf))) {              // the piece is finished
-                en = xw; kk_done = kk;
-                st = 0;
+            // up to kWalkSteps terms, lane by lane under the execution mask, as in the multinomial form's walk
+            if (st == 1) {
+                bool more = u > cdf;
+                int i = 0;
+                while (more) {
+                    SAME_COUNT(a, 4, 1);                           // walk steps
+                    xf = xf + 1.0f;
+                    pm = pm * r;
+                    pm = pm * inv_int(xf);
+                    const float next = cdf + pm;
+                    more = next != cdf && u > next;
+                    cdf = next;
+                    if (++i == kWalkSteps) break;
+                }
+                if (!more) {                                       // the piece is finished
+                    en = (uint32_t)xf; kk_done = kk;
+                    st = 0;
+                }
             }
         }
         if (!DEBUG) supply.give(a, lane, sc, en > 0u && sc.full(), staged);
@@ -296,9 +296,8 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
                         int e = qh + cnt;
                         e = e >= kQCap ? e - kQCap : e;
                         que[(e * qw + 0) * kWave + lane] = __float_as_uint(wk);
-                        que[(e * qw + 1) * kWave + lane] = __float_as_uint(mu);
-                        que[(e * qw + 2) * kWave + lane] = (x[j] & ~511u) | ((uint32_t)k & 511u);   // the uniform uses the top 23 bits
-                        khi = (khi & ~(3u << (2 * e))) | (((uint32_t)k >> 9) << (2 * e));
+                        que[(e * qw + 1) * kWave + lane] = (x[j] & ~511u) | ((uint32_t)k & 511u);   // the uniform uses the top 23 bits
+                        if (kHigh) khi = (khi & ~(3u << (2 * e))) | (((uint32_t)k >> 9) << (2 * e));
                         cnt += 1;
                         SAME_COUNT(a, 1, 1);                       // queued topics
                     }
@@ -315,6 +314,6 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
     if (!DEBUG && live && a.cost) a.cost[tau] = (3u * a.cost[tau] + busy + 2u) >> 2;
 }
 
-inline size_t poisson_lds_bytes() { return 4u * (size_t)kWave * (size_t)(3 * kQCap + 1); }
+inline size_t poisson_lds_bytes() { return 4u * (size_t)kWave * (size_t)(2 * kQCap + 1); }
 
 }  // namespace same
