@@ -178,7 +178,7 @@ int same_lda_debug_draw_poisson(same_lda_t* h, float m_t, const int64_t* task_id
                                 uint32_t* counts_out);
 
 /* Test hook for the scatter of Algorithm 3's two accumulation lines.  A task records its (topic, count) pairs in a
- * slot of 15 and continues in 64-byte chunks taken from a pool in device memory that the handle allocates with its
+ * slot of three and continues in 64-byte chunks of 15 taken from a pool in device memory that the handle allocates with its
  * matrix (at most eight chunks per slot and a quarter of the free memory); counts that find the pool used up are
  * added straight to the word rows.  Results never depend on the pool's size.  This call lowers the number of chunks a
  * sweep may use (0: none; negative: all that were allocated) so that tests reach the fallback at small sizes.

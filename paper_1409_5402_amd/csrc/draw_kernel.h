@@ -8,8 +8,9 @@
 // its task's topics, T = 4*ceil(K/128) consecutive topics (T = 8 at K = 256: the 32 lanes read the
 // task's phi row and its document's theta row as two 16-byte loads each), multiplies them
 // (w_k = theta[d][k] * phi[w][k]) and adds the block's weights left to right.  The 32 block sums of a
-// task go to LDS.  No random numbers are used here and nothing is kept per topic.  (For K = 512 and 1024 the
-// lanes of a half read consecutive 16-byte pieces instead and share the blocks' sums: see COAL below.)
+// task go to LDS.  No random numbers are used here and nothing is kept per topic.  (Up to 64 topics four, eight or
+// sixteen tasks go at a time, scan_lanes lanes each; at K = 512 and from 897 to 1024 the lanes of a half read consecutive
+// 16-byte pieces instead and share the blocks' sums: see COAL below.)
 //
 // Draw (one lane per task).  A lane first turns its task's block sums into running sums S_0..S_31 (left to
 // right, so S_l is the cumulative weight at the end of block l and S_31 = mu, the normaliser of
@@ -122,17 +123,18 @@ __device__ __forceinline__ int first_reaching(float (&P)[N], float y, float& pre
 constexpr int kRefillMin = 24;
 constexpr int kRefillLate = 8;
 constexpr int kRefillLateTrips = 8;
-// VEC: K is a multiple of 4 (16-byte loads), else element-wise loads (TB = 0).  TB: 16-byte loads per matrix that
-// a lane has in flight at a time: a block of T = 4 ceil(K / 128) topics is read in T / (4 TB) batches of TB loads
-// per matrix, TB the largest of 1, 2, 4 that divides T / 4 (one batch of one up to K = 128, one of two up to 256,
-// one of four from 385 to 512, two of four from 897 to 1024).  ONE: a block is a single batch.  KC > 0: the
+// VEC: K is a multiple of 4 (rows are aligned to 16 bytes), else loads of any alignment (load_quad).  TB: 16-byte loads per
+// matrix that a lane has in flight at a time: a block of T = 4 ceil(K / 128) topics is read in T / (4 TB) batches of TB
+// loads per matrix.  ONE: a block is a single batch (up to 896 topics: TB = T / 4, 1 to 7; a K of 300, 640, 768 or 896 in
+// batches of one load took 1.5 to 3 times as long).  TB = 0: fewer than four topics, element by element.  KC > 0: the
 // same kernel with the number of topics a constant (row addresses become shifts, the bounds of the loads vanish).
-// COAL (KC = 128 n, n = 2, 4 or 8): in the scan a load covers 128 consecutive topics per half-wave, four per lane,
-// instead of four topics of every lane's own block: a wave's load touches 8 cache lines, not 64 (blocks of 32
-// topics are a whole line each, and the cache serves a load one line at a time: with 64 lines per load the kernel
-// at K = 1024 was bound there, at half the speed).  The n lanes that hold a block then add its products in the
-// same left-to-right order through a chain of lane-to-lane shifts; the block sums are the same bits.  The steps'
-// reloads of single blocks stay as they are (a lane's block belongs to its own task).
+// COAL (TB = 4: blocks of 16 topics in one batch, or of 32 in two): in the scan a load covers 128 consecutive topics per
+// half-wave, four per lane, instead of four topics of every lane's own block: a wave's load touches 8 cache lines, not 32
+// or 64, and the cache serves a load one line at a time.  The lanes that hold a block then add its products in the
+// same left-to-right order through a chain of lane-to-lane shifts; the block sums are the same bits.  From 897 topics it
+// halves the kernel (1.87 -> 0.91 ms at K = 1000, 9000 news-shaped documents, m = 10); at K = 512 it is even with the other
+// form and at 385 to 511 topics 8 % slower (0.65 against 0.60 ms), so those use the other one.  The steps' reloads of
+// single blocks stay as they are (a lane's block belongs to its own task).
 //
 // The launch positions (tasks in storage order) are shared out in rounds.  A launch has as many workgroups (of one wave)
 // as the device holds at once.  In round 0 every workgroup owns a.first consecutive positions, about half of an equal

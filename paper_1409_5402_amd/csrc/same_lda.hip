@@ -62,7 +62,6 @@ struct Matrix {
     int32_t*  slot_word = nullptr; // [n_slots] word of each slot
     // hot words (training matrices only): their rows of the word-count matrix have private copies
     int16_t*  hot_of = nullptr;    // [V] number of a hot word, -1 for the others
-    int32_t*  hot_word = nullptr;  // [kHotMax] the hot words by number
     int32_t   n_hot = 0;
 };
 
@@ -189,7 +188,7 @@ void free_matrix(same_lda* h, Matrix& M)
     dev_free(h, M.colptr); dev_free(h, M.t_doc); dev_free(h, M.t_word); dev_free(h, M.t_g); dev_free(h, M.order);
     dev_free(h, M.tile_start); dev_free(h, M.cost); dev_free(h, M.nz_doc); dev_free(h, M.rowidx); dev_free(h, M.val);
     dev_free(h, M.theta); dev_free(h, M.ndk); dev_free(h, M.pairs); dev_free(h, M.t_slot); dev_free(h, M.slot_word);
-    dev_free(h, M.hot_of); dev_free(h, M.hot_word); dev_free(h, M.heavy);
+    dev_free(h, M.hot_of); dev_free(h, M.heavy);
     M = Matrix();
 }
 
@@ -233,7 +232,7 @@ hipError_t exclusive_sum(Temps& tmp, const uint32_t* in, uint32_t* out, size_t n
     return hipGetLastError();
 }
 
-// The pool of chunks that continue full pair-list slots (scatter.h).  A task places at most K pairs, 15 of them in
+// The pool of chunks that continue full pair-list slots (scatter.h).  A task places at most K pairs, three of them in
 // its slot; eight chunks per slot cover a sweep from a flat posterior (a hundred copies of a token then reach some
 // eighty topics), and a sweep that needs more sends the rest straight to the word rows.  The pool never takes more
 // than a quarter of the free device memory.  A failed allocation leaves the handle without a pool.
@@ -372,13 +371,12 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
     unsigned long long* word_tok = nullptr;
     if (with_pairs && n > 0) {
         if ((rc = dev_alloc(h, &M.hot_of, (size_t)V))) return rc;
-        if ((rc = dev_alloc(h, &M.hot_word, (size_t)same::kHotMax))) return rc;
         HIP_TRY(h, tmp.get(&word_tok, (size_t)V));
         hipLaunchKernelGGL(same::zero_u64_kernel, dim3(grid_for((size_t)V)), dim3(256), 0, st, word_tok, (size_t)V);
         // the words' token totals, the hot words among them, and what goes with every stats copy below
         auto words_done = [&]() {
             hipLaunchKernelGGL(same::wl_words, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, word_tok, V, (int32_t)same::kHotMax,
-                               M.hot_of, M.hot_word, d_stats);
+                               M.hot_of, d_stats);
             hipLaunchKernelGGL(same::wl_argmax, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, word_tok, V, &d_stats->max_word_tokens,
                                &d_stats->max_word);
             hipError_t e = hipGetLastError();

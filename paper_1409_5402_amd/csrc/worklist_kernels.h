@@ -161,9 +161,9 @@ __global__ __launch_bounds__(256) void wl_word_tokens_plain(const int32_t* __res
 
 // The largest word total, and the hot words: those that hold at least one part in hot_max of all tokens (so at most
 // hot_max of them).  They are numbered in the order the threads arrive; the numbering only names the copies of their
-// rows, no result depends on it.  hot_of[w] = number or -1; hot_word[number] = w.
+// rows, no result depends on it.  hot_of[w] = number or -1.
 __global__ __launch_bounds__(256) void wl_words(const unsigned long long* __restrict__ word_tok, int32_t V, int32_t hot_max,
-                                                int16_t* __restrict__ hot_of, int32_t* __restrict__ hot_word, BuildStats* s)
+                                                int16_t* __restrict__ hot_of, BuildStats* s)
 {
     __shared__ unsigned long long sh[256];
     const int32_t w = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void wl_words(const unsigned long long* __rest
         int16_t idx = -1;
         if (tot > 0ull && tot * (unsigned long long)hot_max >= s->tokens) {
             const uint32_t at = atomicAdd(&s->n_hot, 1u);
-            if (at < (uint32_t)hot_max) { idx = (int16_t)at; hot_word[at] = w; }
+            if (at < (uint32_t)hot_max) idx = (int16_t)at;
         }
         hot_of[w] = idx;
     }
