@@ -357,8 +357,12 @@ int build_matrix(same_lda* h, const same_lda_csc* X, int32_t V, int32_t K, int32
     HIP_TRY(h, hipGetLastError());
 
     // The heavy tasks, which the draw starts with; their number is known when the classes of the pass above are summed.
-    M.heavy_from = same::heavy_from(stats.sizes, stats.n_tasks);
-    for (int c = 1; c < same::kSizeClasses; ++c) if (same::class_start(c) >= M.heavy_from) M.n_heavy += (int64_t)stats.sizes[c];
+    // (A launch of few positions starts them all at once and needs no list: up to kShareAll for each of the twelve
+    // workgroups per compute unit that even the largest kernels have.)
+    if (n > (size_t)same::kShareAll * 12 * 256) {
+        M.heavy_from = same::heavy_from(stats.sizes, stats.n_tasks);
+        for (int c = 1; c < same::kSizeClasses; ++c) if (same::class_start(c) >= M.heavy_from) M.n_heavy += (int64_t)stats.sizes[c];
+    }
     if (M.n_heavy > 0) {
         if ((rc = dev_alloc(h, &M.heavy, (size_t)M.n_heavy))) return rc;
         hipLaunchKernelGGL(same::wl_heavy, dim3((unsigned)((n + same::kHeavyTile - 1) / same::kHeavyTile)), dim3(256), 0, st, M.t_g, (int64_t)n, (uint32_t)M.n_heavy, M.heavy, d_stats);

@@ -65,15 +65,15 @@ def test_pairs_beyond_a_slot(form, limit):
     g.close()
 
 
-@pytest.mark.parametrize("K", [24, 300])
-@pytest.mark.parametrize("G", [1, 3, 8, 1000])
-def test_heavy_tasks_are_drawn_once(G, K):
-    """Counts of one to two for most words and up to 900 for a few: the largest groups are drawn first and passed over
-    later.  Groups smaller than a count, of exactly a count, and no heavy group at all (G = 1)."""
+@pytest.mark.parametrize("K,G", [(4, 1), (4, 3), (4, 1000), (130, 8)])
+def test_heavy_tasks_are_drawn_once(K, G):
+    """Counts of one to two for most words and up to 40 for a few, in a matrix large enough for a list of heavy tasks
+    (more than 128 positions for each of 3072 workgroups): the largest groups are drawn first and passed over later.  Groups
+    smaller than a count, of exactly a count, and no heavy group at all (G = 1); an empty document."""
     rng = np.random.default_rng(8)
-    D, V = 150, 90
-    counts = rng.integers(0, 3, size=(D, V))
-    counts[rng.integers(0, D, 300), rng.integers(0, V, 300)] = rng.integers(3, 900, 300)
+    D, V = 1500, 400
+    counts = rng.integers(1, 3, size=(D, V))
+    counts[rng.integers(0, D, 1500), rng.integers(0, V, 1500)] = rng.integers(3, 41, 1500)
     counts[7, :] = 0
     cols = [np.flatnonzero(r) for r in counts]
     X = oracle.CSC(D, V, np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32),
