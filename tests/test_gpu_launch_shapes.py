@@ -87,3 +87,18 @@ def test_heavy_tasks_are_drawn_once(K, G):
         assert np.array_equal(g.get(binding.NDK), o.ndk)
         assert np.array_equal(g.get(binding.NWK), o.nwk)
     g.close()
+
+
+@pytest.mark.parametrize("extra", [1, 777])
+def test_full_shares_where_phi_is_large(extra):
+    """1024 topics and 33,000 words (135 MB of phi): shares of 512 positions, round after round, before they halve.  Every
+    document and word keeps exactly m copies of each token."""
+    X = matrix(3072 * 512 * 4 + extra, V=33000, seed=3)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, 1024, 0.1, 0.05, 5, 1, 8)
+    m = 2
+    g.sweep(m)
+    docs = np.add.reduceat(X.val.astype(np.int64), X.colptr[:-1])
+    words = np.bincount(X.rowidx, weights=X.val, minlength=X.V).astype(np.int64)
+    assert np.array_equal(np.asarray(g.get(binding.NDK)).reshape(X.D, 1024).sum(1, dtype=np.int64), m * docs)
+    assert np.array_equal(np.asarray(g.get(binding.NWK)).reshape(X.V, 1024).sum(1, dtype=np.int64), m * words)
+    g.close()
