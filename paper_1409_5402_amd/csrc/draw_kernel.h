@@ -34,15 +34,13 @@
 // one piece per lane.  Two consecutive steps of a task share one Philox block.
 #pragma once
 #include <type_traits>
+#include "launch_shape.h"
 #include "scatter.h"
 
 namespace same {
 
-constexpr int kMaxBlocks = 32;                  // blocks of topics per task (= lanes of a half-wave)
 constexpr int kSumStride = kMaxBlocks + 1;      // words between the block sums of two tasks in LDS (more than 64 topics): lanes
                                                 // that read the same block of 64 different tasks hit 32 different banks
-
-__host__ __device__ inline int block_len(int K) { return 4 * ((K + 127) / 128); }
 
 // Lanes that scan a task, and words between the sums of two tasks in LDS: a power of two that covers the blocks of up to
 // 128 topics (blocks of four: one 16-byte load per lane and matrix), 32 beyond, and a padding word.
@@ -328,7 +326,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
             }
         }
         if (!UNIFORM) {
-            const int k0 = hl * T;
+            const int k0 = scan_first_topic(hl, T, nblk);
             // the next pair of new lanes: one for each half-wave (the last one twice if their number is odd)
             auto pick = [&](uint64_t& rem) {
                 const int la = __ffsll((unsigned long long)rem) - 1;
@@ -391,7 +389,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     }
                 }
             } else if constexpr (TB > 0) {
-                // Where every block is whole (K = 32 T: 256 at T = 8) the loads need no bounds.  Blocks of one batch
+                // Where every block in use is whole (256 at T = 8, 200 with 25 of them) the loads need no bounds.  Blocks of one batch
                 // (ONE) and of two batches of four loads go through the pipeline in run(); blocks of other shapes load
                 // the next batch into a second set of registers before the current one is summed (the load there sits
                 // under a condition, and the compiler's wait then covers it too: no overlap, rare shapes).
@@ -568,7 +566,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                         consume(pb, tb, nxt);
                     }
                 };
-                if (KC > 0 || (VEC && !COAL && nblk * T == K)) run(std::true_type{}); else run(std::false_type{});
+                if (KC > 0 || (VEC && !COAL && blocks_fill_row(K))) run(std::true_type{}); else run(std::false_type{});
             } else {   // fewer than four topics
                 while (fresh) {
                     const int src = pick(fresh);
@@ -750,7 +748,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                             }
                             k = k0 + at;
                         };
-                        if (KC > 0 || (VEC && nblk * T == K)) reload(std::true_type{}); else reload(std::false_type{});
+                        if (KC > 0 || (VEC && blocks_fill_row(K))) reload(std::true_type{}); else reload(std::false_type{});
                     } else {
                         int at = 0;
                         auto visit = [&](float wk) {
