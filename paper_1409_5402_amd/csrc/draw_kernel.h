@@ -148,48 +148,7 @@ constexpr int kRefillLateTrips = 8;
 // the ones that had been taken last: 1.7 of 9.9 ms for 6 million tasks at K = 256.  The workgroups share a list of them
 // out before round 0 and pass over them afterwards.
 //
-// Tickets: one counter for every kGroups-th workgroup, zero at launch.  The device does one returning atomic on an
-// address in about 16 ns whatever asks for it; with one counter for segments of 512 positions those atomics were the
-// whole time of small launches (98,000 tasks: 86 us, 26 without) and a fifth of a launch of 9 million tasks
-// (0.567 -> 0.466 ms).  Halving shares need some ten tickets per workgroup, all told, and end with small ones.
-constexpr int kShareMin = 64;           // (32 and 128 measured within 1 %)
-constexpr int kShareAll = 128;          // up to this many positions per workgroup round 0 covers everything
-constexpr int kGroups = 32;             // (8 and 64 measured within 1 %)
-constexpr int kCounterStride = 32;      // words between two counters: a cache line each
-constexpr int kCounterWords = kGroups * kCounterStride;
-
-// Where phi is large (over kPhiLarge bytes) the waves stay in neighbouring documents: shares of kShareMax positions, round
-// after round, and halving ones at the end.  Spread over the whole matrix the waves' pair-list and count lines push phi out
-// of the memory-side cache: 512 topics, 100,000 words (205 MB), 60 million tasks 23.2 ms, in shares of 512 18.9, of 2048
-// 19.7 ms.  At 256 topics (102 MB) the large shares are better by 2 % converged and 6 % from a flat posterior.
-constexpr int kShareMax = 512;
-constexpr int64_t kPhiLarge = 128ll << 20;
-
-struct Shares { int32_t waves, first, full; };   // workgroups of a launch, positions of a share of round 0, full rounds behind it
-inline Shares shares_for(int64_t n, int64_t resident, int64_t phi_bytes)
-{
-    Shares s;
-    s.full = 0;
-    const int64_t per = (n + resident - 1) / resident;
-    if (per <= kShareAll) {                                        // fewer workgroups, none with less than a wave's worth
-        s.first = per < kWave ? kWave : (int32_t)per;
-        s.waves = (int32_t)((n + s.first - 1) / s.first);
-    } else {
-        s.first = (int32_t)(per / (2 * kShareMin) * kShareMin);
-        s.waves = (int32_t)resident;
-        if (phi_bytes > kPhiLarge && s.first > kShareMax) {
-            s.first = kShareMax;
-            s.full = (int32_t)(n / ((int64_t)s.waves * s.first)) - 2;
-        }
-    }
-    return s;
-}
-__device__ __forceinline__ int32_t share_of_round(int32_t first, int round)
-{
-    const int32_t s = round < 31 ? (first >> round) & ~31 : 0;
-    return s < kShareMin ? kShareMin : s;
-}
-
+// (How shares and tickets are dealt out: launch_shape.h.)
 template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 3 || KC == 512 ? 4 : 3)))) void draw_kernel(DrawArgs a)
 {
@@ -872,24 +831,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                 end = (int32_t)(from + a.first < a.n ? from + a.first : a.n);
             }
             if (next >= end) {                                     // the next share (all lanes obtain the same values)
-                const int64_t waves = (int64_t)gridDim.x;          // a multiple of kGroups where round 0 does not cover all
-                int64_t from = waves * a.first;                    // where round 1 begins
+                const int64_t after = (int64_t)gridDim.x * a.first;   // where round 1 begins
+                int64_t from = after;
                 int32_t size = 0;
-                if (from < a.n) {
-                    const uint32_t group = (blockIdx.x >> 3) % kGroups, per_round = gridDim.x / kGroups;
-                    uint32_t t = 0;                                // this group's ticket: shares t * kGroups + group of a round
+                if (after < a.n) {
+                    const uint32_t group = ticket_group(blockIdx.x);
+                    uint32_t t = 0;                                // this group's ticket
                     if (lane == 0) t = atomicAdd(a.counter + kCounterStride * group, 1u);
                     t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
-                    int round = 1;
-                    const uint32_t full = min(t / per_round, (uint32_t)a.full);    // whole rounds of first positions before it
-                    from += waves * a.first * (int64_t)full;
-                    t -= full * per_round;
-                    size = full < (uint32_t)a.full ? a.first : share_of_round(a.first, 1);
-                    while (t >= per_round && from < a.n) {
-                        from += waves * size; t -= per_round; round += 1;
-                        size = share_of_round(a.first, round);
-                    }
-                    from += ((int64_t)t * kGroups + group) * size;
+                    const Share s = share_of_ticket(t, group, gridDim.x, a.first, a.full, a.n);
+                    from = s.from; size = s.size;
                 }
                 drained = from >= a.n;
                 next = drained ? 0 : (int32_t)from;

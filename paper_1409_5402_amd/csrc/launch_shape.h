@@ -11,6 +11,7 @@
 
 namespace same {
 
+constexpr int kWave = 64;                       // lanes per workgroup (one wave)
 constexpr int kMaxBlocks = 32;                  // blocks of topics per task (= lanes of a half-wave)
 
 SAME_HD inline int block_len(int K) { return 4 * ((K + 127) / 128); }
@@ -23,5 +24,77 @@ SAME_HD inline bool blocks_fill_row(int K) { return K % block_len(K) == 0; }
 // past the last block (from 17 on at K = 136, from 25 on at K = 200) load that block once more: a block of their own would lie
 // behind the row, and behind the matrix in its last row.  The sums they write are never read.
 SAME_HD inline int scan_first_topic(int hl, int T, int nblk) { return (hl < nblk ? hl : nblk - 1) * T; }
+
+// Tickets: one counter for every kGroups-th workgroup, zero at launch.  The device does one returning atomic on an
+// address in about 16 ns whatever asks for it; with one counter for segments of 512 positions those atomics were the
+// whole time of small launches (98,000 tasks: 86 us, 26 without) and a fifth of a launch of 9 million tasks
+// (0.567 -> 0.466 ms).  Halving shares need some ten tickets per workgroup, all told, and end with small ones.
+constexpr int kShareMin = 64;           // (32 and 128 measured within 1 %)
+constexpr int kShareAll = 128;          // up to this many positions per workgroup round 0 covers everything
+constexpr int kGroups = 32;             // (8 and 64 measured within 1 %)
+constexpr int kCounterStride = 32;      // words between two counters: a cache line each
+constexpr int kCounterWords = kGroups * kCounterStride;
+
+// Where phi is large (over kPhiLarge bytes) the waves stay in neighbouring documents: shares of kShareMax positions, round
+// after round, and halving ones at the end.  Spread over the whole matrix the waves' pair-list and count lines push phi out
+// of the memory-side cache: 512 topics, 100,000 words (205 MB), 60 million tasks 23.2 ms, in shares of 512 18.9, of 2048
+// 19.7 ms.  At 256 topics (102 MB) the large shares are better by 2 % converged and 6 % from a flat posterior.
+constexpr int kShareMax = 512;
+constexpr int64_t kPhiLarge = 128ll << 20;
+
+struct Shares { int32_t waves, first, full; };   // workgroups of a launch, positions of a share of round 0, full rounds behind it
+inline Shares shares_for(int64_t n, int64_t resident, int64_t phi_bytes)
+{
+    Shares s;
+    s.full = 0;
+    const int64_t per = (n + resident - 1) / resident;
+    if (per <= kShareAll) {                                        // fewer workgroups, none with less than a wave's worth
+        s.first = per < kWave ? kWave : (int32_t)per;
+        s.waves = (int32_t)((n + s.first - 1) / s.first);
+    } else {
+        s.first = (int32_t)(per / (2 * kShareMin) * kShareMin);
+        s.waves = (int32_t)resident;
+        if (phi_bytes > kPhiLarge && s.first > kShareMax) {
+            s.first = kShareMax;
+            s.full = (int32_t)(n / ((int64_t)s.waves * s.first)) - 2;
+        }
+    }
+    return s;
+}
+SAME_HD inline int32_t share_of_round(int32_t first, int round)
+{
+    const int32_t s = round < 31 ? (first >> round) & ~31 : 0;
+    return s < kShareMin ? kShareMin : s;
+}
+
+// The group of a workgroup: runs of eight neighbours, one on each die, belong to the same group, so that a group's shares
+// are not one die's.  All groups have a workgroup only from 8 * kGroups workgroups on, and the shares of a group without one
+// would never be drawn: whole_groups is the number of workgroups of a launch that hands out tickets.
+SAME_HD inline uint32_t ticket_group(uint32_t block) { return (block >> 3) % kGroups; }
+inline int64_t whole_groups(int64_t workgroups)
+{
+    const int64_t n = workgroups / kGroups * kGroups;
+    return n < 8 * kGroups ? 8 * kGroups : n;
+}
+
+// The share that ticket t of a group stands for: `full` rounds of `first` positions for each of `waves` workgroups (a
+// multiple of kGroups) follow round 0, then the halving ones; a group's shares are every kGroups-th of a round.  From n on
+// nothing is left.
+struct Share { int64_t from; int32_t size; };
+SAME_HD inline Share share_of_ticket(uint32_t t, uint32_t group, uint32_t waves, int32_t first, int32_t full, int64_t n)
+{
+    const uint32_t per_round = waves / kGroups;
+    const uint32_t whole = t / per_round < (uint32_t)full ? t / per_round : (uint32_t)full;
+    Share s;
+    s.from = (int64_t)waves * first * ((int64_t)whole + 1);
+    s.size = whole < (uint32_t)full ? first : share_of_round(first, 1);
+    t -= whole * per_round;
+    for (int round = 2; t >= per_round && s.from < n; ++round) {
+        s.from += (int64_t)waves * s.size; t -= per_round;
+        s.size = share_of_round(first, round);
+    }
+    s.from += ((int64_t)t * kGroups + group) * s.size;
+    return s;
+}
 
 }  // namespace same

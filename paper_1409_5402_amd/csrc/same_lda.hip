@@ -513,7 +513,7 @@ void assign_counters(same_lda* h, same::DrawArgs& a, hipStream_t st)
 
 int zero_u32(same_lda* h, uint32_t* p, size_t n, hipStream_t st);
 
-// Workgroups of kernel f that the device holds at once, a multiple of kGroups.  Asked once per handle and kernel.
+// Workgroups of kernel f that the device holds at once, in whole ticket groups.  Asked once per handle and kernel.
 int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t* out)
 {
     for (int i = 0; i < h->n_resident; ++i)
@@ -523,8 +523,7 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t
     HIP_TRY(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     HIP_TRY(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, lds));
     if (per_cu < 1) per_cu = 1;
-    int64_t n = (int64_t)cus * per_cu / same::kGroups * same::kGroups;
-    if (n < same::kGroups) n = same::kGroups;
+    const int64_t n = same::whole_groups((int64_t)cus * per_cu);
     if (h->n_resident < (int)(sizeof h->resident / sizeof h->resident[0])) h->resident[h->n_resident++] = {f, n};
     *out = n;
     return SAME_LDA_OK;

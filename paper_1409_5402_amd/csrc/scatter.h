@@ -2,11 +2,11 @@
 // the launch arguments, the scatter of a task's counts (Algorithm 3, the two accumulation lines) and
 // the kernel that adds the recorded (topic, count) pairs to the word rows.
 #pragma once
+#include "launch_shape.h"
 #include "rng_binom.h"
 
 namespace same {
 
-constexpr int kWave = 64;               // lanes per workgroup (one wave)
 constexpr int kSlotWords = 4;           // words of a pair-list slot: up to 3 (topic, count) pairs and a header
 constexpr int kPairWords = 16;          // words of a chunk that continues it: up to 15 pairs and a header
 constexpr uint32_t kFirstPair = kPairWords - kSlotWords;   // a slot is filled and written like the last quarter of a chunk

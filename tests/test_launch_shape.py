@@ -10,11 +10,35 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 SHIM = r"""
 #include "launch_shape.h"
+#include <vector>
 using namespace same;
+
+// Positions of a launch that are not drawn exactly once when every group that has a workgroup takes tickets until none is left.
+static long undrawn(long n, long resident, long phi_bytes)
+{
+    std::vector<unsigned char> drawn(n, 0);
+    long wrong = 0;
+    auto draw = [&](long from, long size) {
+        for (long i = from; i < from + size && i < n; ++i) if (drawn[i]++) ++wrong;
+    };
+    const Shares s = shares_for(n, resident, phi_bytes);
+    bool has[kGroups] = {};
+    for (long b = 0; b < s.waves; ++b) { draw(b * s.first, s.first); has[ticket_group((uint32_t)b)] = true; }
+    if ((long)s.waves * s.first < n)
+        for (uint32_t g = 0; g < kGroups; ++g)
+            for (uint32_t t = 0; has[g]; ++t) {
+                const Share h = share_of_ticket(t, g, (uint32_t)s.waves, s.first, s.full, n);
+                if (h.from >= n) break;
+                draw(h.from, h.size);
+            }
+    for (long i = 0; i < n; ++i) if (!drawn[i]) ++wrong;
+    return wrong;
+}
 extern "C" {
 int t_block_len(int K) { return block_len(K); }
 int t_blocks_in_use(int K) { return blocks_in_use(K); }
 int t_blocks_fill_row(int K) { return blocks_fill_row(K); }
+long t_undrawn(long n, long workgroups, long phi_bytes) { return undrawn(n, whole_groups(workgroups), phi_bytes); }
 int t_scan_first_topic(int hl, int T, int nblk) { return scan_first_topic(hl, T, nblk); }
 }
 """
@@ -27,7 +51,10 @@ def lib(tmp_path_factory):
     src.write_text(SHIM)
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I", CSRC,
                     str(src), "-o", str(so)], check=True)
-    return ctypes.CDLL(str(so))
+    so = ctypes.CDLL(str(so))
+    so.t_undrawn.argtypes = [ctypes.c_long] * 3
+    so.t_undrawn.restype = ctypes.c_long
+    return so
 
 
 def test_scan_stays_inside_the_row(lib):
@@ -43,3 +70,12 @@ def test_scan_stays_inside_the_row(lib):
         assert max(first) + T <= K, (K, T, nblk)
         assert first[:nblk] == [T * l for l in range(nblk)], K
     assert unguarded > 100
+
+
+@pytest.mark.parametrize("workgroups", [1, 32, 100, 224, 255, 256, 384, 1000, 3072, 4096, 5120])
+def test_every_position_has_one_share(lib, workgroups):
+    """Whatever number of workgroups a device holds at once: the static shares, the whole rounds where phi is large and the
+    halving ones cover every launch position once, and no ticket group is without a workgroup that draws its shares."""
+    for phi_bytes in (1 << 20, 1 << 30):
+        for n in (1, 63, 64, 65, 128 * 256, 128 * 256 + 1, 128 * workgroups, 128 * workgroups + 1, 1000 * workgroups + 77, 2500 * workgroups + 1, 3_000_017):
+            assert lib.t_undrawn(n, workgroups, phi_bytes) == 0, (n, phi_bytes)
