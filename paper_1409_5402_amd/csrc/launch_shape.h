@@ -97,4 +97,23 @@ SAME_HD inline Share share_of_ticket(uint32_t t, uint32_t group, uint32_t waves,
     return s;
 }
 
+// The pool of chunks that continue full pair-list slots: each of `waves` workgroups owns `share` of its `chunks`, the rest is
+// handed out in batches by a counter.  The counter counts batches: a workgroup adds to it once more before it sees that the
+// pool is used up, and the Poisson form has a workgroup for every 64 tasks, up to 2^25 of them.  A counter of
+// chunks came round from 2^24 workgroups on and handed out chunks that already held other tasks' counts.
+constexpr uint32_t kChunkBatch = 256;
+struct Chunks { uint32_t next, end; };          // empty: the pool is used up
+SAME_HD inline Chunks chunk_batch(uint32_t taken, uint32_t waves, uint32_t share, uint32_t chunks)
+{
+    // a pool has fewer than 2^31 chunks and half of it at most is the workgroups' own: no sum below reaches 2^32 before the
+    // limit on `taken` ends it.  (A comparison with the number of batches kept two more scalar registers alive: 1 % at K = 256.)
+    Chunks c = {0u, 0u};
+    const uint32_t next = waves * share + taken * kChunkBatch;
+    if (taken < (1u << 31) / kChunkBatch && next < chunks) {
+        c.next = next;
+        c.end = chunks - next < kChunkBatch ? chunks : next + kChunkBatch;
+    }
+    return c;
+}
+
 }  // namespace same

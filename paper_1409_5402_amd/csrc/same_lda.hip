@@ -128,7 +128,7 @@ struct same_lda {
     float* phi = nullptr;          // [V][K]
     uint32_t* nwk = nullptr;       // [V][K]
     unsigned long long* nk = nullptr;  // [K]
-    uint32_t* draw_counter = nullptr;  // counters of the draw kernel: tickets (kCounterWords), chunks taken and the hot words' mark
+    uint32_t* draw_counter = nullptr;  // counters of the draw kernel: tickets (kCounterWords), batches of chunks taken and the hot words' mark
                                        // (a word each) of a launch on the handle's stream, tickets of a launch on the copy stream
     uint32_t* chunks = nullptr;        // pool of chunks that continue full pair-list slots (launches on the handle's stream)
     uint32_t n_chunks = 0;             // chunks allocated
@@ -612,7 +612,7 @@ same::DrawArgs draw_args(const same_lda* h, const Matrix& M, Copies c, uint32_t 
     const bool pairs_fit = (c.poisson ? 4.0 * most + 128.0 : most) < (double)(1ull << (32 - same::kPairShift));
     a.pairs = (with_words && M.pairs && pairs_fit) ? M.pairs : nullptr;
     a.t_slot = M.t_slot;
-    // the chunk pool continues full slots in the multinomial kernel
+    // the chunk pool continues full slots, in both forms of the draw
     const uint32_t usable = h->chunk_limit >= 0 && h->chunk_limit < (int64_t)h->n_chunks ? (uint32_t)h->chunk_limit : h->n_chunks;
     const bool pool = a.pairs && h->chunks && usable > 0;
     a.chunks = pool ? h->chunks : nullptr;

@@ -42,7 +42,7 @@ struct DrawArgs {
     uint32_t*       pairs;      // [n_slots][kSlotWords] pair list in word order, or null (update nwk directly)
     const int32_t*  t_slot;     // [n_tasks] slot of each task in the pair list, -1 for a task without one
     uint32_t*       chunks;     // [n_chunks][kPairWords] pool of chunks that continue full slots, or null
-    uint32_t*       chunk_counter;  // first chunk of the pool not yet taken by a wave (zero at launch)
+    uint32_t*       chunk_counter;  // batches taken from the common part of the pool (zero at launch)
     uint32_t        n_chunks;   // chunks in the pool (below 2^31)
     uint32_t        chunk_share;    // chunks that are each workgroup's own; the rest is taken from the counter in batches
     int32_t         K;
@@ -162,7 +162,6 @@ __device__ __forceinline__ Scatter make_scatter(const DrawArgs& a, int64_t row, 
 
 // A wave's chunks: its own share of the pool (half the pool is shared out that way: a launch rarely needs more, and the
 // counter's atomics are returning ones on one address, 16 ns each), then batches from the counter.
-constexpr uint32_t kChunkBatch = 256;
 struct ChunkSupply {
     uint32_t next, end;     // not yet handed out
     bool dry;               // the pool has none left for this wave
@@ -180,12 +179,11 @@ struct ChunkSupply {
         if (need_mask == 0) return;
         const uint32_t cnt = (uint32_t)__popcll((unsigned long long)need_mask);
         if (end - next < cnt) {
-            uint32_t first = 0;
-            if (lane == 0) first = atomicAdd(a.chunk_counter, kChunkBatch);
-            first = gridDim.x * a.chunk_share + (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
-            dry = first >= a.n_chunks;
-            next = dry ? 0u : first;
-            end = dry ? 0u : (a.n_chunks - first < kChunkBatch ? a.n_chunks : first + kChunkBatch);
+            uint32_t taken = 0;
+            if (lane == 0) taken = atomicAdd(a.chunk_counter, 1u);
+            const Chunks c = chunk_batch((uint32_t)__builtin_amdgcn_readfirstlane((int)taken), gridDim.x, a.chunk_share, a.n_chunks);
+            next = c.next; end = c.end;
+            dry = next == end;
             if (lane == 0) SAME_COUNT(a, 14, 1);                   // batches of chunks taken
         }
         const uint32_t mine = next + (uint32_t)__popcll((unsigned long long)(need_mask & ((1ull << lane) - 1ull)));

@@ -34,11 +34,29 @@ static long undrawn(long n, long resident, long phi_bytes)
     for (long i = 0; i < n; ++i) if (!drawn[i]) ++wrong;
     return wrong;
 }
+// A launch in which every workgroup wants more chunks than its own share, `busy` of them in their turn: batches that start
+// inside a part of the pool which has been handed out before.
+static long owners_of_one_chunk(unsigned waves, unsigned share, unsigned chunks, unsigned busy)
+{
+    long wrong = 0;
+    uint32_t counter = 0;
+    uint32_t handed = waves * share;
+    for (unsigned w = 0; w < waves; ++w)
+        for (unsigned turn = 0; turn < busy; ++turn) {
+            const Chunks c = chunk_batch(counter, waves, share, chunks);
+            counter += 1u;
+            if (c.next == c.end) break;                            // dry: asks no more
+            if (c.next != handed || c.end > chunks) ++wrong;
+            handed = c.end;
+        }
+    return wrong + (handed != chunks);
+}
 extern "C" {
 int t_block_len(int K) { return block_len(K); }
 int t_blocks_in_use(int K) { return blocks_in_use(K); }
 int t_blocks_fill_row(int K) { return blocks_fill_row(K); }
 long t_undrawn(long n, long workgroups, long phi_bytes) { return undrawn(n, whole_groups(workgroups), phi_bytes); }
+long t_owners_of_one_chunk(unsigned waves, unsigned share, unsigned chunks, unsigned busy) { return owners_of_one_chunk(waves, share, chunks, busy); }
 int t_scan_first_topic(int hl, int T, int nblk) { return scan_first_topic(hl, T, nblk); }
 }
 """
@@ -54,6 +72,8 @@ def lib(tmp_path_factory):
     so = ctypes.CDLL(str(so))
     so.t_undrawn.argtypes = [ctypes.c_long] * 3
     so.t_undrawn.restype = ctypes.c_long
+    so.t_owners_of_one_chunk.argtypes = [ctypes.c_uint] * 4
+    so.t_owners_of_one_chunk.restype = ctypes.c_long
     return so
 
 
@@ -79,3 +99,11 @@ def test_every_position_has_one_share(lib, workgroups):
     for phi_bytes in (1 << 20, 1 << 30):
         for n in (1, 63, 64, 65, 128 * 256, 128 * 256 + 1, 128 * workgroups, 128 * workgroups + 1, 1000 * workgroups + 77, 2500 * workgroups + 1, 3_000_017):
             assert lib.t_undrawn(n, workgroups, phi_bytes) == 0, (n, phi_bytes)
+
+
+@pytest.mark.parametrize("waves,chunks", [(1, 300), (4096, 100_000), (1 << 20, 50_000_000), ((1 << 24) + 9, 1000), ((1 << 25) - 1, (1 << 31) - 1)])
+def test_a_chunk_has_one_owner(lib, waves, chunks):
+    """Workgroups that find the pool used up still add to its counter: up to the 2^25 workgroups of the largest launch of the
+    Poisson form no batch is handed out twice."""
+    share = chunks // 2 // waves
+    assert lib.t_owners_of_one_chunk(waves, share, chunks, 3 if waves > 100 else 1000) == 0
