@@ -85,8 +85,14 @@ struct ZeroTest {
     }
 };
 
-template <bool VEC, bool DEBUG, int KC = 0>   // KC: the number of topics where it is known at compile time
-__global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
+// KC: the number of topics where it is known at compile time.  WAVES: per SIMD.  The kernel for any multiple of 16 needs
+// 133 registers, five more than four waves may have: held to 128 it spills two.  Four waves are the faster form up to 128
+// topics (K = 64: 0.84 against 0.94 ms for 9000 news-shaped documents at 100 copies, 0.90 against 0.97 at 20 from a flat
+// posterior) and up to 256 where many topics receive copies (K = 240: 2.51 against 2.60 ms at 100 copies, but 0.94 against
+// 0.91 at 1.5).  Beyond, three: rows of more waves than that push one another out of the cache (K = 512 from a
+// flat posterior 4.34 against 4.07 ms, K = 1024 7.21 against 6.47).
+template <bool VEC, bool DEBUG, int KC = 0, int WAVES = 3>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) void poisson_draw_kernel(DrawArgs a)
 {
     extern __shared__ uint32_t lds[];
     const int lane = threadIdx.x;
@@ -314,6 +320,7 @@ __global__ __launch_bounds__(kWave) void poisson_draw_kernel(DrawArgs a)
     if (!DEBUG && live && a.cost) a.cost[tau] = (3u * a.cost[tau] + busy + 2u) >> 2;
 }
 
+inline bool poisson_four_waves(int K, float mf) { return K <= 128 || (K <= 256 && mf >= 10.0f); }
 inline size_t poisson_lds_bytes() { return 4u * (size_t)kWave * (size_t)(2 * kQCap + 1); }
 
 }  // namespace same

@@ -565,9 +565,11 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         dim3 grid((unsigned)blocks);
         a.chunk_share = (uint32_t)(a.n_chunks / 2 / blocks);
         const size_t lds = same::poisson_lds_bytes();
-        if (a.K == 256)            hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 256>), grid, block, lds, st, a);
-        else if (a.K % same::kBlk == 0) hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG>), grid, block, lds, st, a);
-        else                       hipLaunchKernelGGL((same::poisson_draw_kernel<false, DEBUG>), grid, block, lds, st, a);
+        if (a.K % same::kBlk != 0) hipLaunchKernelGGL((same::poisson_draw_kernel<false, DEBUG>), grid, block, lds, st, a);
+        else if (a.K == 256)       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 256, 4>), grid, block, lds, st, a);
+        else if (same::poisson_four_waves(a.K, a.mf))
+                                   hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 0, 4>), grid, block, lds, st, a);
+        else                       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG>), grid, block, lds, st, a);
     } else {
         // blocks of 4 * ceil(K / 128) topics, read in batches of one, two or four 16-byte loads per matrix
         // (K = 512 and K = 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the

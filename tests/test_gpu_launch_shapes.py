@@ -102,3 +102,22 @@ def test_full_shares_where_phi_is_large(extra):
     assert np.array_equal(np.asarray(g.get(binding.NDK)).reshape(X.D, 1024).sum(1, dtype=np.int64), m * docs)
     assert np.array_equal(np.asarray(g.get(binding.NWK)).reshape(X.V, 1024).sum(1, dtype=np.int64), m * words)
     g.close()
+
+
+@pytest.mark.parametrize("K,m", [(16, 2.5), (128, 40.5), (144, 2.5), (144, 40.5), (240, 12.25), (272, 40.5), (528, 2.5)])
+def test_poisson_at_any_multiple_of_16(K, m):
+    """Both occupancies of the Poisson kernel for a multiple of 16 topics, at the ends of their ranges: four waves up to 128
+    topics and, from ten copies on, up to 256; three beyond.  Counts against the oracle."""
+    rng = np.random.default_rng(K)
+    counts = rng.integers(1, 9, size=(60, 90)) * (rng.uniform(size=(60, 90)) < 0.4)
+    cols = [np.flatnonzero(r) for r in counts]
+    X = oracle.CSC(60, 90, np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32),
+                   np.concatenate(cols).astype(np.int32), counts[counts > 0].astype(np.float32))
+    o = oracle.OracleLDA(X, K, 0.2, 0.05, seed=17, m0=1, G=4)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.2, 0.05, 17, 1, 4)
+    for _ in range(2):
+        o.sweep_poisson(m)
+        g.sweep_poisson(m)
+        assert np.array_equal(g.get(binding.NDK), o.ndk)
+        assert np.array_equal(g.get(binding.NWK), o.nwk)
+    g.close()
