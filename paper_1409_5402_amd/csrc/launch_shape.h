@@ -97,6 +97,18 @@ SAME_HD inline Share share_of_ticket(uint32_t t, uint32_t group, uint32_t waves,
     return s;
 }
 
+// Workgroups of a draw launch on one compute unit, of the `most` that its registers and LDS allow.  Beyond 1024 topics a block
+// is read in several batches and a wave's theta row again for every pair of tasks (up to 1024 it stays in registers): the rows of
+// the waves on a compute unit have to fit its cache of 32 KB, or every pair fetches a row of up to 8 KB from the next one.
+// 27,000 news-shaped documents, m = 100: K = 1100 with sixteen waves 21.2 ms, with 8, 6 and 4 13.3, 13.2 and 15.6; K = 1540 28.6,
+// and 19.2, 18.4, 21.0; 5000 documents, m = 1: K = 2048 with twelve 3.08 ms, with 8, 6 and 4 3.01, 2.84, 2.72.
+constexpr int kCacheBytes = 32 << 10;
+inline int groups_per_unit(int K, int most)
+{
+    const int fit = K <= 1024 ? most : kCacheBytes / (4 * K);      // 7 down to 4
+    return fit < most ? fit : most;
+}
+
 // The pool of chunks that continue full pair-list slots: each of `waves` workgroups owns `share` of its `chunks`, the rest is
 // handed out in batches by a counter.  The counter counts batches: a workgroup adds to it once more before it sees that the
 // pool is used up, and the Poisson form has a workgroup for every 64 tasks, up to 2^25 of them.  A counter of

@@ -513,8 +513,9 @@ void assign_counters(same_lda* h, same::DrawArgs& a, hipStream_t st)
 
 int zero_u32(same_lda* h, uint32_t* p, size_t n, hipStream_t st);
 
-// Workgroups of kernel f that the device holds at once, in whole ticket groups.  Asked once per handle and kernel.
-int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t* out)
+// Workgroups of kernel f that a launch has: as many as the device holds at once, or as its caches serve (uniform: the kernel
+// reads no rows), in whole ticket groups.  Asked once per handle and kernel.
+int resident_groups(same_lda* h, const void* f, int threads, size_t lds, bool uniform, int64_t* out)
 {
     for (int i = 0; i < h->n_resident; ++i)
         if (h->resident[i].kernel == f) { *out = h->resident[i].groups; return SAME_LDA_OK; }
@@ -523,6 +524,7 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, int64_t
     HIP_TRY(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     HIP_TRY(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, lds));
     if (per_cu < 1) per_cu = 1;
+    if (!uniform) per_cu = same::groups_per_unit(h->K, per_cu);
     const int64_t n = same::whole_groups((int64_t)cus * per_cu);
     if (h->n_resident < (int)(sizeof h->resident / sizeof h->resident[0])) h->resident[h->n_resident++] = {f, n};
     *out = n;
@@ -583,10 +585,10 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         else if (!DEBUG && a.K == 1024) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, false, 4, false, 1024, true>);
         else if (a.K % 4 == 0) f = draw_kernel_for<true, DEBUG>(quads);
         else                   f = draw_kernel_for<false, DEBUG>(quads);
-        // As many one-wave workgroups as the chip holds at once, each with a share of the positions.
+        // One-wave workgroups, each with a share of the positions.
         const size_t lds = same::draw_lds_bytes(a.K, uniform);
         int64_t resident = 0;
-        int rc = resident_groups(h, f, T, lds, &resident);
+        int rc = resident_groups(h, f, T, lds, uniform, &resident);
         if (rc) return rc;
         const same::Shares sh = same::shares_for(a.n, resident, (int64_t)h->V * a.K * 4);
         a.first = sh.first; a.full = sh.full;

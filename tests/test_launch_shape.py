@@ -57,6 +57,7 @@ int t_blocks_in_use(int K) { return blocks_in_use(K); }
 int t_blocks_fill_row(int K) { return blocks_fill_row(K); }
 long t_undrawn(long n, long workgroups, long phi_bytes) { return undrawn(n, whole_groups(workgroups), phi_bytes); }
 long t_owners_of_one_chunk(unsigned waves, unsigned share, unsigned chunks, unsigned busy) { return owners_of_one_chunk(waves, share, chunks, busy); }
+int t_groups_per_unit(int K, int most) { return groups_per_unit(K, most); }
 int t_scan_first_topic(int hl, int T, int nblk) { return scan_first_topic(hl, T, nblk); }
 }
 """
@@ -107,3 +108,9 @@ def test_a_chunk_has_one_owner(lib, waves, chunks):
     Poisson form no batch is handed out twice."""
     share = chunks // 2 // waves
     assert lib.t_owners_of_one_chunk(waves, share, chunks, 3 if waves > 100 else 1000) == 0
+
+
+def test_workgroups_per_compute_unit(lib):
+    """All that fit up to 1024 topics, then as many as have room for a row of theta each in 32 KB; never none, never more than fit."""
+    assert [lib.t_groups_per_unit(K, 16) for K in (1, 256, 1024, 1025, 1170, 1171, 1366, 1639, 2048)] == [16, 16, 16, 7, 7, 6, 5, 4, 4]
+    assert all(1 <= lib.t_groups_per_unit(K, most) <= most for K in range(1, 2049) for most in (1, 3, 12))
