@@ -533,25 +533,23 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, bool un
 
 // The draw kernel for blocks of 4 * quads topics (VEC: rows are aligned to 16 bytes).  Up to 896 topics a block is one batch
 // of loads, up to 1024 two in the contiguous form, beyond that batches of the largest of 4, 2, 1 that divides it.  The
-// debug hook draws a handful of tasks: one kernel for all blocks of more than one quad.
+// debug hook takes the same form of the kernel as the sweep: what it returns was drawn by the code that sweeps run.
 template <bool VEC, bool DEBUG>
 const void* draw_kernel_for(int quads)
 {
-    if (quads == 1) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, true>);
-    if constexpr (!DEBUG) {
-        switch (quads) {
-            case 2:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 2, true>);
-            case 3:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 3, true>);
-            case 4:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 4, true>);
-            case 5:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 5, true>);
-            case 6:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 6, true>);
-            case 7:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 7, true>);
-            case 8:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 4, false, 0, true>);
-            default: break;
-        }
-        if (quads % 4 == 0) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 4, false>);
-        if (quads % 2 == 0) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, false, 2, false>);
+    switch (quads) {
+        case 1:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, true>);
+        case 2:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 2, true>);
+        case 3:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 3, true>);
+        case 4:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, true>);
+        case 5:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 5, true>);
+        case 6:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 6, true>);
+        case 7:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 7, true>);
+        case 8:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, false, 0, true>);
+        default: break;
     }
+    if (quads % 4 == 0) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, false>);
+    if (quads % 2 == 0) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 2, false>);
     return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, false>);
 }
 
@@ -573,16 +571,16 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
                                    hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 0, 4>), grid, block, lds, st, a);
         else                       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG>), grid, block, lds, st, a);
     } else {
-        // blocks of 4 * ceil(K / 128) topics, read in batches of one, two or four 16-byte loads per matrix
-        // (K = 512 and K = 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
+        // blocks of 4 * ceil(K / 128) topics, read in batches of one to seven 16-byte loads per matrix
+        // (K = 512 and from 897 to 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
         // kernel is bound by vector-ALU issue, the extra additions of that form cost more than the fewer cache lines save)
         const int quads = same::block_len(a.K) / 4;                // 16-byte loads per block and matrix
         const void* f = nullptr;
         if (uniform)      f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
         else if (a.K < 4) f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
-        else if (!DEBUG && a.K == 256)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, false, 2, true, 256>);
-        else if (!DEBUG && a.K == 512)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, false, 4, true, 512, true>);
-        else if (!DEBUG && a.K == 1024) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, false, 4, false, 1024, true>);
+        else if (a.K == 256)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true, 256>);
+        else if (a.K == 512)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true>);
+        else if (a.K == 1024) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false, 1024, true>);
         else if (a.K % 4 == 0) f = draw_kernel_for<true, DEBUG>(quads);
         else                   f = draw_kernel_for<false, DEBUG>(quads);
         // One-wave workgroups, each with a share of the positions.

@@ -3,6 +3,7 @@ argument validation that needs no GPU, the schedules and the corpus generator.""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -71,3 +72,13 @@ def test_generator_shapes_and_determinism():
     assert tok[:50].sum() > tok[250:].sum()
     s = c.slice_docs(10, 20)
     assert s.D == 10 and s.nnz == colptr[20] - colptr[10]
+
+
+def test_debug_hook_draws_with_the_sweeps_kernels():
+    """Every form of the two draw kernels that the library holds for sweeps it holds for the debug hooks as well: single tasks
+    that are compared with the oracle are drawn by the code that sweeps run."""
+    names = subprocess.run(["nm", "-C", binding.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    for kernel, at in (("draw_kernel", 2), ("poisson_draw_kernel", 1)):
+        forms = {tuple(f.split(", ")) for f in re.findall(r"__device_stub__%s<([^>]*)>" % kernel, names)}
+        by_debug = {which: {f[:at] + f[at + 1:] for f in forms if f[at] == which} for which in ("false", "true")}
+        assert len(by_debug["false"]) >= 3 and by_debug["false"] == by_debug["true"], kernel
