@@ -91,16 +91,16 @@ __device__ __forceinline__ float gamma_variable(float a, uint32_t seed_lo, uint3
 // theta[d][k] = Gamma(n_dk + m*alpha) / m; rows_per_block documents per workgroup
 __global__ __launch_bounds__(256) void gamma_theta_kernel(const uint32_t* __restrict__ ndk, float* __restrict__ theta, int D, int K,
                                                          float mf, float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass,
-                                                         int rows_per_block)
+                                                         uint32_t rows_per_block)
 {
     const RowSplit<1> s(K);
     if (s.group >= s.groups) return;
-    const int r0 = blockIdx.x * rows_per_block, r1 = min(D, r0 + rows_per_block);
+    const Rows b = rows_of_block(blockIdx.x, rows_per_block, (uint32_t)D);
     for (int k = s.unit; k < K; k += s.groups == 1 ? 256 : K)
-        for (int d = r0 + s.group; d < r1; d += s.groups) {
+        for (uint32_t d = b.from + s.group; d < b.to; d += s.groups) {
             const size_t i = (size_t)d * K + k;
             const float a = (float)ndk[i] + prior;
-            theta[i] = gamma_variable(a, seed_lo, seed_hi, (uint32_t)d, (uint32_t)k, pass) / mf;
+            theta[i] = gamma_variable(a, seed_lo, seed_hi, d, (uint32_t)k, pass) / mf;
         }
 }
 
@@ -112,22 +112,21 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_phi_kernel(uint32_t* __re
                                                                  const uint32_t* __restrict__ hot_used,
                                                                  int hot_max, int hot_copies, float* __restrict__ phi, int V, int K,
                                                                  float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass,
-                                                                 int rows_per_block, double* __restrict__ partial)
+                                                                 uint32_t rows_per_block, double* __restrict__ partial)
 {
     __shared__ double sh[kGammaThreads];
     const RowSplit<1, kGammaThreads> s(K);
-    const int r0 = blockIdx.x * rows_per_block;
-    const int r1 = min(V, r0 + rows_per_block);
+    const Rows b = rows_of_block(blockIdx.x, rows_per_block, (uint32_t)V);
     const bool copies = hot_of != nullptr && *hot_used != 0u;
     for (int k = s.unit; k < K; k += s.groups == 1 ? kGammaThreads : K) {
         double acc = 0.0;
         if (s.group < s.groups) {
-            for (int r = r0 + s.group; r < r1; r += s.groups) {
+            for (uint32_t r = b.from + s.group; r < b.to; r += s.groups) {
                 const size_t i = (size_t)r * K + k;
                 uint32_t n[1] = {nwk[i]};
                 const int hot = copies ? (int)hot_of[r] : -1;
                 if (hot >= 0 && take_in_copies<1>(nwk, V, K, hot, hot_max, hot_copies, k, n)) nwk[i] = n[0];
-                const float g = gamma_variable((float)n[0] + prior, seed_lo, seed_hi, (uint32_t)r, (uint32_t)k, pass);
+                const float g = gamma_variable((float)n[0] + prior, seed_lo, seed_hi, r, (uint32_t)k, pass);
                 phi[i] = g;
                 acc += (double)g;
             }
@@ -149,14 +148,14 @@ __global__ __launch_bounds__(256) void gamma_phi_totals_kernel(const double* __r
 }
 
 __global__ __launch_bounds__(256) void gamma_phi_normalise_kernel(float* __restrict__ phi, int V, int K, const float* __restrict__ total,
-                                                                 int rows_per_block)
+                                                                 uint32_t rows_per_block)
 {
     const RowSplit<1> s(K);
     if (s.group >= s.groups) return;
-    const int r0 = blockIdx.x * rows_per_block, r1 = min(V, r0 + rows_per_block);
+    const Rows b = rows_of_block(blockIdx.x, rows_per_block, (uint32_t)V);
     for (int k = s.unit; k < K; k += s.groups == 1 ? 256 : K) {
         const float t = total[k];
-        for (int r = r0 + s.group; r < r1; r += s.groups) phi[(size_t)r * K + k] = phi[(size_t)r * K + k] / t;
+        for (uint32_t r = b.from + s.group; r < b.to; r += s.groups) phi[(size_t)r * K + k] = phi[(size_t)r * K + k] / t;
     }
 }
 

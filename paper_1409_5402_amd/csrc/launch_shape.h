@@ -97,6 +97,26 @@ SAME_HD inline Share share_of_ticket(uint32_t t, uint32_t group, uint32_t waves,
     return s;
 }
 
+// Kernels over rows: workgroup b owns `per_block` of them, the last one the rest.  Numbers of rows reach 2^31 - 1, with the hot
+// words' copies behind them 2^31 + 2^13: all of it is unsigned, and no sum here passes 2^32 for per_block below 2^30.
+struct Rows { uint32_t from, to; };
+SAME_HD inline Rows rows_of_block(uint32_t block, uint32_t per_block, uint32_t rows)
+{
+    Rows r;
+    r.from = block * per_block;
+    r.to = r.from + per_block < rows ? r.from + per_block : rows;
+    return r;
+}
+SAME_HD inline uint32_t blocks_of_rows(uint32_t rows, uint32_t per_block) { return (rows + per_block - 1u) / per_block; }
+
+// The next document of a loop in strides; false past the last one.  (d + step itself may pass 2^31.)
+SAME_HD inline bool next_document(int32_t& d, int32_t step, int32_t D)
+{
+    if (d >= D - step) return false;
+    d += step;
+    return true;
+}
+
 // Workgroups of a draw launch on one compute unit, of the `most` that its registers and LDS allow.  Beyond 1024 topics a block
 // is read in several batches and a wave's theta row again for every pair of tasks (up to 1024 it stays in registers): the rows of
 // the waves on a compute unit have to fit its cache of 32 KB, or every pair fetches a row of up to 8 KB from the next one.

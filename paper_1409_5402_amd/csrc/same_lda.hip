@@ -663,13 +663,13 @@ int update_totals(same_lda* h, Matrix* M, int32_t n_hot, float m, hipStream_t st
     a.nwk = h->nwk; a.nk = h->nk; a.V = h->V; a.K = h->K; a.hot_used = hot_used(h);
     a.n_hot = n_hot; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
     // at least two turns of four rows per thread, and at most 512 workgroups (64-bit atomics per topic)
-    const int rows = h->V + n_hot * same::kHotCopies, at_once = 8 * same::rows_at_once(h->K);
-    a.rows_per_block = (rows + 511) / 512;
+    const uint32_t rows = (uint32_t)h->V + (uint32_t)(n_hot * same::kHotCopies), at_once = 8u * (uint32_t)same::rows_at_once(h->K);
+    a.rows_per_block = same::blocks_of_rows(rows, 512u);
     if (a.rows_per_block < at_once) a.rows_per_block = at_once;
-    a.total_blocks = (rows + a.rows_per_block - 1) / a.rows_per_block;
+    a.total_blocks = same::blocks_of_rows(rows, a.rows_per_block);
     a.ndk = M ? M->ndk : nullptr; a.theta = M ? M->theta : nullptr;
     a.n_theta = M ? (size_t)M->D * h->K : 0; a.mf = m; a.alpha = h->alpha;
-    const unsigned blocks = (unsigned)(a.total_blocks + (a.n_theta ? grid_for((a.n_theta + 3) / 4) : 0));
+    const unsigned blocks = a.total_blocks + (a.n_theta ? (unsigned)grid_for((a.n_theta + 3) / 4) : 0u);
     if (h->K % 4 == 0) hipLaunchKernelGGL(same::totals_theta_kernel<4>, dim3(blocks), dim3(256), 0, st, a);
     else               hipLaunchKernelGGL(same::totals_theta_kernel<1>, dim3(blocks), dim3(256), 0, st, a);
     HIP_TRY(h, hipGetLastError());
@@ -690,8 +690,8 @@ int update_collapsed(same_lda* h, Matrix& M, float m, float rho, hipStream_t st)
     const int at_once = same::rows_at_once(h->K);
     int turns = h->V / (at_once * 1024);
     turns = turns < 1 ? 1 : (turns > 8 ? 8 : turns);
-    a.rows_per_block = turns * at_once;
-    const unsigned blocks = (unsigned)((h->V + a.rows_per_block - 1) / a.rows_per_block);
+    a.rows_per_block = (uint32_t)(turns * at_once);
+    const unsigned blocks = same::blocks_of_rows((uint32_t)h->V, a.rows_per_block);
     if (h->K % 4 == 0) hipLaunchKernelGGL(same::phi_update_kernel<4>, dim3(blocks), dim3(256), 0, st, a);
     else               hipLaunchKernelGGL(same::phi_update_kernel<1>, dim3(blocks), dim3(256), 0, st, a);
     HIP_TRY(h, hipGetLastError());
@@ -702,8 +702,8 @@ int update_collapsed(same_lda* h, Matrix& M, float m, float rho, hipStream_t st)
 int sample_theta(same_lda* h, Matrix& M, float m, uint32_t pword, hipStream_t st)
 {
     if (M.D == 0) return SAME_LDA_OK;
-    const int rows = 4 * (h->K >= 256 ? 1 : 256 / h->K);
-    hipLaunchKernelGGL(same::gamma_theta_kernel, dim3((unsigned)((M.D + rows - 1) / rows)), dim3(256), 0, st, M.ndk, M.theta, M.D, h->K, m,
+    const uint32_t rows = 4u * (h->K >= 256 ? 1u : 256u / (uint32_t)h->K);
+    hipLaunchKernelGGL(same::gamma_theta_kernel, dim3(same::blocks_of_rows((uint32_t)M.D, rows)), dim3(256), 0, st, M.ndk, M.theta, M.D, h->K, m,
                        m * h->alpha, (uint32_t)h->seed, (uint32_t)(h->seed >> 32), pword, rows);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
@@ -712,7 +712,7 @@ int sample_theta(same_lda* h, Matrix& M, float m, uint32_t pword, hipStream_t st
 // phi drawn from its Dirichlet conditionals: Gamma variables, their sums over words in a fixed order, division.
 int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_t st)
 {
-    const int blocks = (h->V + kGammaRows - 1) / kGammaRows;
+    const int blocks = (int)same::blocks_of_rows((uint32_t)h->V, kGammaRows);
     // the topic totals are part of the readable state, kept current as after a collapsed update
     const int rc = update_totals(h, nullptr, M.n_hot, m, st);
     if (rc) return rc;
@@ -721,8 +721,8 @@ int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_
                        pword, kGammaRows, h->gamma_partial);
     hipLaunchKernelGGL(same::gamma_phi_totals_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, st, h->gamma_partial,
                        blocks, h->K, h->gamma_total);
-    const int rows = 8 * (h->K >= 256 ? 1 : 256 / h->K);
-    hipLaunchKernelGGL(same::gamma_phi_normalise_kernel, dim3((unsigned)((h->V + rows - 1) / rows)), dim3(256), 0, st, h->phi, h->V, h->K,
+    const uint32_t rows = 8u * (h->K >= 256 ? 1u : 256u / (uint32_t)h->K);
+    hipLaunchKernelGGL(same::gamma_phi_normalise_kernel, dim3(same::blocks_of_rows((uint32_t)h->V, rows)), dim3(256), 0, st, h->phi, h->V, h->K,
                        h->gamma_total, rows);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
@@ -836,7 +836,7 @@ int same_lda_init(same_lda_t** out, const same_lda_csc* X, int32_t K, float alph
     if (!rc) rc = dev_alloc(h, &h->phi, (size_t)h->V * K);
     if (!rc) rc = dev_alloc(h, &h->nwk, nwk_elements(h));
     if (!rc) rc = dev_alloc(h, &h->nk, (size_t)K);
-    if (!rc) rc = dev_alloc(h, &h->gamma_partial, (size_t)((h->V + kGammaRows - 1) / kGammaRows) * K);
+    if (!rc) rc = dev_alloc(h, &h->gamma_partial, (size_t)same::blocks_of_rows((uint32_t)h->V, kGammaRows) * K);
     if (!rc) rc = dev_alloc(h, &h->gamma_total, (size_t)K);
     if (!rc) rc = dev_alloc(h, &h->vb_psi, (size_t)K);
     if (!rc) rc = dev_alloc(h, &h->draw_counter, (size_t)kSecondCounters + same::kCounterWords);

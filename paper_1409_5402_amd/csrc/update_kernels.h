@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_shape.h"
 #include "rng_binom.h"
 
 namespace same {
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __res
 // loads in flight per thread; one 64-bit atomic per topic and workgroup (a few hundred of them: 1563 on every topic's
 // address were most of the 55 us this took at V = 100,000, K = 256).  The other workgroups update theta.
 struct TotalsArgs {
-    const uint32_t* nwk; unsigned long long* nk; int V, K, n_hot, hot_max, hot_copies, rows_per_block, total_blocks;
+    const uint32_t* nwk; unsigned long long* nk; int V, K, n_hot, hot_max, hot_copies; uint32_t rows_per_block, total_blocks;
     const uint32_t* hot_used;              // 0: the copies have taken nothing
     const uint32_t* ndk; float* theta; size_t n_theta; float mf, alpha;
 };
@@ -159,33 +160,34 @@ struct TotalsArgs {
 template <int W>
 __global__ __launch_bounds__(256) void totals_theta_kernel(TotalsArgs a)
 {
-    if ((int)blockIdx.x >= a.total_blocks) {
+    if (blockIdx.x >= a.total_blocks) {
         theta_update(a.ndk, a.theta, a.n_theta, a.mf, a.alpha, (size_t)(blockIdx.x - a.total_blocks) * 256u + threadIdx.x,
                      (size_t)(gridDim.x - a.total_blocks) * 256u);
         return;
     }
     __shared__ unsigned long long sh[256 * W];
     const RowSplit<W> s(a.K);
-    const int rows = a.V + (a.n_hot > 0 && *a.hot_used != 0u ? a.n_hot * a.hot_copies : 0);
-    const int r0 = blockIdx.x * a.rows_per_block, r1 = min(rows, r0 + a.rows_per_block);
-    auto row = [&](int r) {
-        int64_t at = r;
-        if (r >= a.V) { const int j = r - a.V; at = a.V + (int64_t)(j / a.n_hot) * a.hot_max + j % a.n_hot; }
-        return a.nwk + (size_t)at * a.K;
+    const uint32_t V = (uint32_t)a.V, rows = V + (a.n_hot > 0 && *a.hot_used != 0u ? (uint32_t)(a.n_hot * a.hot_copies) : 0u);
+    const Rows b = rows_of_block(blockIdx.x, a.rows_per_block, rows);
+    const uint32_t groups = (uint32_t)s.groups;
+    auto row = [&](uint32_t r) {
+        size_t at = r;
+        if (r >= V) { const int j = (int)(r - V); at = (size_t)V + (size_t)(j / a.n_hot) * a.hot_max + j % a.n_hot; }
+        return a.nwk + at * a.K;
     };
     for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
         unsigned long long acc[W] = {};
         if (s.group < s.groups) {
-            for (int r = r0 + s.group; r < r1; r += 4 * s.groups) {
+            for (uint32_t r = b.from + s.group; r < b.to; r += 4 * groups) {
                 uint32_t v[4][W];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int rj = r + j * s.groups;
-                    load_unit<W>(row(rj < r1 ? rj : r) + W * u, v[j]);
+                for (uint32_t j = 0; j < 4u; ++j) {
+                    const uint32_t rj = r + j * groups;
+                    load_unit<W>(row(rj < b.to ? rj : r) + W * u, v[j]);
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (r + j * s.groups < r1) for (int c = 0; c < W; ++c) acc[c] += v[j][c];
+                for (uint32_t j = 0; j < 4u; ++j)
+                    if (r + j * groups < b.to) for (int c = 0; c < W; ++c) acc[c] += v[j][c];
             }
         }
         if (s.groups > 1) {                                        // the row groups' sums of a topic
@@ -229,7 +231,7 @@ __device__ __forceinline__ bool take_in_copies(uint32_t* __restrict__ nwk, int V
 struct PhiArgs {
     uint32_t* nwk; const unsigned long long* nk; float* phi; const int16_t* hot_of;   // hot_of null: no hot words
     const uint32_t* hot_used;              // 0: their copies have taken nothing
-    int V, K, hot_max, hot_copies, rows_per_block;
+    int V, K, hot_max, hot_copies; uint32_t rows_per_block;
     float mf, beta, vbeta, rho;
 };
 
@@ -238,14 +240,14 @@ __global__ __launch_bounds__(256) void phi_update_kernel(PhiArgs a)
 {
     const RowSplit<W> s(a.K);
     if (s.group >= s.groups) return;
-    const int r0 = blockIdx.x * a.rows_per_block, r1 = min(a.V, r0 + a.rows_per_block);
+    const Rows b = rows_of_block(blockIdx.x, a.rows_per_block, (uint32_t)a.V);
     const bool copies = a.hot_of != nullptr && *a.hot_used != 0u;
     const float one_minus_rho = 1.0f - a.rho;
     for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
         float den[W];
 #pragma unroll
         for (int c = 0; c < W; ++c) den[c] = (float)a.nk[W * u + c] / a.mf + a.vbeta;
-        for (int r = r0 + s.group; r < r1; r += s.groups) {
+        for (uint32_t r = b.from + s.group; r < b.to; r += s.groups) {
             const size_t at = (size_t)r * a.K + W * u;
             uint32_t n[W];
             load_unit<W>(a.nwk + at, n);

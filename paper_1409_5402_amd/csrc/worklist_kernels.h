@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_shape.h"
+
 namespace same {
 
 // Filled by the kernels below; first_bad is the smallest (index << 2 | code) over all defects found,
@@ -83,7 +85,8 @@ __global__ __launch_bounds__(256) void wl_scan_docs(const int32_t* __restrict__ 
     const int sub = threadIdx.x & (kDocLanes - 1);
     const int32_t docs_at_once = (int32_t)(gridDim.x * (256 / kDocLanes));
     if (blockIdx.x == 0 && threadIdx.x == 0) ntask[nnz] = 0u;
-    for (int32_t d = (int32_t)(blockIdx.x * (256 / kDocLanes) + threadIdx.x / kDocLanes); d < D; d += docs_at_once) {
+    int32_t d = (int32_t)(blockIdx.x * (256 / kDocLanes) + threadIdx.x / kDocLanes);
+    if (d < D) do {
         const int64_t c0 = colptr[d], c1 = colptr[d + 1];
         if (c1 < c0 && sub == 0) atomicMin(&s->first_bad, ((unsigned long long)d << 2) | 1ull);
         const int64_t lo = c0 < 0 ? 0 : c0, hi = c1 < nnz ? c1 : nnz;
@@ -112,7 +115,7 @@ __global__ __launch_bounds__(256) void wl_scan_docs(const int32_t* __restrict__ 
         for (int o = kDocLanes / 2; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
         if (sub == 0) doc_tok[d] = mine;
         doc_max = mine > doc_max ? mine : doc_max;
-    }
+    } while (next_document(d, docs_at_once, D));
     if (ones) atomicAdd(&sh_sizes[0], ones);
     for (int o = 32; o > 0; o >>= 1) {
         tok += __shfl_xor(tok, o); tasks += __shfl_xor(tasks, o);

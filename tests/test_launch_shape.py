@@ -58,6 +58,25 @@ int t_blocks_fill_row(int K) { return blocks_fill_row(K); }
 long t_undrawn(long n, long workgroups, long phi_bytes) { return undrawn(n, whole_groups(workgroups), phi_bytes); }
 long t_owners_of_one_chunk(unsigned waves, unsigned share, unsigned chunks, unsigned busy) { return owners_of_one_chunk(waves, share, chunks, busy); }
 int t_groups_per_unit(int K, int most) { return groups_per_unit(K, most); }
+// Rows near `rows` that belong to no workgroup, to two, or to one past the end.
+long t_rows_without_owner(unsigned rows, unsigned per_block)
+{
+    const uint32_t blocks = blocks_of_rows(rows, per_block);
+    long wrong = rows_of_block(blocks - 1, per_block, rows).to != rows;
+    for (uint32_t b = blocks > 5 ? blocks - 5 : 0; b < blocks; ++b) {
+        const Rows r = rows_of_block(b, per_block, rows);
+        wrong += r.from >= r.to || r.to > rows || (b > 0 && rows_of_block(b - 1, per_block, rows).to != r.from);
+    }
+    return wrong;
+}
+// Documents of one thread's loop that are not in [0, D) or do not ascend; the last one must be within a stride of D.
+long t_documents_out_of_range(int first, int step, int D)
+{
+    long wrong = 0;
+    int32_t d = first, before = first - 1;
+    if (d < D) do { wrong += d < 0 || d >= D || d <= before; before = d; } while (wrong == 0 && next_document(d, step, D));
+    return wrong + (first < D && D - step > before);
+}
 int t_scan_first_topic(int hl, int T, int nblk) { return scan_first_topic(hl, T, nblk); }
 }
 """
@@ -73,6 +92,9 @@ def lib(tmp_path_factory):
     so = ctypes.CDLL(str(so))
     so.t_undrawn.argtypes = [ctypes.c_long] * 3
     so.t_undrawn.restype = ctypes.c_long
+    so.t_rows_without_owner.argtypes = [ctypes.c_uint] * 2
+    so.t_rows_without_owner.restype = ctypes.c_long
+    so.t_documents_out_of_range.restype = ctypes.c_long
     so.t_owners_of_one_chunk.argtypes = [ctypes.c_uint] * 4
     so.t_owners_of_one_chunk.restype = ctypes.c_long
     return so
@@ -114,3 +136,15 @@ def test_workgroups_per_compute_unit(lib):
     """All that fit up to 1024 topics, then as many as have room for a row of theta each in 32 KB; never none, never more than fit."""
     assert [lib.t_groups_per_unit(K, 16) for K in (1, 256, 1024, 1025, 1170, 1171, 1366, 1639, 2048)] == [16, 16, 16, 7, 7, 6, 5, 4, 4]
     assert all(1 <= lib.t_groups_per_unit(K, most) <= most for K in range(1, 2049) for most in (1, 3, 12))
+
+
+def test_rows_and_documents_up_to_the_largest_number(lib):
+    """Rows are shared out and documents gone through without a sum that passes its type, up to 2^31 - 1 of them (and the
+    hot words' copies behind the words)."""
+    most = 2**31 - 1
+    for rows in (1, 7, 1024, 1025, 100_000, most - 1023, most - 1, most, most + 8192):
+        for per_block in (1, 4, 64, 1024, 2048, (rows + 511) // 512):
+            assert lib.t_rows_without_owner(rows, per_block) == 0, (rows, per_block)
+    for D in (0, 1, 16_383, 16_384, 16_385, 3_000_000, most - 16_384, most - 300, most):
+        for first in (0, 5, 16_383):
+            assert lib.t_documents_out_of_range(first, 16_384, D) == 0, (D, first)
