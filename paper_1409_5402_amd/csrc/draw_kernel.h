@@ -839,7 +839,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     uint32_t t = 0;                                // this group's ticket
                     if (lane == 0) t = atomicAdd(a.counter + kCounterStride * group, 1u);
                     t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
-                    const Share s = share_of_ticket(t, group, gridDim.x, a.first, a.full, a.n);
+                    const Share s = share_of_ticket(t, group, gridDim.x, a.first, a.n);
                     from = s.from; size = s.size;
                 }
                 drained = from >= a.n;

@@ -35,18 +35,10 @@ constexpr int kGroups = 32;             // (8 and 64 measured within 1 %)
 constexpr int kCounterStride = 32;      // words between two counters: a cache line each
 constexpr int kCounterWords = kGroups * kCounterStride;
 
-// Where phi is large (over kPhiLarge bytes) the waves stay in neighbouring documents: shares of kShareMax positions, round
-// after round, and halving ones at the end.  Spread over the whole matrix the waves' pair-list and count lines push phi out
-// of the memory-side cache: 512 topics, 100,000 words (205 MB), 60 million tasks 23.2 ms, in shares of 512 18.9, of 2048
-// 19.7 ms.  At 256 topics (102 MB) the large shares are better by 2 % converged and 6 % from a flat posterior.
-constexpr int kShareMax = 512;
-constexpr int64_t kPhiLarge = 128ll << 20;
-
-struct Shares { int32_t waves, first, full; };   // workgroups of a launch, positions of a share of round 0, full rounds behind it
-inline Shares shares_for(int64_t n, int64_t resident, int64_t phi_bytes)
+struct Shares { int32_t waves, first; };        // workgroups of a launch, positions of a share of round 0
+inline Shares shares_for(int64_t n, int64_t resident)
 {
     Shares s;
-    s.full = 0;
     const int64_t per = (n + resident - 1) / resident;
     if (per <= kShareAll) {                                        // fewer workgroups, none with less than a wave's worth
         s.first = per < kWave ? kWave : (int32_t)per;
@@ -54,10 +46,6 @@ inline Shares shares_for(int64_t n, int64_t resident, int64_t phi_bytes)
     } else {
         s.first = (int32_t)(per / (2 * kShareMin) * kShareMin);
         s.waves = (int32_t)resident;
-        if (phi_bytes > kPhiLarge && s.first > kShareMax) {
-            s.first = kShareMax;
-            s.full = (int32_t)(n / ((int64_t)s.waves * s.first)) - 2;
-        }
     }
     return s;
 }
@@ -77,18 +65,15 @@ inline int64_t whole_groups(int64_t workgroups)
     return n < 8 * kGroups ? 8 * kGroups : n;
 }
 
-// The share that ticket t of a group stands for: `full` rounds of `first` positions for each of `waves` workgroups (a
-// multiple of kGroups) follow round 0, then the halving ones; a group's shares are every kGroups-th of a round.  From n on
-// nothing is left.
+// The share that ticket t of a group stands for, in a launch of `waves` workgroups (a multiple of kGroups): a group's shares
+// are every kGroups-th of a round.  From n on nothing is left.
 struct Share { int64_t from; int32_t size; };
-SAME_HD inline Share share_of_ticket(uint32_t t, uint32_t group, uint32_t waves, int32_t first, int32_t full, int64_t n)
+SAME_HD inline Share share_of_ticket(uint32_t t, uint32_t group, uint32_t waves, int32_t first, int64_t n)
 {
     const uint32_t per_round = waves / kGroups;
-    const uint32_t whole = t / per_round < (uint32_t)full ? t / per_round : (uint32_t)full;
     Share s;
-    s.from = (int64_t)waves * first * ((int64_t)whole + 1);
-    s.size = whole < (uint32_t)full ? first : share_of_round(first, 1);
-    t -= whole * per_round;
+    s.from = (int64_t)waves * first;                               // round 1
+    s.size = share_of_round(first, 1);
     for (int round = 2; t >= per_round && s.from < n; ++round) {
         s.from += (int64_t)waves * s.size; t -= per_round;
         s.size = share_of_round(first, round);
@@ -117,15 +102,21 @@ SAME_HD inline bool next_document(int32_t& d, int32_t step, int32_t D)
     return true;
 }
 
-// Workgroups of a draw launch on one compute unit, of the `most` that its registers and LDS allow.  Beyond 1024 topics a block
-// is read in several batches and a wave's theta row again for every pair of tasks (up to 1024 it stays in registers): the rows of
-// the waves on a compute unit have to fit its cache of 32 KB, or every pair fetches a row of up to 8 KB from the next one.
-// 27,000 news-shaped documents, m = 100: K = 1100 with sixteen waves 21.2 ms, with 8, 6 and 4 13.3, 13.2 and 15.6; K = 1540 28.6,
-// and 19.2, 18.4, 21.0; 5000 documents, m = 1: K = 2048 with twelve 3.08 ms, with 8, 6 and 4 3.01, 2.84, 2.72.
-constexpr int kCacheBytes = 32 << 10;
+// Workgroups of a draw launch on one compute unit, of the `most` that its registers and LDS allow: the steps (and beyond 1024
+// topics, where a block is read in several batches, the scan of every pair of tasks) read the theta row of the wave's document
+// again and again, and the rows of the waves on a compute unit have to stay in its cache of 32 KB, or they come from the next
+// one.  Measured with news-shaped documents at m = 100, ms per sweep:
+//   K = 512    120,000 documents  sixteen 10.3  fourteen 9.9  twelve 10.4;  60,000 and 30,000 words  5.0 (5.8)  4.5  4.7
+//   K = 1100    27,000            sixteen 21.2  eight 13.3    six 13.2      four 15.6
+//   K = 1540    27,000            sixteen 28.6  eight 19.2    six 18.4      four 21.0
+//   K = 2048     5,000, m = 1     twelve 3.08   eight 3.01    six 2.84      four 2.72
+// (5.8 in shares that halve from the first, 5.0 in shares of 512: with fourteen waves it makes no difference.)  Up to 512
+// topics the phi blocks need some of the cache too; below 449 and from 513 to 1024 no limit applies (the scan holds its theta
+// rows in registers there; K = 1024 with ten and seven waves instead of twelve: 6.4, 6.8, 8.5 ms for 40,000 documents).
 inline int groups_per_unit(int K, int most)
 {
-    const int fit = K <= 1024 ? most : kCacheBytes / (4 * K);      // 7 down to 4
+    const int row = 4 * K;
+    const int fit = K > 1024 ? (32 << 10) / row : (K <= 512 ? (28 << 10) / row : most);
     return fit < most ? fit : most;
 }
 

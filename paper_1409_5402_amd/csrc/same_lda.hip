@@ -588,8 +588,8 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         int64_t resident = 0;
         int rc = resident_groups(h, f, T, lds, uniform, &resident);
         if (rc) return rc;
-        const same::Shares sh = same::shares_for(a.n, resident, (int64_t)h->V * a.K * 4);
-        a.first = sh.first; a.full = sh.full;
+        const same::Shares sh = same::shares_for(a.n, resident);
+        a.first = sh.first;
         if ((int64_t)sh.waves * sh.first >= a.n) { a.n_heavy = 0; a.heavy_from = ~0u; }   // every task starts at once
         a.chunk_share = a.n_chunks / 2 / (uint32_t)sh.waves;
         void* args[] = {&a};
@@ -606,7 +606,7 @@ unsigned long long* g_stats = nullptr;   // profiling builds only
 same::DrawArgs draw_args(const same_lda* h, const Matrix& M, Copies c, uint32_t pass_word, bool with_words)
 {
     same::DrawArgs a;
-    a.n = M.n_tasks; a.counter = nullptr; a.first = 0; a.full = 0; a.t_doc = M.t_doc; a.t_word = M.t_word; a.t_g = M.t_g; a.order = M.order; a.cost = M.cost; a.ids = nullptr;
+    a.n = M.n_tasks; a.counter = nullptr; a.first = 0; a.t_doc = M.t_doc; a.t_word = M.t_word; a.t_g = M.t_g; a.order = M.order; a.cost = M.cost; a.ids = nullptr;
     a.theta = M.theta; a.phi = h->phi; a.ndk = M.ndk; a.nwk = with_words ? h->nwk : nullptr;
     // a pair holds a count below 2^(32 - kPairShift): m * largest group must fit
     // (a Poisson count may exceed its rate: four times the rate plus 128 is beyond any count the walk can return)

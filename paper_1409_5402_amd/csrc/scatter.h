@@ -25,7 +25,6 @@ struct DrawArgs {
     int64_t         n;          // tasks in this launch
     uint32_t*       counter;    // multinomial form: [kCounterWords] tickets for shares of the positions (zero at launch)
     int32_t         first;      // multinomial form: launch positions of a workgroup's first share
-    int32_t         full;       // and the rounds of shares of the same size behind it
     const int32_t*  heavy;      // multinomial form: [n_heavy] ids of the tasks of at least heavy_from tokens
     int32_t         n_heavy;
     uint32_t        heavy_from;

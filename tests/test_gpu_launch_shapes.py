@@ -91,7 +91,7 @@ def test_heavy_tasks_are_drawn_once(K, G):
 
 @pytest.mark.parametrize("extra", [1, 777])
 def test_full_shares_where_phi_is_large(extra):
-    """1024 topics and 33,000 words (135 MB of phi): shares of 512 positions, round after round, before they halve.  Every
+    """1024 topics and 33,000 words (135 MB of phi), 6.3 million tasks: shares by tickets round after round.  Every
     document and word keeps exactly m copies of each token."""
     X = matrix(3072 * 512 * 4 + extra, V=33000, seed=3)
     g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, 1024, 0.1, 0.05, 5, 1, 8)

@@ -14,20 +14,20 @@ SHIM = r"""
 using namespace same;
 
 // Positions of a launch that are not drawn exactly once when every group that has a workgroup takes tickets until none is left.
-static long undrawn(long n, long resident, long phi_bytes)
+static long undrawn(long n, long resident)
 {
     std::vector<unsigned char> drawn(n, 0);
     long wrong = 0;
     auto draw = [&](long from, long size) {
         for (long i = from; i < from + size && i < n; ++i) if (drawn[i]++) ++wrong;
     };
-    const Shares s = shares_for(n, resident, phi_bytes);
+    const Shares s = shares_for(n, resident);
     bool has[kGroups] = {};
     for (long b = 0; b < s.waves; ++b) { draw(b * s.first, s.first); has[ticket_group((uint32_t)b)] = true; }
     if ((long)s.waves * s.first < n)
         for (uint32_t g = 0; g < kGroups; ++g)
             for (uint32_t t = 0; has[g]; ++t) {
-                const Share h = share_of_ticket(t, g, (uint32_t)s.waves, s.first, s.full, n);
+                const Share h = share_of_ticket(t, g, (uint32_t)s.waves, s.first, n);
                 if (h.from >= n) break;
                 draw(h.from, h.size);
             }
@@ -55,7 +55,7 @@ extern "C" {
 int t_block_len(int K) { return block_len(K); }
 int t_blocks_in_use(int K) { return blocks_in_use(K); }
 int t_blocks_fill_row(int K) { return blocks_fill_row(K); }
-long t_undrawn(long n, long workgroups, long phi_bytes) { return undrawn(n, whole_groups(workgroups), phi_bytes); }
+long t_undrawn(long n, long workgroups) { return undrawn(n, whole_groups(workgroups)); }
 long t_owners_of_one_chunk(unsigned waves, unsigned share, unsigned chunks, unsigned busy) { return owners_of_one_chunk(waves, share, chunks, busy); }
 int t_groups_per_unit(int K, int most) { return groups_per_unit(K, most); }
 // Rows near `rows` that belong to no workgroup, to two, or to one past the end.
@@ -90,7 +90,7 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I", CSRC,
                     str(src), "-o", str(so)], check=True)
     so = ctypes.CDLL(str(so))
-    so.t_undrawn.argtypes = [ctypes.c_long] * 3
+    so.t_undrawn.argtypes = [ctypes.c_long] * 2
     so.t_undrawn.restype = ctypes.c_long
     so.t_rows_without_owner.argtypes = [ctypes.c_uint] * 2
     so.t_rows_without_owner.restype = ctypes.c_long
@@ -117,11 +117,10 @@ def test_scan_stays_inside_the_row(lib):
 
 @pytest.mark.parametrize("workgroups", [1, 32, 100, 224, 255, 256, 384, 1000, 3072, 4096, 5120])
 def test_every_position_has_one_share(lib, workgroups):
-    """Whatever number of workgroups a device holds at once: the static shares, the whole rounds where phi is large and the
-    halving ones cover every launch position once, and no ticket group is without a workgroup that draws its shares."""
-    for phi_bytes in (1 << 20, 1 << 30):
-        for n in (1, 63, 64, 65, 128 * 256, 128 * 256 + 1, 128 * workgroups, 128 * workgroups + 1, 1000 * workgroups + 77, 2500 * workgroups + 1, 3_000_017):
-            assert lib.t_undrawn(n, workgroups, phi_bytes) == 0, (n, phi_bytes)
+    """Whatever number of workgroups a device holds at once: the static shares and the halving ones
+    cover every launch position once, and no ticket group is without a workgroup that draws its shares."""
+    for n in (1, 63, 64, 65, 128 * 256, 128 * 256 + 1, 128 * workgroups, 128 * workgroups + 1, 1000 * workgroups + 77, 2500 * workgroups + 1, 3_000_017):
+        assert lib.t_undrawn(n, workgroups) == 0, n
 
 
 @pytest.mark.parametrize("waves,chunks", [(1, 300), (4096, 100_000), (1 << 20, 50_000_000), ((1 << 24) + 9, 1000), ((1 << 25) - 1, (1 << 31) - 1)])
@@ -133,8 +132,9 @@ def test_a_chunk_has_one_owner(lib, waves, chunks):
 
 
 def test_workgroups_per_compute_unit(lib):
-    """All that fit up to 1024 topics, then as many as have room for a row of theta each in 32 KB; never none, never more than fit."""
-    assert [lib.t_groups_per_unit(K, 16) for K in (1, 256, 1024, 1025, 1170, 1171, 1366, 1639, 2048)] == [16, 16, 16, 7, 7, 6, 5, 4, 4]
+    """As many as have room for a row of theta each in 28 KB up to 512 topics, all that fit up to 1024, then by 32 KB; never
+    none, never more than fit."""
+    assert [lib.t_groups_per_unit(K, 16) for K in (1, 256, 448, 512, 513, 1024, 1025, 1170, 1171, 1366, 1639, 2048)] == [16, 16, 16, 14, 16, 16, 7, 7, 6, 5, 4, 4]
     assert all(1 <= lib.t_groups_per_unit(K, most) <= most for K in range(1, 2049) for most in (1, 3, 12))
 
 
