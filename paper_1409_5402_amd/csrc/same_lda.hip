@@ -563,7 +563,7 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         const int64_t blocks = (a.n + T - 1) / T;
         if (blocks >= (int64_t)1 << 31) return fail(h, SAME_LDA_EINVAL, "too many draw tasks for one launch");
         dim3 grid((unsigned)blocks);
-        a.chunk_share = (uint32_t)(a.n_chunks / 2 / blocks);
+        a.chunk_share = same::chunk_share(a.n_chunks, a.n, blocks);
         const size_t lds = same::poisson_lds_bytes();
         if (a.K % same::kBlk != 0) hipLaunchKernelGGL((same::poisson_draw_kernel<false, DEBUG>), grid, block, lds, st, a);
         else if (a.K == 256)       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 256, 4>), grid, block, lds, st, a);
@@ -591,7 +591,7 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         const same::Shares sh = same::shares_for(a.n, resident);
         a.first = sh.first;
         if ((int64_t)sh.waves * sh.first >= a.n) { a.n_heavy = 0; a.heavy_from = ~0u; }   // every task starts at once
-        a.chunk_share = a.n_chunks / 2 / (uint32_t)sh.waves;
+        a.chunk_share = same::chunk_share(a.n_chunks, a.n, sh.waves);
         void* args[] = {&a};
         HIP_TRY(h, hipLaunchKernel(f, dim3((unsigned)sh.waves), block, args, lds, st));
     }

@@ -159,8 +159,8 @@ __device__ __forceinline__ Scatter make_scatter(const DrawArgs& a, int64_t row, 
     return s;
 }
 
-// A wave's chunks: its own share of the pool (half the pool is shared out that way: a launch rarely needs more, and the
-// counter's atomics are returning ones on one address, 16 ns each), then batches from the counter.
+// A wave's chunks: its own share of the pool (chunk_share: the counter's atomics are returning ones on one address, 16 ns
+// each), then batches from the counter.
 struct ChunkSupply {
     uint32_t next, end;     // not yet handed out
     bool dry;               // the pool has none left for this wave

@@ -77,6 +77,7 @@ long t_documents_out_of_range(int first, int step, int D)
     if (d < D) do { wrong += d < 0 || d >= D || d <= before; before = d; } while (wrong == 0 && next_document(d, step, D));
     return wrong + (first < D && D - step > before);
 }
+unsigned t_chunk_share(unsigned chunks, long n, long waves) { return chunk_share(chunks, n, waves); }
 int t_scan_first_topic(int hl, int T, int nblk) { return scan_first_topic(hl, T, nblk); }
 }
 """
@@ -90,6 +91,8 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I", CSRC,
                     str(src), "-o", str(so)], check=True)
     so = ctypes.CDLL(str(so))
+    so.t_chunk_share.argtypes = [ctypes.c_uint, ctypes.c_long, ctypes.c_long]
+    so.t_chunk_share.restype = ctypes.c_uint
     so.t_undrawn.argtypes = [ctypes.c_long] * 2
     so.t_undrawn.restype = ctypes.c_long
     so.t_rows_without_owner.argtypes = [ctypes.c_uint] * 2
@@ -127,7 +130,8 @@ def test_every_position_has_one_share(lib, workgroups):
 def test_a_chunk_has_one_owner(lib, waves, chunks):
     """Workgroups that find the pool used up still add to its counter: up to the 2^25 workgroups of the largest launch of the
     Poisson form no batch is handed out twice."""
-    share = chunks // 2 // waves
+    share = lib.t_chunk_share(chunks, 64 * waves, waves)
+    assert share * waves <= chunks // 2
     assert lib.t_owners_of_one_chunk(waves, share, chunks, 3 if waves > 100 else 1000) == 0
 
 
@@ -148,3 +152,12 @@ def test_rows_and_documents_up_to_the_largest_number(lib):
     for D in (0, 1, 16_383, 16_384, 16_385, 3_000_000, most - 16_384, most - 300, most):
         for first in (0, 5, 16_383):
             assert lib.t_documents_out_of_range(first, 16_384, D) == 0, (D, first)
+
+
+def test_own_chunks_stay_close_together(lib):
+    """The workgroups' own shares of the pool follow what a launch needs and not the size of the pool (eight chunks per task
+    and more): the chunks in use stay within a few times their number."""
+    for n, waves in ((100_000, 1563), (6_000_000, 4096), (60_000_000, 3584), (60_000_000, 937_500)):
+        share = lib.t_chunk_share(min(10 * n, 2**31 - 1), n, waves)
+        assert share * waves <= n // 2 and share >= n // 2 // waves
+        assert lib.t_chunk_share(7, n, waves) == 0 and lib.t_chunk_share(0, n, waves) == 0
