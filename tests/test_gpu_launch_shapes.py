@@ -121,3 +121,31 @@ def test_poisson_at_any_multiple_of_16(K, m):
         assert np.array_equal(g.get(binding.NDK), o.ndk)
         assert np.array_equal(g.get(binding.NWK), o.nwk)
     g.close()
+
+
+# One number of topics and more for every form of the draw kernel that the other tests leave out: blocks that fill the row but are
+# fewer than 32 (136, 200, 1200: the last word's and the last document's rows end the matrices), one batch of three to
+# seven loads per block, aligned (388, 770, 896) and not (259, 333, 509, 641, 701, 893, 895), the contiguous scan with a ragged
+# end (897, 1001, 1023), and several batches of one, two and four loads (1028 and 1283, 1156, 1200 and 1795, 1540).
+@pytest.mark.parametrize("K", [136, 200, 259, 333, 388, 509, 641, 701, 770, 893, 895, 896, 897, 1001, 1023, 1028, 1156, 1200, 1283, 1540, 1795])
+def test_every_form_of_the_draw_kernel(K):
+    """Sweeps in full and single tasks through the debug hook, which draws with the same form, against the oracle."""
+    rng = np.random.default_rng(K)
+    counts = rng.integers(1, 13, size=(37, 53)) * (rng.uniform(size=(37, 53)) < 0.35)
+    counts[2, :] = 0
+    counts[:, 52] = counts[36, :] = 1
+    cols = [np.flatnonzero(r) for r in counts]
+    X = oracle.CSC(37, 53, np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32),
+                   np.concatenate(cols).astype(np.int32), counts[counts > 0].astype(np.float32))
+    m, G, seed = 7, 4, 99
+    o = oracle.OracleLDA(X, K, 0.2, 0.01, seed=seed, m0=m, G=G)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.2, 0.01, seed, m, G)
+    ids = np.unique(np.concatenate([rng.choice(g.task_count, 70, replace=False), [0, g.task_count - 1]]))
+    for _ in range(2):
+        assert np.array_equal(g.debug_draw(m, ids), oracle.draw_tasks(X, K, G, m, seed, oracle.pass_word(g.pass_index), o.theta, o.phi, ids))
+        o.sweep(m)
+        g.sweep(m)
+        assert np.array_equal(g.get(binding.NDK), o.ndk)
+        assert np.array_equal(g.get(binding.NWK), o.nwk)
+        assert np.array_equal(g.get(binding.THETA), o.theta) and np.array_equal(g.get(binding.PHI), o.phi)
+    g.close()
