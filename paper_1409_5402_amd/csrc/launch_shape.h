@@ -102,21 +102,27 @@ SAME_HD inline bool next_document(int32_t& d, int32_t step, int32_t D)
     return true;
 }
 
-// Workgroups of a draw launch on one compute unit, of the `most` that its registers and LDS allow: the steps (and beyond 1024
-// topics, where a block is read in several batches, the scan of every pair of tasks) read the theta row of the wave's document
-// again and again, and the rows of the waves on a compute unit have to stay in its cache of 32 KB, or they come from the next
-// one.  Measured with news-shaped documents at m = 100, ms per sweep:
-//   K = 512    120,000 documents  sixteen 10.3  fourteen 9.9  twelve 10.4;  60,000 and 30,000 words  5.0 (5.8)  4.5  4.7
-//   K = 1100    27,000            sixteen 21.2  eight 13.3    six 13.2      four 15.6
-//   K = 1540    27,000            sixteen 28.6  eight 19.2    six 18.4      four 21.0
-//   K = 2048     5,000, m = 1     twelve 3.08   eight 3.01    six 2.84      four 2.72
-// (5.8 in shares that halve from the first, 5.0 in shares of 512: with fourteen waves it makes no difference.)  Up to 512
-// topics the phi blocks need some of the cache too; below 449 and from 513 to 1024 no limit applies (the scan holds its theta
-// rows in registers there; K = 1024 with ten and seven waves instead of twelve: 6.4, 6.8, 8.5 ms for 40,000 documents).
+// Workgroups of one wave that a compute unit's LDS holds: it has 160 KB and hands it out in pieces of 1280 bytes.  The runtime's
+// occupancy query divides without rounding up: it says 15 for the 10,496 bytes of K = 512 where 14 run at once (measured: one more
+// takes twice the time; 16 at 10,240 bytes, 14 up to 11,520, 12 up to 12,800).  The last 256 workgroups of such a launch
+// began when the others had ended, each with its share of round 0: 270,000 documents 21.7 ms instead of 16.9.
+inline int lds_groups(int64_t bytes)
+{
+    const int64_t pieces = (bytes + 1279) / 1280;
+    return (int)(160 * 1024 / 1280 / (pieces > 0 ? pieces : 1));
+}
+
+// Workgroups of a draw launch on one compute unit, of the `most` that fit.  Beyond 1024 topics a block is read in several
+// batches and a wave's theta row again for every pair of tasks (up to 1024 it stays in registers): the rows of the waves on a
+// compute unit have to fit its cache of 32 KB, or every pair fetches a row of up to 8 KB from the next one.  News-shaped
+// documents at m = 100, ms per sweep:
+//   K = 1100   27,000 documents    sixteen 21.2  eight 13.3  six 13.2  four 15.6
+//   K = 1540   27,000              sixteen 28.6  eight 19.2  six 18.4  four 21.0
+//   K = 2048    5,000, m = 1       twelve 3.08   eight 3.01  six 2.84  four 2.72
+// At K = 1024 fewer are slower: 40,000 documents twelve 6.4, ten 6.8, seven 8.5.
 inline int groups_per_unit(int K, int most)
 {
-    const int row = 4 * K;
-    const int fit = K > 1024 ? (32 << 10) / row : (K <= 512 ? (28 << 10) / row : most);
+    const int fit = K <= 1024 ? most : (32 << 10) / (4 * K);       // 7 down to 4
     return fit < most ? fit : most;
 }
 

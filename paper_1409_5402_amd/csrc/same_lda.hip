@@ -523,6 +523,8 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, bool un
     HIP_TRY(h, hipGetDevice(&dev));
     HIP_TRY(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     HIP_TRY(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, lds));
+    const int by_lds = same::lds_groups((int64_t)lds);             // the query does not round LDS up to what the device hands out
+    if (per_cu > by_lds) per_cu = by_lds;
     if (per_cu < 1) per_cu = 1;
     if (!uniform) per_cu = same::groups_per_unit(h->K, per_cu);
     const int64_t n = same::whole_groups((int64_t)cus * per_cu);
