@@ -1352,7 +1352,7 @@ int same_lda_synchronize(same_lda_t* h)
 }
 
 #ifdef SAME_STATS
-// Profiling builds only: device array of 8 event counters filled by the draw kernel.
+// Profiling builds only: device array of event counters filled by the draw kernel.
 void same_lda_stats_buffer(unsigned long long* device_counters) { g_stats = device_counters; }
 #endif
 

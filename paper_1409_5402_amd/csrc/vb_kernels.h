@@ -111,8 +111,9 @@ __device__ __forceinline__ float wave_sum_4(const float (&v)[4], int lane)
 
 // One wave per document, lanes across topics (lane l owns topics 256 c + 4 l .. + 3 of chunk c: a row of b is read
 // with 16-byte loads, 1 KB per instruction), K a multiple of 4 and at most 256 CH.  The document's gamma, a and the
-// sums over its nonzeros stay in registers over all iterations; two nonzeros are in flight at a time (up to 512
-// topics: four, and the next four behind them).
+// sums over its nonzeros stay with the wave over all iterations, in registers but for 32 (up to 256 topics) or 14 (up to
+// 512) of them, which the limit on waves sends to scratch; two nonzeros are in flight at a time (up to 512 topics: four,
+// and the next four behind them).
 template <int CH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 6 : (CH == 2 ? 3 : 1)))) void vb_estep_kernel(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
                                                        const float* __restrict__ val, int32_t D, int K,
