@@ -85,13 +85,14 @@ struct ZeroTest {
     }
 };
 
-// KC: the number of topics where it is known at compile time.  WAVES: per SIMD.  The kernel for any multiple of 16 needs
-// 133 registers, five more than four waves may have: held to 128 it spills two.  Four waves are the faster form up to 128
-// topics (K = 64: 0.84 against 0.94 ms for 9000 news-shaped documents at 100 copies, 0.90 against 0.97 at 20 from a flat
-// posterior) and up to 256 where many topics receive copies (K = 240: 2.51 against 2.60 ms at 100 copies, but 0.94 against
-// 0.91 at 1.5).  Beyond, three: rows of more waves than that push one another out of the cache (K = 512 from a
-// flat posterior 4.34 against 4.07 ms, K = 1024 7.21 against 6.47).
-template <bool VEC, bool DEBUG, int KC = 0, int WAVES = 3>
+// KC: the number of topics where it is known at compile time.  WAVES: the least number per SIMD that the registers are held to
+// (1: the compiler's own choice).  The kernel for any multiple of 16 needs 133 registers, three waves; held to the 128 of four
+// waves it spills two.  Four waves are the faster form up to 128 topics (K = 64: 0.84 against 0.94 ms for 9000 news-shaped
+// documents at 100 copies, 0.90 against 0.97 at 20 from a flat posterior) and up to 256 where many topics receive copies
+// (K = 240: 2.51 against 2.60 ms at 100 copies, but 0.94 against 0.91 at 1.5).  Beyond, three: rows of more waves than that push one
+// another out of the cache (K = 512 from a flat posterior 4.34 against 4.07 ms, K = 1024 7.21 against 6.47).  K = 256 has 126
+// registers by itself (holding it to four waves only changes the schedule: 0.7 % slower).
+template <bool VEC, bool DEBUG, int KC = 0, int WAVES = 1>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) void poisson_draw_kernel(DrawArgs a)
 {
     extern __shared__ uint32_t lds[];

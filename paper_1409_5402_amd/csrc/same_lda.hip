@@ -568,7 +568,7 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         a.chunk_share = same::chunk_share(a.n_chunks, a.n, blocks);
         const size_t lds = same::poisson_lds_bytes();
         if (a.K % same::kBlk != 0) hipLaunchKernelGGL((same::poisson_draw_kernel<false, DEBUG>), grid, block, lds, st, a);
-        else if (a.K == 256)       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 256, 4>), grid, block, lds, st, a);
+        else if (a.K == 256)       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 256>), grid, block, lds, st, a);
         else if (same::poisson_four_waves(a.K, a.mf))
                                    hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 0, 4>), grid, block, lds, st, a);
         else                       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG>), grid, block, lds, st, a);
