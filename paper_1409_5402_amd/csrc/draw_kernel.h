@@ -106,11 +106,15 @@ __device__ __forceinline__ int first_reaching(float (&P)[N], float y, float& pre
     int idx = 0;
 #pragma unroll
     for (int h = M / 2; h > 0; h >>= 1) {
-        const bool below = h <= N && !(P[h <= N ? h - 1 : 0] >= y);    // (N is no power of two: the last value stands for the rest)
-        prev = below ? P[h <= N ? h - 1 : 0] : prev;
+        const float at = P[h <= N ? h - 1 : 0];
+        const bool below = h <= N && !(at >= y);                   // (N is no power of two: the last value stands for the rest)
+        prev = below ? at : prev;
         idx = below ? idx + h : idx;
 #pragma unroll
-        for (int j = 0; j < h - 1; ++j) if (j < N) P[j] = below ? P[j + h < N ? j + h : N - 1] : P[j];
+        for (int j = 0; j < h - 1; ++j) if (j < N) {
+            const float lo = P[j], hi = P[j + h < N ? j + h : N - 1];   // values: selected as elements of the array they become
+            P[j] = below ? hi : lo;                                     // a variable index, 25 comparisons at N = 8
+        }
     }
     return idx;
 }
