@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
         __syncthreads();
         for (int k = lane; k < K; k += kWave) {
             const uint32_t v = rows[i * K + k];
-            if (v) { atomicAdd(a.ndk + (size_t)doc * K + k, v); rows[i * K + k] = 0u; }
+            if (v) { add_global(a.ndk + (size_t)doc * K + k, v); rows[i * K + k] = 0u; }
         }
         __syncthreads();
     };
@@ -818,8 +818,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
         }
 #endif
         if (en > 0u) {
-            if (myrow >= 0) atomicAdd(rows + myrow * K + ek, en);
-            else atomicAdd(a.ndk + (size_t)sc.drow * K + ek, en);
+            if (myrow >= 0) add_lds(rows + myrow * K + ek, en);
+            else add_global(a.ndk + (size_t)sc.drow * K + ek, en);
             sc.emit_word(a, ek, en, w, staged);
         }
     };

@@ -62,6 +62,18 @@ struct DrawArgs {
 #define SAME_COUNT(a, i, v) do { } while (0)
 #endif
 
+// Additions to LDS and to device memory, with the kind of memory in the pointer's type.  Two branches that add to the one and to
+// the other through plain pointers become one flat addition to a selected address: a dozen more instructions for the
+// address, and whatever waits for LDS next also waits for the additions that went to memory.
+__device__ __forceinline__ void add_lds(uint32_t* p, uint32_t v)
+{
+    __hip_atomic_fetch_add((__attribute__((address_space(3))) uint32_t*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void add_global(uint32_t* p, uint32_t v)
+{
+    __hip_atomic_fetch_add((__attribute__((address_space(1))) uint32_t*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Rows of [V][K] that very many tasks update at once (the most frequent words: their tasks spread copies
 // over many topics, fill their pair-list slot and send the rest straight to the row) are a bottleneck of
 // their own: atomics on a handful of lines are served by a handful of memory channels, one after the other.
@@ -109,7 +121,7 @@ struct Scatter {
             row = (size_t)a.V + (size_t)(blockIdx.x % kHotCopies) * kHotMax + (size_t)hot;
             *a.hot_used = 1u;
         }
-        atomicAdd(a.nwk + row * a.K + k, n);
+        add_global(a.nwk + row * a.K + k, n);
     }
     // the word's half of a count (the caller adds it to the document's row itself)
     __device__ __forceinline__ void emit_word(const DrawArgs& a, int k, uint32_t n, int32_t w, Staged& t)
@@ -226,8 +238,11 @@ __global__ __launch_bounds__(kReduceThreads) void word_reduce_kernel(const uint3
         const uint4 slot = reinterpret_cast<const uint4*>(pairs)[s];
         const int32_t w = slot_word[s];
         const bool in_tab = w - w0 < rows;
-        uint32_t* dst = in_tab ? tab + ((w - w0) * copies + mine) * stride : nwk + (size_t)w * K;
-        auto add = [&](uint32_t p) { atomicAdd(dst + (p & ((1u << kPairShift) - 1u)), p >> kPairShift); };
+        uint32_t* in_lds = tab + (in_tab ? ((w - w0) * copies + mine) * stride : 0);
+        auto add = [&](uint32_t p) {
+            const uint32_t k = p & ((1u << kPairShift) - 1u), n = p >> kPairShift;
+            if (in_tab) add_lds(in_lds + k, n); else add_global(nwk + (size_t)w * K + k, n);
+        };
         uint32_t head = slot.w;
         {
             const uint32_t cnt = (head & kPairLink) ? 3u : head - kFirstPair;   // 0 to 3
