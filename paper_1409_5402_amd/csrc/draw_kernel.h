@@ -14,7 +14,7 @@
 //
 // Draw (one lane per task).  A lane first turns its task's block sums into running sums S_0..S_31 (left to
 // right, so S_l is the cumulative weight at the end of block l and S_31 = mu, the normaliser of
-// Algorithm 3).  The cumulative weight at topic k of block l is P_k = S_{l-1} + (running sum inside the
+// Algorithm 3; in LDS word l holds the weight below block l, S_{l-1}).  The cumulative weight at topic k of block l is P_k = S_{l-1} + (running sum inside the
 // block): topic k owns the interval (P_{k-1}, P_k] of (0, mu).  The N = m*g copies are N uniform points
 // on (0, mu); they are placed from the top, one step per topic that receives copies.  With R copies
 // left, all below U:
@@ -119,6 +119,8 @@ __device__ __forceinline__ int first_reaching(float (&P)[N], float y, float& pre
     return idx;
 }
 
+constexpr int kRecips = 64;     // reciprocals 1/x that a wave keeps in LDS for its pmf walks: a multiple of kWalkSteps
+
 // Idle lanes that make the wave fetch new tasks: kRefillMin; fewer are enough when the last refill is kRefillLateTrips
 // trips back, since tasks are then long and a refill is a small part of their cost (from a flat posterior, 83 steps per
 // task, 12 of the 64 lanes were idle on average; converged, a refill comes every three trips).
@@ -159,8 +161,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     extern __shared__ uint32_t lds[];
     constexpr bool SMALL = !UNIFORM && KC == 0 && (TB == 0 || (TB == 1 && ONE));   // up to 128 topics: blocks of four
     const int kStride = UNIFORM ? 1 : (SMALL ? sum_stride(a.K) : kSumStride);      // (weights of one need no sums)
-    float* sums = reinterpret_cast<float*>(lds);                   // [64 lanes][kStride]: block sums, then running sums
-    uint32_t* acc = lds + (kStride - 1);                           // piece totals by owner lane: lane l's is acc[l * kStride],
+    const float* recips = reinterpret_cast<const float*>(lds);     // [kRecips]: 1, 1/2, 1/3, ...
+    float* sums = reinterpret_cast<float*>(lds) + kRecips;         // [64 lanes][kStride]: block sums, then the weight below each block
+    uint32_t* acc = lds + kRecips + (kStride - 1);                 // piece totals by owner lane: lane l's is acc[l * kStride],
                                                                    // the word of its row of sums that pads the stride
     const int lane = threadIdx.x;
     const int K = KC > 0 ? KC : a.K;                              // KC: the number of topics where it is known at compile time
@@ -172,7 +175,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     // in storage order: the 64 lanes hold tasks of one or two documents at a time).  Counts are added here and
     // reach the matrix in one pass over the row when the wave has left the document; tasks of a document that
     // has no row here add to the matrix at once.
-    uint32_t* rows = lds + (size_t)kWave * kStride;                // [n_rows][K]
+    uint32_t* rows = lds + kRecips + (size_t)kWave * kStride;      // [n_rows][K]
     const int n_rows = DEBUG ? 0 : doc_rows(K);
     int tag0 = -1, tag1 = -1;                                      // the documents of rows 0 and 1 (wave-uniform), -1: free
     int myrow = -1;                                                // the row of this lane's document, -1: none
@@ -190,6 +193,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     bool drained = false;                                          // nothing is left to take
     ChunkSupply supply(a);
     acc[lane * kStride] = 0u;
+    static_assert(kRecips == kWave, "a reciprocal per lane");
+    reinterpret_cast<float*>(lds)[lane] = inv_int((float)(lane + 1));
+    __syncthreads();
+    const float* my_sums = sums + lane * kStride;
 
     // ---- the lane's current task
 #ifdef SAME_STATS
@@ -197,6 +204,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
 #endif
     bool open = false;      // a task was taken and its slot of the pair list is not yet closed
     int32_t d = 0, w = 0;
+    // Its rows of theta and phi, as addresses: from d and w they take nine instructions a step (more where K is no constant).
+    // Not where the four registers are not to be had without spilling others.
+    constexpr bool kRowAddr = KC > 0 || (ONE && (TB <= 2 || TB == 4 || TB == 5));
+    const float* th_row = a.theta;
+    const float* ph_row = a.phi;
     Scatter sc;
     sc.drow = 0; sc.dst = nullptr; sc.npairs = 0;
     Staged staged;          // its last pairs, on their way to the pair list
@@ -214,7 +226,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                             // 3: holds a binomial of several pieces, waiting for the wave to share it
     uint32_t bR = 0, L = 0, bstep = 0;
     float r = 0.f, lq = 0.f, pm = 0.f, cdf = 0.f, u = 0.f;
-    float xf = 0.f, left = 0.f;                                    // the walk: successes so far, trials left
+    float left = 0.f;                                              // the walk: trials not yet counted as successes
+    int walked = 0;                                                // and terms added in earlier trips
     bool flip = false;
     int kk = 0;
 
@@ -245,6 +258,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
             d = a.t_doc[tau];
             w = a.t_word[tau];
             const uint32_t tokens = a.t_g[tau];
+            if (!UNIFORM && kRowAddr) { th_row = a.theta + (size_t)d * K; ph_row = a.phi + (size_t)w * K; }
 #ifdef SAME_STATS
             R_task_g = tokens;
 #endif
@@ -548,15 +562,51 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
             if (UNIFORM) {
                 run = (float)K;                                    // weights of one need no sums
             } else {
-                for (int l = 0; l < nblk; ++l) {
-                    run = run + sums[lane * kStride + l];
+                for (int l = 0; l < nblk; ++l) {                   // word l becomes the weight below block l
+                    const float b = sums[lane * kStride + l];
                     sums[lane * kStride + l] = run;
+                    run = run + b;
                 }
                 // the steps' search probes up to the next power of two
                 if (KC == 0) for (int l = nblk; (l & (l - 1)) != 0; ++l) sums[lane * kStride + l] = run;
             }
             U = run;
         }
+    };
+
+    // Up to kWalkSteps terms of the pmf of a binomial of n trials, lane by lane: a lane that has its count drops out (the
+    // execution mask costs scalar instructions, selections would cost vector ones) and the wave leaves with its last lane.
+    // The terms' reciprocals come from LDS, eight at a time (all the walks of a wave begin at 1).  The trials left are
+    // a whole float below 2^24: exact.  With none left the next term is zero, which ends the walk one too late: the
+    // caller takes fewer than none for none.  True if the walk goes on.  A term takes seven vector instructions; with
+    // its reciprocal computed, successes counted and trials tested it took twelve, twice the cycles.  (Constants for the
+    // first eight terms and a table in memory for the others, two copies of the loop, made the kernel 15 % slower.)
+    auto walk = [&](float& pm, float& cdf, float& left, float r, float u, int from) {
+        float inv[kWalkSteps];
+        {
+            const int at = from < kRecips ? from : 0;              // a multiple of kWalkSteps
+            const float4 v0 = *reinterpret_cast<const float4*>(recips + at), v1 = *reinterpret_cast<const float4*>(recips + at + 4);
+            inv[0] = v0.x; inv[1] = v0.y; inv[2] = v0.z; inv[3] = v0.w;
+            inv[4] = v1.x; inv[5] = v1.y; inv[6] = v1.z; inv[7] = v1.w;
+        }
+        if (from >= kRecips) {                                     // rare: a piece has an expectation of 32 at most
+#pragma unroll
+            for (int i = 0; i < kWalkSteps; ++i) inv[i] = inv_int((float)(from + i + 1));
+        }
+        bool more = u > cdf;
+#pragma unroll
+        for (int i = 0; i < kWalkSteps; ++i) {
+            if (!more) break;
+            SAME_COUNT(a, 4, 1);                                   // pmf terms
+            pm = pm * r;
+            pm = pm * left;
+            pm = pm * inv[i];
+            left = left - 1.0f;
+            const float next_cdf = cdf + pm;
+            more = next_cdf != cdf && u > next_cdf;
+            cdf = next_cdf;
+        }
+        return more && left > 0.0f;
     };
 
     // Binomials cut into pieces.  The pieces are independent (own uniform each): those of all the
@@ -593,18 +643,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     const uint32_t sel = (jp - 1u) & 3u;
                     uj = uniform_from_word(sel == 0u ? xb[0] : sel == 1u ? xb[1] : sel == 2u ? xb[2] : xb[3]);
                 }
-                uint32_t xj = 0;
-                float cdfj = pmj;
-                while (uj > cdfj && xj < nj) {
-                    xj += 1;
-                    pmj = pmj * orr;
-                    pmj = pmj * (float)(nj - xj + 1u);
-                    pmj = pmj * inv_int((float)xj);
-                    const float next_cdf = cdfj + pmj;
-                    if (next_cdf == cdfj) break;
-                    cdfj = next_cdf;
-                }
-                if (xj > 0) atomicAdd(acc + owner * kStride, xj);
+                float cdfj = pmj, leftj = (float)nj;
+                for (int from = 0; walk(pmj, cdfj, leftj, orr, uj, from); from += kWalkSteps) { }
+                const uint32_t xj = nj - (uint32_t)__builtin_fmaxf(leftj, 0.0f);
+                if (xj > 0) add_lds(acc + owner * kStride, xj);
             }
         }
         __syncthreads();
@@ -651,24 +693,22 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     prev = c - 1.0f;
                     k = (int)prev;
                 } else {
-                    // the first block whose cumulative weight reaches y (S_31 >= U >= y; entries past the last block
-                    // repeat it), and prev = the cumulative weight below that block
-                    const float* S = sums + lane * kStride;
-                    int l = 0;
+                    // the first block whose cumulative weight reaches y (mu >= U >= y; entries past the last block repeat
+                    // mu), and prev = the cumulative weight below that block, read once the block is known
+                    const float* S = my_sums;
 #pragma unroll
                     for (int h = kMaxBlocks / 2; h > 0; h >>= 1) {
                         if (KC == 0 && h >= nblk) continue;
-                        const float v = S[l + h - 1];
-                        const bool below = !(v >= y);
-                        prev = below ? v : prev;
-                        l = below ? l + h : l;
+                        S += !(S[h] >= y) ? h : 0;
                     }
-                    if (KC == 0) l = min(l, nblk - 1);             // (only negative weights could lead past it)
+                    int l = (int)(S - my_sums);
+                    if (KC == 0) { l = min(l, nblk - 1); S = my_sums + l; }   // (only negative weights could lead past it)
+                    prev = *S;
                     // inside the block: rebuild P_k from the block's weights.  Its last P_k is the block's cumulative
                     // weight, the same sum in the same order, so the search ends inside the block.
                     const int k0 = l * T;
-                    const float* __restrict__ th = a.theta + (size_t)d * K;   // the task's rows
-                    const float* __restrict__ ph = a.phi + (size_t)w * K;
+                    const float* __restrict__ th = kRowAddr ? th_row : a.theta + (size_t)d * K;
+                    const float* __restrict__ ph = kRowAddr ? ph_row : a.phi + (size_t)w * K;
                     const float base = prev;
                     float rs = 0.0f;
                     if (TB > 0) {
@@ -754,7 +794,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     u = uniform_from_word(xb);
                     if (((float)Rm * qq) <= kPieceMean) {          // one piece of Rm trials
                         const float pm0 = expneg((float)Rm * lq);
-                        xf = 0.0f; left = (float)Rm; pm = pm0; cdf = pm0;
+                        walked = 0; left = (float)Rm; pm = pm0; cdf = pm0;
                         st = 1;
                     } else {                                       // pieces of L trials: shared by the wave
                         L = (uint32_t)(kPieceMean / qq);
@@ -780,28 +820,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
             }
         }
         if (__any(st == 1)) {
-            // Up to kWalkSteps terms of the pmf per trip, lane by lane: a lane that has its count drops out of the loop
-            // (the execution mask costs scalar instructions, selections would cost vector ones) and the wave leaves it
-            // with its last lane.  The numbers of successes and of trials left are whole floats below 2^24: exact.
             if (lane == 0) SAME_COUNT(a, 12, 1);                       // trips with a walk
             if (st == 1) {
-                bool more = u > cdf;
-                int i = 0;
-                while (more) {
-                    SAME_COUNT(a, 4, 1);                           // pmf terms
-                    xf = xf + 1.0f;
-                    pm = pm * r;
-                    pm = pm * left;
-                    pm = pm * inv_int(xf);
-                    left = left - 1.0f;
-                    const float next_cdf = cdf + pm;
-                    more = next_cdf != cdf && left > 0.0f && u > next_cdf;
-                    cdf = next_cdf;
-                    if (++i == kWalkSteps) break;
-                }
-                if (!more) {                                       // the binomial is known
-                    const uint32_t x = (uint32_t)xf;
-                    const uint32_t nk = flip ? bR - x : x;
+                if (walk(pm, cdf, left, r, u, walked)) {
+                    walked += kWalkSteps;
+                } else {                                           // the binomial is known
+                    const uint32_t rest = (uint32_t)__builtin_fmaxf(left, 0.0f);
+                    const uint32_t nk = flip ? rest : bR - rest;
                     ek = kk; en = 1u + nk;
                     R -= nk;
                     st = 0;
@@ -866,6 +891,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     if (n_rows > 1 && tag1 >= 0) flush_row(1, tag1);
 }
 
-inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kWave * (size_t)(uniform ? 1 : sum_stride(K)) + (size_t)doc_rows(K) * (size_t)K); }
+inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kRecips + (size_t)kWave * (size_t)(uniform ? 1 : sum_stride(K)) + (size_t)doc_rows(K) * (size_t)K); }
 
 }  // namespace same
