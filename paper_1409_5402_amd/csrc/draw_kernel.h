@@ -51,6 +51,12 @@ __host__ __device__ inline int sum_stride(int K) { return scan_lanes(K) + 1; }
 // A second row at K = 256 would serve the waves that straddle two documents, but its kilobyte costs two of the
 // fifteen waves a compute unit holds, which costs more.
 __host__ __device__ inline int doc_rows(int K) { return K <= 128 ? 2 : (K <= 1024 ? 1 : 0); }
+// Whether the document of each row of counts also has its row of theta in LDS, for the reload of a step's block.  Sixteen waves'
+// rows of theta and their pieces of phi do not fit the 32 KB of a compute unit's cache for long, and every load of a step
+// takes it a cycle per lane.  ms per draw without / with, 15,000 news-shaped documents at m = 10 (two waves fewer per
+// compute unit with): K = 260 0.589 / 0.622, 300 0.612 / 0.595, 384 1.35 / 1.30, 640 1.00 / 0.95, 800 1.76 / 1.34, 890
+// 1.87 / 1.64; K = 256 with as many waves on both sides within 1 %; from 897, where a wave would need 16 KB, 900 1.34 / 1.48.
+__host__ __device__ constexpr bool theta_rows(int K) { return K >= 288 && K <= 896; }
 
 // The value of v in the next lower lane (lanes 0, 16, 32, 48 receive 0): a row shift inside the vector ALU.
 __device__ __forceinline__ float from_lane_below(float v)
@@ -80,6 +86,22 @@ __device__ __forceinline__ float4 load_quad(const float* __restrict__ row, int e
         return (WHOLE || e < K) ? *reinterpret_cast<const float4*>(row + e) : make_float4(0.f, 0.f, 0.f, 0.f);
     } else {
         const float4_any v = *reinterpret_cast<const float4_any*>(row + (e < K - 4 ? e : K - 4));
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+}
+typedef __attribute__((address_space(3))) float lds_float;
+template <bool ALIGNED, bool WHOLE>
+__device__ __forceinline__ float4 lds_quad(const lds_float* row, int e, int K)
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) f4 lds_f4;
+    typedef __attribute__((address_space(3))) float4_any lds_f4_any;
+    if constexpr (ALIGNED) {
+        if (!WHOLE && e >= K) return make_float4(0.f, 0.f, 0.f, 0.f);
+        const f4 v = *(const lds_f4*)(row + e);
+        return make_float4(v.x, v.y, v.z, v.w);
+    } else {
+        const float4_any v = *(const lds_f4_any*)(row + (e < K - 4 ? e : K - 4));
         return make_float4(v.x, v.y, v.z, v.w);
     }
 }
@@ -156,7 +178,7 @@ constexpr int kRefillLateTrips = 8;
 //
 // (How shares and tickets are dealt out: launch_shape.h.)
 template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 3 || KC == 512 ? 4 : 3)))) void draw_kernel(DrawArgs a)
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 3 ? 4 : 3)))) void draw_kernel(DrawArgs a)
 {
     extern __shared__ uint32_t lds[];
     constexpr bool SMALL = !UNIFORM && KC == 0 && (TB == 0 || (TB == 1 && ONE));   // up to 128 topics: blocks of four
@@ -180,6 +202,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     int tag0 = -1, tag1 = -1;                                      // the documents of rows 0 and 1 (wave-uniform), -1: free
     int myrow = -1;                                                // the row of this lane's document, -1: none
     for (int i = lane; i < n_rows * K; i += kWave) rows[i] = 0u;
+    // (theta_row: they have their rows of theta beside them)
+    constexpr bool kThetaRow = !UNIFORM && !DEBUG && TB > 0 && (KC > 0 ? theta_rows(KC) : TB >= 3);
+    const bool theta_row = kThetaRow && theta_rows(K);
+    float* th_rows = reinterpret_cast<float*>(rows) + n_rows * K;   // [n_rows][K]: theta of those documents
     // the wave's positions not yet handed out
     int32_t next, end;
     bool heavy;                                                    // they are positions of the list of heavy tasks
@@ -244,6 +270,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
         __syncthreads();
     };
 
+    // Theta of document doc beside row i of the LDS counts (whole wave).
+    auto load_theta = [&](int i, int doc) {
+        if (theta_row) {
+            const float* __restrict__ t = a.theta + (size_t)doc * K;
+            for (int k = lane; k < K; k += kWave) th_rows[i * K + k] = t[k];
+        }
+    };
+
     // Idle lanes take the next positions, the wave scans the new tasks' block sums (two tasks at a time, one
     // per half-wave: lane hl of a half owns block hl), each new lane turns its sums into running sums.
     auto refill = [&](uint64_t idle_mask) {
@@ -293,12 +327,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     flush_row(0, tag0);
                     if (myrow == 0) myrow = -1;
                     tag0 = dn;
+                    load_theta(0, dn);
                     if (take && d == dn) myrow = 0;
                     break;
                 }
                 const int old = free_row == 0 ? tag0 : tag1;
                 if (old >= 0) flush_row(free_row, old);
                 if (free_row == 0) tag0 = dn; else tag1 = dn;
+                load_theta(free_row, dn);
                 if (take && d == dn) myrow = free_row;
             }
         }
@@ -722,9 +758,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                                 const int kb = k0 + N * b;
                                 float4 pv[N / 4], tv[N / 4];
 #pragma unroll
-                                for (int c = 0; c < N / 4; ++c) {
-                                    pv[c] = load_quad<VEC, WHOLE>(ph, kb + 4 * c, K);
-                                    tv[c] = load_quad<VEC, WHOLE>(th, kb + 4 * c, K);
+                                for (int c = 0; c < N / 4; ++c) pv[c] = load_quad<VEC, WHOLE>(ph, kb + 4 * c, K);
+                                if (kThetaRow && theta_row && myrow >= 0) {
+                                    const lds_float* tr = (const lds_float*)(th_rows + (n_rows > 1 ? myrow * K : 0));
+#pragma unroll
+                                    for (int c = 0; c < N / 4; ++c) tv[c] = lds_quad<VEC, WHOLE>(tr, kb + 4 * c, K);
+                                } else {
+#pragma unroll
+                                    for (int c = 0; c < N / 4; ++c) tv[c] = load_quad<VEC, WHOLE>(th, kb + 4 * c, K);
                                 }
                                 float P[N];
 #pragma unroll
@@ -891,6 +932,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     if (n_rows > 1 && tag1 >= 0) flush_row(1, tag1);
 }
 
-inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kRecips + (size_t)kWave * (size_t)(uniform ? 1 : sum_stride(K)) + (size_t)doc_rows(K) * (size_t)K); }
+inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kRecips + (size_t)kWave * (size_t)(uniform ? 1 : sum_stride(K)) + (size_t)doc_rows(K) * (size_t)K * (uniform || !theta_rows(K) ? 1u : 2u)); }
 
 }  // namespace same

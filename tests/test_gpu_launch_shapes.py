@@ -149,3 +149,24 @@ def test_every_form_of_the_draw_kernel(K):
         assert np.array_equal(g.get(binding.NWK), o.nwk)
         assert np.array_equal(g.get(binding.THETA), o.theta) and np.array_equal(g.get(binding.PHI), o.phi)
     g.close()
+
+
+# the ends of the range in which a document's theta row is in LDS (288 to 896), aligned and not, and its neighbours
+@pytest.mark.parametrize("K", [284, 287, 288, 291, 512, 892, 895, 896, 900])
+def test_theta_rows_beside_the_counts(K):
+    """Documents of one to 120 words, so that waves hold tasks of one, of two and of dozens of documents: lanes whose document
+    has a row in LDS, lanes whose row went to another document, lanes that never had one.  Counts against the oracle."""
+    rng = np.random.default_rng(K)
+    lens = np.concatenate([rng.integers(1, 4, 90), rng.integers(20, 121, 60)])
+    rng.shuffle(lens)
+    rowidx = np.concatenate([np.sort(rng.choice(130, n, replace=False)) for n in lens]).astype(np.int32)
+    val = rng.integers(1, 5, size=len(rowidx)).astype(np.float32)
+    X = oracle.CSC(len(lens), 130, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), rowidx, val)
+    o = oracle.OracleLDA(X, K, 0.2, 0.05, seed=23, m0=1, G=3)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.2, 0.05, 23, 1, 3)
+    for m in (1, 30, 4):
+        o.sweep(m)
+        g.sweep(m)
+        assert np.array_equal(g.get(binding.NDK), o.ndk)
+        assert np.array_equal(g.get(binding.NWK), o.nwk)
+    g.close()
