@@ -156,4 +156,25 @@ SAME_HD inline Chunks chunk_batch(uint32_t taken, uint32_t waves, uint32_t share
     return c;
 }
 
+// Whether the normaliser's workgroups share the words out among the dies (sddmm_kernel.h): where phi is several times a die's
+// 4 MB of cache and its rows are long enough to outweigh the list of nonzeros that each wave then makes, and documents have
+// enough words for an eighth of them to be a run.  ms without / with, 30,000 news-shaped documents:
+//   V = 100,000   K = 128 0.178 / 0.212   150 0.261 / 0.276   200 0.361 / 0.326   (100,000 documents) 256 1.46 / 1.20
+//   K = 256       V = 30,000 0.344 / 0.302   60,000 0.419 / 0.338   100,000 and documents of 60 tokens 0.098 / 0.110
+//   K = 512       V = 8,000 0.611 / 0.488   20,000 0.809 / 0.546        K = 1000   V = 10,000 1.64 / 0.91
+inline bool sddmm_sliced(int64_t V, int K, int64_t nnz, int64_t D)
+{
+    return K > 176 && V * K >= 3000000 && nnz >= 65536 && nnz >= 64 * D;
+}
+
+// Nonzeros that a wave of the normaliser looks through: enough to share its start, few enough for four waves per SIMD.
+constexpr int kSddmmStretch = 512;
+inline int sddmm_stretch(bool sliced, int64_t nnz)
+{
+    if (sliced) return kSddmmStretch;
+    int n = 64;
+    while (n > 16 && nnz < (int64_t)n * 4096) n /= 2;
+    return n;
+}
+
 }  // namespace same

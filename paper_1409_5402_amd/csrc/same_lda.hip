@@ -18,6 +18,7 @@
 #include "draw_kernel.h"
 #include "gamma_kernels.h"
 #include "poisson_kernel.h"
+#include "sddmm_kernel.h"
 #include "update_kernels.h"
 #include "vb_kernels.h"
 #include "worklist_kernels.h"
@@ -777,17 +778,38 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
 }
 
 // mu of every nonzero of M from M's theta and the handle's phi
+template <int LANES, int CH>
+void launch_sddmm_rows(const same::SddmmArgs& a, dim3 grid, bool sliced, hipStream_t st)
+{
+    const dim3 block(64 * same::kSddmmWaves);
+    if (a.K % 4 == 0) {
+        if (sliced) hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, true, 8>), grid, block, 0, st, a);
+        else        hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, true, 1>), grid, block, 0, st, a);
+    } else {
+        if (sliced) hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, false, 8>), grid, block, 0, st, a);
+        else        hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, false, 1>), grid, block, 0, st, a);
+    }
+}
+
 void launch_sddmm(same_lda* h, const Matrix& M, float* mu)
 {
-    const int waves_per_block = 4;
-    const int64_t waves = (M.nnz + same::kSddmmChunk - 1) / same::kSddmmChunk;
-    const dim3 grid((unsigned)((waves + waves_per_block - 1) / waves_per_block)), block(64 * waves_per_block);
-    if (h->K % 4 == 0 && h->K <= 256)
-        hipLaunchKernelGGL(same::sddmm_small_kernel, grid, block, 0, h->stream, M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, mu);
-    else if (h->K % 4 == 0)
-        hipLaunchKernelGGL(same::sddmm_kernel<true>, grid, block, 0, h->stream, M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, mu);
-    else
-        hipLaunchKernelGGL(same::sddmm_kernel<false>, grid, block, 0, h->stream, M.nz_doc, M.rowidx, M.nnz, h->K, M.theta, h->phi, mu);
+    const int K = h->K;
+    same::SddmmArgs a;
+    a.nz_doc = M.nz_doc; a.rowidx = M.rowidx; a.nnz = M.nnz; a.K = K; a.theta = M.theta; a.phi = h->phi; a.mu = mu;
+    if (K < 4) {
+        hipLaunchKernelGGL(same::sddmm_few_kernel, dim3((unsigned)((M.nnz + 255) / 256)), dim3(256), 0, h->stream, a);
+        return;
+    }
+    const bool sliced = same::sddmm_sliced(h->V, K, M.nnz, M.D);
+    a.stretch = same::sddmm_stretch(sliced, M.nnz);
+    const int64_t waves = (M.nnz + a.stretch - 1) / a.stretch;
+    const dim3 grid((unsigned)((waves + same::kSddmmWaves - 1) / same::kSddmmWaves * (sliced ? 8 : 1)));
+    if (K <= 64)        launch_sddmm_rows<16, 1>(a, grid, sliced, h->stream);
+    else if (K <= 128)  launch_sddmm_rows<32, 1>(a, grid, sliced, h->stream);
+    else if (K <= 256)  launch_sddmm_rows<64, 1>(a, grid, sliced, h->stream);
+    else if (K <= 512)  launch_sddmm_rows<64, 2>(a, grid, sliced, h->stream);
+    else if (K <= 1024) launch_sddmm_rows<64, 4>(a, grid, sliced, h->stream);
+    else                launch_sddmm_rows<64, 8>(a, grid, sliced, h->stream);
 }
 
 size_t state_bytes(const same_lda* h, int32_t which)

@@ -9,6 +9,7 @@
 // multiplied by a constant (mu_i takes the same factor): rows of b are stored divided by their largest entry,
 // with the logarithm of that entry beside them, and the normaliser is returned as log mu.
 #pragma once
+#include "sddmm_kernel.h"
 #include "update_kernels.h"
 
 namespace same {
@@ -89,26 +90,6 @@ __global__ __launch_bounds__(256) void vb_exp_elog_beta_kernel(const float* __re
     if (lane == 0) shift[w] = (float)top;
 }
 
-// The sums of four values over the wave: lane l returns that of value l & 3.  Two steps inside groups of four lanes turn
-// four values per lane into one, the other four steps then work on a single value: 17 vector instructions where four
-// sums of their own take 44.
-__device__ __forceinline__ float wave_sum_4(const float (&v)[4], int lane)
-{
-    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0;
-    auto exchange = [](float keep, float give, auto ctrl) {
-        return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), decltype(ctrl)::value, 0xF, 0xF, true));
-    };
-    const float r01 = exchange(b0 ? v[1] : v[0], b0 ? v[0] : v[1], std::integral_constant<int, 0xB1>{});   // lane ^ 1
-    const float r23 = exchange(b0 ? v[3] : v[2], b0 ? v[2] : v[3], std::integral_constant<int, 0xB1>{});
-    float r = exchange(b1 ? r23 : r01, b1 ? r01 : r23, std::integral_constant<int, 0x4E>{});               // lane ^ 2
-    r = dpp_add<0x124>(r);                                         // rotations inside a row of 16 by 4 and 8
-    r = dpp_add<0x128>(r);
-    auto p16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(r), __float_as_uint(r), false, false);     // rows 0 and 1, 2 and 3
-    r = __uint_as_float(p16[0]) + __uint_as_float(p16[1]);
-    auto p32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);     // the halves
-    return __uint_as_float(p32[0]) + __uint_as_float(p32[1]);
-}
-
 // One wave per document, lanes across topics (lane l owns topics 256 c + 4 l .. + 3 of chunk c: a row of b is read
 // with 16-byte loads, 1 KB per instruction), K a multiple of 4 and at most 256 CH.  The document's gamma, a and the
 // sums over its nonzeros stay with the wave over all iterations, in registers but for 32 (up to 256 topics) or 14 (up to
@@ -157,7 +138,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 6
             // Up to 512 topics: four nonzeros per round, and the rows of the next round are loaded while this round is
             // worked off.  Every round issues the same loads, past the document's end with the index of its last nonzero and
             // a count of zero, so that the number of loads in flight behind the ones a round waits for is fixed and the wait
-            // lets them fly.  The four normalisers end in lanes l & 3 (wave_sum_4), so that one division serves all four; the
+            // lets them fly.  The four normalisers end in lanes l & 3 (lane_sum_4), so that one division serves all four; the
             // quotients then go to scalar registers.  (Two nonzeros per round with a division and a tree of their own, ids
             // in vector registers: 9.58 ms for 60,000 news-shaped documents and five iterations at K = 256, now 6.13 ms; with five
             // and four waves per SIMD instead of six 6.57 and 6.46 ms.)
@@ -190,7 +171,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 6
                     }
                     sj[j] = t;
                 }
-                const float m = wave_sum_4(sj, lane);
+                const float m = lane_sum_4<64>(sj, lane);
                 const double q = cnt > 0.f ? (double)cnt / (double)m : 0.0;
                 const int qlo = __double2loint(q), qhi = __double2hiint(q);
 #pragma unroll

@@ -170,3 +170,28 @@ def test_theta_rows_beside_the_counts(K):
         assert np.array_equal(g.get(binding.NDK), o.ndk)
         assert np.array_equal(g.get(binding.NWK), o.nwk)
     g.close()
+
+
+# every form of the normaliser kernel, at both ends of its range and off multiples of four; sliced: words shared out among
+# workgroups (more than 176 topics, at least 3 million entries of phi, 65,536 nonzeros, 64 per document)
+@pytest.mark.parametrize("K,V,D,most", [
+    *[(K, 90, 70, 60) for K in (1, 3, 4, 5, 15, 16, 17, 50, 63, 64, 65, 100, 127, 128, 129, 177, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048)],
+    *[(K, V, 500, 300) for K, V in ((177, 17000), (256, 12000), (257, 12000), (509, 6000), (512, 6000), (1001, 3000), (1024, 3000), (2045, 1500), (2048, 1500))]])
+def test_normaliser_in_every_form(K, V, D, most):
+    """mu against sums in double: documents from empty to `most` words, one topic of one word infinite.  Products of one sign
+    in a chain of 4 ceil(K / 256) and a tree of six: an error of half an ulp per step."""
+    rng = np.random.default_rng(K + V)
+    lens = rng.integers(0, most + 1, size=D)
+    lens[[0, D // 2, D - 1]] = 0, most, 1
+    rowidx = np.concatenate([np.sort(rng.choice(V, n, replace=False)) for n in lens]).astype(np.int32)
+    colptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    g = binding.SameLDA(D, V, colptr, rowidx, np.ones(len(rowidx), np.float32), K, 0.1, 0.05, 1, 1)
+    theta = rng.gamma(0.5, size=(D, K)).astype(np.float32) + np.float32(0.01)
+    phi = (rng.gamma(0.5, size=(V, K)) / V).astype(np.float32)
+    phi[rowidx[-1], K - 1] = np.inf
+    g.set(binding.THETA, theta)
+    g.set(binding.PHI, phi)
+    doc = np.repeat(np.arange(D), lens)
+    want = np.concatenate([(theta[doc[i:i + 4096]].astype(np.float64) * phi[rowidx[i:i + 4096]]).sum(1) for i in range(0, len(doc), 4096)])
+    np.testing.assert_allclose(g.sddmm(), want, rtol=(4 * -(-K // 256) + 8) * 2.0 ** -24, atol=0)
+    g.close()
