@@ -1227,8 +1227,6 @@ int same_lda_vb_estep(same_lda_t* h, const float* b, const float* shift, float a
     if (iters < 0) return fail(h, SAME_LDA_EINVAL, "iters must be >= 0 (got %d)", iters);
     if (M.D == 0 || iters == 0) return SAME_LDA_OK;
     if (!b || !gamma) return fail(h, SAME_LDA_EINVAL, "vb_estep: b and gamma must be device pointers");
-    const int waves_per_block = 4;
-    const unsigned blocks = (unsigned)((M.D + waves_per_block - 1) / waves_per_block);
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     if (h->timing) {
         if (!h->pool.empty()) { ev = h->pool.back(); h->pool.pop_back(); }
@@ -1236,16 +1234,22 @@ int same_lda_vb_estep(same_lda_t* h, const float* b, const float* shift, float a
         HIP_TRY(h, hipEventRecord(ev.first, h->stream));
     }
     const int K = h->K;
-    const dim3 grid(blocks), block(64 * waves_per_block);
-#define SAME_VB_LAUNCH(CH) hipLaunchKernelGGL(same::vb_estep_kernel<CH>, grid, block, 0, h->stream, M.colptr, M.rowidx, M.val, \
-                                              M.D, K, b, shift, alpha, iters, gamma, log_mu_out)
-    if (K % 4 != 0)
-        hipLaunchKernelGGL(same::vb_estep_any_kernel, grid, block, (size_t)waves_per_block * (2 * K + (K + 1) / 2) * sizeof(double), h->stream, M.colptr,
-                           M.rowidx, M.val, M.D, K, b, shift, alpha, iters, gamma, log_mu_out);
-    else if (K <= 256)  SAME_VB_LAUNCH(1);
-    else if (K <= 512)  SAME_VB_LAUNCH(2);
-    else if (K <= 1024) SAME_VB_LAUNCH(4);
-    else                SAME_VB_LAUNCH(8);
+    const same::VbArgs v = {M.colptr, M.rowidx, M.val, M.D, K, b, shift, alpha, iters, gamma, log_mu_out};
+#define SAME_VB_LAUNCH(LANES, CH) do { \
+        const dim3 grid((unsigned)M.D), block(64); \
+        const size_t lds = same::vb_lds_bytes(K, LANES); \
+        if (K % 4 == 0) hipLaunchKernelGGL((same::vb_estep_kernel<LANES, CH, true>), grid, block, lds, h->stream, v); \
+        else            hipLaunchKernelGGL((same::vb_estep_kernel<LANES, CH, false>), grid, block, lds, h->stream, v); \
+    } while (0)
+    if (K < 4)
+        hipLaunchKernelGGL(same::vb_estep_few_kernel, dim3((unsigned)((M.D + 3) / 4)), dim3(256), (size_t)4 * (2 * K + (K + 1) / 2) * sizeof(double), h->stream,
+                           M.colptr, M.rowidx, M.val, M.D, K, b, shift, alpha, iters, gamma, log_mu_out);
+    else if (K <= 64)   SAME_VB_LAUNCH(16, 1);
+    else if (K <= 128)  SAME_VB_LAUNCH(32, 1);
+    else if (K <= 256)  SAME_VB_LAUNCH(64, 1);
+    else if (K <= 512)  SAME_VB_LAUNCH(64, 2);
+    else if (K <= 1024) SAME_VB_LAUNCH(64, 4);
+    else                SAME_VB_LAUNCH(64, 8);
 #undef SAME_VB_LAUNCH
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && h->timing) { e = hipEventRecord(ev.second, h->stream); if (e == hipSuccess) h->events.push_back(ev); }

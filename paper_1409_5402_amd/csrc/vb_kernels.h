@@ -90,178 +90,180 @@ __global__ __launch_bounds__(256) void vb_exp_elog_beta_kernel(const float* __re
     if (lane == 0) shift[w] = (float)top;
 }
 
-// One wave per document, lanes across topics (lane l owns topics 256 c + 4 l .. + 3 of chunk c: a row of b is read
-// with 16-byte loads, 1 KB per instruction), K a multiple of 4 and at most 256 CH.  The document's gamma, a and the
-// sums over its nonzeros stay with the wave over all iterations, in registers but for 32 (up to 256 topics) or 14 (up to
-// 512) of them, which the limit on waves sends to scratch; two nonzeros are in flight at a time (up to 512 topics: four,
-// and the next four behind them).
-template <int CH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 6 : (CH == 2 ? 3 : 1)))) void vb_estep_kernel(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
-                                                       const float* __restrict__ val, int32_t D, int K,
-                                                       const float* __restrict__ b, const float* __restrict__ shift,
-                                                       float alpha, int iters, float* __restrict__ gamma,
-                                                       float* __restrict__ log_mu_out)
+// A wave per document, one in a workgroup.  A group of LANES lanes (16 up to 64 topics, 32 up to 128, else 64) takes four
+// nonzeros per round, CH 16-byte loads of a lane per row of b (K <= 4 LANES CH; ALIGNED: K is a multiple of 4, else a row's
+// last load is moved back into it and what it repeats has no weight).  gamma, a and, at the end of an iteration, the groups'
+// sums over their nonzeros are in LDS, where a lane owns every 64th topic.
+//
+// Bound by the rows of b: 69 GB of them for 60,000 news-shaped documents and five iterations at K = 256, of which the second-level
+// caches (4 MB a die) miss half, and by the conversions and sums in double behind them (16 of some 28 vector instructions per
+// nonzero).  The rows of the next round are loaded while a round is worked off; every turn issues the same loads, past the
+// document's end with its last nonzero's index and a count of zero, so that the wait before a round's arithmetic has a fixed
+// number of younger loads behind it.  The four normalisers of a group end in lanes l & 3 (lane_sum_4): one division serves
+// all four.  ms per launch before (all lanes on one nonzero, gamma and sums in registers, LDS off multiples of four) and now, five
+// iterations: that case 6.13 and 5.02; 20,000 documents at K = 50 4.61 and 0.40, 128 2.22 and 0.91, 333 26.8 and 2.94, 512 4.20
+// and 3.50, 1000 9.31 and 7.69.  (Two to sixteen waves per document, so that its rows might be found in the caches again:
+// slower the more there are, 8.9 ms with sixteen; rows kept in registers over the iterations: the constants of the logarithm
+// and exponential in double already fill them.)
+struct VbArgs {
+    const int32_t* colptr; const int32_t* rowidx; const float* val; int32_t D; int K;
+    const float* b; const float* shift; float alpha; int iters; float* gamma; float* log_mu;
+};
+inline size_t vb_lds_bytes(int K, int lanes) { return 8u * ((size_t)(64 / lanes + 1) * K) + 4u * (size_t)K; }
+
+// Four waves per SIMD up to 256 topics (five and six, with 24 registers and more in scratch: 5.99 and 6.83 ms for the case above),
+// three up to 512, two up to 1024.
+template <int LANES, int CH, bool ALIGNED>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 : (CH == 2 ? 3 : (CH == 4 ? 2 : 1))))) void vb_estep_kernel(VbArgs p)
 {
-    const int lane = threadIdx.x & 63;
-    // one document per wave: its number is the same in every lane, so that word ids come through the scalar cache and a
-    // row's address is a scalar
-    const int32_t d = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-    if (d >= D) return;                                            // the whole wave
-    const int64_t lo = colptr[d], hi = colptr[d + 1];
-    float* __restrict__ grow = gamma + (size_t)d * K;
-    // gamma and the sums over the document's nonzeros are kept in double from one iteration to the next: the
-    // iteration converges slowly along some directions, and binary32 rounding fed back ten times shows at 1e-5
-    double g[CH][4], acc[CH][4];
+    typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int kGroups = 64 / LANES, kRound = 4 * kGroups;
+    extern __shared__ double vb_lds[];
+    const int K = p.K, lane = threadIdx.x;
+    const int sub = lane & (LANES - 1), grp = lane / LANES;
+    double* sums = vb_lds;                                         // [kGroups][K]: the groups' sums over their nonzeros
+    double* g = sums + kGroups * K;                                // [K]: gamma, in double from one iteration to the next: the iteration
+                                                                   // converges slowly along some directions, and binary32
+                                                                   // rounding fed back ten times shows at 1e-5
+    float* av = reinterpret_cast<float*>(g + K);                   // [K]: a
+    const int32_t d = (int32_t)blockIdx.x;
+    const int32_t lo = p.colptr[d], n = p.colptr[d + 1] - lo;      // the document's nonzeros
+    const int32_t* __restrict__ ids = p.rowidx + lo;
+    const float* __restrict__ val = p.val + lo;
+    float* __restrict__ grow = p.gamma + (size_t)d * K;
+    for (int k = lane; k < K; k += 64) g[k] = (double)grow[k];
+
+    int off[CH];                                                   // the lane's topics: CH windows of four inside the row
+    bool ok[CH][4];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const int k = 256 * c + 4 * lane;
-        const float4 v = k < K ? *reinterpret_cast<const float4*>(grow + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-        g[c][0] = v.x; g[c][1] = v.y; g[c][2] = v.z; g[c][3] = v.w;
-    }
-    for (int it = 0; it < iters; ++it) {
-        double s = 0.0;
+        const int k = 4 * (LANES * c + sub);
+        off[c] = k < K - 4 ? k : K - 4;
 #pragma unroll
-        for (int c = 0; c < CH; ++c) s += (g[c][0] + g[c][1]) + (g[c][2] + g[c][3]);
+        for (int j = 0; j < 4; ++j) ok[c][j] = off[c] + j >= k;
+    }
+    auto rows = [&](int first, float4 (&bv)[4][CH], float& cnt) {  // the round that begins with nonzero `first`
+        const int i0 = first + (kGroups > 1 ? 4 * grp : 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = i0 + j < n ? i0 + j : n - 1;
+            const float* __restrict__ row = p.b + (size_t)ids[i] * K;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                if constexpr (ALIGNED) {
+                    bv[j][c] = *reinterpret_cast<const float4*>(row + off[c]);
+                } else {
+                    const float4_any v = *reinterpret_cast<const float4_any*>(row + off[c]);
+                    bv[j][c] = make_float4(v.x, v.y, v.z, v.w);
+                }
+            }
+        }
+        const int i = i0 + (lane & 3);
+        cnt = i < n ? val[i] : 0.f;
+    };
+    for (int it = 0; it < p.iters; ++it) {
+        __syncthreads();
+        double s = 0.0;
+#pragma unroll 1
+        for (int k = lane; k < K; k += 64) s += g[k];
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
         const double ps = digamma_d(s);
+#pragma unroll 1
+        for (int k = lane; k < K; k += 64) av[k] = (float)exp(digamma_d(g[k]) - ps);
+        __syncthreads();
         float4 a[CH];
+        double acc[CH][4];
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const bool in = 256 * c + 4 * lane < K;
-            a[c].x = in ? (float)exp(digamma_d(g[c][0]) - ps) : 0.f;
-            a[c].y = in ? (float)exp(digamma_d(g[c][1]) - ps) : 0.f;
-            a[c].z = in ? (float)exp(digamma_d(g[c][2]) - ps) : 0.f;
-            a[c].w = in ? (float)exp(digamma_d(g[c][3]) - ps) : 0.f;
+            a[c].x = ok[c][0] ? av[off[c]] : 0.f;     a[c].y = ok[c][1] ? av[off[c] + 1] : 0.f;
+            a[c].z = ok[c][2] ? av[off[c] + 2] : 0.f; a[c].w = ok[c][3] ? av[off[c] + 3] : 0.f;
             acc[c][0] = 0.0; acc[c][1] = 0.0; acc[c][2] = 0.0; acc[c][3] = 0.0;
         }
-        if constexpr (CH <= 2) {
-            // Up to 512 topics: four nonzeros per round, and the rows of the next round are loaded while this round is
-            // worked off.  Every round issues the same loads, past the document's end with the index of its last nonzero and
-            // a count of zero, so that the number of loads in flight behind the ones a round waits for is fixed and the wait
-            // lets them fly.  The four normalisers end in lanes l & 3 (lane_sum_4), so that one division serves all four; the
-            // quotients then go to scalar registers.  (Two nonzeros per round with a division and a tree of their own, ids
-            // in vector registers: 9.58 ms for 60,000 news-shaped documents and five iterations at K = 256, now 6.13 ms; with five
-            // and four waves per SIMD instead of six 6.57 and 6.46 ms.)
-            const int64_t last = hi - 1;
-            const int sub = lane & 3;
-            auto rows = [&](int64_t i0, float4 (&bv)[4][CH]) {
+        auto work = [&](int first, const float4 (&bv)[4][CH], float cnt) {
+            float sj[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int64_t i = i0 + j < hi ? i0 + j : last;
-                    const float* __restrict__ p = b + (size_t)rowidx[i] * K;
+            for (int j = 0; j < 4; ++j) {
+                sj[j] = 0.f;
 #pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        const int k = 256 * c + 4 * lane;
-                        bv[j][c] = k < K ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int c = 0; c < CH; ++c) {
+                    if constexpr (ALIGNED) {
+                        float x = __builtin_fmaf(a[c].x, bv[j][c].x, sj[j]);
+                        x = __builtin_fmaf(a[c].y, bv[j][c].y, x);
+                        x = __builtin_fmaf(a[c].z, bv[j][c].z, x);
+                        x = __builtin_fmaf(a[c].w, bv[j][c].w, x);
+                        sj[j] = ok[c][0] ? x : sj[j];
+                    } else {
+                        sj[j] = ok[c][0] ? __builtin_fmaf(a[c].x, bv[j][c].x, sj[j]) : sj[j];
+                        sj[j] = ok[c][1] ? __builtin_fmaf(a[c].y, bv[j][c].y, sj[j]) : sj[j];
+                        sj[j] = ok[c][2] ? __builtin_fmaf(a[c].z, bv[j][c].z, sj[j]) : sj[j];
+                        sj[j] = ok[c][3] ? __builtin_fmaf(a[c].w, bv[j][c].w, sj[j]) : sj[j];
                     }
                 }
+            }
+            const float m = lane_sum_4<LANES>(sj, lane);
+            const double q = cnt > 0.f ? (double)cnt / (double)m : 0.0;
+            const int qlo = __double2loint(q), qhi = __double2hiint(q);
+            // Value j's quotient from lane j of every row of 16, the same in all rows of a group.  (Every fourth lane has one, but added
+            // up in another order: the document's topics would see different normalisers of one nonzero.)
+            auto add = [&](int j, auto ctrl) {
+                const double rj = __hiloint2double(__builtin_amdgcn_update_dpp(0, qhi, decltype(ctrl)::value, 0xF, 0xF, true),
+                                                   __builtin_amdgcn_update_dpp(0, qlo, decltype(ctrl)::value, 0xF, 0xF, true));
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    acc[c][0] = __builtin_fma(rj, (double)bv[j][c].x, acc[c][0]);
+                    acc[c][1] = __builtin_fma(rj, (double)bv[j][c].y, acc[c][1]);
+                    acc[c][2] = __builtin_fma(rj, (double)bv[j][c].z, acc[c][2]);
+                    acc[c][3] = __builtin_fma(rj, (double)bv[j][c].w, acc[c][3]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             };
-            auto counts = [&](int64_t i0) { const int64_t i = i0 + sub; return i < hi ? val[i] : 0.f; };
-            auto work = [&](int64_t i, const float4 (&bv)[4][CH], float cnt) {
-                float sj[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float t = 0.f;
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        t = __builtin_fmaf(a[c].x, bv[j][c].x, t);
-                        t = __builtin_fmaf(a[c].y, bv[j][c].y, t);
-                        t = __builtin_fmaf(a[c].z, bv[j][c].z, t);
-                        t = __builtin_fmaf(a[c].w, bv[j][c].w, t);
-                    }
-                    sj[j] = t;
-                }
-                const float m = lane_sum_4<64>(sj, lane);
-                const double q = cnt > 0.f ? (double)cnt / (double)m : 0.0;
-                const int qlo = __double2loint(q), qhi = __double2hiint(q);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const double r = __hiloint2double(__builtin_amdgcn_readlane(qhi, j), __builtin_amdgcn_readlane(qlo, j));
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        acc[c][0] = __builtin_fma(r, (double)bv[j][c].x, acc[c][0]);
-                        acc[c][1] = __builtin_fma(r, (double)bv[j][c].y, acc[c][1]);
-                        acc[c][2] = __builtin_fma(r, (double)bv[j][c].z, acc[c][2]);
-                        acc[c][3] = __builtin_fma(r, (double)bv[j][c].w, acc[c][3]);
-                    }
-                }
-                if (log_mu_out != nullptr && it == iters - 1 && lane < 4 && i + lane < hi)
-                    log_mu_out[i + lane] = logf(m) + (shift ? shift[rowidx[i + lane]] : 0.f);
-            };
-            if (lo < hi) {
-                float4 b0[4][CH], b1[4][CH];
-                float c0 = counts(lo), c1;
-                rows(lo, b0);
-                for (int64_t i = lo; i < hi; i += 8) {             // two rounds per turn: no copies between the two sets
-                    rows(i + 4, b1);
-                    c1 = counts(i + 4);
-                    __builtin_amdgcn_sched_barrier(0);             // the next round's loads first, then this round's work
-                    work(i, b0, c0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (i + 4 >= hi) break;
-                    rows(i + 8, b0);
-                    c0 = counts(i + 8);
-                    __builtin_amdgcn_sched_barrier(0);
-                    work(i + 4, b1, c1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+            __builtin_amdgcn_sched_barrier(0);
+            add(0, std::integral_constant<int, 0x150>{});
+            add(1, std::integral_constant<int, 0x151>{});
+            add(2, std::integral_constant<int, 0x152>{});
+            add(3, std::integral_constant<int, 0x153>{});
+            if (p.log_mu != nullptr && it == p.iters - 1) {
+                const int i = first + 4 * grp + (lane & 3);
+                if (sub < 4 && i < n) p.log_mu[lo + i] = logf(m) + (p.shift ? p.shift[ids[i]] : 0.f);
             }
-        } else
-        for (int64_t i = lo; i < hi; i += 2) {
-            const bool two = i + 1 < hi;
-            const int32_t w0 = rowidx[i], w1 = two ? rowidx[i + 1] : w0;
-            const float c0 = val[i], c1 = two ? val[i + 1] : 0.f;
-            const float* __restrict__ p0 = b + (size_t)w0 * K;
-            const float* __restrict__ p1 = b + (size_t)w1 * K;
-            float4 b0[CH], b1[CH];
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int k = 256 * c + 4 * lane;
-                b0[c] = k < K ? *reinterpret_cast<const float4*>(p0 + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-                b1[c] = k < K ? *reinterpret_cast<const float4*>(p1 + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                s0 = __builtin_fmaf(a[c].x, b0[c].x, s0); s0 = __builtin_fmaf(a[c].y, b0[c].y, s0);
-                s0 = __builtin_fmaf(a[c].z, b0[c].z, s0); s0 = __builtin_fmaf(a[c].w, b0[c].w, s0);
-                s1 = __builtin_fmaf(a[c].x, b1[c].x, s1); s1 = __builtin_fmaf(a[c].y, b1[c].y, s1);
-                s1 = __builtin_fmaf(a[c].z, b1[c].z, s1); s1 = __builtin_fmaf(a[c].w, b1[c].w, s1);
-            }
-            const float m0 = wave_sum(s0), m1 = wave_sum(s1);
-            const double r0 = (double)c0 / (double)m0, r1 = two ? (double)c1 / (double)m1 : 0.0;
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                acc[c][0] = __builtin_fma(r0, (double)b0[c].x, __builtin_fma(r1, (double)b1[c].x, acc[c][0]));
-                acc[c][1] = __builtin_fma(r0, (double)b0[c].y, __builtin_fma(r1, (double)b1[c].y, acc[c][1]));
-                acc[c][2] = __builtin_fma(r0, (double)b0[c].z, __builtin_fma(r1, (double)b1[c].z, acc[c][2]));
-                acc[c][3] = __builtin_fma(r0, (double)b0[c].w, __builtin_fma(r1, (double)b1[c].w, acc[c][3]));
-            }
-            if (log_mu_out != nullptr && it == iters - 1 && lane == 0) {
-                log_mu_out[i] = logf(m0) + (shift ? shift[w0] : 0.f);
-                if (two) log_mu_out[i + 1] = logf(m1) + (shift ? shift[w1] : 0.f);
+        };
+        if (n > 0) {
+            float4 b0[4][CH], b1[4][CH];
+            float c0, c1;
+            rows(0, b0, c0);
+            for (int i = 0; ; i += 2 * kRound) {                   // two rounds per turn: no copies between the two sets
+                rows(i + kRound, b1, c1);
+                __builtin_amdgcn_sched_barrier(0);                 // the next round's loads first, then this round's work
+                work(i, b0, c0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + kRound >= n) break;
+                rows(i + 2 * kRound, b0, c0);
+                __builtin_amdgcn_sched_barrier(0);
+                work(i + kRound, b1, c1);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 2 * kRound >= n) break;
             }
         }
+        double* mine = sums + grp * K;
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            if (256 * c + 4 * lane < K) {                          // topics past K stay zero: they are part of the row sum
-                g[c][0] = __builtin_fma((double)a[c].x, acc[c][0], (double)alpha);
-                g[c][1] = __builtin_fma((double)a[c].y, acc[c][1], (double)alpha);
-                g[c][2] = __builtin_fma((double)a[c].z, acc[c][2], (double)alpha);
-                g[c][3] = __builtin_fma((double)a[c].w, acc[c][3], (double)alpha);
-            }
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) if (ok[c][j]) mine[off[c] + j] = acc[c][j];
+        __syncthreads();
+#pragma unroll 1
+        for (int k = lane; k < K; k += 64) {
+            double total = 0.0;
+#pragma unroll
+            for (int i = 0; i < kGroups; ++i) total += sums[i * K + k];
+            g[k] = __builtin_fma((double)av[k], total, (double)p.alpha);
         }
     }
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int k = 256 * c + 4 * lane;
-        if (k < K) *reinterpret_cast<float4*>(grow + k) = make_float4((float)g[c][0], (float)g[c][1], (float)g[c][2], (float)g[c][3]);
-    }
+    for (int k = lane; k < K; k += 64) grow[k] = (float)g[k];       // the lane's own
 }
 
-// Any K (not a multiple of 4): the same steps with the document's vectors in LDS (gamma and the sums in double, a in
-// binary32: 20 K bytes per wave).
-__global__ __launch_bounds__(256) void vb_estep_any_kernel(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
+// Fewer than four topics: a wave per document, the same steps with the document's vectors in LDS (gamma and the sums in
+// double, a in binary32: 20 K bytes per wave).
+__global__ __launch_bounds__(256) void vb_estep_few_kernel(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
                                                            const float* __restrict__ val, int32_t D, int K,
                                                            const float* __restrict__ b, const float* __restrict__ shift,
                                                            float alpha, int iters, float* __restrict__ gamma,

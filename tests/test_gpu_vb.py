@@ -137,3 +137,19 @@ def test_estep_news_full_size_sampled_documents_and_row_sums():
         np.testing.assert_allclose(gam[lo:lo + 500], g_o, rtol=RTOL)
         np.testing.assert_allclose(lmu[colptr[lo]:colptr[lo + 500]], np.log(mu_o), rtol=RTOL, atol=1e-5)
     g.close()
+
+
+# the numbers of topics at which the E-step's lanes per nonzero, loads per row and windows change, aligned and not
+@pytest.mark.parametrize("K", [2, 4, 5, 16, 17, 63, 65, 100, 127, 128, 129, 131, 255, 257, 260, 512, 513, 1023, 1024, 1025, 2045])
+def test_estep_in_every_form(K):
+    """Documents of 0 to 40 words (rounds of 4, 8 and 16 nonzeros with every remainder), three iterations."""
+    rng = np.random.default_rng(K)
+    counts = np.zeros((44, 61), np.int64)
+    for d in range(41):
+        counts[d, rng.choice(61, d, replace=False)] = rng.integers(1, 9, d)
+    X = csc_from_dense(counts)
+    lam = rng.gamma(0.5, 1.0, size=(X.V, K)) + 1e-3
+    g0 = rng.gamma(2.0, 1.0, size=(X.D, K)) + 0.05
+    gam, lmu, g_o, lmu_o = run_both(X, K, 0.3, 3, lam, g0)
+    np.testing.assert_allclose(gam, g_o, rtol=RTOL)
+    np.testing.assert_allclose(lmu, lmu_o, rtol=RTOL, atol=1e-5)
