@@ -141,10 +141,11 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_phi_kernel(uint32_t* __re
     }
 }
 
-// total[k] = sum of the block sums (double, in a fixed order), rounded to binary32
-__global__ __launch_bounds__(256) void gamma_phi_totals_kernel(const double* __restrict__ partial, int blocks, int K, float* __restrict__ total)
+// total[k] = sum of the block sums (double, in a fixed order), rounded to binary32; and the topic totals from their copies
+__global__ __launch_bounds__(256) void gamma_phi_totals_kernel(const double* __restrict__ partial, int blocks, int K, float* __restrict__ total,
+                                                              NkCopies copies, unsigned long long* __restrict__ nk)
 {
-    column_sums(partial, blocks, K, [&](int k, double sum) { total[k] = (float)sum; });
+    column_sums(partial, blocks, K, [&](int k, double sum) { total[k] = (float)sum; nk[k] = nk_total(copies, K, k); });
 }
 
 __global__ __launch_bounds__(256) void gamma_phi_normalise_kernel(float* __restrict__ phi, int V, int K, const float* __restrict__ total,

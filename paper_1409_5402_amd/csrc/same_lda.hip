@@ -128,7 +128,7 @@ struct same_lda {
     hipStream_t copy_stream = nullptr;
     float* phi = nullptr;          // [V][K]
     uint32_t* nwk = nullptr;       // [V][K]
-    unsigned long long* nk = nullptr;  // [K]
+    unsigned long long* nk = nullptr;  // [1 + nk_copies_for(K)][K]: n_k, then the copies that the documents' workgroups add to
     uint32_t* draw_counter = nullptr;  // counters of the draw kernel: tickets (kCounterWords), batches of chunks taken and the hot words' mark
                                        // (a word each) of a launch on the handle's stream, tickets of a launch on the copy stream
     uint32_t* chunks = nullptr;        // pool of chunks that continue full pair-list slots (launches on the handle's stream)
@@ -503,6 +503,7 @@ int check_m(same_lda* h, int32_t m, const Matrix& M)
 // have no pair list and therefore no use for the chunk pool: they run beside launches on the handle's stream, which own it.
 bool beside(const same_lda* h, hipStream_t st) { return st == h->copy_stream && st != h->stream; }
 size_t counter_words(const same_lda* h, hipStream_t st) { return beside(h, st) ? same::kCounterWords : same::kCounterWords + 2; }
+same::NkCopies nk_copies(const same_lda* h) { return {h->nk + h->K, same::nk_copies_for(h->K)}; }
 uint32_t* hot_used(const same_lda* h) { return h->draw_counter + same::kCounterWords + 1; }
 
 void assign_counters(same_lda* h, same::DrawArgs& a, hipStream_t st)
@@ -659,34 +660,44 @@ int update_theta(same_lda* h, Matrix& M, float m, hipStream_t st)
     return SAME_LDA_OK;
 }
 
-// n_k of the counts in h->nwk (cleared by run_pass), and theta of M unless it is null.
-int update_totals(same_lda* h, Matrix* M, int32_t n_hot, float m, hipStream_t st)
+// After the draw `drawn` on M, whose pair list completes the counts of words: the word rows, the copies of n_k (both cleared by
+// run_pass) and, if with_theta, theta of M.
+int finish_counts(same_lda* h, Matrix& M, const same::DrawArgs& drawn, bool with_theta, float m, hipStream_t st)
 {
-    same::TotalsArgs a;
-    a.nwk = h->nwk; a.nk = h->nk; a.V = h->V; a.K = h->K; a.hot_used = hot_used(h);
-    a.n_hot = n_hot; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
-    // at least two turns of four rows per thread, and at most 512 workgroups (64-bit atomics per topic)
-    const uint32_t rows = (uint32_t)h->V + (uint32_t)(n_hot * same::kHotCopies), at_once = 8u * (uint32_t)same::rows_at_once(h->K);
-    a.rows_per_block = same::blocks_of_rows(rows, 512u);
-    if (a.rows_per_block < at_once) a.rows_per_block = at_once;
-    a.total_blocks = same::blocks_of_rows(rows, a.rows_per_block);
-    a.ndk = M ? M->ndk : nullptr; a.theta = M ? M->theta : nullptr;
-    a.n_theta = M ? (size_t)M->D * h->K : 0; a.mf = m; a.alpha = h->alpha;
-    const unsigned blocks = a.total_blocks + (a.n_theta ? (unsigned)grid_for((a.n_theta + 3) / 4) : 0u);
-    if (h->K % 4 == 0) hipLaunchKernelGGL(same::totals_theta_kernel<4>, dim3(blocks), dim3(256), 0, st, a);
-    else               hipLaunchKernelGGL(same::totals_theta_kernel<1>, dim3(blocks), dim3(256), 0, st, a);
+    const bool aligned = h->K % 4 == 0;
+    same::ThetaArgs t;
+    t.ndk = M.ndk; t.theta = with_theta ? M.theta : nullptr; t.nk = nk_copies(h); t.D = (uint32_t)M.D; t.K = h->K; t.mf = m; t.alpha = h->alpha;
+    // at least a turn of four rows per thread, and at most 512 workgroups (64-bit atomics per topic)
+    const uint32_t at_once = 4u * (uint32_t)same::rows_at_once(h->K);
+    t.rows_per_block = same::blocks_of_rows(t.D, 512u);
+    if (t.rows_per_block < at_once) t.rows_per_block = at_once;
+    t.blocks = same::blocks_of_rows(t.D, t.rows_per_block);
+    same::ReduceArgs r = {};
+    int64_t blocks = t.blocks;
+    size_t lds = (size_t)256 * (aligned ? 4 : 1) * sizeof(unsigned long long);
+    if (drawn.pairs && drawn.n > 0) {
+        r.pairs = drawn.pairs; r.chunks = drawn.chunks; r.n_chunks = drawn.n_chunks; r.slot_word = M.slot_word; r.n = M.n_slots;
+        r.K = h->K; r.nwk = h->nwk;
+        r.chunk = same::reduce_chunk(M.n_slots); r.rows = same::reduce_rows(h->K, r.chunk);
+        blocks += (M.n_slots + r.chunk - 1) / r.chunk;
+        const size_t table = (size_t)r.rows * (h->K + 1) * sizeof(uint32_t);
+        if (lds < table) lds = table;
+    }
+    if (blocks == 0) return SAME_LDA_OK;
+    if (aligned) hipLaunchKernelGGL(same::counts_kernel<4>, dim3((unsigned)blocks), dim3(256), lds, st, t, r);
+    else         hipLaunchKernelGGL(same::counts_kernel<1>, dim3((unsigned)blocks), dim3(256), lds, st, t, r);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }
 
-// The collapsed update: n_k and theta in one launch, phi in another.
-int update_collapsed(same_lda* h, Matrix& M, float m, float rho, hipStream_t st)
+// The collapsed update after the draw `drawn`: the word rows, n_k and theta in one launch, phi in another.
+int update_collapsed(same_lda* h, Matrix& M, const same::DrawArgs& drawn, float m, float rho, hipStream_t st)
 {
     const int32_t n_hot = M.n_hot;
-    int rc = update_totals(h, &M, n_hot, m, st);
+    int rc = finish_counts(h, M, drawn, true, m, st);
     if (rc) return rc;
     same::PhiArgs a;
-    a.nwk = h->nwk; a.nk = h->nk; a.phi = h->phi; a.hot_of = n_hot > 0 ? M.hot_of : nullptr; a.hot_used = hot_used(h);
+    a.nwk = h->nwk; a.copies = nk_copies(h); a.nk = h->nk; a.phi = h->phi; a.hot_of = n_hot > 0 ? M.hot_of : nullptr; a.hot_used = hot_used(h);
     a.V = h->V; a.K = h->K; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
     a.mf = m; a.beta = h->beta; a.vbeta = (float)h->V * h->beta; a.rho = rho;
     // up to eight rows per thread, fewer where that leaves less than four workgroups per compute unit
@@ -716,14 +727,11 @@ int sample_theta(same_lda* h, Matrix& M, float m, uint32_t pword, hipStream_t st
 int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_t st)
 {
     const int blocks = (int)same::blocks_of_rows((uint32_t)h->V, kGammaRows);
-    // the topic totals are part of the readable state, kept current as after a collapsed update
-    const int rc = update_totals(h, nullptr, M.n_hot, m, st);
-    if (rc) return rc;
     hipLaunchKernelGGL(same::gamma_phi_kernel, dim3(blocks), dim3(same::kGammaThreads), 0, st, h->nwk, M.n_hot > 0 ? M.hot_of : nullptr, hot_used(h),
                        same::kHotMax, same::kHotCopies, h->phi, h->V, h->K, m * h->beta, (uint32_t)h->seed, (uint32_t)(h->seed >> 32),
                        pword, kGammaRows, h->gamma_partial);
     hipLaunchKernelGGL(same::gamma_phi_totals_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, st, h->gamma_partial,
-                       blocks, h->K, h->gamma_total);
+                       blocks, h->K, h->gamma_total, nk_copies(h), h->nk);
     const uint32_t rows = 8u * (h->K >= 256 ? 1u : 256u / (uint32_t)h->K);
     hipLaunchKernelGGL(same::gamma_phi_normalise_kernel, dim3(same::blocks_of_rows((uint32_t)h->V, rows)), dim3(256), 0, st, h->phi, h->V, h->K,
                        h->gamma_total, rows);
@@ -731,9 +739,10 @@ int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_
     return SAME_LDA_OK;
 }
 
-// One pass of draws on M.  uniform: weights are all ones (initialisation).
+// One pass of draws on M.  uniform: weights are all ones (initialisation).  with_words: the counts of words are still to be
+// completed from the pair list (finish_counts, with the arguments in *drawn).
 int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, bool with_words, bool timed,
-             hipStream_t st)
+             hipStream_t st, same::DrawArgs* drawn = nullptr)
 {
     int rc;
     if (!uniform && c.poisson && M.n_tiles > 0) {               // the Poisson kernel takes its tasks in cost order
@@ -746,8 +755,8 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
     {   // one launch of its own, so that the events around the draw kernel bracket that kernel alone.  The hot words'
         // copies need no clearing: the parameter update that follows every pass with words leaves them clear.
         const size_t cells = (size_t)M.D * h->K, word_cells = with_words ? (size_t)h->V * h->K : 0;
-        const same::ClearArgs z = {{M.ndk, h->nwk, a.counter, reinterpret_cast<uint32_t*>(h->nk)},
-                                   {cells, word_cells, counter_words(h, st), with_words ? (size_t)2 * h->K : 0}};
+        const same::ClearArgs z = {{M.ndk, h->nwk, a.counter, reinterpret_cast<uint32_t*>(h->nk + h->K)},
+                                   {cells, word_cells, counter_words(h, st), with_words ? (size_t)2 * same::nk_copies_for(h->K) * h->K : 0}};
         hipLaunchKernelGGL(same::clear_kernel, dim3(grid_for((cells > word_cells ? cells : word_cells) / 4 + 1)), dim3(256), 0, st, z);
         HIP_TRY(h, hipGetLastError());
     }
@@ -766,14 +775,7 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
         HIP_TRY(h, hipEventRecord(ev.second, st));
         h->events.push_back(ev);
     }
-    if (a.pairs && a.n > 0) {
-        const int chunk = same::reduce_chunk(M.n_slots), rows = same::reduce_rows(h->K, chunk);
-        const int64_t blocks = (M.n_slots + chunk - 1) / chunk;
-        hipLaunchKernelGGL(same::word_reduce_kernel, dim3((unsigned)blocks), dim3((unsigned)(chunk / 2 < same::kReduceThreads ? chunk / 2 : same::kReduceThreads)),
-                           (size_t)rows * (h->K + 1) * sizeof(uint32_t), st, a.pairs, a.chunks, a.n_chunks, M.slot_word, M.n_slots,
-                           h->K, rows, chunk, h->nwk);
-        HIP_TRY(h, hipGetLastError());
-    }
+    if (drawn) *drawn = a;
     return SAME_LDA_OK;
 }
 
@@ -859,14 +861,15 @@ int same_lda_init(same_lda_t** out, const same_lda_csc* X, int32_t K, float alph
     if (!rc) rc = check_m(h, m0, h->X);
     if (!rc) rc = dev_alloc(h, &h->phi, (size_t)h->V * K);
     if (!rc) rc = dev_alloc(h, &h->nwk, nwk_elements(h));
-    if (!rc) rc = dev_alloc(h, &h->nk, (size_t)K);
+    if (!rc) rc = dev_alloc(h, &h->nk, (size_t)(1 + same::nk_copies_for(K)) * K);
     if (!rc) rc = dev_alloc(h, &h->gamma_partial, (size_t)same::blocks_of_rows((uint32_t)h->V, kGammaRows) * K);
     if (!rc) rc = dev_alloc(h, &h->gamma_total, (size_t)K);
     if (!rc) rc = dev_alloc(h, &h->vb_psi, (size_t)K);
     if (!rc) rc = dev_alloc(h, &h->draw_counter, (size_t)kSecondCounters + same::kCounterWords);
     if (!rc) rc = zero_u32(h, h->nwk + (size_t)h->V * K, nwk_elements(h) - (size_t)h->V * K, h->stream);   // the hot words' copies
-    if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m0), pass_word(0, 0), true, true, false, h->stream);
-    if (!rc) rc = update_collapsed(h, h->X, (float)m0, 1.0f, h->stream);
+    same::DrawArgs drawn;
+    if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m0), pass_word(0, 0), true, true, false, h->stream, &drawn);
+    if (!rc) rc = update_collapsed(h, h->X, drawn, (float)m0, 1.0f, h->stream);
     if (!rc) { hipError_t e = hipStreamSynchronize(h->stream); if (e != hipSuccess) rc = fail(h, SAME_LDA_EHIP, "init: %s", hipGetErrorString(e)); }
     if (rc) { g_init_error = h->error; same_lda_free(h); return rc; }
     h->pass = 1;
@@ -880,8 +883,9 @@ int same_lda_sweep(same_lda_t* h, int32_t m_t, float rho_t)
     if (!h) return SAME_LDA_EINVAL;
     if (!(rho_t > 0.f) || rho_t > 1.f) return fail(h, SAME_LDA_EINVAL, "rho must be in (0, 1] (got %g)", (double)rho_t);
     int rc = check_m(h, m_t, h->X);
-    if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream);
-    if (!rc) rc = update_collapsed(h, h->X, (float)m_t, rho_t, h->stream);
+    same::DrawArgs drawn;
+    if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream, &drawn);
+    if (!rc) rc = update_collapsed(h, h->X, drawn, (float)m_t, rho_t, h->stream);
     if (!rc) h->pass += 1;
     return rc;
 }
@@ -890,7 +894,10 @@ int same_lda_sweep_sampled(same_lda_t* h, int32_t m_t)
 {
     if (!h) return SAME_LDA_EINVAL;
     int rc = check_m(h, m_t, h->X);
-    if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream);
+    same::DrawArgs drawn;
+    if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream, &drawn);
+    // the topic totals are part of the readable state, kept current as after a collapsed update
+    if (!rc) rc = finish_counts(h, h->X, drawn, false, (float)m_t, h->stream);
     if (!rc) rc = sample_theta(h, h->X, (float)m_t, pass_word(h->pass, 2), h->stream);
     if (!rc) rc = sample_phi(h, h->X, (float)m_t, pass_word(h->pass, 3), h->stream);
     if (!rc) h->pass += 1;
@@ -902,8 +909,9 @@ int same_lda_sweep_poisson(same_lda_t* h, float m_t, float rho_t)
     if (!h) return SAME_LDA_EINVAL;
     if (!(rho_t > 0.f) || rho_t > 1.f) return fail(h, SAME_LDA_EINVAL, "rho must be in (0, 1] (got %g)", (double)rho_t);
     int rc = check_mf(h, m_t, h->X);
-    if (!rc) rc = run_pass(h, h->X, Copies::real(m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream);
-    if (!rc) rc = update_collapsed(h, h->X, m_t, rho_t, h->stream);
+    same::DrawArgs drawn;
+    if (!rc) rc = run_pass(h, h->X, Copies::real(m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream, &drawn);
+    if (!rc) rc = update_collapsed(h, h->X, drawn, m_t, rho_t, h->stream);
     if (!rc) h->pass += 1;
     return rc;
 }

@@ -217,13 +217,23 @@ constexpr int kSlotMinTasks = 2;         // (32 measured 1.5 % slower on the res
                                         // updates of rare words are atomics on lines that have long left the cache)
 constexpr int kReduceThreads = kReduceChunk / 2;    // at most: two slots per thread, the kernel waits on its loads, many waves hide that
 
-__global__ __launch_bounds__(kReduceThreads) void word_reduce_kernel(const uint32_t* __restrict__ pairs,
-                                                          const uint32_t* __restrict__ chunks, uint32_t n_chunks,
-                                                          const int32_t* __restrict__ slot_word, int64_t n, int K,
-                                                          int rows, int chunk, uint32_t* __restrict__ nwk)
+struct ReduceArgs {
+    const uint32_t* pairs; const uint32_t* chunks; uint32_t n_chunks;
+    const int32_t* slot_word; int64_t n;   // [n] slots
+    int K, rows, chunk; uint32_t* nwk;
+};
+
+// The slots of workgroup `block`; tab: [rows][K + 1] of LDS.
+__device__ __forceinline__ void word_reduce(const ReduceArgs& a, uint32_t block, uint32_t* tab)
 {
-    extern __shared__ uint32_t tab[];                              // [rows][K + 1]
-    const int64_t s0 = (int64_t)blockIdx.x * chunk;
+    const uint32_t* __restrict__ pairs = a.pairs;
+    const uint32_t* __restrict__ chunks = a.chunks;
+    const int32_t* __restrict__ slot_word = a.slot_word;
+    uint32_t* __restrict__ nwk = a.nwk;
+    const uint32_t n_chunks = a.n_chunks;
+    const int64_t n = a.n;
+    const int K = a.K, rows = a.rows, chunk = a.chunk;
+    const int64_t s0 = (int64_t)block * chunk;
     const int64_t s1 = s0 + chunk < n ? s0 + chunk : n;
     const int32_t w0 = slot_word[s0];
     const int32_t w1 = slot_word[s1 - 1];                          // the last word of the range

@@ -8,6 +8,7 @@
 
 #include "launch_shape.h"
 #include "rng_binom.h"
+#include "scatter.h"
 
 namespace same {
 
@@ -146,35 +147,37 @@ __global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __res
     theta_update(ndk, theta, n, mf, alpha, (size_t)blockIdx.x * 256u + threadIdx.x, (size_t)gridDim.x * 256u);
 }
 
-// n_k = sum over words of n_wk[w][k], exact in 64-bit integers (any order gives the same value), and, beside it in the
-// same launch, theta.  The first total_blocks workgroups take rows_per_block rows each of the word-count matrix and of
-// the hot words' copies that follow it (row V + copy * hot_max + number; only the n_hot numbers in use), four rows of
-// loads in flight per thread; one 64-bit atomic per topic and workgroup (a few hundred of them: 1563 on every topic's
-// address were most of the 55 us this took at V = 100,000, K = 256).  The other workgroups update theta.
-struct TotalsArgs {
-    const uint32_t* nwk; unsigned long long* nk; int V, K, n_hot, hot_max, hot_copies; uint32_t rows_per_block, total_blocks;
-    const uint32_t* hot_used;              // 0: the copies have taken nothing
-    const uint32_t* ndk; float* theta; size_t n_theta; float mf, alpha;
+// n_k, the copies of topic k, exact in 64-bit integers (any order gives the same value), and theta.  Every copy is in n_dk and
+// in n_wk; the sum is taken over n_dk, which theta reads anyway and which is complete when the draw ends.  A workgroup owns
+// rows_per_block documents, four rows of loads in flight per thread, and ends with one 64-bit atomic per topic, on one of a few
+// copies of the totals: the 512 of a launch on one address take longer than the rest of it where that is small (K = 64, 50,000
+// documents: 18 us a sweep).  Who needs the totals adds the copies up (nk_total), which every workgroup of the phi update
+// does: eight copies up to 128 topics, down to one at 1024 (with eight there 110 us of 4.6 ms lost).
+inline int nk_copies_for(int K) { return K <= 128 ? 8 : (K <= 256 ? 4 : (K <= 512 ? 2 : 1)); }
+struct NkCopies { unsigned long long* p; int n; };
+__device__ __forceinline__ unsigned long long nk_total(const NkCopies& a, int K, int k)
+{
+    unsigned long long n = 0;
+    if (a.n == 8) {                                                // all loads in flight together
+#pragma unroll
+        for (int c = 0; c < 8; ++c) n += a.p[(size_t)c * K + k];
+    } else {
+        for (int c = 0; c < a.n; ++c) n += a.p[(size_t)c * K + k];
+    }
+    return n;
+}
+struct ThetaArgs {
+    const uint32_t* ndk; float* theta;     // theta null: totals alone
+    NkCopies nk; uint32_t D; int K; uint32_t rows_per_block, blocks;
+    float mf, alpha;
 };
 
 template <int W>
-__global__ __launch_bounds__(256) void totals_theta_kernel(TotalsArgs a)
+__device__ __forceinline__ void theta_totals(const ThetaArgs& a, uint32_t block, unsigned long long* sh)   // sh: [256 * W]
 {
-    if (blockIdx.x >= a.total_blocks) {
-        theta_update(a.ndk, a.theta, a.n_theta, a.mf, a.alpha, (size_t)(blockIdx.x - a.total_blocks) * 256u + threadIdx.x,
-                     (size_t)(gridDim.x - a.total_blocks) * 256u);
-        return;
-    }
-    __shared__ unsigned long long sh[256 * W];
     const RowSplit<W> s(a.K);
-    const uint32_t V = (uint32_t)a.V, rows = V + (a.n_hot > 0 && *a.hot_used != 0u ? (uint32_t)(a.n_hot * a.hot_copies) : 0u);
-    const Rows b = rows_of_block(blockIdx.x, a.rows_per_block, rows);
+    const Rows b = rows_of_block(block, a.rows_per_block, a.D);
     const uint32_t groups = (uint32_t)s.groups;
-    auto row = [&](uint32_t r) {
-        size_t at = r;
-        if (r >= V) { const int j = (int)(r - V); at = (size_t)V + (size_t)(j / a.n_hot) * a.hot_max + j % a.n_hot; }
-        return a.nwk + at * a.K;
-    };
     for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
         unsigned long long acc[W] = {};
         if (s.group < s.groups) {
@@ -183,11 +186,20 @@ __global__ __launch_bounds__(256) void totals_theta_kernel(TotalsArgs a)
 #pragma unroll
                 for (uint32_t j = 0; j < 4u; ++j) {
                     const uint32_t rj = r + j * groups;
-                    load_unit<W>(row(rj < b.to ? rj : r) + W * u, v[j]);
+                    load_unit<W>(a.ndk + (size_t)(rj < b.to ? rj : r) * a.K + W * u, v[j]);
                 }
 #pragma unroll
-                for (uint32_t j = 0; j < 4u; ++j)
-                    if (r + j * groups < b.to) for (int c = 0; c < W; ++c) acc[c] += v[j][c];
+                for (uint32_t j = 0; j < 4u; ++j) {
+                    const uint32_t rj = r + j * groups;
+                    if (rj >= b.to) break;
+                    for (int c = 0; c < W; ++c) acc[c] += v[j][c];
+                    if (a.theta == nullptr) continue;
+                    float* t = a.theta + (size_t)rj * a.K + W * u;
+                    float x[W];
+                    for (int c = 0; c < W; ++c) x[c] = (float)v[j][c] / a.mf + a.alpha;
+                    if constexpr (W == 4) *reinterpret_cast<float4*>(t) = make_float4(x[0], x[1], x[2], x[3]);
+                    else *t = x[0];
+                }
             }
         }
         if (s.groups > 1) {                                        // the row groups' sums of a topic
@@ -198,8 +210,22 @@ __global__ __launch_bounds__(256) void totals_theta_kernel(TotalsArgs a)
                     for (int c = 0; c < W; ++c) acc[c] += sh[(g * s.units + s.unit) * W + c];
             if (s.group != 0) break;
         }
-        for (int c = 0; c < W; ++c) if (acc[c]) atomicAdd(a.nk + W * u + c, acc[c]);
+        for (int c = 0; c < W; ++c) if (acc[c]) atomicAdd(a.nk.p + (size_t)(block % (uint32_t)a.nk.n) * a.K + W * u + c, acc[c]);
     }
+}
+
+// What follows a draw and needs nothing but its counts: the word rows from the pair list, and beside it in the same launch (the
+// first t.blocks workgroups) the topic totals and theta.  One after the other the two took 12 and 11 us of the 72 us of a
+// sweep over 4,000 documents at K = 50, 36 and 18 of 460 at 50,000 documents and K = 64; together
+// tiny_fit's ten sweeps take 410 instead of 460 us, those five 390 instead of 440, and at K = 1024 the totals' pass over 400 MB
+// of n_wk is gone (140 us).
+template <int W>
+__global__ __launch_bounds__(256) void counts_kernel(ThetaArgs t, ReduceArgs r)
+{
+    static_assert(kReduceThreads == 256, "workgroups of both kinds");
+    extern __shared__ __align__(16) uint32_t counts_lds[];
+    if (blockIdx.x < t.blocks) theta_totals<W>(t, blockIdx.x, reinterpret_cast<unsigned long long*>(counts_lds));
+    else                       word_reduce(r, blockIdx.x - t.blocks, counts_lds);
 }
 
 // The copies of a hot word's row (scatter.h): their counts of the W topics from `at` on are added to n and
@@ -229,7 +255,7 @@ __device__ __forceinline__ bool take_in_copies(uint32_t* __restrict__ nwk, int V
 // phi_hat = (n_wk/m + beta) / (n_k/m + V*beta);  phi = rho == 1 ? phi_hat : (1-rho)*phi + rho*phi_hat.
 // A hot word's row first takes in its copies, which are left clear.
 struct PhiArgs {
-    uint32_t* nwk; const unsigned long long* nk; float* phi; const int16_t* hot_of;   // hot_of null: no hot words
+    uint32_t* nwk; NkCopies copies; unsigned long long* nk; float* phi; const int16_t* hot_of;   // nk: out; hot_of null: no hot words
     const uint32_t* hot_used;              // 0: their copies have taken nothing
     int V, K, hot_max, hot_copies; uint32_t rows_per_block;
     float mf, beta, vbeta, rho;
@@ -246,7 +272,11 @@ __global__ __launch_bounds__(256) void phi_update_kernel(PhiArgs a)
     for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
         float den[W];
 #pragma unroll
-        for (int c = 0; c < W; ++c) den[c] = (float)a.nk[W * u + c] / a.mf + a.vbeta;
+        for (int c = 0; c < W; ++c) {
+            const unsigned long long n_k = nk_total(a.copies, a.K, W * u + c);
+            if (blockIdx.x == 0 && s.group == 0) a.nk[W * u + c] = n_k;
+            den[c] = (float)n_k / a.mf + a.vbeta;
+        }
         for (uint32_t r = b.from + s.group; r < b.to; r += s.groups) {
             const size_t at = (size_t)r * a.K + W * u;
             uint32_t n[W];

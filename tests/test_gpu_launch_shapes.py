@@ -195,3 +195,18 @@ def test_normaliser_in_every_form(K, V, D, most):
     want = np.concatenate([(theta[doc[i:i + 4096]].astype(np.float64) * phi[rowidx[i:i + 4096]]).sum(1) for i in range(0, len(doc), 4096)])
     np.testing.assert_allclose(g.sddmm(), want, rtol=(4 * -(-K // 256) + 8) * 2.0 ** -24, atol=0)
     g.close()
+
+
+# one, two, four and eight copies of the topic totals, at the ends of their ranges; more documents than workgroups that add them up
+@pytest.mark.parametrize("K", [1, 3, 128, 129, 256, 257, 512, 513])
+def test_topic_totals_are_the_counts(K):
+    """n_k against both count matrices after every form of a sweep (whole numbers, so no tolerance)."""
+    X = matrix(9000, V=3, seed=K)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.3, 0.05, 5, 1, 8)
+    for sweep in (None, lambda: g.sweep(3), lambda: g.sweep_poisson(2.5), lambda: g.sweep_sampled(2), lambda: g.sweep(1, 0.5)):
+        if sweep:
+            sweep()
+        nk = np.asarray(g.get(binding.NK)).astype(np.int64)
+        assert np.array_equal(nk, np.asarray(g.get(binding.NDK)).reshape(X.D, K).sum(0, dtype=np.int64))
+        assert np.array_equal(nk, np.asarray(g.get(binding.NWK)).reshape(X.V, K).sum(0, dtype=np.int64))
+    g.close()
