@@ -122,6 +122,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
     ChunkSupply supply(a);
     Staged staged;
     acc[lane] = 0u;
+    // 1/x for x = 1 to 64, the factors of the walks below (computed, three instructions each, a third of a term: poisson_sweep 3.98 and, from the table, 3.78 ms; K = 64 0.71, 0.58)
+    float* recips = reinterpret_cast<float*>(acc + kWave);
+    recips[lane] = inv_int((float)(lane + 1));
+    __syncthreads();
 
     StreamKey key;
     key.seed_lo = a.seed_lo; key.seed_hi = a.seed_hi;
@@ -151,10 +155,40 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
     int st = 0;             // 0: between draws, 1: walking a single piece,
                             // 3: holds a variable of several pieces, waiting for the wave to share it
     uint32_t np = 0;
-    float r = 0.f, pm = 0.f, cdf = 0.f, u = 0.f, xf = 0.f;
+    float r = 0.f, pm = 0.f, cdf = 0.f, u = 0.f;
+    uint32_t walked = 0;    // terms added so far
     int waited = 0;         // trips since a variable of several pieces has been waiting
     int kk = 0;
     uint32_t busy = 0;      // trips in which this lane had work: its cost for the next ordering
+
+    // Up to kWalkSteps terms of the pmf, lane by lane under the execution mask, as in the multinomial form's walk; x terms have
+    // been added before, a multiple of kWalkSteps.  True if the walk goes on.
+    auto walk = [&](float& pm, float& cdf, uint32_t& x, float r, float u) {
+        float inv[kWalkSteps];
+        {
+            const uint32_t at = x < (uint32_t)kWave ? x : 0u;
+            const float4 v0 = *reinterpret_cast<const float4*>(recips + at), v1 = *reinterpret_cast<const float4*>(recips + at + 4);
+            inv[0] = v0.x; inv[1] = v0.y; inv[2] = v0.z; inv[3] = v0.w;
+            inv[4] = v1.x; inv[5] = v1.y; inv[6] = v1.z; inv[7] = v1.w;
+        }
+        if (x >= (uint32_t)kWave) {                                // rare: a piece's rate is 32 at most
+#pragma unroll
+            for (int i = 0; i < kWalkSteps; ++i) inv[i] = inv_int((float)(x + i + 1));
+        }
+        bool more = u > cdf;
+#pragma unroll
+        for (int i = 0; i < kWalkSteps; ++i) {
+            if (!more) break;
+            SAME_COUNT(a, 4, 1);                                   // walk steps
+            x += 1;
+            pm = pm * r;
+            pm = pm * inv[i];
+            const float next = cdf + pm;
+            more = next != cdf && u > next;
+            cdf = next;
+        }
+        return more;
+    };
 
     // Variables cut into pieces.  The pieces are independent (own uniform each): those of all the
     // lanes in state 3 are numbered consecutively and dealt out over the 64 lanes; every owner
@@ -190,14 +224,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
                 }
                 uint32_t xj = 0;
                 float cdfj = pmj;
-                while (uj > cdfj) {
-                    xj += 1;
-                    pmj = pmj * orr;
-                    pmj = pmj * inv_int((float)xj);
-                    const float next = cdfj + pmj;
-                    if (next == cdfj) break;
-                    cdfj = next;
-                }
+                while (walk(pmj, cdfj, xj, orr, uj)) { }
                 if (xj > 0) atomicAdd(acc + owner, xj);
             }
         }
@@ -233,7 +260,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
                 if (lam <= kPieceMean) {                           // one piece
                     r = lam;
                     const float pm0 = expneg(lam);
-                    xf = 0.0f; pm = pm0; cdf = pm0;
+                    walked = 0; pm = pm0; cdf = pm0;
                     st = 1;
                 } else {                                           // equal pieces: shared by the wave
                     np = (uint32_t)(lam / kPieceMean) + 1u;
@@ -250,24 +277,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
             if (share) { en = pool(pend); kk_done = kk; }
         }
         if (__any(st == 1)) {
-            // up to kWalkSteps terms, lane by lane under the execution mask, as in the multinomial form's walk
-            if (st == 1) {
-                bool more = u > cdf;
-                int i = 0;
-                while (more) {
-                    SAME_COUNT(a, 4, 1);                           // walk steps
-                    xf = xf + 1.0f;
-                    pm = pm * r;
-                    pm = pm * inv_int(xf);
-                    const float next = cdf + pm;
-                    more = next != cdf && u > next;
-                    cdf = next;
-                    if (++i == kWalkSteps) break;
-                }
-                if (!more) {                                       // the piece is finished
-                    en = (uint32_t)xf; kk_done = kk;
-                    st = 0;
-                }
+            if (st == 1 && !walk(pm, cdf, walked, r, u)) {         // the piece is finished
+                en = walked; kk_done = kk;
+                st = 0;
             }
         }
         if (!DEBUG) supply.give(a, lane, sc, en > 0u && sc.full(), staged);
@@ -322,6 +334,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
 }
 
 inline bool poisson_four_waves(int K, float mf) { return K <= 128 || (K <= 256 && mf >= 10.0f); }
-inline size_t poisson_lds_bytes() { return 4u * (size_t)kWave * (size_t)(2 * kQCap + 1); }
+inline size_t poisson_lds_bytes() { return 4u * (size_t)kWave * (size_t)(2 * kQCap + 2); }
 
 }  // namespace same
