@@ -19,7 +19,7 @@
 // u + Nf*(q*(1+1e-4) + 1e-6) <= 1 - 1e-4, evaluated without a division (see ZeroTest), which
 // implies the former.  A topic of zero weight passes it.
 #pragma once
-#include "scatter.h"
+#include "draw_kernel.h"
 
 namespace same {
 
@@ -27,30 +27,36 @@ constexpr int kBlk = 16;                // topics per block of the Poisson kerne
 constexpr int kQCap = 16;               // queued topics per lane between drains (drain when > kQCap - 4; 8, 12 and 16
                                         // measured 3.12, 3.02 and 3.00 ms for 6 million tasks at K = 256)
 
-// The sixteen theta and phi values of one block, loaded ahead of their use (K % 16 == 0 only).
+// How a block's rows are read.  kWhole: K is a multiple of 16, aligned loads.  kQuads: any K from 4 on, loads of any
+// alignment that stay inside the row (load_quad); the last block's products are shifted into place.  kFew: element by
+// element.  (Every K that is no multiple of 16 was read element by element: 9,000 news-shaped documents, K = 100 1.47 and now
+// 0.40 ms per draw, K = 200 3.12 and 0.82, K = 1000 17.7 and 4.1.)
+constexpr int kFew = 0, kQuads = 1, kWhole = 2;
+
+// The sixteen theta and phi values of one block, loaded ahead of their use (not kFew).
 struct PhiBlock { float4 v[kBlk / 4]; float4 t[kBlk / 4]; };
 
-template <bool VEC>
-__device__ __forceinline__ PhiBlock load_phi(const float* __restrict__ th, const float* __restrict__ ph, int b)
+template <int READ>
+__device__ __forceinline__ PhiBlock load_phi(const float* __restrict__ th, const float* __restrict__ ph, int b, int K)
 {
     PhiBlock r;
-    if (VEC) {
+    if (READ != kFew) {
 #pragma unroll
         for (int v = 0; v < kBlk / 4; ++v) {
-            r.v[v] = *reinterpret_cast<const float4*>(ph + b * kBlk + 4 * v);
-            r.t[v] = *reinterpret_cast<const float4*>(th + b * kBlk + 4 * v);
+            r.v[v] = load_quad<READ == kWhole, true>(ph, b * kBlk + 4 * v, K);
+            r.t[v] = load_quad<READ == kWhole, true>(th, b * kBlk + 4 * v, K);
         }
     }
     return r;
 }
 
 // The 16 weights of block b (zero beyond K).
-template <bool VEC>
+template <int READ>
 __device__ __forceinline__ void block_weights(const float* __restrict__ th, const float* __restrict__ ph,
                                               const PhiBlock& pre, int b, int K, float (&wv)[kBlk])
 {
     const int k0 = b * kBlk;
-    if (VEC) {
+    if (READ != kFew) {
 #pragma unroll
         for (int v = 0; v < kBlk / 4; ++v) {
             const float4 t = pre.t[v];
@@ -59,6 +65,14 @@ __device__ __forceinline__ void block_weights(const float* __restrict__ th, cons
             wv[4 * v + 1] = t.y * c.y;
             wv[4 * v + 2] = t.z * c.z;
             wv[4 * v + 3] = t.w * c.w;
+        }
+        if (READ == kQuads && k0 + kBlk > K) {                     // the last block (the same for the whole wave)
+#pragma unroll
+            for (int v = 0; v < kBlk / 4; ++v) {
+                float x[4] = {wv[4 * v], wv[4 * v + 1], wv[4 * v + 2], wv[4 * v + 3]};
+                shift_quad<false>(x, k0 + 4 * v, K);
+                wv[4 * v] = x[0]; wv[4 * v + 1] = x[1]; wv[4 * v + 2] = x[2]; wv[4 * v + 3] = x[3];
+            }
         }
     } else {
 #pragma unroll
@@ -86,13 +100,13 @@ struct ZeroTest {
 };
 
 // KC: the number of topics where it is known at compile time.  WAVES: the least number per SIMD that the registers are held to
-// (1: the compiler's own choice).  The kernel for any multiple of 16 needs 133 registers, three waves; held to the 128 of four
+// (1: the compiler's own choice).  The kernel for any multiple of 16 needs 134 registers, three waves; held to the 128 of four
 // waves it spills two.  Four waves are the faster form up to 128 topics (K = 64: 0.84 against 0.94 ms for 9000 news-shaped
 // documents at 100 copies, 0.90 against 0.97 at 20 from a flat posterior) and up to 256 where many topics receive copies
 // (K = 240: 2.51 against 2.60 ms at 100 copies, but 0.94 against 0.91 at 1.5).  Beyond, three: rows of more waves than that push one
-// another out of the cache (K = 512 from a flat posterior 4.34 against 4.07 ms, K = 1024 7.21 against 6.47).  K = 256 has 126
-// registers by itself (holding it to four waves only changes the schedule: 0.7 % slower).
-template <bool VEC, bool DEBUG, int KC = 0, int WAVES = 1>
+// another out of the cache (K = 512 from a flat posterior 4.34 against 4.07 ms, K = 1024 7.21 against 6.47).  K = 256 has 128
+// registers by itself (holding it to four waves only changes the schedule: 0.7 % slower), the kernel for any K (kQuads) 125.
+template <int READ, bool DEBUG, int KC = 0, int WAVES = 1>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) void poisson_draw_kernel(DrawArgs a)
 {
     extern __shared__ uint32_t lds[];
@@ -122,7 +136,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
     ChunkSupply supply(a);
     Staged staged;
     acc[lane] = 0u;
-    // 1/x for x = 1 to 64, the factors of the walks below (computed, three instructions each, a third of a term: poisson_sweep 3.98 and, from the table, 3.78 ms; K = 64 0.71, 0.58)
+    // 1/x for x = 1 to 64, the factors of the walks below (three instructions each where computed, a third of a term:
+    // poisson_sweep 3.98 and, from the table, 3.78 ms; K = 64 at 100 copies 0.71 and 0.58)
     float* recips = reinterpret_cast<float*>(acc + kWave);
     recips[lane] = inv_int((float)(lane + 1));
     __syncthreads();
@@ -137,12 +152,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
     float mu = 0.0f;
     {
         float P = 0.0f;
-        PhiBlock cur = load_phi<VEC>(th, ph, 0);
+        PhiBlock cur = load_phi<READ>(th, ph, 0, K);
         for (int b = 0; b < nblk; ++b) {
             PhiBlock nxt = cur;
-            if (b + 1 < nblk) nxt = load_phi<VEC>(th, ph, b + 1);
+            if (b + 1 < nblk) nxt = load_phi<READ>(th, ph, b + 1, K);
             float wv[kBlk];
-            block_weights<VEC>(th, ph, cur, b, K, wv);
+            block_weights<READ>(th, ph, cur, b, K, wv);
 #pragma unroll
             for (int j = 0; j < kBlk; ++j) P = P + wv[j];
             cur = nxt;
@@ -292,14 +307,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
 
     // ---- pass 2: blocks from last to first
     {
-        PhiBlock cur = load_phi<VEC>(th, ph, nblk - 1);
+        PhiBlock cur = load_phi<READ>(th, ph, nblk - 1, K);
         const ZeroTest zt(Nf);
         for (int b = nblk - 1; b >= 0; --b) {
             if (!__any(Nf > 0.0f)) break;
             PhiBlock nxt = cur;
-            if (b > 0) nxt = load_phi<VEC>(th, ph, b - 1);
+            if (b > 0) nxt = load_phi<READ>(th, ph, b - 1, K);
             float wv[kBlk];
-            block_weights<VEC>(th, ph, cur, b, K, wv);
+            block_weights<READ>(th, ph, cur, b, K, wv);
             cur = nxt;
 #pragma unroll
             for (int g = kBlk / 4 - 1; g >= 0; --g) {
@@ -310,7 +325,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) 
                     const int k = b * kBlk + g * 4 + j;
                     const float wk = wv[g * 4 + j];
                     // a zero weight passes the test
-                    const bool cand = (VEC || k < K) && Nf > 0.0f && !zt.surely_zero(wk, mu, x[j]);
+                    const bool cand = (READ == kWhole || k < K) && Nf > 0.0f && !zt.surely_zero(wk, mu, x[j]);
                     if (cand) {
                         int e = qh + cnt;
                         e = e >= kQCap ? e - kQCap : e;

@@ -569,11 +569,13 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         dim3 grid((unsigned)blocks);
         a.chunk_share = same::chunk_share(a.n_chunks, a.n, blocks);
         const size_t lds = same::poisson_lds_bytes();
-        if (a.K % same::kBlk != 0) hipLaunchKernelGGL((same::poisson_draw_kernel<false, DEBUG>), grid, block, lds, st, a);
-        else if (a.K == 256)       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 256>), grid, block, lds, st, a);
-        else if (same::poisson_four_waves(a.K, a.mf))
-                                   hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG, 0, 4>), grid, block, lds, st, a);
-        else                       hipLaunchKernelGGL((same::poisson_draw_kernel<true, DEBUG>), grid, block, lds, st, a);
+        const bool whole = a.K % same::kBlk == 0;
+        if (a.K < 4)         hipLaunchKernelGGL((same::poisson_draw_kernel<same::kFew, DEBUG>), grid, block, lds, st, a);
+        else if (a.K == 256) hipLaunchKernelGGL((same::poisson_draw_kernel<same::kWhole, DEBUG, 256>), grid, block, lds, st, a);
+        else if (whole && same::poisson_four_waves(a.K, a.mf))
+                             hipLaunchKernelGGL((same::poisson_draw_kernel<same::kWhole, DEBUG, 0, 4>), grid, block, lds, st, a);
+        else if (whole)      hipLaunchKernelGGL((same::poisson_draw_kernel<same::kWhole, DEBUG>), grid, block, lds, st, a);
+        else                 hipLaunchKernelGGL((same::poisson_draw_kernel<same::kQuads, DEBUG>), grid, block, lds, st, a);
     } else {
         // blocks of 4 * ceil(K / 128) topics, read in batches of one to seven 16-byte loads per matrix
         // (K = 512 and from 897 to 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the

@@ -210,3 +210,25 @@ def test_topic_totals_are_the_counts(K):
         assert np.array_equal(nk, np.asarray(g.get(binding.NDK)).reshape(X.D, K).sum(0, dtype=np.int64))
         assert np.array_equal(nk, np.asarray(g.get(binding.NWK)).reshape(X.V, K).sum(0, dtype=np.int64))
     g.close()
+
+
+# numbers of topics that are no multiple of 16: rows that end inside a block of loads at every remainder, fewer than four topics,
+# few copies and many
+@pytest.mark.parametrize("K,m", [(1, 3.5), (3, 3.5), (4, 3.5), (5, 40.5), (15, 2.5), (17, 40.5), (30, 2.5), (50, 40.5), (100, 2.5), (127, 40.5), (150, 2.5), (200, 40.5),
+                                 (255, 2.5), (257, 2.5), (333, 40.5), (1001, 2.5)])
+def test_poisson_at_any_number_of_topics(K, m):
+    """Counts against the oracle; the last word and the last document, whose rows end the matrices, are drawn for as well."""
+    rng = np.random.default_rng(K)
+    counts = rng.integers(1, 9, size=(50, 70)) * (rng.uniform(size=(50, 70)) < 0.4)
+    counts[:, 69] = counts[49, :] = 1
+    cols = [np.flatnonzero(r) for r in counts]
+    X = oracle.CSC(50, 70, np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32),
+                   np.concatenate(cols).astype(np.int32), counts[counts > 0].astype(np.float32))
+    o = oracle.OracleLDA(X, K, 0.2, 0.05, seed=19, m0=1, G=4)
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.2, 0.05, 19, 1, 4)
+    for _ in range(2):
+        o.sweep_poisson(m)
+        g.sweep_poisson(m)
+        assert np.array_equal(g.get(binding.NDK), o.ndk)
+        assert np.array_equal(g.get(binding.NWK), o.nwk)
+    g.close()
