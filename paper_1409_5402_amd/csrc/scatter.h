@@ -84,7 +84,7 @@ constexpr int kHotCopies = 32;          // copies of a hot word's row
 
 // Where the counts of one task go.  Every placed count goes to the document's row at once (an atomic:
 // several waves may hold tasks of one document).  The word's row is updated either the same way or, when
-// the launch has a pair list, later by word_reduce_kernel: the task records (topic, count) in its slot of
+// the launch has a pair list, later by word_reduce (counts_kernel): the task records (topic, count) in its slot of
 // the list (slots are in word order), so that the scattered updates of [V][K] become one streaming pass
 // with all updates of a row close together.  A slot is four words: three pairs and, last, a header.  A task that
 // places more than three pairs continues in chunks of 15 pairs and a header taken from a pool: the header of a full
