@@ -1,6 +1,7 @@
 // Who works on what in the draw kernels: the arithmetic of their launches and loads, without any device code, so that a
 // host program can check it for every size.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __HIPCC__
@@ -124,6 +125,16 @@ inline int groups_per_unit(int K, int most)
 {
     const int fit = K <= 1024 ? most : (32 << 10) / (4 * K);       // 7 down to 4
     return fit < most ? fit : most;
+}
+
+// The topic totals' memory, in 64-bit words: the copies that the documents' workgroups add to, then the totals.  The copies come
+// first because they are cleared with 16-byte stores: behind the totals they would start half-way between two for every odd K.
+inline int nk_copies_for(int K) { return K <= 128 ? 8 : (K <= 256 ? 4 : (K <= 512 ? 2 : 1)); }
+struct TotalsLayout { size_t copies, copy_words, totals, words; };
+inline TotalsLayout totals_layout(int K)
+{
+    const size_t n = (size_t)nk_copies_for(K) * (size_t)K;
+    return {0, n, n, n + (size_t)K};
 }
 
 // The pool of chunks that continue full pair-list slots: each of `waves` workgroups owns `share` of its `chunks`, the rest is

@@ -29,6 +29,7 @@ thread_local std::string g_init_error;
 
 constexpr int32_t kTileDocs = 16;   // documents per tile of the processing order
 constexpr int kSecondCounters = same::kCounterWords + 32;   // where the copy stream's tickets start (a cache line of their own)
+static_assert(kSecondCounters % 4 == 0, "cleared with 16-byte stores");
 constexpr int kGammaRows = 64;      // rows of n_wk per workgroup of the sampled phi step
 
 // Device copy of one sparse matrix plus its draw work list.
@@ -128,7 +129,7 @@ struct same_lda {
     hipStream_t copy_stream = nullptr;
     float* phi = nullptr;          // [V][K]
     uint32_t* nwk = nullptr;       // [V][K]
-    unsigned long long* nk = nullptr;  // [1 + nk_copies_for(K)][K]: n_k, then the copies that the documents' workgroups add to
+    unsigned long long* nk = nullptr;  // n_k and, before it, the copies that the documents' workgroups add to (totals_layout)
     uint32_t* draw_counter = nullptr;  // counters of the draw kernel: tickets (kCounterWords), batches of chunks taken and the hot words' mark
                                        // (a word each) of a launch on the handle's stream, tickets of a launch on the copy stream
     uint32_t* chunks = nullptr;        // pool of chunks that continue full pair-list slots (launches on the handle's stream)
@@ -503,7 +504,8 @@ int check_m(same_lda* h, int32_t m, const Matrix& M)
 // have no pair list and therefore no use for the chunk pool: they run beside launches on the handle's stream, which own it.
 bool beside(const same_lda* h, hipStream_t st) { return st == h->copy_stream && st != h->stream; }
 size_t counter_words(const same_lda* h, hipStream_t st) { return beside(h, st) ? same::kCounterWords : same::kCounterWords + 2; }
-same::NkCopies nk_copies(const same_lda* h) { return {h->nk + h->K, same::nk_copies_for(h->K)}; }
+same::NkCopies nk_copies(const same_lda* h) { return {h->nk + same::totals_layout(h->K).copies, same::nk_copies_for(h->K)}; }
+unsigned long long* nk_totals(const same_lda* h) { return h->nk + same::totals_layout(h->K).totals; }
 uint32_t* hot_used(const same_lda* h) { return h->draw_counter + same::kCounterWords + 1; }
 
 void assign_counters(same_lda* h, same::DrawArgs& a, hipStream_t st)
@@ -699,7 +701,7 @@ int update_collapsed(same_lda* h, Matrix& M, const same::DrawArgs& drawn, float 
     int rc = finish_counts(h, M, drawn, true, m, st);
     if (rc) return rc;
     same::PhiArgs a;
-    a.nwk = h->nwk; a.copies = nk_copies(h); a.nk = h->nk; a.phi = h->phi; a.hot_of = n_hot > 0 ? M.hot_of : nullptr; a.hot_used = hot_used(h);
+    a.nwk = h->nwk; a.copies = nk_copies(h); a.nk = nk_totals(h); a.phi = h->phi; a.hot_of = n_hot > 0 ? M.hot_of : nullptr; a.hot_used = hot_used(h);
     a.V = h->V; a.K = h->K; a.hot_max = same::kHotMax; a.hot_copies = same::kHotCopies;
     a.mf = m; a.beta = h->beta; a.vbeta = (float)h->V * h->beta; a.rho = rho;
     // up to eight rows per thread, fewer where that leaves less than four workgroups per compute unit
@@ -733,7 +735,7 @@ int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_
                        same::kHotMax, same::kHotCopies, h->phi, h->V, h->K, m * h->beta, (uint32_t)h->seed, (uint32_t)(h->seed >> 32),
                        pword, kGammaRows, h->gamma_partial);
     hipLaunchKernelGGL(same::gamma_phi_totals_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, st, h->gamma_partial,
-                       blocks, h->K, h->gamma_total, nk_copies(h), h->nk);
+                       blocks, h->K, h->gamma_total, nk_copies(h), nk_totals(h));
     const uint32_t rows = 8u * (h->K >= 256 ? 1u : 256u / (uint32_t)h->K);
     hipLaunchKernelGGL(same::gamma_phi_normalise_kernel, dim3(same::blocks_of_rows((uint32_t)h->V, rows)), dim3(256), 0, st, h->phi, h->V, h->K,
                        h->gamma_total, rows);
@@ -757,8 +759,8 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
     {   // one launch of its own, so that the events around the draw kernel bracket that kernel alone.  The hot words'
         // copies need no clearing: the parameter update that follows every pass with words leaves them clear.
         const size_t cells = (size_t)M.D * h->K, word_cells = with_words ? (size_t)h->V * h->K : 0;
-        const same::ClearArgs z = {{M.ndk, h->nwk, a.counter, reinterpret_cast<uint32_t*>(h->nk + h->K)},
-                                   {cells, word_cells, counter_words(h, st), with_words ? (size_t)2 * same::nk_copies_for(h->K) * h->K : 0}};
+        const same::ClearArgs z = {{M.ndk, h->nwk, a.counter, reinterpret_cast<uint32_t*>(nk_copies(h).p)},
+                                   {cells, word_cells, counter_words(h, st), with_words ? 2 * same::totals_layout(h->K).copy_words : 0}};
         hipLaunchKernelGGL(same::clear_kernel, dim3(grid_for((cells > word_cells ? cells : word_cells) / 4 + 1)), dim3(256), 0, st, z);
         HIP_TRY(h, hipGetLastError());
     }
@@ -835,7 +837,7 @@ void* state_ptr(same_lda* h, int32_t which)
         case SAME_LDA_PHI:   return h->phi;
         case SAME_LDA_NDK:   return h->X.ndk;
         case SAME_LDA_NWK:   return h->nwk;
-        case SAME_LDA_NK:    return h->nk;
+        case SAME_LDA_NK:    return nk_totals(h);
         default:             return nullptr;
     }
 }
@@ -863,7 +865,7 @@ int same_lda_init(same_lda_t** out, const same_lda_csc* X, int32_t K, float alph
     if (!rc) rc = check_m(h, m0, h->X);
     if (!rc) rc = dev_alloc(h, &h->phi, (size_t)h->V * K);
     if (!rc) rc = dev_alloc(h, &h->nwk, nwk_elements(h));
-    if (!rc) rc = dev_alloc(h, &h->nk, (size_t)(1 + same::nk_copies_for(K)) * K);
+    if (!rc) rc = dev_alloc(h, &h->nk, same::totals_layout(K).words);
     if (!rc) rc = dev_alloc(h, &h->gamma_partial, (size_t)same::blocks_of_rows((uint32_t)h->V, kGammaRows) * K);
     if (!rc) rc = dev_alloc(h, &h->gamma_total, (size_t)K);
     if (!rc) rc = dev_alloc(h, &h->vb_psi, (size_t)K);

@@ -152,8 +152,7 @@ __global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __res
 // rows_per_block documents, four rows of loads in flight per thread, and ends with one 64-bit atomic per topic, on one of a few
 // copies of the totals: the 512 of a launch on one address take longer than the rest of it where that is small (K = 64, 50,000
 // documents: 18 us a sweep).  Who needs the totals adds the copies up (nk_total), which every workgroup of the phi update
-// does: eight copies up to 128 topics, down to one at 1024 (with eight there 110 us of 4.6 ms lost).
-inline int nk_copies_for(int K) { return K <= 128 ? 8 : (K <= 256 ? 4 : (K <= 512 ? 2 : 1)); }
+// does: eight copies up to 128 topics, down to one at 1024 (nk_copies_for; with eight there 110 us of 4.6 ms lost).
 struct NkCopies { unsigned long long* p; int n; };
 __device__ __forceinline__ unsigned long long nk_total(const NkCopies& a, int K, int k)
 {

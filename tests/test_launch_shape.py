@@ -78,6 +78,15 @@ long t_documents_out_of_range(int first, int step, int D)
     if (d < D) do { wrong += d < 0 || d >= D || d <= before; before = d; } while (wrong == 0 && next_document(d, step, D));
     return wrong + (first < D && D - step > before);
 }
+// The totals' memory: copies that 16-byte stores cannot clear whole, arrays that overlap or end behind it.
+int t_totals_wrong(int K)
+{
+    const TotalsLayout t = totals_layout(K);
+    const size_t ends[2] = {t.copies + t.copy_words, t.totals + (size_t)K};
+    int wrong = 8 * t.copies % 16 != 0 || t.copy_words != (size_t)nk_copies_for(K) * K;
+    wrong += !(ends[0] <= t.totals || ends[1] <= t.copies) || ends[0] > t.words || ends[1] > t.words;
+    return wrong;
+}
 unsigned t_chunk_share(unsigned chunks, long n, long waves) { return chunk_share(chunks, n, waves); }
 int t_scan_first_topic(int hl, int T, int nblk) { return scan_first_topic(hl, T, nblk); }
 }
@@ -157,3 +166,8 @@ def test_own_chunks_stay_close_together(lib):
         share = lib.t_chunk_share(min(10 * n, 2**31 - 1), n, waves)
         assert share * waves <= n // 2 and share >= n // 2 // waves
         assert lib.t_chunk_share(7, n, waves) == 0 and lib.t_chunk_share(0, n, waves) == 0
+
+
+def test_topic_totals_have_their_place(lib):
+    """The copies of the totals start where a 16-byte store may, whatever the number of topics, and share nothing with the totals."""
+    assert [K for K in range(1, 2049) if lib.t_totals_wrong(K)] == []
