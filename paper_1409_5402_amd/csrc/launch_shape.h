@@ -167,6 +167,11 @@ SAME_HD inline Chunks chunk_batch(uint32_t taken, uint32_t waves, uint32_t share
     return c;
 }
 
+// Nonzero number `first + at` of a document of n, past the end its last one.  A document may have all of the 2^31 - 1 nonzeros
+// of a matrix, and the E-step loads rounds ahead, up to kVbAhead numbers past the end: they are unsigned.
+constexpr uint32_t kVbAhead = 48;       // three rounds of four groups of four
+SAME_HD inline uint32_t vb_nonzero(uint32_t first, uint32_t at, uint32_t n) { return first + at < n ? first + at : n - 1u; }
+
 // Whether the normaliser's workgroups share the words out among the dies (sddmm_kernel.h): where phi is several times a die's
 // 4 MB of cache and its rows are long enough to outweigh the list of nonzeros that each wave then makes, and documents have
 // enough words for an eighth of them to be a run.  ms without / with, 30,000 news-shaped documents:

@@ -127,7 +127,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 
                                                                    // rounding fed back ten times shows at 1e-5
     float* av = reinterpret_cast<float*>(g + K);                   // [K]: a
     const int32_t d = (int32_t)blockIdx.x;
-    const int32_t lo = p.colptr[d], n = p.colptr[d + 1] - lo;      // the document's nonzeros
+    const int32_t lo = p.colptr[d];
+    const uint32_t n = (uint32_t)(p.colptr[d + 1] - lo);           // the document's nonzeros
     const int32_t* __restrict__ ids = p.rowidx + lo;
     const float* __restrict__ val = p.val + lo;
     float* __restrict__ grow = p.gamma + (size_t)d * K;
@@ -142,12 +143,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 
 #pragma unroll
         for (int j = 0; j < 4; ++j) ok[c][j] = off[c] + j >= k;
     }
-    auto rows = [&](int first, float4 (&bv)[4][CH], float& cnt) {  // the round that begins with nonzero `first`
-        const int i0 = first + (kGroups > 1 ? 4 * grp : 0);
+    static_assert(3 * kRound <= kVbAhead, "rounds loaded ahead");
+    auto rows = [&](uint32_t first, float4 (&bv)[4][CH], float& cnt) {   // the round that begins with nonzero `first`
+        const uint32_t i0 = first + (kGroups > 1 ? 4u * grp : 0u);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = i0 + j < n ? i0 + j : n - 1;
-            const float* __restrict__ row = p.b + (size_t)ids[i] * K;
+        for (uint32_t j = 0; j < 4u; ++j) {
+            const float* __restrict__ row = p.b + (size_t)ids[vb_nonzero(i0, j, n)] * K;
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
                 if constexpr (ALIGNED) {
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 
                 }
             }
         }
-        const int i = i0 + (lane & 3);
+        const uint32_t i = i0 + (lane & 3);
         cnt = i < n ? val[i] : 0.f;
     };
     for (int it = 0; it < p.iters; ++it) {
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 
             a[c].z = ok[c][2] ? av[off[c] + 2] : 0.f; a[c].w = ok[c][3] ? av[off[c] + 3] : 0.f;
             acc[c][0] = 0.0; acc[c][1] = 0.0; acc[c][2] = 0.0; acc[c][3] = 0.0;
         }
-        auto work = [&](int first, const float4 (&bv)[4][CH], float cnt) {
+        auto work = [&](uint32_t first, const float4 (&bv)[4][CH], float cnt) {
             float sj[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 
             add(2, std::integral_constant<int, 0x152>{});
             add(3, std::integral_constant<int, 0x153>{});
             if (p.log_mu != nullptr && it == p.iters - 1) {
-                const int i = first + 4 * grp + (lane & 3);
+                const uint32_t i = first + 4 * grp + (lane & 3);
                 if (sub < 4 && i < n) p.log_mu[lo + i] = logf(m) + (p.shift ? p.shift[ids[i]] : 0.f);
             }
         };
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 ? 4 
             float4 b0[4][CH], b1[4][CH];
             float c0, c1;
             rows(0, b0, c0);
-            for (int i = 0; ; i += 2 * kRound) {                   // two rounds per turn: no copies between the two sets
+            for (uint32_t i = 0; ; i += 2 * kRound) {              // two rounds per turn: no copies between the two sets
                 rows(i + kRound, b1, c1);
                 __builtin_amdgcn_sched_barrier(0);                 // the next round's loads first, then this round's work
                 work(i, b0, c0);

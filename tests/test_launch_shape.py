@@ -87,6 +87,18 @@ int t_totals_wrong(int K)
     wrong += !(ends[0] <= t.totals || ends[1] <= t.copies) || ends[0] > t.words || ends[1] > t.words;
     return wrong;
 }
+// Nonzeros that the last turns of the E-step's loop over a document of n name, rounds loaded ahead included, outside [0, n).
+long t_nonzeros_out_of_range(unsigned n, unsigned round)
+{
+    long wrong = 0;
+    const unsigned last = (n - 1u) / (2u * round);
+    for (unsigned t = last > 3u ? last - 3u : 0u; t <= last; ++t)
+        for (unsigned at = 0; at < 3u * round; ++at) {
+            const long i = (long)t * 2 * round + at, got = vb_nonzero(t * 2u * round, at, n);
+            wrong += got != (i < (long)n ? i : (long)n - 1) || at >= kVbAhead;
+        }
+    return wrong;
+}
 unsigned t_chunk_share(unsigned chunks, long n, long waves) { return chunk_share(chunks, n, waves); }
 int t_scan_first_topic(int hl, int T, int nblk) { return scan_first_topic(hl, T, nblk); }
 }
@@ -109,6 +121,8 @@ def lib(tmp_path_factory):
     so.t_rows_without_owner.argtypes = [ctypes.c_uint] * 2
     so.t_rows_without_owner.restype = ctypes.c_long
     so.t_documents_out_of_range.restype = ctypes.c_long
+    so.t_nonzeros_out_of_range.argtypes = [ctypes.c_uint] * 2
+    so.t_nonzeros_out_of_range.restype = ctypes.c_long
     so.t_owners_of_one_chunk.argtypes = [ctypes.c_uint] * 4
     so.t_owners_of_one_chunk.restype = ctypes.c_long
     return so
@@ -171,3 +185,10 @@ def test_own_chunks_stay_close_together(lib):
 def test_topic_totals_have_their_place(lib):
     """The copies of the totals start where a 16-byte store may, whatever the number of topics, and share nothing with the totals."""
     assert [K for K in range(1, 2049) if lib.t_totals_wrong(K)] == []
+
+
+@pytest.mark.parametrize("round_", [4, 8, 16])
+def test_nonzeros_of_a_round_exist(lib, round_):
+    """The E-step's rounds, the ones loaded ahead among them, name nonzeros of their document, up to a document of 2^31 - 1."""
+    for n in (1, 2, 3, round_, 2 * round_ + 1, 1000, 2**31 - 100, 2**31 - 33, 2**31 - 2, 2**31 - 1):
+        assert lib.t_nonzeros_out_of_range(n, round_) == 0, n
