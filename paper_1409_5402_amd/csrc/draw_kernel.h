@@ -180,7 +180,7 @@ constexpr int kRefillLateTrips = 8;
 template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 3 ? 4 : 3)))) void draw_kernel(DrawArgs a)
 {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     constexpr bool SMALL = !UNIFORM && KC == 0 && (TB == 0 || (TB == 1 && ONE));   // up to 128 topics: blocks of four
     const int kStride = UNIFORM ? 1 : (SMALL ? sum_stride(a.K) : kSumStride);      // (weights of one need no sums)
     const float* recips = reinterpret_cast<const float*>(lds);     // [kRecips]: 1, 1/2, 1/3, ...

@@ -109,7 +109,7 @@ struct ZeroTest {
 template <int READ, bool DEBUG, int KC = 0, int WAVES = 1>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(WAVES))) void poisson_draw_kernel(DrawArgs a)
 {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     const int lane = threadIdx.x;
     const int K = KC > 0 ? KC : a.K;
     const int nblk = (K + kBlk - 1) / kBlk;

@@ -192,3 +192,15 @@ def test_nonzeros_of_a_round_exist(lib, round_):
     """The E-step's rounds, the ones loaded ahead among them, name nonzeros of their document, up to a document of 2^31 - 1."""
     for n in (1, 2, 3, round_, 2 * round_ + 1, 1000, 2**31 - 100, 2**31 - 33, 2**31 - 2, 2**31 - 1):
         assert lib.t_nonzeros_out_of_range(n, round_) == 0, n
+
+
+def test_lds_arrays_are_aligned_for_the_widest_access():
+    """Dynamic LDS that is accessed 16 bytes at a time is declared with that alignment (the E-step's arrays of double are not:
+    8 bytes at most)."""
+    arrays = []
+    for name in sorted(os.listdir(CSRC)):
+        with open(os.path.join(CSRC, name)) as f:
+            arrays += [(name, line.strip()) for line in f if "extern __shared__" in line]
+    assert len(arrays) >= 5
+    for name, line in arrays:
+        assert "extern __shared__ double" in line or "__align__(16)" in line, (name, line)
