@@ -231,8 +231,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     bool open = false;      // a task was taken and its slot of the pair list is not yet closed
     int32_t d = 0, w = 0;
     // Its rows of theta and phi, as addresses: from d and w they take nine instructions a step (more where K is no constant).
-    // Not where the four registers are not to be had without spilling others.
-    constexpr bool kRowAddr = KC > 0 || (ONE && (TB <= 2 || TB == 4 || TB == 5));
+    // Not where the four registers are not to be had without spilling others, and not at K = 1024 (from a flat posterior
+    // at m = 100, documents of 60 and 330 tokens, 6.17 and 6.86 ms with them, 5.90 and 6.67 without).
+    constexpr bool kRowAddr = KC == 256 || KC == 512 || (KC == 0 && ONE && (TB <= 2 || TB == 4 || TB == 5));
     const float* th_row = a.theta;
     const float* ph_row = a.phi;
     Scatter sc;
@@ -730,16 +731,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     k = (int)prev;
                 } else {
                     // the first block whose cumulative weight reaches y (mu >= U >= y; entries past the last block repeat
-                    // mu), and prev = the cumulative weight below that block, read once the block is known
-                    const float* S = my_sums;
+                    // mu), and prev = the cumulative weight below that block
+                    int l = 0;
 #pragma unroll
                     for (int h = kMaxBlocks / 2; h > 0; h >>= 1) {
                         if (KC == 0 && h >= nblk) continue;
-                        S += !(S[h] >= y) ? h : 0;
+                        const float v = my_sums[l + h];            // (an address kept in place of l, prev read at the end: K = 1024
+                        const bool below = !(v >= y);              // from a flat posterior at m = 100 6.79 in place of 6.17 ms,
+                        prev = below ? v : prev;                   // K = 350 with its row of theta 3.36 and 3.19)
+                        l = below ? l + h : l;
                     }
-                    int l = (int)(S - my_sums);
-                    if (KC == 0) { l = min(l, nblk - 1); S = my_sums + l; }   // (only negative weights could lead past it)
-                    prev = *S;
+                    if (KC == 0) l = min(l, nblk - 1);             // (only negative weights could lead past it)
                     // inside the block: rebuild P_k from the block's weights.  Its last P_k is the block's cumulative
                     // weight, the same sum in the same order, so the search ends inside the block.
                     const int k0 = l * T;
