@@ -51,12 +51,6 @@ __host__ __device__ inline int sum_stride(int K) { return scan_lanes(K) + 1; }
 // A second row at K = 256 would serve the waves that straddle two documents, but its kilobyte costs two of the
 // fifteen waves a compute unit holds, which costs more.
 __host__ __device__ inline int doc_rows(int K) { return K <= 128 ? 2 : (K <= 1024 ? 1 : 0); }
-// Whether the document of each row of counts also has its row of theta in LDS, for the reload of a step's block.  Sixteen waves'
-// rows of theta and their pieces of phi do not fit the 32 KB of a compute unit's cache for long, and every load of a step
-// takes it a cycle per lane.  ms per draw without / with, 15,000 news-shaped documents at m = 10 (two waves fewer per
-// compute unit with): K = 260 0.589 / 0.622, 300 0.612 / 0.595, 384 1.35 / 1.30, 640 1.00 / 0.95, 800 1.76 / 1.34, 890
-// 1.87 / 1.64; K = 256 with as many waves on both sides within 1 %; from 897, where a wave would need 16 KB, 900 1.34 / 1.48.
-__host__ __device__ constexpr bool theta_rows(int K) { return K >= 288 && K <= 896; }
 
 // The value of v in the next lower lane (lanes 0, 16, 32, 48 receive 0): a row shift inside the vector ALU.
 __device__ __forceinline__ float from_lane_below(float v)
@@ -177,7 +171,10 @@ constexpr int kRefillLateTrips = 8;
 // out before round 0 and pass over them afterwards.
 //
 // (How shares and tickets are dealt out: launch_shape.h.)
-template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false>
+//
+// THETA: the document of the row of counts also has its row of theta in LDS, for the reload of a step's block (theta_rows in
+// launch_shape.h).
+template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false, bool THETA = false>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 3 ? 4 : 3)))) void draw_kernel(DrawArgs a)
 {
     extern __shared__ __align__(16) uint32_t lds[];
@@ -202,10 +199,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     int tag0 = -1, tag1 = -1;                                      // the documents of rows 0 and 1 (wave-uniform), -1: free
     int myrow = -1;                                                // the row of this lane's document, -1: none
     for (int i = lane; i < n_rows * K; i += kWave) rows[i] = 0u;
-    // (theta_row: they have their rows of theta beside them)
-    constexpr bool kThetaRow = !UNIFORM && !DEBUG && TB > 0 && (KC > 0 ? theta_rows(KC) : TB >= 3);
-    const bool theta_row = kThetaRow && theta_rows(K);
-    float* th_rows = reinterpret_cast<float*>(rows) + n_rows * K;   // [n_rows][K]: theta of those documents
+    static_assert(!THETA || (ONE && TB >= 3 && !UNIFORM && !DEBUG), "theta_rows");
+    float* th_row_lds = reinterpret_cast<float*>(rows) + K;        // THETA: [K], theta of that document (one row at these K)
     // the wave's positions not yet handed out
     int32_t next, end;
     bool heavy;                                                    // they are positions of the list of heavy tasks
@@ -233,7 +228,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     // Its rows of theta and phi, as addresses: from d and w they take nine instructions a step (more where K is no constant).
     // Not where the four registers are not to be had without spilling others, and not at K = 1024 (from a flat posterior
     // at m = 100, documents of 60 and 330 tokens, 6.17 and 6.86 ms with them, 5.90 and 6.67 without).
-    constexpr bool kRowAddr = KC == 256 || KC == 512 || (KC == 0 && ONE && (TB <= 2 || TB == 4 || TB == 5));
+    constexpr bool kRowAddr = KC == 256 || KC == 512 || (KC == 0 && ONE && (TB <= 2 || TB == 4 || (TB == 5 && (VEC || !THETA))));
     const float* th_row = a.theta;
     const float* ph_row = a.phi;
     Scatter sc;
@@ -271,11 +266,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
         __syncthreads();
     };
 
-    // Theta of document doc beside row i of the LDS counts (whole wave).
-    auto load_theta = [&](int i, int doc) {
-        if (theta_row) {
+    // Theta of document doc beside its LDS counts (whole wave).
+    auto load_theta = [&](int doc) {
+        if (THETA) {
             const float* __restrict__ t = a.theta + (size_t)doc * K;
-            for (int k = lane; k < K; k += kWave) th_rows[i * K + k] = t[k];
+            for (int k = lane; k < K; k += kWave) th_row_lds[k] = t[k];
         }
     };
 
@@ -328,14 +323,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                     flush_row(0, tag0);
                     if (myrow == 0) myrow = -1;
                     tag0 = dn;
-                    load_theta(0, dn);
+                    load_theta(dn);
                     if (take && d == dn) myrow = 0;
                     break;
                 }
                 const int old = free_row == 0 ? tag0 : tag1;
                 if (old >= 0) flush_row(free_row, old);
                 if (free_row == 0) tag0 = dn; else tag1 = dn;
-                load_theta(free_row, dn);
+                load_theta(dn);
                 if (take && d == dn) myrow = free_row;
             }
         }
@@ -761,8 +756,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
                                 float4 pv[N / 4], tv[N / 4];
 #pragma unroll
                                 for (int c = 0; c < N / 4; ++c) pv[c] = load_quad<VEC, WHOLE>(ph, kb + 4 * c, K);
-                                if (kThetaRow && theta_row && myrow >= 0) {
-                                    const lds_float* tr = (const lds_float*)(th_rows + (n_rows > 1 ? myrow * K : 0));
+                                if (THETA && myrow >= 0) {
+                                    const lds_float* tr = (const lds_float*)th_row_lds;
 #pragma unroll
                                     for (int c = 0; c < N / 4; ++c) tv[c] = lds_quad<VEC, WHOLE>(tr, kb + 4 * c, K);
                                 } else {
@@ -934,6 +929,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ?
     if (n_rows > 1 && tag1 >= 0) flush_row(1, tag1);
 }
 
-inline size_t draw_lds_bytes(int K, bool uniform) { return 4u * ((size_t)kRecips + (size_t)kWave * (size_t)(uniform ? 1 : sum_stride(K)) + (size_t)doc_rows(K) * (size_t)K * (uniform || !theta_rows(K) ? 1u : 2u)); }
+inline size_t draw_lds_bytes(int K, bool uniform, bool theta)
+{
+    return 4u * ((size_t)kRecips + (size_t)kWave * (size_t)(uniform ? 1 : sum_stride(K)) + (size_t)(doc_rows(K) + (theta ? 1 : 0)) * (size_t)K);
+}
 
 }  // namespace same

@@ -537,20 +537,33 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, bool un
     return SAME_LDA_OK;
 }
 
+// The draw kernel for blocks of one batch of TB loads, with the rows of theta in LDS or without.
+template <bool VEC, bool DEBUG, int TB>
+const void* one_batch_kernel(bool theta)
+{
+    constexpr bool some = !DEBUG && same::theta_rows_some(TB), all = !DEBUG && same::theta_rows_all(TB, VEC);
+    if constexpr (some) {
+        if (all || theta) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, TB, true, 0, false, true>);
+    }
+    if constexpr (!all) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, TB, true>);
+    return nullptr;
+}
+
 // The draw kernel for blocks of 4 * quads topics (VEC: rows are aligned to 16 bytes).  Up to 896 topics a block is one batch
 // of loads, up to 1024 two in the contiguous form, beyond that batches of the largest of 4, 2, 1 that divides it.  The
-// debug hook takes the same form of the kernel as the sweep: what it returns was drawn by the code that sweeps run.
+// debug hook takes the same form of the kernel as the sweep, but for the rows in LDS: its lanes add to count rows of their own in
+// memory, and the reload of a step's block reads theta there as well, where a sweep may have the row in LDS (theta_rows).
 template <bool VEC, bool DEBUG>
-const void* draw_kernel_for(int quads)
+const void* draw_kernel_for(int quads, bool theta)
 {
     switch (quads) {
-        case 1:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 1, true>);
-        case 2:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 2, true>);
-        case 3:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 3, true>);
-        case 4:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, true>);
-        case 5:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 5, true>);
-        case 6:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 6, true>);
-        case 7:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 7, true>);
+        case 1:  return one_batch_kernel<VEC, DEBUG, 1>(theta);
+        case 2:  return one_batch_kernel<VEC, DEBUG, 2>(theta);
+        case 3:  return one_batch_kernel<VEC, DEBUG, 3>(theta);
+        case 4:  return one_batch_kernel<VEC, DEBUG, 4>(theta);
+        case 5:  return one_batch_kernel<VEC, DEBUG, 5>(theta);
+        case 6:  return one_batch_kernel<VEC, DEBUG, 6>(theta);
+        case 7:  return one_batch_kernel<VEC, DEBUG, 7>(theta);
         case 8:  return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, 4, false, 0, true>);
         default: break;
     }
@@ -583,16 +596,17 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         // (K = 512 and from 897 to 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
         // kernel is bound by vector-ALU issue, the extra additions of that form cost more than the fewer cache lines save)
         const int quads = same::block_len(a.K) / 4;                // 16-byte loads per block and matrix
+        const bool theta = !uniform && !DEBUG && same::theta_rows(a.K, a.m);
         const void* f = nullptr;
         if (uniform)      f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
         else if (a.K < 4) f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
         else if (a.K == 256)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true, 256>);
-        else if (a.K == 512)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true>);
+        else if (a.K == 512)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true, !DEBUG>);
         else if (a.K == 1024) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false, 1024, true>);
-        else if (a.K % 4 == 0) f = draw_kernel_for<true, DEBUG>(quads);
-        else                   f = draw_kernel_for<false, DEBUG>(quads);
+        else if (a.K % 4 == 0) f = draw_kernel_for<true, DEBUG>(quads, theta);
+        else                   f = draw_kernel_for<false, DEBUG>(quads, theta);
         // One-wave workgroups, each with a share of the positions.
-        const size_t lds = same::draw_lds_bytes(a.K, uniform);
+        const size_t lds = same::draw_lds_bytes(a.K, uniform, theta);
         int64_t resident = 0;
         int rc = resident_groups(h, f, T, lds, uniform, &resident);
         if (rc) return rc;
