@@ -174,8 +174,21 @@ constexpr int kRefillLateTrips = 8;
 //
 // THETA: the document of the row of counts also has its row of theta in LDS, for the reload of a step's block (theta_rows in
 // launch_shape.h).
+//
+// Waves per SIMD: four where 128 registers hold the kernel, else three, and two where three would keep up to 63 registers and
+// 140 bytes a lane in scratch (rows that are not aligned from 641 to 1024 topics, 7 loads per matrix in flight).  ms per draw with
+// three / two, documents of 60 tokens from a flat posterior and of 330 with topics formed, m = 16 and then 100: K = 701 1.90 / 1.65,
+// 1.32 / 1.12 and 6.23 / 5.37, 3.08 / 2.69; K = 895 3.21 / 1.99, 2.04 / 1.27 and 12.2 / 6.08, 5.52 / 2.90; K = 896 1.80 / 1.69,
+// 1.19 / 1.09 and 5.71 / 5.16, 2.59 / 2.36; K = 1001 2.69 / 2.31, 1.49 / 1.43 and 9.23 / 7.37, 3.39 / 3.33, but at m = 1 0.80 / 0.88
+// and 0.72 / 0.73.
+constexpr int draw_waves(bool uniform, bool vec, int tb, bool one, int kc, bool coal)
+{
+    if (uniform) return 6;
+    if (tb <= 3) return 4;
+    return (one && tb == 7) || (!vec && ((one && tb == 6) || (coal && kc == 0))) ? 2 : 3;
+}
 template <bool UNIFORM, bool VEC, bool DEBUG, int TB, bool ONE, int KC = 0, bool COAL = false, bool THETA = false>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(UNIFORM ? 6 : (TB <= 3 ? 4 : 3)))) void draw_kernel(DrawArgs a)
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(draw_waves(UNIFORM, VEC, TB, ONE, KC, COAL)))) void draw_kernel(DrawArgs a)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     constexpr bool SMALL = !UNIFORM && KC == 0 && (TB == 0 || (TB == 1 && ONE));   // up to 128 topics: blocks of four

@@ -127,8 +127,8 @@ inline int groups_per_unit(int K, int most)
     return fit < most ? fit : most;
 }
 
-// Whether the document of a draw wave's row of counts also has its row of theta in LDS, for the reload of a step's block, in a
-// sweep at m copies.  Sixteen waves' rows of theta and their pieces of phi do not fit the 32 KB of a compute unit's cache for
+// Whether the document of a draw wave's row of counts also has its row of theta in LDS, for the reload of a step's block.
+// Sixteen waves' rows of theta and their pieces of phi do not fit the 32 KB of a compute unit's cache for
 // long, and every load of a step takes it a cycle per lane; the row costs up to a quarter of the waves and some registers.
 // ms per draw without / with, 2 million tokens in documents of 60 tokens from a flat posterior and in documents of 330 with topics formed:
 //   up to 287 topics                 K = 260  m = 1 0.278 / 0.297, 0.270 / 0.286   m = 16 0.875 / 0.899, 0.773 / 0.803: never
@@ -138,20 +138,18 @@ inline int groups_per_unit(int K, int most)
 //   any alignment                    K = 333  m = 1 0.349 / 0.320, 0.320 / 0.301   m = 16 1.202 / 0.989, 0.868 / 0.804
 //   to 640, any alignment            K = 601  m = 1 0.650 / 0.586, 0.545 / 0.504   m = 100 5.324 / 4.451, 2.454 / 2.487
 //   to 768, aligned                  K = 768  m = 1 0.685 / 0.650, 0.553 / 0.541   m = 16 1.770 / 1.525, 1.100 / 1.016
-//           any alignment            K = 701  m = 1 0.767 / 0.694, 0.643 / 0.598   m = 16 2.083 / 1.868, 1.367 / 1.365
-//                                    m = 100 6.282 / 6.263, 3.035 / 3.175: up to 16 copies
-//   to 896, aligned                  K = 896  m = 1 0.857 / 0.785, 0.706 / 0.640   m = 100 6.055 / 5.810, 2.770 / 2.663
-//           any alignment            K = 895  m = 4 1.704 / 1.551, 1.220 / 1.142   m = 16 3.158 / 3.207, 1.986 / 2.039: up to 4 copies
+//           any alignment            K = 701  m = 1 0.686 / 0.653, 0.566 / 0.546   m = 16 1.729 / 1.646, 1.175 / 1.124
+//                                    m = 100 5.357 / 5.372, 2.581 / 2.693
+//   to 896, aligned                  K = 896  (three waves per SIMD) m = 1 0.857 / 0.785, 0.706 / 0.640   m = 100 6.055 / 5.810, 2.770 / 2.663
+//           any alignment            K = 895  m = 1 1.051 / 0.928, 0.858 / 0.771   m = 16 2.274 / 1.992, 1.391 / 1.270
+//                                    m = 100 6.396 / 6.075, 2.891 / 2.903
 // From 897 topics on a block is more than one batch of loads and a wave would need 16 KB.
 SAME_HD constexpr bool theta_rows_some(int quads) { return quads >= 3 && quads <= 7; }
-SAME_HD constexpr bool theta_rows_all(int quads, bool aligned) { return quads == 5 || (aligned ? quads == 6 || quads == 7 : quads == 4); }
-inline bool theta_rows(int K, uint32_t m)
+SAME_HD constexpr bool theta_rows_all(int quads, bool aligned) { return quads >= 5 ? quads <= 7 : quads == 4 && !aligned; }
+inline bool theta_rows(int K)
 {
     const int quads = block_len(K) / 4;
-    const bool aligned = K % 4 == 0;
-    if (quads == 3 || quads == 4) return K >= 288 && (!aligned || blocks_fill_row(K));
-    if (!aligned && quads == 6) return m <= 16;
-    if (!aligned && quads == 7) return m <= 4;
+    if (quads == 3 || quads == 4) return K >= 288 && (K % 4 != 0 || blocks_fill_row(K));
     return theta_rows_some(quads);
 }
 

@@ -596,7 +596,7 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         // (K = 512 and from 897 to 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
         // kernel is bound by vector-ALU issue, the extra additions of that form cost more than the fewer cache lines save)
         const int quads = same::block_len(a.K) / 4;                // 16-byte loads per block and matrix
-        const bool theta = !uniform && !DEBUG && same::theta_rows(a.K, a.m);
+        const bool theta = !uniform && !DEBUG && same::theta_rows(a.K);
         const void* f = nullptr;
         if (uniform)      f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
         else if (a.K < 4) f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);

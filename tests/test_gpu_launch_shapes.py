@@ -152,7 +152,7 @@ def test_every_form_of_the_draw_kernel(K):
 
 
 # the ends of the ranges in which a document's theta row is in LDS (288 to 896), aligned and not, whole blocks and not, and their
-# neighbours; up to 16 copies at 701, up to 4 at 769 and 895
+# neighbours
 @pytest.mark.parametrize("K", [284, 287, 288, 291, 292, 384, 385, 448, 500, 512, 516, 640, 641, 701, 768, 769, 892, 895, 896, 900])
 def test_theta_rows_beside_the_counts(K):
     """Documents of one to 120 words, so that waves hold tasks of one, of two and of dozens of documents: lanes whose document

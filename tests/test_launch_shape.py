@@ -62,17 +62,15 @@ int t_lds_groups(long bytes) { return lds_groups(bytes); }
 long t_theta_rows_wrong()
 {
     long wrong = 0;
-    for (int K = 1; K <= 2048; ++K)
-        for (unsigned m = 1; m <= 300; ++m) {
-            const int quads = block_len(K) / 4;
-            const bool on = theta_rows(K, m), one_batch = quads <= 7, one_row = K > 128 && K <= 1024;
-            wrong += on && !(one_batch && one_row && theta_rows_some(quads));
-            wrong += K >= 288 && theta_rows_all(quads, K % 4 == 0) && !on;
-            wrong += on && m > 1 && !theta_rows(K, m - 1);         // never for many copies alone
-        }
+    for (int K = 1; K <= 2048; ++K) {
+        const int quads = block_len(K) / 4;
+        const bool on = theta_rows(K), one_batch = quads <= 7, one_row = K > 128 && K <= 1024;
+        wrong += on && !(one_batch && one_row && theta_rows_some(quads));
+        wrong += theta_rows_all(quads, K % 4 == 0) && !on;
+    }
     return wrong;
 }
-int t_theta_rows(int K, unsigned m) { return theta_rows(K, m); }
+int t_theta_rows(int K) { return theta_rows(K); }
 int t_groups_per_unit(int K, int most) { return groups_per_unit(K, most); }
 // Rows near `rows` that belong to no workgroup, to two, or to one past the end.
 long t_rows_without_owner(unsigned rows, unsigned per_block)
@@ -225,6 +223,5 @@ def test_theta_rows_only_where_the_kernel_has_them(lib):
     """The rule asks for rows of theta in LDS only at sizes whose form of the draw kernel is instantiated with them (blocks of one
     batch of loads, one row of counts), and at every size where it is instantiated with them alone."""
     assert lib.t_theta_rows_wrong() == 0
-    for K, m, on in ((287, 1, 0), (288, 1, 1), (292, 1, 0), (289, 100, 1), (500, 1, 0), (512, 100, 1), (701, 16, 1), (701, 17, 0),
-                     (895, 4, 1), (895, 5, 0), (896, 100, 1), (897, 1, 0), (1024, 1, 0), (2048, 1, 0)):
-        assert bool(lib.t_theta_rows(K, m)) == bool(on), (K, m)
+    for K, on in ((287, 0), (288, 1), (292, 0), (289, 1), (448, 1), (500, 0), (512, 1), (516, 1), (701, 1), (895, 1), (896, 1), (897, 0), (1024, 0)):
+        assert bool(lib.t_theta_rows(K)) == bool(on), K
