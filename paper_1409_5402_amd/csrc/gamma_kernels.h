@@ -104,7 +104,8 @@ __global__ __launch_bounds__(256) void gamma_theta_kernel(const uint32_t* __rest
         }
 }
 
-// phi[w][k] = Gamma(n_wk + m*beta), and the sum of each topic over this block's rows (double, in a fixed order).  A hot
+// phi[w][k] = Gamma(n_wk + m*beta), the sum of each topic over this block's rows (double, in a fixed order) and its copies in
+// them, added to the copies of n_k (n_k over n_dk cost a pass over that matrix).  A hot
 // word's row first takes in its copies, as in phi_update_kernel.  1024 threads per workgroup: the variables are long
 // chains of arithmetic, and the block sums' scratch fixes the number of workgroups, not that of waves.
 constexpr int kGammaThreads = 1024;
@@ -112,20 +113,23 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_phi_kernel(uint32_t* __re
                                                                  const uint32_t* __restrict__ hot_used,
                                                                  int hot_max, int hot_copies, float* __restrict__ phi, int V, int K,
                                                                  float prior, uint32_t seed_lo, uint32_t seed_hi, uint32_t pass,
-                                                                 uint32_t rows_per_block, double* __restrict__ partial)
+                                                                 uint32_t rows_per_block, double* __restrict__ partial, NkCopies totals)
 {
     __shared__ double sh[kGammaThreads];
+    __shared__ unsigned long long sh_n[kGammaThreads];
     const RowSplit<1, kGammaThreads> s(K);
     const Rows b = rows_of_block(blockIdx.x, rows_per_block, (uint32_t)V);
     const bool copies = hot_of != nullptr && *hot_used != 0u;
     for (int k = s.unit; k < K; k += s.groups == 1 ? kGammaThreads : K) {
         double acc = 0.0;
+        unsigned long long copies_k = 0;                           // the topic's copies in these rows
         if (s.group < s.groups) {
             for (uint32_t r = b.from + s.group; r < b.to; r += s.groups) {
                 const size_t i = (size_t)r * K + k;
                 uint32_t n[1] = {nwk[i]};
                 const int hot = copies ? (int)hot_of[r] : -1;
                 if (hot >= 0 && take_in_copies<1>(nwk, V, K, hot, hot_max, hot_copies, k, n)) nwk[i] = n[0];
+                copies_k += n[0];
                 const float g = gamma_variable((float)n[0] + prior, seed_lo, seed_hi, r, (uint32_t)k, pass);
                 phi[i] = g;
                 acc += (double)g;
@@ -133,10 +137,12 @@ __global__ __launch_bounds__(kGammaThreads) void gamma_phi_kernel(uint32_t* __re
         }
         if (s.groups > 1) {
             sh[threadIdx.x] = acc;
+            sh_n[threadIdx.x] = copies_k;
             __syncthreads();
             if (s.group != 0) break;
-            for (int g = 1; g < s.groups; ++g) acc += sh[g * K + k];
+            for (int g = 1; g < s.groups; ++g) { acc += sh[g * K + k]; copies_k += sh_n[g * K + k]; }
         }
+        if (copies_k) atomicAdd(totals.p + (size_t)(blockIdx.x % (uint32_t)totals.n) * K + k, copies_k);
         partial[(size_t)blockIdx.x * K + k] = acc;
     }
 }

@@ -163,6 +163,39 @@ inline TotalsLayout totals_layout(int K)
     return {0, n, n, n + (size_t)K};
 }
 
+// How the totals and theta (update_kernels.h) go over n_dk.  `fold` documents at a time have a multiple of four counts and start on
+// a 16-byte boundary, whatever the number of topics: a thread owns the same 16 bytes of every `fold` documents, four topics that
+// depend on its unit alone.  Units beyond a workgroup's 256 threads are other workgroups' (turns), split so that few threads
+// are left over; groups of `per` threads take `fold` documents each.
+struct TotalsSplit { int fold, units, turns, per, groups; };
+inline TotalsSplit totals_split(int K)
+{
+    TotalsSplit s;
+    s.fold = K % 4 == 0 ? 1 : (K % 2 == 0 ? 2 : 4);
+    s.units = s.fold * K / 4;
+    int busy = 0;
+    const int least = (s.units + 255) / 256;
+    for (int turns = least; turns <= (least > 1 ? least + 3 : 1); ++turns) {
+        const int per = (s.units + turns - 1) / turns;
+        if (256 / per * per > busy) { busy = 256 / per * per; s.turns = turns; s.per = per; s.groups = 256 / per; }
+    }
+    return s;
+}
+struct TotalsBlocks { uint32_t rows, rows_per_block, blocks; };    // rows of `fold` documents; workgroups, all turns
+inline TotalsBlocks totals_blocks(const TotalsSplit& s, uint32_t D)
+{
+    // at least a turn of four rows per thread, and at most some 512 workgroups (64-bit atomics per topic)
+    TotalsBlocks b;
+    b.rows = D / (uint32_t)s.fold;
+    const uint32_t at_once = 4u * (uint32_t)s.groups;
+    b.rows_per_block = blocks_of_rows(b.rows, s.turns < 8 ? 512u / (uint32_t)s.turns : 64u);
+    if (b.rows_per_block < at_once) b.rows_per_block = at_once;
+    b.blocks = blocks_of_rows(b.rows, b.rows_per_block);
+    if (b.blocks == 0 && D > 0) b.blocks = 1;                      // fewer documents than one row: the first workgroup's (the rest of D / fold)
+    b.blocks *= (uint32_t)s.turns;
+    return b;
+}
+
 // The pool of chunks that continue full pair-list slots: each of `waves` workgroups owns `share` of its `chunks`, the rest is
 // handed out in batches by a counter.  The counter counts batches: a workgroup adds to it once more before it sees that the
 // pool is used up, and the Poisson form has a workgroup for every 64 tasks, up to 2^25 of them.  A counter of

@@ -678,21 +678,20 @@ int update_theta(same_lda* h, Matrix& M, float m, hipStream_t st)
     return SAME_LDA_OK;
 }
 
-// After the draw `drawn` on M, whose pair list completes the counts of words: the word rows, the copies of n_k (both cleared by
-// run_pass) and, if with_theta, theta of M.
+// After the draw `drawn` on M, whose pair list completes the counts of words: the word rows and, if with_theta, theta of M and
+// the copies of n_k (all but theta cleared by run_pass).
 int finish_counts(same_lda* h, Matrix& M, const same::DrawArgs& drawn, bool with_theta, float m, hipStream_t st)
 {
-    const bool aligned = h->K % 4 == 0;
-    same::ThetaArgs t;
-    t.ndk = M.ndk; t.theta = with_theta ? M.theta : nullptr; t.nk = nk_copies(h); t.D = (uint32_t)M.D; t.K = h->K; t.mf = m; t.alpha = h->alpha;
-    // at least a turn of four rows per thread, and at most 512 workgroups (64-bit atomics per topic)
-    const uint32_t at_once = 4u * (uint32_t)same::rows_at_once(h->K);
-    t.rows_per_block = same::blocks_of_rows(t.D, 512u);
-    if (t.rows_per_block < at_once) t.rows_per_block = at_once;
-    t.blocks = same::blocks_of_rows(t.D, t.rows_per_block);
+    same::ThetaArgs t = {};
+    int64_t blocks = 0;
+    size_t lds = 0;
+    if (with_theta) {
+        t.ndk = M.ndk; t.theta = M.theta; t.nk = nk_copies(h); t.D = (uint32_t)M.D; t.K = h->K; t.mf = m; t.alpha = h->alpha;
+        t.split = same::totals_split(h->K); t.blocks = same::totals_blocks(t.split, t.D);
+        blocks = t.blocks.blocks;
+        lds = (size_t)h->K * sizeof(unsigned long long);
+    }
     same::ReduceArgs r = {};
-    int64_t blocks = t.blocks;
-    size_t lds = (size_t)256 * (aligned ? 4 : 1) * sizeof(unsigned long long);
     if (drawn.pairs && drawn.n > 0) {
         r.pairs = drawn.pairs; r.chunks = drawn.chunks; r.n_chunks = drawn.n_chunks; r.slot_word = M.slot_word; r.n = M.n_slots;
         r.K = h->K; r.nwk = h->nwk;
@@ -702,8 +701,7 @@ int finish_counts(same_lda* h, Matrix& M, const same::DrawArgs& drawn, bool with
         if (lds < table) lds = table;
     }
     if (blocks == 0) return SAME_LDA_OK;
-    if (aligned) hipLaunchKernelGGL(same::counts_kernel<4>, dim3((unsigned)blocks), dim3(256), lds, st, t, r);
-    else         hipLaunchKernelGGL(same::counts_kernel<1>, dim3((unsigned)blocks), dim3(256), lds, st, t, r);
+    hipLaunchKernelGGL(same::counts_kernel, dim3((unsigned)blocks), dim3(256), lds, st, t, r);
     HIP_TRY(h, hipGetLastError());
     return SAME_LDA_OK;
 }
@@ -747,7 +745,7 @@ int sample_phi(same_lda* h, const Matrix& M, float m, uint32_t pword, hipStream_
     const int blocks = (int)same::blocks_of_rows((uint32_t)h->V, kGammaRows);
     hipLaunchKernelGGL(same::gamma_phi_kernel, dim3(blocks), dim3(same::kGammaThreads), 0, st, h->nwk, M.n_hot > 0 ? M.hot_of : nullptr, hot_used(h),
                        same::kHotMax, same::kHotCopies, h->phi, h->V, h->K, m * h->beta, (uint32_t)h->seed, (uint32_t)(h->seed >> 32),
-                       pword, kGammaRows, h->gamma_partial);
+                       pword, kGammaRows, h->gamma_partial, nk_copies(h));
     hipLaunchKernelGGL(same::gamma_phi_totals_kernel, dim3(same::column_sum_blocks(h->K)), dim3(256), 0, st, h->gamma_partial,
                        blocks, h->K, h->gamma_total, nk_copies(h), nk_totals(h));
     const uint32_t rows = 8u * (h->K >= 256 ? 1u : 256u / (uint32_t)h->K);
@@ -914,7 +912,7 @@ int same_lda_sweep_sampled(same_lda_t* h, int32_t m_t)
     int rc = check_m(h, m_t, h->X);
     same::DrawArgs drawn;
     if (!rc) rc = run_pass(h, h->X, Copies::whole((uint32_t)m_t), pass_word(h->pass, 0), false, true, h->timing, h->stream, &drawn);
-    // the topic totals are part of the readable state, kept current as after a collapsed update
+    // (the topic totals, part of the readable state, come with the Gamma variables of the words)
     if (!rc) rc = finish_counts(h, h->X, drawn, false, (float)m_t, h->stream);
     if (!rc) rc = sample_theta(h, h->X, (float)m_t, pass_word(h->pass, 2), h->stream);
     if (!rc) rc = sample_phi(h, h->X, (float)m_t, pass_word(h->pass, 3), h->stream);

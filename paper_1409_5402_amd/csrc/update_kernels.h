@@ -148,8 +148,9 @@ __global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __res
 }
 
 // n_k, the copies of topic k, exact in 64-bit integers (any order gives the same value), and theta.  Every copy is in n_dk and
-// in n_wk; the sum is taken over n_dk, which theta reads anyway and which is complete when the draw ends.  A workgroup owns
-// rows_per_block documents, four rows of loads in flight per thread, and ends with one 64-bit atomic per topic, on one of a few
+// in n_wk; the sum is taken over n_dk, which theta reads anyway and which is complete when the draw ends (the sampled form, whose
+// theta is another kernel's, takes it over n_wk in gamma_phi_kernel).  A workgroup owns a range of documents, 16-byte accesses at
+// every number of topics (totals_split), four in flight per thread, and ends with one 64-bit atomic per topic, on one of a few
 // copies of the totals: the 512 of a launch on one address take longer than the rest of it where that is small (K = 64, 50,000
 // documents: 18 us a sweep).  Who needs the totals adds the copies up (nk_total), which every workgroup of the phi update
 // does: eight copies up to 128 topics, down to one at 1024 (nk_copies_for; with eight there 110 us of 4.6 ms lost).
@@ -166,65 +167,70 @@ __device__ __forceinline__ unsigned long long nk_total(const NkCopies& a, int K,
     return n;
 }
 struct ThetaArgs {
-    const uint32_t* ndk; float* theta;     // theta null: totals alone
-    NkCopies nk; uint32_t D; int K; uint32_t rows_per_block, blocks;
+    const uint32_t* ndk; float* theta;
+    NkCopies nk; uint32_t D; int K; TotalsSplit split; TotalsBlocks blocks;
     float mf, alpha;
 };
 
-template <int W>
-__device__ __forceinline__ void theta_totals(const ThetaArgs& a, uint32_t block, unsigned long long* sh)   // sh: [256 * W]
+__device__ __forceinline__ void theta_totals(const ThetaArgs& a, uint32_t block, unsigned long long* tot)   // tot: [K] of LDS
 {
-    const RowSplit<W> s(a.K);
-    const Rows b = rows_of_block(block, a.rows_per_block, a.D);
-    const uint32_t groups = (uint32_t)s.groups;
-    for (int u = s.unit; u < s.units; u += s.groups == 1 ? 256 : s.units) {
-        unsigned long long acc[W] = {};
-        if (s.group < s.groups) {
-            for (uint32_t r = b.from + s.group; r < b.to; r += 4 * groups) {
-                uint32_t v[4][W];
+    const TotalsSplit& s = a.split;
+    const int K = a.K;
+    const uint32_t turns = (uint32_t)s.turns, groups = (uint32_t)s.groups;
+    for (int k = threadIdx.x; k < K; k += 256) tot[k] = 0ull;
+    __syncthreads();
+    auto add = [&](int k, unsigned long long v) {
+        if (v) __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long*)(tot + k), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    const uint32_t group = threadIdx.x / (uint32_t)s.per;
+    const int unit = (int)(block % turns) * s.per + (int)(threadIdx.x % (uint32_t)s.per);
+    const size_t row = 4 * (size_t)s.units;                        // counts of `fold` documents
+    if (group < groups && unit < s.units) {
+        const Rows b = rows_of_block(block / turns, a.blocks.rows_per_block, a.blocks.rows);
+        unsigned long long acc[4] = {};
+        for (uint32_t r = b.from + group; r < b.to; r += 4u * groups) {
+            uint32_t v[4][4];
 #pragma unroll
-                for (uint32_t j = 0; j < 4u; ++j) {
-                    const uint32_t rj = r + j * groups;
-                    load_unit<W>(a.ndk + (size_t)(rj < b.to ? rj : r) * a.K + W * u, v[j]);
-                }
+            for (uint32_t j = 0; j < 4u; ++j) {
+                const uint32_t rj = r + j * groups;
+                load_unit<4>(a.ndk + (rj < b.to ? rj : r) * row + 4 * unit, v[j]);
+            }
 #pragma unroll
-                for (uint32_t j = 0; j < 4u; ++j) {
-                    const uint32_t rj = r + j * groups;
-                    if (rj >= b.to) break;
-                    for (int c = 0; c < W; ++c) acc[c] += v[j][c];
-                    if (a.theta == nullptr) continue;
-                    float* t = a.theta + (size_t)rj * a.K + W * u;
-                    float x[W];
-                    for (int c = 0; c < W; ++c) x[c] = (float)v[j][c] / a.mf + a.alpha;
-                    if constexpr (W == 4) *reinterpret_cast<float4*>(t) = make_float4(x[0], x[1], x[2], x[3]);
-                    else *t = x[0];
-                }
+            for (uint32_t j = 0; j < 4u; ++j) {
+                const uint32_t rj = r + j * groups;
+                if (rj >= b.to) break;
+                float x[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { acc[c] += v[j][c]; x[c] = (float)v[j][c] / a.mf + a.alpha; }
+                *reinterpret_cast<float4*>(a.theta + rj * row + 4 * unit) = make_float4(x[0], x[1], x[2], x[3]);
             }
         }
-        if (s.groups > 1) {                                        // the row groups' sums of a topic
-            for (int c = 0; c < W; ++c) sh[threadIdx.x * W + c] = acc[c];
-            __syncthreads();
-            if (s.group == 0)
-                for (int g = 1; g < s.groups; ++g)
-                    for (int c = 0; c < W; ++c) acc[c] += sh[(g * s.units + s.unit) * W + c];
-            if (s.group != 0) break;
-        }
-        for (int c = 0; c < W; ++c) if (acc[c]) atomicAdd(a.nk.p + (size_t)(block % (uint32_t)a.nk.n) * a.K + W * u + c, acc[c]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) add((4 * unit + c) % K, acc[c]);
     }
+    if (block == 0) {                                              // the documents that fill no whole row: fewer than `fold`
+        const size_t from = a.blocks.rows * row, n = (size_t)a.D * K - from;
+        for (size_t i = threadIdx.x; i < n; i += 256) {
+            const uint32_t v = a.ndk[from + i];
+            add((int)(i % (uint32_t)K), v);
+            a.theta[from + i] = (float)v / a.mf + a.alpha;
+        }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < K; k += 256) if (tot[k]) atomicAdd(a.nk.p + (size_t)(block % (uint32_t)a.nk.n) * K + k, tot[k]);
 }
 
 // What follows a draw and needs nothing but its counts: the word rows from the pair list, and beside it in the same launch (the
-// first t.blocks workgroups) the topic totals and theta.  One after the other the two took 12 and 11 us of the 72 us of a
+// first t.blocks.blocks workgroups) the topic totals and theta.  One after the other the two took 12 and 11 us of the 72 us of a
 // sweep over 4,000 documents at K = 50, 36 and 18 of 460 at 50,000 documents and K = 64; together
 // tiny_fit's ten sweeps take 410 instead of 460 us, those five 390 instead of 440, and at K = 1024 the totals' pass over 400 MB
 // of n_wk is gone (140 us).
-template <int W>
 __global__ __launch_bounds__(256) void counts_kernel(ThetaArgs t, ReduceArgs r)
 {
     static_assert(kReduceThreads == 256, "workgroups of both kinds");
     extern __shared__ __align__(16) uint32_t counts_lds[];
-    if (blockIdx.x < t.blocks) theta_totals<W>(t, blockIdx.x, reinterpret_cast<unsigned long long*>(counts_lds));
-    else                       word_reduce(r, blockIdx.x - t.blocks, counts_lds);
+    if (blockIdx.x < t.blocks.blocks) theta_totals(t, blockIdx.x, reinterpret_cast<unsigned long long*>(counts_lds));
+    else                              word_reduce(r, blockIdx.x - t.blocks.blocks, counts_lds);
 }
 
 // The copies of a hot word's row (scatter.h): their counts of the W topics from `at` on are added to n and

@@ -233,3 +233,24 @@ def test_poisson_at_any_number_of_topics(K, m):
         assert np.array_equal(g.get(binding.NDK), o.ndk)
         assert np.array_equal(g.get(binding.NWK), o.nwk)
     g.close()
+
+
+# n_dk in rows of one, two or four documents: fewer documents than a row, one row and a rest, several
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 50, 129, 257, 258, 1001, 1026, 2047])
+@pytest.mark.parametrize("D", [1, 2, 3, 5, 6, 23])
+def test_theta_and_totals_of_few_documents(D, K):
+    """theta is n_dk / m + alpha in binary32, element by element, and n_k the sum over either matrix, collapsed and sampled."""
+    rng = np.random.default_rng(D)
+    lens = rng.integers(1, 8, size=D)
+    rowidx = np.concatenate([np.sort(rng.choice(7, n, replace=False)) for n in lens]).astype(np.int32)
+    X = oracle.CSC(D, 7, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), rowidx, rng.integers(1, 4, size=len(rowidx)).astype(np.float32))
+    g = binding.SameLDA(X.D, X.V, X.colptr, X.rowidx, X.val, K, 0.3, 0.05, 5, 1, 8)
+    for sweep, m in ((lambda: g.sweep(7), 7), (lambda: g.sweep_sampled(2), 0), (lambda: g.sweep_poisson(2.5), 2.5)):
+        sweep()
+        ndk = np.asarray(g.get(binding.NDK)).reshape(D, K)
+        nk = np.asarray(g.get(binding.NK)).astype(np.int64)
+        assert np.array_equal(nk, ndk.sum(0, dtype=np.int64))
+        assert np.array_equal(nk, np.asarray(g.get(binding.NWK)).reshape(X.V, K).sum(0, dtype=np.int64))
+        if m:
+            assert np.array_equal(g.get(binding.THETA), ndk.astype(np.float32) / np.float32(m) + np.float32(0.3))
+    g.close()

@@ -70,6 +70,33 @@ long t_theta_rows_wrong()
     }
     return wrong;
 }
+// Counts of a D x K matrix that the workgroups of the totals do not take exactly once, accesses off a 16-byte boundary, and workgroups
+// with less than half of their threads in use where there are several turns.
+long t_totals_counts_wrong(unsigned D, int K)
+{
+    const TotalsSplit s = totals_split(K);
+    const TotalsBlocks t = totals_blocks(s, D);
+    std::vector<unsigned char> taken((size_t)D * K, 0);
+    const size_t row = 4 * (size_t)s.units;
+    long wrong = row != (size_t)s.fold * K || s.per * s.groups > 256 || s.per * s.turns < s.units || (s.turns > 1 && 2 * s.per * s.groups < 256);
+    for (unsigned block = 0; block < t.blocks; ++block) {
+        const Rows b = rows_of_block(block / s.turns, t.rows_per_block, t.rows);
+        for (unsigned i = 0; i < 256; ++i) {
+            const unsigned group = i / s.per;
+            const int unit = (int)(block % s.turns) * s.per + (int)(i % s.per);
+            if (group >= (unsigned)s.groups || unit >= s.units) continue;
+            for (unsigned r = b.from + group; r < b.to; r += s.groups)
+                for (int c = 0; c < 4; ++c) {
+                    const size_t at = r * row + 4 * unit + c;
+                    if (at >= taken.size() || taken[at]++ || (at - c) % 4 != 0 || at % K != (size_t)((4 * unit + c) % K)) ++wrong;
+                }
+        }
+        if (block == 0) for (size_t i = t.rows * row; i < taken.size(); ++i) if (taken[i]++) ++wrong;
+    }
+    for (unsigned char c : taken) if (!c) ++wrong;
+    return wrong;
+}
+long t_totals_blocks(unsigned D, int K) { return totals_blocks(totals_split(K), D).blocks; }
 int t_theta_rows(int K) { return theta_rows(K); }
 int t_groups_per_unit(int K, int most) { return groups_per_unit(K, most); }
 // Rows near `rows` that belong to no workgroup, to two, or to one past the end.
@@ -225,3 +252,12 @@ def test_theta_rows_only_where_the_kernel_has_them(lib):
     assert lib.t_theta_rows_wrong() == 0
     for K, on in ((287, 0), (288, 1), (292, 0), (289, 1), (448, 1), (500, 0), (512, 1), (516, 1), (701, 1), (895, 1), (896, 1), (897, 0), (1024, 0)):
         assert bool(lib.t_theta_rows(K)) == bool(on), K
+
+
+def test_totals_take_every_count_once(lib):
+    """n_dk in rows of one, two or four documents: every count once, on 16-byte boundaries, its topic the thread's own."""
+    for D in (1, 2, 3, 4, 7):
+        assert [K for K in range(1, 2049) if lib.t_totals_counts_wrong(D, K)] == [], D
+    for K in (1, 2, 3, 4, 5, 50, 64, 129, 255, 256, 257, 258, 333, 512, 513, 1001, 1024, 1025, 1030, 2046, 2047, 2048):
+        assert lib.t_totals_counts_wrong(2999, K) == 0, K
+        assert lib.t_totals_blocks(0, K) == 0 and lib.t_totals_blocks(2**31 - 1, K) <= 1024
