@@ -175,7 +175,8 @@ constexpr int kRefillLateTrips = 8;
 // THETA: the document of the row of counts also has its row of theta in LDS, for the reload of a step's block (theta_rows in
 // launch_shape.h).
 //
-// Waves per SIMD: four where 128 registers hold the kernel, else three, and two where three would keep up to 63 registers and
+// Waves per SIMD: five for fewer than four topics (60,000 documents of 30 tokens, m = 1 and 100: K = 3 with four 13 and 5 % slower,
+// K = 1 12 and 12 %), four where 128 registers hold the kernel, else three, and two where three would keep up to 63 registers and
 // 140 bytes a lane in scratch (rows that are not aligned from 641 to 1024 topics, 7 loads per matrix in flight).  ms per draw with
 // three / two, documents of 60 tokens from a flat posterior and of 330 with topics formed, m = 16 and then 100: K = 701 1.90 / 1.65,
 // 1.32 / 1.12 and 6.23 / 5.37, 3.08 / 2.69; K = 895 3.21 / 1.99, 2.04 / 1.27 and 12.2 / 6.08, 5.52 / 2.90; K = 896 1.80 / 1.69,
@@ -184,6 +185,7 @@ constexpr int kRefillLateTrips = 8;
 constexpr int draw_waves(bool uniform, bool vec, int tb, bool one, int kc, bool coal)
 {
     if (uniform) return 6;
+    if (tb == 0) return 5;
     if (tb <= 3) return 4;
     return (one && tb == 7) || (!vec && ((one && tb == 6) || (coal && kc == 0))) ? 2 : 3;
 }
