@@ -237,9 +237,10 @@ SAME_HD inline uint32_t vb_nonzero(uint32_t first, uint32_t at, uint32_t n) { re
 //   V = 100,000   K = 128 0.178 / 0.212   150 0.261 / 0.276   200 0.361 / 0.326   (100,000 documents) 256 1.46 / 1.20
 //   K = 256       V = 30,000 0.344 / 0.302   60,000 0.419 / 0.338   100,000 and documents of 60 tokens 0.098 / 0.110
 //   K = 512       V = 8,000 0.611 / 0.488   20,000 0.809 / 0.546        K = 1000   V = 10,000 1.64 / 0.91
+constexpr int kSddmmSliced = 176;       // not up to this many topics
 inline bool sddmm_sliced(int64_t V, int K, int64_t nnz, int64_t D)
 {
-    return K > 176 && V * K >= 3000000 && nnz >= 65536 && nnz >= 64 * D;
+    return K > kSddmmSliced && V * K >= 3000000 && nnz >= 65536 && nnz >= 64 * D;
 }
 
 // Nonzeros that a wave of the normaliser looks through: enough to share its start, few enough for four waves per SIMD.

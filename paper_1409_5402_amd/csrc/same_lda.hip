@@ -796,17 +796,12 @@ int run_pass(same_lda* h, Matrix& M, Copies c, uint32_t pword, bool uniform, boo
 }
 
 // mu of every nonzero of M from M's theta and the handle's phi
-template <int LANES, int CH>
-void launch_sddmm_rows(const same::SddmmArgs& a, dim3 grid, bool sliced, hipStream_t st)
+template <int LANES, int CH, int SLICES>
+void launch_sddmm_rows(const same::SddmmArgs& a, dim3 grid, hipStream_t st)
 {
     const dim3 block(64 * same::kSddmmWaves);
-    if (a.K % 4 == 0) {
-        if (sliced) hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, true, 8>), grid, block, 0, st, a);
-        else        hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, true, 1>), grid, block, 0, st, a);
-    } else {
-        if (sliced) hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, false, 8>), grid, block, 0, st, a);
-        else        hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, false, 1>), grid, block, 0, st, a);
-    }
+    if (a.K % 4 == 0) hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, true, SLICES>), grid, block, 0, st, a);
+    else              hipLaunchKernelGGL((same::sddmm_kernel<LANES, CH, false, SLICES>), grid, block, 0, st, a);
 }
 
 void launch_sddmm(same_lda* h, const Matrix& M, float* mu)
@@ -822,12 +817,20 @@ void launch_sddmm(same_lda* h, const Matrix& M, float* mu)
     a.stretch = same::sddmm_stretch(sliced, M.nnz);
     const int64_t waves = (M.nnz + a.stretch - 1) / a.stretch;
     const dim3 grid((unsigned)((waves + same::kSddmmWaves - 1) / same::kSddmmWaves * (sliced ? 8 : 1)));
-    if (K <= 64)        launch_sddmm_rows<16, 1>(a, grid, sliced, h->stream);
-    else if (K <= 128)  launch_sddmm_rows<32, 1>(a, grid, sliced, h->stream);
-    else if (K <= 256)  launch_sddmm_rows<64, 1>(a, grid, sliced, h->stream);
-    else if (K <= 512)  launch_sddmm_rows<64, 2>(a, grid, sliced, h->stream);
-    else if (K <= 1024) launch_sddmm_rows<64, 4>(a, grid, sliced, h->stream);
-    else                launch_sddmm_rows<64, 8>(a, grid, sliced, h->stream);
+    static_assert(same::kSddmmSliced >= 128, "the forms of 16 and 32 lanes exist without slices alone");
+    if (K <= 64)        launch_sddmm_rows<16, 1, 1>(a, grid, h->stream);
+    else if (K <= 128)  launch_sddmm_rows<32, 1, 1>(a, grid, h->stream);
+    else if (!sliced) {
+        if (K <= 256)       launch_sddmm_rows<64, 1, 1>(a, grid, h->stream);
+        else if (K <= 512)  launch_sddmm_rows<64, 2, 1>(a, grid, h->stream);
+        else if (K <= 1024) launch_sddmm_rows<64, 4, 1>(a, grid, h->stream);
+        else                launch_sddmm_rows<64, 8, 1>(a, grid, h->stream);
+    } else {
+        if (K <= 256)       launch_sddmm_rows<64, 1, 8>(a, grid, h->stream);
+        else if (K <= 512)  launch_sddmm_rows<64, 2, 8>(a, grid, h->stream);
+        else if (K <= 1024) launch_sddmm_rows<64, 4, 8>(a, grid, h->stream);
+        else                launch_sddmm_rows<64, 8, 8>(a, grid, h->stream);
+    }
 }
 
 size_t state_bytes(const same_lda* h, int32_t which)
