@@ -210,11 +210,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(draw_wave
     // reach the matrix in one pass over the row when the wave has left the document; tasks of a document that
     // has no row here add to the matrix at once.
     uint32_t* rows = lds + kRecips + (size_t)kWave * kStride;      // [n_rows][K]
-    const int n_rows = DEBUG ? 0 : doc_rows(K);
+    const int n_rows = DEBUG && !THETA ? 0 : doc_rows(K);          // (DEBUG: for the row of theta alone)
     int tag0 = -1, tag1 = -1;                                      // the documents of rows 0 and 1 (wave-uniform), -1: free
     int myrow = -1;                                                // the row of this lane's document, -1: none
     for (int i = lane; i < n_rows * K; i += kWave) rows[i] = 0u;
-    static_assert(!THETA || (ONE && TB >= 3 && !UNIFORM && !DEBUG), "theta_rows");
+    static_assert(!THETA || (ONE && TB >= 3 && !UNIFORM), "theta_rows");
     float* th_row_lds = reinterpret_cast<float*>(rows) + K;        // THETA: [K], theta of that document (one row at these K)
     // the wave's positions not yet handed out
     int32_t next, end;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(draw_wave
     // Adds row i of the LDS counts to the matrix row of document doc and clears it (whole wave).
     auto flush_row = [&](int i, int doc) {
         __syncthreads();
-        for (int k = lane; k < K; k += kWave) {
+        if (!DEBUG) for (int k = lane; k < K; k += kWave) {
             const uint32_t v = rows[i * K + k];
             if (v) { add_global(a.ndk + (size_t)doc * K + k, v); rows[i * K + k] = 0u; }
         }
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(draw_wave
         }
 #endif
         if (en > 0u) {
-            if (myrow >= 0) add_lds(rows + myrow * K + ek, en);
+            if (!DEBUG && myrow >= 0) add_lds(rows + myrow * K + ek, en);
             else add_global(a.ndk + (size_t)sc.drow * K + ek, en);
             sc.emit_word(a, ek, en, w, staged);
         }

@@ -541,7 +541,7 @@ int resident_groups(same_lda* h, const void* f, int threads, size_t lds, bool un
 template <bool VEC, bool DEBUG, int TB>
 const void* one_batch_kernel(bool theta)
 {
-    constexpr bool some = !DEBUG && same::theta_rows_some(TB), all = !DEBUG && same::theta_rows_all(TB, VEC);
+    constexpr bool some = same::theta_rows_some(TB), all = same::theta_rows_all(TB, VEC);
     if constexpr (some) {
         if (all || theta) return reinterpret_cast<const void*>(same::draw_kernel<false, VEC, DEBUG, TB, true, 0, false, true>);
     }
@@ -551,8 +551,8 @@ const void* one_batch_kernel(bool theta)
 
 // The draw kernel for blocks of 4 * quads topics (VEC: rows are aligned to 16 bytes).  Up to 896 topics a block is one batch
 // of loads, up to 1024 two in the contiguous form, beyond that batches of the largest of 4, 2, 1 that divides it.  The
-// debug hook takes the same form of the kernel as the sweep, but for the rows in LDS: its lanes add to count rows of their own in
-// memory, and the reload of a step's block reads theta there as well, where a sweep may have the row in LDS (theta_rows).
+// debug hook takes the same form of the kernel as the sweep, the row of theta in LDS included; only its lanes add to count rows of
+// their own in memory.
 template <bool VEC, bool DEBUG>
 const void* draw_kernel_for(int quads, bool theta)
 {
@@ -596,12 +596,12 @@ int launch_draw(same_lda* h, same::DrawArgs a, bool uniform, bool poisson, hipSt
         // (K = 512 and from 897 to 1024: the scan reads a row 512 contiguous bytes per half-wave and load; at K = 256, where the
         // kernel is bound by vector-ALU issue, the extra additions of that form cost more than the fewer cache lines save)
         const int quads = same::block_len(a.K) / 4;                // 16-byte loads per block and matrix
-        const bool theta = !uniform && !DEBUG && same::theta_rows(a.K);
+        const bool theta = !uniform && same::theta_rows(a.K);
         const void* f = nullptr;
         if (uniform)      f = reinterpret_cast<const void*>(same::draw_kernel<true, false, DEBUG, 0, true>);
         else if (a.K < 4) f = reinterpret_cast<const void*>(same::draw_kernel<false, false, DEBUG, 0, true>);
         else if (a.K == 256)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 2, true, 256>);
-        else if (a.K == 512)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true, !DEBUG>);
+        else if (a.K == 512)  f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, true, 512, true, true>);
         else if (a.K == 1024) f = reinterpret_cast<const void*>(same::draw_kernel<false, true, DEBUG, 4, false, 1024, true>);
         else if (a.K % 4 == 0) f = draw_kernel_for<true, DEBUG>(quads, theta);
         else                   f = draw_kernel_for<false, DEBUG>(quads, theta);
