@@ -278,9 +278,9 @@ __device__ __forceinline__ void word_reduce(const ReduceArgs& a, uint32_t block,
         }
     }
     __syncthreads();
-    // A word whose slots all lie in this workgroup's range is updated by no other workgroup of this launch (and
-    // nothing else runs beside the launch): its row takes plain additions.  Only the first and the last word of
-    // the range may share their rows with the neighbours.
+    // A word whose slots all lie in this workgroup's range is updated by no other workgroup: the others that reduce own other
+    // slots, those of the same launch that work on documents never write n_wk, and the draw has ended.  Its row takes plain
+    // additions.  Only the first and the last word of the range may share their rows with the neighbours.
     const bool first_shared = s0 > 0 && slot_word[s0 - 1] == w0;
     const bool last_shared = s1 < n && slot_word[s1] == w1;
     uint32_t* base = nwk + (size_t)w0 * K;                         // row w0 + r, topic k is at base[r*K + k]
@@ -295,8 +295,8 @@ __device__ __forceinline__ void word_reduce(const ReduceArgs& a, uint32_t block,
     }
 }
 
-// Slots per workgroup, two per thread: kReduceChunk, or as few as leave two workgroups per compute unit.  The table
-// shrinks with it.
+// Slots per workgroup of 256 threads: one per thread while that is at most 512 workgroups (two per compute unit), else two
+// (kReduceChunk).  The table shrinks with it.
 inline int reduce_chunk(int64_t n) { int c = 256; while (c < kReduceChunk && (int64_t)c * 512 < n) c *= 2; return c; }
 inline int reduce_rows(int K, int chunk) { const int r = 8 * chunk / K; return r < 1 ? 1 : (r > 64 ? 64 : r); }
 

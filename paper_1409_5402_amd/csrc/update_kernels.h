@@ -124,10 +124,11 @@ __device__ __forceinline__ void load_unit(const uint32_t* __restrict__ p, uint32
     }
 }
 
-// theta = n_dk / m + alpha   (divide, then add), n elements from thread `first` of `stride` on
-__device__ __forceinline__ void theta_update(const uint32_t* __restrict__ ndk, float* __restrict__ theta, size_t n, float mf, float alpha,
-                                             size_t first, size_t stride)
+// theta = n_dk / m + alpha   (divide, then add), n elements
+__global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __restrict__ ndk, float* __restrict__ theta,
+                                                          size_t n, float mf, float alpha)
 {
+    const size_t first = (size_t)blockIdx.x * 256u + threadIdx.x, stride = (size_t)gridDim.x * 256u;
     const size_t quads = n / 4;
     for (size_t i = first; i < quads; i += stride) {
         const uint4 c = reinterpret_cast<const uint4*>(ndk)[i];
@@ -139,12 +140,6 @@ __device__ __forceinline__ void theta_update(const uint32_t* __restrict__ ndk, f
         reinterpret_cast<float4*>(theta)[i] = t;
     }
     if (first < (n & 3u)) theta[4 * quads + first] = (float)ndk[4 * quads + first] / mf + alpha;
-}
-
-__global__ __launch_bounds__(256) void theta_update_kernel(const uint32_t* __restrict__ ndk, float* __restrict__ theta,
-                                                          size_t n, float mf, float alpha)
-{
-    theta_update(ndk, theta, n, mf, alpha, (size_t)blockIdx.x * 256u + threadIdx.x, (size_t)gridDim.x * 256u);
 }
 
 // n_k, the copies of topic k, exact in 64-bit integers (any order gives the same value), and theta.  Every copy is in n_dk and
@@ -341,7 +336,7 @@ __global__ __launch_bounds__(256) void doc_log_total_kernel(const float* __restr
     if (lane == 0) out[d] = log(s);
 }
 
-// Per nonzero: c * (log mu - log theta total), mu from the normaliser kernels below (a nonzero per thread with a running
+// Per nonzero: c * (log mu - log theta total), mu from the normaliser (sddmm_kernel.h; a nonzero per thread with a running
 // sum over its two rows took 1.82 ms for 6.7 million nonzeros at K = 256, lines of two rows per lane; the normaliser
 // kernel and this one 0.60 ms).  Block partial sums (double) go to part[].
 __global__ __launch_bounds__(256) void loglik_kernel(int64_t nnz, const int32_t* __restrict__ nz_doc,

@@ -96,10 +96,10 @@ __global__ __launch_bounds__(256) void vb_exp_elog_beta_kernel(const float* __re
 // sums over their nonzeros are in LDS, where a lane owns every 64th topic.
 //
 // Bound by the rows of b: 69 GB of them for 60,000 news-shaped documents and five iterations at K = 256, of which the second-level
-// caches (4 MB a die) miss half, and by the conversions and sums in double behind them (16 of some 28 vector instructions per
-// nonzero).  The rows of the next round are loaded while a round is worked off; every turn issues the same loads, past the
-// document's end with its last nonzero's index and a count of zero, so that the wait before a round's arithmetic has a fixed
-// number of younger loads behind it.  The four normalisers of a group end in lanes l & 3 (lane_sum_4): one division serves
+// caches (4 MB a die) miss half, and by the conversions and sums in double behind them (per nonzero and lane at K = 256
+// four conversions and four fused additions, beside four in binary32).  The rows of the next round are loaded while a round is
+// worked off; every turn issues the same loads, past the document's end with its last nonzero's index and a count of zero, so that
+// the wait before a round's arithmetic has a fixed number of younger loads behind it.  The four normalisers of a group end in lanes l & 3 (lane_sum_4): one division serves
 // all four.  ms per launch before (all lanes on one nonzero, gamma and sums in registers, LDS off multiples of four) and now, five
 // iterations: that case 6.13 and 5.02; 20,000 documents at K = 50 4.61 and 0.40, 128 2.22 and 0.91, 333 26.8 and 2.94, 512 4.20
 // and 3.50, 1000 9.31 and 7.69.  (Two to sixteen waves per document, so that its rows might be found in the caches again:

@@ -77,7 +77,8 @@ __global__ __launch_bounds__(256) void wl_scan_docs(const int32_t* __restrict__ 
                                                     int32_t* __restrict__ nz_doc, uint32_t* __restrict__ ntask,
                                                     unsigned long long* __restrict__ doc_tok, BuildStats* s)
 {
-    __shared__ uint32_t sh_sizes[kSizeClasses];                    // little LDS: the pass runs beside the draw kernel, which leaves 12 KB
+    __shared__ uint32_t sh_sizes[kSizeClasses];                    // (a sweep's draw beside it may hold all LDS: at K = 256 sixteen
+                                                                   // workgroups a compute unit, eight pieces of 1,280 bytes each)
     for (int c = threadIdx.x; c < kSizeClasses; c += 256) sh_sizes[c] = 0u;
     __syncthreads();
     unsigned long long tok = 0ull, tasks = 0ull, doc_max = 0ull;
