@@ -241,9 +241,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(draw_wave
     bool open = false;      // a task was taken and its slot of the pair list is not yet closed
     int32_t d = 0, w = 0;
     // Its rows of theta and phi, as addresses: from d and w they take nine instructions a step (more where K is no constant).
-    // Not where the four registers are not to be had without spilling others, and not at K = 1024 (from a flat posterior
+    // Not where the four registers are not to be had without spilling others (rows that are not aligned up to 128 topics: six in scratch
+    // with them, K = 125 at m = 100 1.119 and 1.070 ms a sweep), and not at K = 1024 (from a flat posterior
     // at m = 100, documents of 60 and 330 tokens, 6.17 and 6.86 ms with them, 5.90 and 6.67 without).
-    constexpr bool kRowAddr = KC == 256 || KC == 512 || (KC == 0 && ONE && (TB <= 2 || TB == 4 || (TB == 5 && (VEC || !THETA))));
+    constexpr bool kRowAddr = KC == 256 || KC == 512 ||
+                              (KC == 0 && ONE && (TB == 0 || (TB == 1 && VEC) || TB == 2 || TB == 4 || (TB == 5 && (VEC || !THETA))));
     const float* th_row = a.theta;
     const float* ph_row = a.phi;
     Scatter sc;
@@ -943,6 +945,22 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(draw_wave
     if (n_rows > 0 && tag0 >= 0) flush_row(0, tag0);
     if (n_rows > 1 && tag1 >= 0) flush_row(1, tag1);
 }
+
+// Registers left for what runs beside a sweep.  Sixteen waves a compute unit are four per SIMD; at 128 registers (what the
+// compiler takes if it may) they hold the whole file, and the staging of the next minibatch, whose first upload is a copy kernel where
+// the column pointers are short, stands still until the draw ends.  Held to 112 up to 128 topics (where LDS has room too, the matrix
+// build's first pass gets in with 64 left) and to 120 up to 384; not the forms of three loads with rows that are not aligned, which
+// would keep ten registers in scratch (K = 350 at m = 100 12 % slower).  us per step of a stream, free / held (before the table of
+// reciprocals, which took them over the line): documents of 354 tokens from a flat posterior, m = 30, 280e6 / K tokens: K = 50
+// 1915 / 1736 (1756), 128 1168 / 1124 (1152), 200 1107 / 910 (952), 250 1013 / 862 (867), 300 946 / 820 (803).  Sweeps by themselves
+// are within 1 %, at K = 300 (three registers in scratch) 3 % slower.
+// The attribute counts half of the unified file: 56 are 112 registers.
+template __attribute__((amdgpu_num_vgpr(56))) __global__ void draw_kernel<false, true, false, 1, true, 0, false, false>(DrawArgs);
+template __attribute__((amdgpu_num_vgpr(56))) __global__ void draw_kernel<false, false, false, 1, true, 0, false, false>(DrawArgs);
+template __attribute__((amdgpu_num_vgpr(60))) __global__ void draw_kernel<false, true, false, 2, true, 0, false, false>(DrawArgs);
+template __attribute__((amdgpu_num_vgpr(60))) __global__ void draw_kernel<false, false, false, 2, true, 0, false, false>(DrawArgs);
+template __attribute__((amdgpu_num_vgpr(60))) __global__ void draw_kernel<false, true, false, 3, true, 0, false, false>(DrawArgs);
+template __attribute__((amdgpu_num_vgpr(60))) __global__ void draw_kernel<false, true, false, 3, true, 0, false, true>(DrawArgs);
 
 inline size_t draw_lds_bytes(int K, bool uniform, bool theta)
 {

@@ -71,8 +71,10 @@ __global__ void wl_init_stats(BuildStats* s)
 // column pointers are reported and not followed.  (A search of the column pointers per nonzero and separate passes for
 // the totals of documents and words took 0.32, 0.10 and 0.43 ms for a minibatch of 7.7 million nonzeros.)
 // ntask has nnz + 1 entries; the last one is set to 0 so that an exclusive sum over all of them ends with the total.
+// Held to 32 registers (the attribute counts half of them): beside a draw of four waves of 120 a SIMD has no more.  us per step of a
+// stream at K = 200, documents of 354 tokens, with 34 and 31: 959 and 910; K = 300 and 60 tokens 826 and 768.
 constexpr int kDocLanes = 16;
-__global__ __launch_bounds__(256) void wl_scan_docs(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(16))) void wl_scan_docs(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
                                                     const float* __restrict__ val, int32_t D, int64_t nnz, int32_t V, uint32_t G,
                                                     int32_t* __restrict__ nz_doc, uint32_t* __restrict__ ntask,
                                                     unsigned long long* __restrict__ doc_tok, BuildStats* s)

@@ -261,3 +261,27 @@ def test_totals_take_every_count_once(lib):
     for K in (1, 2, 3, 4, 5, 50, 64, 129, 255, 256, 257, 258, 333, 512, 513, 1001, 1024, 1025, 1030, 2046, 2047, 2048):
         assert lib.t_totals_counts_wrong(2999, K) == 0, K
         assert lib.t_totals_blocks(0, K) == 0 and lib.t_totals_blocks(2**31 - 1, K) <= 1024
+
+
+def test_registers_left_beside_a_sweep():
+    """Four waves of a draw on a SIMD leave registers for the staging of the next minibatch, whose uploads and passes otherwise
+    wait for the draw to end.  The numbers are the compiler's, in the metadata of the library built here."""
+    msgpack = pytest.importorskip("msgpack")
+    from paper_1409_5402_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
+    with open(build.LIB, "rb") as f:
+        image = f.read()
+    at = image.index(b"amdhsa.kernels") - 2                        # a map of a few entries, the first key's length before it
+    unpacker = msgpack.Unpacker(raw=False, strict_map_key=False)
+    unpacker.feed(image[at:at + (4 << 20)])
+    registers = {k[".name"]: k[".vgpr_count"] for k in unpacker.unpack()["amdhsa.kernels"]}
+
+    def draw(aligned, quads, theta):
+        return registers["_ZN4same11draw_kernelILb0ELb%dELb0ELi%dELb1ELi0ELb0ELb%dEEEvNS_8DrawArgsE" % (aligned, quads, theta)]
+    for aligned in (0, 1):
+        assert draw(aligned, 1, 0) <= 112
+        assert draw(aligned, 2, 0) <= 120
+    for theta in (0, 1):
+        assert draw(1, 3, theta) <= 120
+    assert next(v for k, v in registers.items() if "wl_scan_docs" in k) <= 512 - 4 * 120
